@@ -97,21 +97,19 @@ int launch_tall(const GemmArgs& a, dim3 grid, hipStream_t st) {
     return HAQ_OK;
 }
 
+}  // namespace
+
 int cu_count() {
-    static int n_cu = 0;
-    if (n_cu == 0) {
+    static const int n_cu = [] {
         int devid = 0, v = 0;
-        if (hipGetDevice(&devid) == hipSuccess && hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, devid) == hipSuccess && v > 0)
-            n_cu = v;
-        else
-            n_cu = 256;
-    }
+        if (hipGetDevice(&devid) == hipSuccess && hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, devid) == hipSuccess && v > 0) return v;
+        return 256;
+    }();
     return n_cu;
 }
 
-}  // namespace
-
 int launch_gemm(const GemmArgs& a, int epi, hipStream_t st) {
+    if (skinny_supported(a) && (epi == EPI_LINEAR || epi == EPI_LINEAR_ASYM)) return launch_skinny(a, epi == EPI_LINEAR_ASYM, st);
     const int ntn = cdiv(a.N, BN);
     // upper bound on the M tiles: exact for one matrix; rows/BM plus one partial tile per group otherwise
     const int mt = a.offsets ? a.max_rows / BM + a.n_sel : cdiv(a.M, BM);

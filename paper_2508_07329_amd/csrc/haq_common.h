@@ -112,6 +112,7 @@ struct QuantArgs {
     int32_t* zp;
 };
 int launch_quant(const QuantArgs& a, hipStream_t st);
+int cu_count();  // compute units of the current device (256 if that cannot be asked)
 
 enum { EPI_LINEAR = 0, EPI_SWIGLU = 1, EPI_LINEAR_ASYM = 2, EPI_SWIGLU_ASYM = 3 };
 
@@ -150,6 +151,10 @@ struct GemmArgs {
     const ColsumTab* cstab; // grouped: per-expert column sums, on the device
 };
 int launch_gemm(const GemmArgs& a, int epi, hipStream_t st);
+// Dense problems of at most SKINNY_MAX_ROWS token rows (skinny.hip): the weights are streamed once into registers.
+constexpr int SKINNY_MAX_ROWS = 128;
+bool skinny_supported(const GemmArgs& a);
+int launch_skinny(const GemmArgs& a, bool asym, hipStream_t st);
 int launch_asym_quant(const __half* x, int64_t ldx, const float* s, int T, int K, int8_t* q_cm, int64_t R, uint8_t* q_rm,
                       int64_t ldq, float* scale, int32_t* zp, hipStream_t st);
 

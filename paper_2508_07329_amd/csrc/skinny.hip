@@ -1,0 +1,157 @@
+// Dense W8A8 linear for short batches (at most 128 token rows): the weights are streamed from HBM
+// once, straight into MFMA operand registers, as on the decode path of the routed expert FFN.
+//
+// Bound: the weight stream (K N bytes).  The tiled GEMM cannot draw it at these batches: its grid is one
+// work-group per 128 or 256 channels (32 on a 4096-channel layer), with two K-steps of 16 KB in flight each.
+// Here a work-group owns 16 C channels and splits K over its 8 waves (a 64-byte K-step each in turn), every wave
+// keeps DEPTH K-steps of fragments in flight, and the exact int32 partial sums are added in LDS.
+// v_mfma_i32_16x16x64_i8: the weights are the first operand (16 channels x 64 k, lane = channel, 16-byte chunk), a
+// block of 16 token rows the second, so a lane ends up with four consecutive channels of one row.
+// Measured (weights cold, us; before = the tiled GEMM):
+//   rows             1          16          32          64         128
+//   4096 x 16384   27.8-12.6   27.8-12.9   28.0-14.4   28.4-15.7   28.7-21.3   (13.2 at the rate of a large copy)
+//   16384 x 4096   81.0-14.1   80.4-14.8   80.8-19.1   81.3-25.5   80.6-36.5   (13.2; the token rows are re-read per unit)
+//   768 x 3072      7.4- 3.3    7.5- 3.4    7.5- 4.2    7.8- 4.4    7.7- 6.3
+#include "haq_common.h"
+
+namespace haq {
+
+namespace {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef const __attribute__((address_space(1))) v4i* gptr_v4i;
+__device__ __forceinline__ v4i gload16(const int8_t* p) { return *(gptr_v4i)(uintptr_t)p; }
+__device__ __forceinline__ v4i gload16_stream(const int8_t* p) { return __builtin_nontemporal_load((gptr_v4i)(uintptr_t)p); }
+
+constexpr int SK_WAVES = 8;
+
+// C: blocks of 16 channels per work-group; RB: blocks of 16 token rows; WPS: waves per SIMD (register budget).
+template <int C, int RB, int DEPTH, int WPS, bool ASYM>
+__global__ __launch_bounds__(SK_WAVES * 64, WPS) void skinny_linear_kernel(GemmArgs a) {
+    __shared__ int sum[C * RB][4][64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, q = lane >> 4;
+    const int n0 = blockIdx.x * (16 * C);
+    const int nk = (a.K + 63) / 64;  // a last partial K-step reads chunks past K: the weights are zero there
+    const int n = nk > wave ? (nk - wave + SK_WAVES - 1) / SK_WAVES : 0;  // this wave's K-steps: wave, wave + 8, ...
+    const size_t wstep = (size_t)4 * SK_WAVES * a.Npad * 16, xstep = (size_t)4 * SK_WAVES * a.R * 16;
+    const int8_t* pw = a.B + ((size_t)(4 * wave + q) * a.Npad + n0 + l16) * 16;
+    const int8_t* px = a.A + (size_t)(4 * wave + q) * a.R * 16;
+    int xoff[RB];  // rows past the last one re-read it (their results are dropped)
+#pragma unroll
+    for (int b = 0; b < RB; ++b) xoff[b] = min(16 * b + l16, a.M - 1) * 16;
+
+    v4i acc[C][RB];
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int b = 0; b < RB; ++b) acc[c][b] = v4i{0, 0, 0, 0};
+    struct Frag {
+        v4i w[C], x[RB];
+    };
+    auto fetch = [&](Frag& f) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) f.w[c] = gload16_stream(pw + c * 256);
+#pragma unroll
+        for (int b = 0; b < RB; ++b) f.x[b] = gload16(px + xoff[b]);
+    };
+    auto mac = [&](const Frag& f) {
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int b = 0; b < RB; ++b) acc[c][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f.w[c], f.x[b], acc[c][b], 0, 0, 0);
+    };
+    Frag fr[DEPTH];
+    int fetched = 0;  // the loads stay unconditional: past this wave's last K-step they re-read it
+    auto next = [&](Frag& f) {
+        fetch(f);
+        if (++fetched < n) {
+            pw += wstep;
+            px += xstep;
+        }
+    };
+    if (n > 0) {
+#pragma unroll
+        for (int i = 0; i < DEPTH; ++i) next(fr[i]);
+    }
+    for (int i = tid; i < C * RB * 256; i += SK_WAVES * 64) (&sum[0][0][0])[i] = 0;
+    __syncthreads();
+    if (n > 0) {
+        int k = 0;
+        for (; k + DEPTH < n; k += DEPTH) {
+#pragma unroll
+            for (int i = 0; i < DEPTH; ++i) {
+                mac(fr[i]);
+                next(fr[i]);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < DEPTH; ++i)
+            if (k + i < n) mac(fr[i]);
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int b = 0; b < RB; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) atomicAdd(&sum[c * RB + b][r][lane], acc[c][b][r]);  // exact: the order is immaterial
+    }
+    __syncthreads();
+    for (int i = tid; i < C * RB * 64; i += SK_WAVES * 64) {
+        const int cb = i >> 6, ln = i & 63;
+        const int row = 16 * (cb % RB) + (ln & 15), ch = n0 + 16 * (cb / RB) + 4 * (ln >> 4);
+        if (row >= a.M || ch >= a.N) continue;
+        const float sx = a.sx[row];
+        const int zshift = ASYM ? 128 - a.zp[row] : 0;
+        __half hv[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            int v = sum[cb][r][ln];
+            if (ASYM) v += zshift * a.colsum[ch + r];
+            if (a.acc_dbg) a.acc_dbg[(size_t)row * a.N + ch + r] = v;
+            float f = dequant(v, sx, a.sw[ch + r]);
+            if (a.act == HAQ_ACT_RELU) f = fmaxf(f, 0.0f);
+            hv[r] = f2h(f);
+        }
+        *reinterpret_cast<uint2*>(a.Y + (size_t)row * a.ldy + ch) = *reinterpret_cast<const uint2*>(hv);
+    }
+}
+
+template <int C, int RB, int DEPTH, int WPS>
+int launch_one(const GemmArgs& a, bool asym, hipStream_t st) {
+    const dim3 grid(cdiv(a.N, 16 * C));
+    if (asym)
+        hipLaunchKernelGGL((skinny_linear_kernel<C, RB, DEPTH, WPS, true>), grid, dim3(SK_WAVES * 64), 0, st, a);
+    else
+        hipLaunchKernelGGL((skinny_linear_kernel<C, RB, DEPTH, WPS, false>), grid, dim3(SK_WAVES * 64), 0, st, a);
+    HAQ_CHECK_HIP(hipGetLastError());
+    return HAQ_OK;
+}
+
+}  // namespace
+
+bool skinny_supported(const GemmArgs& a) { return !a.offsets && a.M >= 1 && a.M <= SKINNY_MAX_ROWS; }
+
+int launch_skinny(const GemmArgs& a, bool asym, hipStream_t st) {
+    static_assert(SKINNY_MAX_ROWS == 128, "eight blocks of 16 rows");
+    // 64 channels per work-group share every token fragment, but only from 128 such units on do enough CUs draw
+    // weights: 12672 channels, 16 rows of 3168: 9.9 us against 13.2 with 16 channels, 64 rows: 13.6 against 22.9;
+    // 4096 channels, 16 rows of 4096: 8.3 us against 5.8, 64 rows: 12.0 against 8.0.
+    const int C = a.N / 64 >= 128 ? 4 : 1;
+    const int RB = (a.M + 15) / 16;
+#define HAQ_SKINNY(c, b, d, w) \
+    if (C == c && RB <= b) return launch_one<c, b, d, w>(a, asym, st)
+    HAQ_SKINNY(1, 1, 4, 4);
+    HAQ_SKINNY(1, 2, 6, 4);
+    HAQ_SKINNY(1, 4, 4, 4);
+    HAQ_SKINNY(1, 6, 5, 2);
+    HAQ_SKINNY(1, 8, 4, 2);
+    HAQ_SKINNY(4, 1, 4, 4);
+    HAQ_SKINNY(4, 2, 5, 2);
+    HAQ_SKINNY(4, 4, 4, 2);
+    HAQ_SKINNY(4, 6, 3, 2);
+    HAQ_SKINNY(4, 8, 2, 2);
+#undef HAQ_SKINNY
+    return HAQ_ERR_UNSUPPORTED;
+}
+
+}  // namespace haq

@@ -1,0 +1,46 @@
+"""Kernel variants that a rule on sizes picks: each at the edges of its range, against the CPU oracle, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import haq_inputs as hi
+import oracle
+import paper_2508_07329_amd as haq
+from tests import offline
+from tests.gpu_util import bits_equal, dev, diff_report, host
+
+pytestmark = pytest.mark.gpu
+
+
+def _linear_both_codes(T, K, N, act):
+    """The dense linear in symmetric and in asymmetric codes, with and without the accumulator dump."""
+    X, _, _ = hi.hidden_states(T + K + N, T, K, n_outlier=max(1, K // 200))
+    s, Wq, sw = offline.quantize_linear(X, hi.gaussian_weight(T + K + N, 0, K, N))
+    x, s_d, wq = dev(X), dev(s), dev(Wq)
+    wp, sw_d, cs, a = haq.haq_pack_weight(wq), dev(sw), haq.haq_weight_colsum(wq), oracle.ACT[act]
+    y_ref, acc_ref, _, _ = oracle.w8a8_linear(X, s, Wq, sw, act, full=True)
+    y, acc, _, _ = haq.haq_w8a8_linear(x, s_d, wp, sw_d, N, a, debug=True)
+    assert bits_equal(host(acc), acc_ref), diff_report(host(acc), acc_ref)
+    assert bits_equal(host(y), y_ref)
+    wide = torch.full((T, N + 24), 7.0, dtype=torch.float16, device=x.device)   # rows with a gap between them
+    haq.haq_w8a8_linear(x, s_d, wp, sw_d, N, a, out=wide[:, :N])
+    assert bits_equal(host(wide[:, :N]).copy(), y_ref) and bool((wide[:, N:] == 7.0).all())
+    if K <= 16384:
+        y_ref, acc_ref, _, _, _ = oracle.w8a8_linear_asym(X, s, Wq, sw, act, full=True)
+        y, acc, _, _, _ = haq.haq_w8a8_linear_asym(x, s_d, wp, sw_d, cs, N, a, debug=True)
+        assert bits_equal(host(acc), acc_ref), diff_report(host(acc), acc_ref)
+        assert bits_equal(host(y), y_ref)
+        assert bits_equal(host(haq.haq_w8a8_linear_asym(x, s_d, wp, sw_d, cs, N, a)), y_ref)
+
+
+@pytest.mark.parametrize("T,K,N,act", [
+    (1, 16, 16, "none"), (15, 80, 48, "relu"), (16, 448, 272, "none"), (17, 512, 16, "relu"), (32, 1040, 528, "none"),
+    (33, 2064, 80, "relu"), (64, 3584, 48, "none"), (65, 960, 112, "relu"), (96, 2560, 16, "none"), (97, 2112, 64, "none"),
+    (128, 4112, 272, "relu"), (129, 528, 272, "none"),
+    # 128 units of 64 channels and more: four channel blocks per work-group, the last unit partly past the last channel
+    (1, 64, 8192, "relu"), (16, 592, 8208, "none"), (31, 208, 8240, "relu"), (64, 1344, 8224, "none"), (90, 912, 8192, "relu"),
+    (128, 1104, 8208, "none")])
+def test_short_batch_linear_at_the_edges_of_its_variants(T, K, N, act):
+    """Row blocks of 16 (1, 2, 4, 6, 8 of them; 129 rows take the tiled GEMM), K-steps that do and do not divide among
+    the eight waves and the prefetch depth, a last partial K-step, channel units past the last channel."""
+    _linear_both_codes(T, K, N, act)
