@@ -869,6 +869,20 @@ __global__ void pack_kernel(const int8_t* w1, const int8_t* w3, int K, int Nsrc,
 
 }  // namespace
 
+// Rows of the register-resident kernels' work-groups (RS rows per thread, G row groups of CL chunk lanes).
+// A row is a chain of one load, one reduction and one store, so a short batch takes as long as the work-group with the
+// most rows: one row each while that gives every CU at most one (8 rows of 16384: 12.4 -> 6.9 us, 256 rows of 4096:
+// 9.4 -> 5.7), two up to four rows per CU (512 rows of 4096: 9.7 -> 6.7), and eight, whose codes fill the 128-byte
+// lines of the packed operand, from there on (1024 rows of 4096: 9.0 with two, 10.6 with eight; 2048 rows: 14.1, 12.0).
+struct QuantSplit {
+    int RS, G;
+};
+QuantSplit short_split(int rows, int CL, int G, int n_cu) {
+    if (rows <= n_cu) return {1, 1};
+    if (rows <= 4 * n_cu) return {2, CL < 256 ? 256 / CL : 1};
+    return {QBLOCK_ROWS / G > 4 ? 4 : QBLOCK_ROWS / G, G};
+}
+
 int launch_quant(const QuantArgs& a, hipStream_t st) {
     if (a.T <= 0) return HAQ_OK;
     const int nchunk = a.K / 16;
@@ -885,13 +899,7 @@ int launch_quant(const QuantArgs& a, hipStream_t st) {
         // work-group per CU
         constexpr int LRS = 2;
         const int rows = a.tab ? a.max_rows : a.T;
-        static int n_cu = 0;
-        if (n_cu == 0) {
-            int devid = 0, v = 0;
-            HAQ_CHECK_HIP(hipGetDevice(&devid));
-            HAQ_CHECK_HIP(hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, devid));
-            n_cu = v > 64 ? v : 256;
-        }
+        const int n_cu = cu_count();
         if (rows / (LRS * G) >= n_cu) {
             const size_t red_bytes = 4 * (QMAX_THREADS / 64) * LRS * sizeof(float);  // maxima and (asymmetric codes) minima
             const size_t lds = (size_t)qstage_rows(LRS * G) * qstage_pitch(nchunk) + red_bytes;
@@ -912,14 +920,14 @@ int launch_quant(const QuantArgs& a, hipStream_t st) {
             return HAQ_OK;
         }
         if (a.zp_dest) return HAQ_ERR_UNSUPPORTED;  // asymmetric codes: only the pipelined kernel; the caller has a row kernel
-        // otherwise the register-resident single pass, at most 4 rows per thread
-        const int RS = QBLOCK_ROWS / G > 4 ? 4 : QBLOCK_ROWS / G;
-        const int brows = RS * G;
+        // otherwise the register-resident single pass
+        const QuantSplit sp = short_split(rows, CL, G, n_cu);
+        const int brows = sp.RS * sp.G;
         const int nb = a.tab ? a.max_rows / brows + a.n_sel : cdiv(a.T, brows);
-        switch (RS) {
-            case 4: hipLaunchKernelGGL(smooth_quant_reg_kernel<4>, dim3(nb), dim3(threads), 0, st, a, CL); break;
-            case 2: hipLaunchKernelGGL(smooth_quant_reg_kernel<2>, dim3(nb), dim3(threads), 0, st, a, CL); break;
-            default: hipLaunchKernelGGL(smooth_quant_reg_kernel<1>, dim3(nb), dim3(threads), 0, st, a, CL); break;
+        switch (sp.RS) {
+            case 4: hipLaunchKernelGGL(smooth_quant_reg_kernel<4>, dim3(nb), dim3(CL * sp.G), 0, st, a, CL); break;
+            case 2: hipLaunchKernelGGL(smooth_quant_reg_kernel<2>, dim3(nb), dim3(CL * sp.G), 0, st, a, CL); break;
+            default: hipLaunchKernelGGL(smooth_quant_reg_kernel<1>, dim3(nb), dim3(CL * sp.G), 0, st, a, CL); break;
         }
         HAQ_CHECK_HIP(hipGetLastError());
         return HAQ_OK;
@@ -943,10 +951,10 @@ int launch_asym_quant(const __half* x, int64_t ldx, const float* s, int T, int K
     if (CL > QMAX_THREADS) return HAQ_ERR_UNSUPPORTED;  // K > 16384: not built for the asymmetric variant
     int G = QMAX_THREADS / CL;
     G = G >= 8 ? 8 : G >= 4 ? 4 : G >= 2 ? 2 : 1;
-    const int RS = QBLOCK_ROWS / G > 4 ? 4 : QBLOCK_ROWS / G;
-    const int threads = CL * G, nb = cdiv(T, RS * G);
+    const QuantSplit sp = short_split(T, CL, G, cu_count());
+    const int threads = CL * sp.G, nb = cdiv(T, sp.RS * sp.G);
     AsymQuantArgs a{x, ldx, s, T, K, q_cm, R, q_rm, ldq, scale, zp};
-    switch (RS) {
+    switch (sp.RS) {
         case 4: hipLaunchKernelGGL(asym_quant_kernel<4>, dim3(nb), dim3(threads), 0, st, a, CL); break;
         case 2: hipLaunchKernelGGL(asym_quant_kernel<2>, dim3(nb), dim3(threads), 0, st, a, CL); break;
         default: hipLaunchKernelGGL(asym_quant_kernel<1>, dim3(nb), dim3(threads), 0, st, a, CL); break;

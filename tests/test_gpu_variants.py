@@ -44,3 +44,23 @@ def test_short_batch_linear_at_the_edges_of_its_variants(T, K, N, act):
     """Row blocks of 16 (1, 2, 4, 6, 8 of them; 129 rows take the tiled GEMM), K-steps that do and do not divide among
     the eight waves and the prefetch depth, a last partial K-step, channel units past the last channel."""
     _linear_both_codes(T, K, N, act)
+
+
+@pytest.mark.parametrize("T,K", [(256, 816), (257, 80), (511, 4112), (1024, 528), (1025, 336), (256, 16384), (257, 8208), (1030, 1040)])
+def test_short_batch_quantisers_at_the_edges_of_their_row_split(T, K):
+    """One, two and eight rows per work-group (the line lies at one and at four rows per compute unit, 256 of them)."""
+    X, _, _ = hi.hidden_states(T + K, T, K, n_outlier=max(1, K // 200))
+    X[T // 2] = 0
+    W = hi.gaussian_weight(T + K, 0, K, 16)
+    s, Wq, sw = offline.quantize_linear(X, W)
+    q_ref, sx_ref = oracle.w8a8_linear(X, s, Wq, sw, "none", full=True)[2:]
+    q, sx = haq.haq_smooth_quant_act(dev(X), dev(s))
+    assert bits_equal(host(q), q_ref) and bits_equal(host(sx), sx_ref)
+    qp, sx = haq.haq_quant_act_packed(dev(X), dev(s))
+    rows = host(qp).reshape(-1, haq.haq_packed_act_rows(T), 16)[:K // 16, :T]
+    assert np.array_equal(rows.transpose(1, 0, 2).reshape(T, K), q_ref) and bits_equal(host(sx), sx_ref)
+    wq = dev(Wq)
+    y_ref, _, q_ref, sx_ref, zp_ref = oracle.w8a8_linear_asym(X, s, Wq, sw, "none", full=True)
+    y, _, q, sx, zp = haq.haq_w8a8_linear_asym(dev(X), dev(s), haq.haq_pack_weight(wq), dev(sw), haq.haq_weight_colsum(wq), 16, debug=True)
+    assert bits_equal(host(q), q_ref) and bits_equal(host(sx), sx_ref) and bits_equal(host(zp), zp_ref)
+    assert bits_equal(host(y), y_ref)
