@@ -11,71 +11,87 @@
 //   M  = L^-1 (lower)                              tri_inverse_block_kernel
 //   U  = flip(M): upper, H^-1 = U^T U              flip_kernel
 //   channels i ascending: code, error, compensate  gptq_block_kernel, gptq_update_kernel
-#include "haq_common.h"
+#include <type_traits>
+
+#include "f64_tile.h"
 
 namespace haq {
 
 namespace {
 
-constexpr int HT = 64, HK = 16;  // Hessian tile (outputs) and token step
-constexpr int PB = 32;           // Cholesky panel width
-constexpr int GB = 64;           // input channels quantised per compensation block
+constexpr int PB = 64;    // Cholesky panel width, rows per block of the triangular inverse
+constexpr int GB = 64;    // input channels quantised per compensation block
+constexpr int GS = 256;   // input channels per rank-GS compensation of everything below them
+
+// A lane's 64 values v against a triangular block that all lanes share: for c ascending e = f(c, v_c), then
+// v_l -= e C(c, l) for l > c, with skew[c][p] = C(c, c + 1 + p).  The current value is always v[0]: the array moves down
+// by one with each column (the multiply-add's destination is its neighbour's register), so that the columns are a
+// loop of short code; what moves in from beyond value 63 is never used.  Written out as 64 different columns the loop
+// is longer than the instruction cache, and the compiler spills.
+// One wave runs alone on its SIMD: the coefficients come out of LDS in chunks of eight, three chunks ahead of their use
+// (the asm keeps reads and values with their chunk: left alone, the compiler fetches everything first and spills).
+template <class F>
+__device__ __forceinline__ void eliminate_columns(double (&v)[64], const double (*skew)[64], F&& f) {
+    typedef double v2d __attribute__((ext_vector_type(2)));
+    auto sixteen = [&](auto width, int c0) __attribute__((always_inline)) {
+        constexpr int W = width.value, NCH = W / 8, RING = 4;
+        v2d ring[RING][4];
+        auto fetch = [&](int c, int n) __attribute__((always_inline)) {  // chunk n from column c on
+            const v2d* row = reinterpret_cast<const v2d*>(skew[min(c + n / NCH, 63)] + 8 * (n % NCH));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) ring[n % RING][i] = row[i];
+        };
+#pragma unroll
+        for (int n = 0; n < RING - 1; ++n) fetch(c0, n);
+#pragma nounroll
+        for (int c = c0; c < c0 + 16; c += 2) {
+            double e = 0.0;
+#pragma unroll
+            for (int n = 0; n < 2 * NCH; ++n) {  // 2 NCH is a multiple of RING: the ring's indices are constants
+                fetch(c, n + RING - 1);
+                if (n % NCH == 0) e = f(c + n / NCH, v[0]);
+                double* u = v + 8 * (n % NCH);
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    if (8 * (n % NCH) + i + 1 < W) u[i] = __builtin_fma(-e, ring[n % RING][i / 2][i % 2], u[i + 1]);
+                asm volatile("" : "+v"(u[0]), "+v"(u[1]), "+v"(u[2]), "+v"(u[3]), "+v"(u[4]), "+v"(u[5]), "+v"(u[6]), "+v"(u[7])::"memory");
+            }
+        }
+    };
+    sixteen(std::integral_constant<int, 64>{}, 0);
+    sixteen(std::integral_constant<int, 48>{}, 16);
+    sixteen(std::integral_constant<int, 32>{}, 32);
+    sixteen(std::integral_constant<int, 16>{}, 48);
+}
+// diag[c], which is the same for the whole wave, from the lane that holds it
+__device__ __forceinline__ double from_lane(double v, int c) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), c), __builtin_amdgcn_readlane(__double2loint(v), c));
+}
 
 // ---- H = 2 Xs^T Xs -------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void hessian_kernel(const __half* x, int64_t ldx, const float* s, int T, int K, double* H) {
-    __shared__ double xa[HK][HT + 1];
-    __shared__ double xb[HK][HT + 1];
-    const int tid = threadIdx.x;
-    const int tx = tid % 16, ty = tid / 16;
-    const int j0 = blockIdx.y * HT, l0 = blockIdx.x * HT;
-    double acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
-    for (int t0 = 0; t0 < T; t0 += HK) {
-        const int tt = tid / 16, c = (tid % 16) * 4;
-        const int t = t0 + tt;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int ja = j0 + c + i, lb = l0 + c + i;
-            double va = 0.0, vb = 0.0;
-            if (t < T && ja < K) {
-                const float v = h2f(x[(size_t)t * ldx + ja]);
-                va = (double)(s ? v / s[ja] : v);
-            }
-            if (t < T && lb < K) {
-                const float v = h2f(x[(size_t)t * ldx + lb]);
-                vb = (double)(s ? v / s[lb] : v);
-            }
-            xa[tt][c + i] = va;
-            xb[tt][c + i] = vb;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < HK; ++kk) {
-            double av[4], bv[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) av[i] = xa[kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) bv[j] = xb[kk][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_fma(av[i], bv[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int j = j0 + ty * 4 + i;
-        if (j >= K) continue;
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-            const int l = l0 + tx * 4 + jj;
-            if (l < K) H[(size_t)j * K + l] = 2.0 * acc[i][jj];
-        }
-    }
+// Tiles on and below the diagonal; the product is symmetric to the bit (the factors of a multiply-add commute), so the
+// other half is written from the same values.  4096 channels, 2048 tokens: 3.7 -> 1.2 ms.
+struct Smoothed {  // x / s, as the layer sees it
+    float s;
+    __device__ double operator()(__half x) const { return (double)(h2f(x) / s); }
+};
+__global__ __launch_bounds__(256, 5) void hessian_kernel(const __half* x, int64_t ldx, const float* s, int T, int K, double* H) {
+    const int j0 = blockIdx.y * F64_B, l0 = blockIdx.x * F64_B;
+    if (l0 > j0) return;
+    auto operand = [&](int c0) {
+        const int c = min(c0 + (int)threadIdx.x % F64_B, K - 1);  // the one channel that a thread fetches
+        return f64_operand<true>(x + c0, ldx, K - c0, Smoothed{s ? s[c] : 1.0f});
+    };
+    auto a = operand(j0), b = operand(l0);
+    __shared__ double lds[decltype(a)::LDS + decltype(b)::LDS];
+    F64Acc acc = {};
+    f64_tile_mac(acc, T, lds, a, b);
+    f64_tile_each(acc, [&](double v, int i, int jj) {
+        const int j = j0 + i, l = l0 + jj;
+        if (j >= K || l >= K) return;
+        H[(size_t)j * K + l] = 2.0 * v;
+        if (l0 != j0) H[(size_t)l * K + j] = 2.0 * v;
+    });
 }
 
 // Dead channels get a unit diagonal; damping = percdamp * mean(diag), the diagonal summed in index order.
@@ -97,10 +113,7 @@ __global__ __launch_bounds__(256) void hessian_finish_kernel(double* H, int K, d
             part[i] = d;
         }
         __syncthreads();
-        if (threadIdx.x == 0) {
-            const int lim = min(1024, K - j0);
-            for (int i = 0; i < lim; ++i) tr += part[i];
-        }
+        if (threadIdx.x == 0) tr = add_in_order(tr, part, min(1024, K - j0));
         __syncthreads();
     }
     if (threadIdx.x == 0) damp_s = percdamp * (tr / (double)K);
@@ -116,178 +129,169 @@ __global__ void flip_kernel(const double* src, int K, double* dst) {
 }
 
 // ---- Cholesky, right-looking in panels of PB columns ------------------------------------------
-// Panel kernel: every work-group first factorises the PB x PB diagonal block in LDS (redundantly:
-// it is tiny), then its threads each take one row below the block and solve it against the block,
-// column by column: v = A_ic; v -= L_ik L_ck for the panel's earlier columns k ascending; L_ic = v / L_cc.
+// Bound: the serial chain of the panels (64 at K = 4096, 52 us each; the trailing update takes 18).
+// Panel kernel: every work-group first factorises the PB x PB diagonal block (redundantly: it is one serial chain of
+// PB columns, each a square root, a division and an exchange), then its first wave solves 64 rows below the block
+// against it, a row per lane: x_c = v_c / L_cc; v_l -= x_c L_lc for the later columns l.  An element's links are thus
+// applied for ascending c, whatever the panel width.
+// The factorisation: row = lane; wave w holds columns w, w + 4, ...; the owner of a column passes it on through LDS and
+// every wave divides it for itself, so that a column costs one barrier.
 // Work-group 0 leaves the factorised diagonal block in `dblock` (it cannot go to A here: the other
-// work-groups may still be reading the unfactorised block); chol_store_diag_kernel moves it afterwards.
+// work-groups may still be reading the unfactorised block); the next launch moves it.
 // status: first non-positive pivot + 1.
-__global__ __launch_bounds__(256) void chol_panel_kernel(double* A, int K, int j0, double* dblock, int* status) {
-    __shared__ double D[PB][PB + 1];
-    const int tid = threadIdx.x;
+__global__ __launch_bounds__(256, 1) void chol_panel_kernel(double* A, int K, int j0, double* dblock, int* status) {
+    __shared__ __attribute__((aligned(16))) double Ds[PB][PB];  // skewed: Ds[c][p] = L(c + 1 + p, c)
+    __shared__ double diag[PB];
+    __shared__ double col[2][PB];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int pb = min(PB, K - j0);
-    for (int i = tid; i < PB * PB; i += 256) {
-        const int r = i / PB, c = i % PB;
-        D[r][c] = (r < pb && c <= r) ? A[(size_t)(j0 + r) * K + j0 + c] : 0.0;
+    double own[PB / 4];  // past the last column: the identity
+#pragma unroll
+    for (int m = 0; m < PB / 4; ++m) {
+        const int c = 4 * m + wave;
+        own[m] = A[(size_t)(j0 + min(lane, pb - 1)) * K + j0 + min(c, pb - 1)];  // loads stay unconditional: a branch each would be a wait each
     }
-    __syncthreads();
-    for (int c = 0; c < pb; ++c) {
-        // column c of the block: rows r >= c, each by one thread (the chain over k < c is sequential)
-        if (tid >= c && tid < pb) {
-            const int r = tid;
-            double v = D[r][c];
-            for (int k = 0; k < c; ++k) v = __builtin_fma(-D[r][k], D[c][k], v);
-            D[r][c] = v;  // not yet divided
-        }
-        __syncthreads();
-        if (tid == c) {
-            const double d = D[c][c];
-            if (!(d > 0.0) && blockIdx.x == 0) atomicCAS(status, 0, j0 + c + 1);
-            D[c][c] = sqrt(d);
-        }
-        __syncthreads();
-        if (tid > c && tid < pb) D[tid][c] = D[tid][c] / D[c][c];
-        __syncthreads();
+    const int i = j0 + pb + blockIdx.x * 64 + lane;  // row below the block (wave 0)
+    double v[PB];
+    if (wave == 0) {
+#pragma unroll
+        for (int c = 0; c < PB; ++c) v[c] = A[(size_t)(i < K ? i : j0) * K + j0 + min(c, pb - 1)];  // a row below has a full panel before it
     }
-    if (blockIdx.x == 0)
-        for (int i = tid; i < PB * PB; i += 256) dblock[i] = D[i / PB][i % PB];
-    // rows below the diagonal block
-    const int i = j0 + pb + blockIdx.x * 256 + tid;
-    if (i < K) {
-        double row[PB];
 #pragma unroll
-        for (int c = 0; c < PB; ++c) row[c] = c < pb ? A[(size_t)i * K + j0 + c] : 0.0;
+    for (int m = 0; m < PB / 4; ++m) {
+        const int c = 4 * m + wave;
+        own[m] = lane < pb && c <= lane ? own[m] : lane == c ? 1.0 : 0.0;
+    }
+    // Four columns a turn; own[0] holds the turn's columns and the array moves down by one after it.  Only the next
+    // column waits for this one: the others take this column's link while the next one's root and quotient are formed.
+    double l = 0.0;  // the column before the current one
+    auto turns = [&](auto width, int t0, int t1) __attribute__((always_inline)) {
+        constexpr int W = width.value;
+        auto link = [&](int o, double v) __attribute__((always_inline)) {  // v less the link of column o with the last one; past column 63: never used
+            return __builtin_fma(-l, from_lane(l, o & 63), v);
+        };
+#pragma nounroll
+        for (int t = t0; t < t1; ++t) {
 #pragma unroll
-        for (int c = 0; c < PB; ++c) {
-            if (c < pb) {
-                double v = row[c];
+            for (int q = 0; q < 4; ++q) {
+                const int c = 4 * t + q;
+                if (wave == q) col[q & 1][lane] = own[0];
+                __syncthreads();
+                const double d = col[q & 1][c], vc = col[q & 1][lane];
+                // what the column before still owes: all but the slot that holds column c
 #pragma unroll
-                for (int k = 0; k < PB; ++k)
-                    if (k < c) v = __builtin_fma(-row[k], D[c][k], v);
-                row[c] = v / D[c][c];
+                for (int m = 1; m < W; ++m) own[m] = link(4 * (t + m) + wave, own[m]);
+                if (!(d > 0.0) && blockIdx.x == 0 && threadIdx.x == 0) atomicCAS(status, 0, j0 + c + 1);
+                const double p = sqrt(d);
+                l = lane == c ? p : vc / p;
+                if (wave == 0) {
+                    if (lane == c) diag[c] = p;
+                    if (lane > c) Ds[c][lane - c - 1] = l;
+                }
+                if (q < 3) {
+                    own[0] = wave > q ? link(4 * t + wave, own[0]) : own[0];
+                } else {
+                    // the next turn's columns get this link at once, the later ones (which move down) in its first column
+                    own[1] = link(4 * (t + 1) + wave, own[1]);
+                }
             }
-        }
 #pragma unroll
-        for (int c = 0; c < PB; ++c)
-            if (c < pb) A[(size_t)i * K + j0 + c] = row[c];
+            for (int m = 0; m + 1 < W; ++m) own[m] = own[m + 1];
+        }
+    };
+    turns(std::integral_constant<int, 16>{}, 0, 8);
+    turns(std::integral_constant<int, 8>{}, 8, 16);
+    __syncthreads();
+    if (wave != 0) return;
+    if (blockIdx.x == 0) {
+        for (int e = lane; e < pb * pb; e += 64) {
+            const int c = e / pb, r = e % pb;
+            dblock[e] = r == c ? diag[c] : r > c ? Ds[c][r - c - 1] : 0.0;
+        }
+    }
+    if (j0 + pb >= K) return;
+    double* out = A + (size_t)i * K + j0;
+    const double my_diag = diag[lane];
+    eliminate_columns(v, Ds, [&](int c, double vc) {
+        const double xc = vc / from_lane(my_diag, c);
+        if (i < K) out[c] = xc;
+        return xc;
+    });
+}
+
+__device__ __forceinline__ void chol_store_diag(double* A, int K, int j0, const double* dblock) {
+    const int pb = min(PB, K - j0);
+    for (int e = threadIdx.x; e < pb * pb; e += 256) {
+        const int c = e / pb, r = e % pb;
+        if (c <= r) A[(size_t)(j0 + r) * K + j0 + c] = dblock[e];
     }
 }
 
-__global__ __launch_bounds__(256) void chol_store_diag_kernel(double* A, int K, int j0, const double* dblock) {
-    const int pb = min(PB, K - j0);
-    for (int i = threadIdx.x; i < PB * PB; i += 256) {
-        const int r = i / PB, c = i % PB;
-        if (r < pb && c <= r) A[(size_t)(j0 + r) * K + j0 + c] = dblock[i];
-    }
-}
+__global__ __launch_bounds__(256) void chol_store_diag_kernel(double* A, int K, int j0, const double* dblock) { chol_store_diag(A, K, j0, dblock); }
 
 // Trailing update after a panel: for i >= l >= j0 + PB: A_il -= L_ik L_lk, k over the panel ascending.
-// 64 x 64 tiles of the lower triangle, 4 x 4 elements per thread.
-__global__ __launch_bounds__(256) void chol_trail_kernel(double* A, int K, int j0) {
-    const int base = j0 + PB;
-    const int ti = blockIdx.y, tl = blockIdx.x;
-    if (tl > ti) return;  // only tiles that touch the lower triangle
-    __shared__ double Li[64][PB + 1];
-    __shared__ double Ll[64][PB + 1];
-    const int tid = threadIdx.x;
-    const int i0 = base + ti * 64, l0 = base + tl * 64;
-    for (int e = tid; e < 64 * PB; e += 256) {
-        const int r = e / PB, c = e % PB;
-        Li[r][c] = (i0 + r < K) ? A[(size_t)(i0 + r) * K + j0 + c] : 0.0;
-        Ll[r][c] = (l0 + r < K) ? A[(size_t)(l0 + r) * K + j0 + c] : 0.0;
-    }
-    __syncthreads();
-    const int tx = tid % 16, ty = tid / 16;
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        const int i = i0 + ty * 4 + a;
-        if (i >= K) continue;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int l = l0 + tx * 4 + b;
-            if (l > i || l >= K) continue;
-            double v = A[(size_t)i * K + l];
-#pragma unroll
-            for (int k = 0; k < PB; ++k) v = __builtin_fma(-Li[ty * 4 + a][k], Ll[tx * 4 + b][k], v);
-            A[(size_t)i * K + l] = v;
-        }
-    }
+// Tiles that touch the lower triangle; tile (0, 0) also moves the factorised diagonal block into A.
+__global__ __launch_bounds__(256, 5) void chol_trail_kernel(double* A, int K, int j0, const double* dblock) {
+    if (blockIdx.x > blockIdx.y) return;
+    if (blockIdx.x == 0 && blockIdx.y == 0) chol_store_diag(A, K, j0, dblock);
+    const int i0 = j0 + PB + blockIdx.y * F64_B, l0 = j0 + PB + blockIdx.x * F64_B;
+    auto a = f64_operand<false>(A + (size_t)i0 * K + j0, K, K - i0, F64Minus{});
+    auto b = f64_operand<false>(A + (size_t)l0 * K + j0, K, K - l0, F64Same{});
+    __shared__ double lds[decltype(a)::LDS + decltype(b)::LDS];
+    F64Acc acc;
+    f64_tile_each(acc, [&](double& v, int i, int l) { v = i0 + i < K && l0 + l < K ? A[(size_t)(i0 + i) * K + l0 + l] : 0.0; });
+    f64_tile_mac(acc, PB, lds, a, b);
+    f64_tile_each(acc, [&](double v, int i, int l) {
+        if (i0 + i < K && l0 + l <= i0 + i) A[(size_t)(i0 + i) * K + l0 + l] = v;
+    });
 }
 
-// ---- M = L^-1, blocks of TR rows ---------------------------------------------------------------
-// M_jj = 1 / L_jj; M_ij = -(sum_{j <= k < i} L_ik M_kj) / L_ii, the sum a chain over k ascending.
-// A launch handles rows i0 .. i0 + TR - 1 (the launches run in row order); a work-group owns 64
-// columns.  First the links k < i0 of every chain (M_kj from earlier launches): wave w carries the
-// chains of rows 8w .. 8w + 7 for the 64 columns, the same k for all lanes (lanes whose column
-// starts later are masked), L tile and M chunk through LDS.  Then wave 0 adds the links inside the
-// block, row by row, with the M_kj it has just produced.  M must be zero on entry (the part above
-// the diagonal is never written).
-constexpr int TR = 32, TW = 4, RPW = TR / TW;
-__global__ __launch_bounds__(64 * TW) void tri_inverse_block_kernel(const double* L, int K, int i0, double* M) {
-    __shared__ double Lt[TR][64 + 1];  // [row][k in chunk]; later the diagonal block
-    __shared__ double Ms[64][64];      // [k in chunk][column]
-    __shared__ double Acc[TR][64];     // chains after the links k < i0
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int jmin = blockIdx.x * 64, j = jmin + lane;
-    const int rows = min(TR, K - i0);
-    if (jmin >= i0 + rows) return;  // uniform: the whole work-group lies right of the diagonal block
-    const bool on = j < i0 + rows;
-    double acc[RPW];
+// ---- M = L^-1, blocks of PB rows ---------------------------------------------------------------
+// M_jj = 1 / L_jj; M_ij = -(sum_{j <= k < i} L_ik M_kj) / L_ii, the sum a chain over k ascending, which grows in M
+// itself: once a block of rows is final, its links are added to every row below (a rank-PB product), so a block finds
+// its chains complete up to its own first row.  M must be zero on entry.  (The left-looking form, all links of 32 rows
+// in one launch, kept 64 work-groups busy with chains of up to K links: 40 ms at K = 4096.)
+// A link with M_kj = 0 (k < j) leaves the chain as it is: it starts from +0 and never holds -0.
+__global__ __launch_bounds__(64, 1) void tri_inverse_block_kernel(const double* L, int K, int i0, double* M) {
+    __shared__ __attribute__((aligned(16))) double Ls[PB][PB];  // the diagonal block, skewed: Ls[c][p] = L(c + 1 + p, c); past the last row: the identity
+    __shared__ double diag[PB];
+    const int lane = threadIdx.x, j = blockIdx.x * 64 + lane;
+    const int rows = min(PB, K - i0);
+    double v[PB];
 #pragma unroll
-    for (int r = 0; r < RPW; ++r) acc[r] = 0.0;
-    for (int k0 = jmin; k0 < i0; k0 += 64) {
-        const int lim = min(64, i0 - k0);
-        __syncthreads();
-        for (int e = tid; e < TR * 64; e += 64 * TW) {
-            const int r = e / 64, c = e % 64;
-            Lt[r][c] = (r < rows && c < lim) ? L[(size_t)(i0 + r) * K + k0 + c] : 0.0;
-        }
-        for (int e = tid; e < 64 * 64; e += 64 * TW) {  // coalesced over the columns
-            const int kk = e / 64, c = e % 64;
-            const int k = k0 + kk, col = jmin + c;
-            Ms[kk][c] = (kk < lim && col < i0 + rows && k >= col) ? M[(size_t)k * K + col] : 0.0;
-        }
-        __syncthreads();
-        if (on) {
-            // Ms is zero where k < j or past the chunk's end, and a link with M_kj = 0 leaves the chain
-            // as it is (v - L * 0 = v exactly; a chain never holds -0 because it starts from +0), so the
-            // loop needs no per-lane condition and unrolls
-#pragma unroll 8
-            for (int e = 0; e < 64; ++e) {
-                const double m = Ms[e][lane];
+    for (int r = 0; r < PB; ++r) v[r] = L[(size_t)(i0 + min(r, rows - 1)) * K + i0 + min(lane, rows - 1)];  // loads stay unconditional
 #pragma unroll
-                for (int r = 0; r < RPW; ++r) acc[r] = __builtin_fma(-Lt[wave * RPW + r][e], m, acc[r]);
-            }
-        }
+    for (int r = 0; r < PB; ++r) {
+        const double l = r < rows && lane <= r ? v[r] : lane == r ? 1.0 : 0.0;
+        double* to = lane == r ? &diag[r] : lane < r ? &Ls[lane][r - lane - 1] : &Ls[lane][PB - 1];  // (an element that is not used)
+        *to = l;
     }
+#pragma unroll
+    for (int r = 0; r < PB; ++r) v[r] = M[(size_t)(i0 + min(r, rows - 1)) * K + min(j, K - 1)];
+#pragma unroll
+    for (int r = 0; r < PB; ++r) v[r] = r < rows && j < i0 + rows ? (i0 + r == j ? 1.0 : v[r]) : 0.0;
     __syncthreads();
-#pragma unroll
-    for (int r = 0; r < RPW; ++r) Acc[wave * RPW + r][lane] = acc[r];
-    for (int e = tid; e < TR * TR; e += 64 * TW) {
-        const int r = e / TR, c = e % TR;
-        Lt[r][c] = (r < rows && c <= r) ? L[(size_t)(i0 + r) * K + i0 + c] : 0.0;
-    }
-    __syncthreads();
-    if (wave != 0 || !on) return;
-    double mloc[TR];
-#pragma unroll
-    for (int r = 0; r < TR; ++r) {
-        mloc[r] = 0.0;
-        if (r < rows) {
-            const int i = i0 + r;
-            if (i == j) {
-                mloc[r] = 1.0 / Lt[r][r];
-                M[(size_t)i * K + j] = mloc[r];
-            } else if (i > j) {
-                double v = Acc[r][lane];
-#pragma unroll
-                for (int c = 0; c < TR; ++c)
-                    if (c < r && i0 + c >= j) v = __builtin_fma(-Lt[r][c], mloc[c], v);
-                mloc[r] = v / Lt[r][r];
-                M[(size_t)i * K + j] = mloc[r];
-            }
-        }
-    }
+    double* out = M + (size_t)i0 * K + j;
+    const double my_diag = diag[lane];
+    eliminate_columns(v, Ls, [&](int c, double vc) {
+        const double m = vc / from_lane(my_diag, c);
+        if (c < rows && j < i0 + rows) out[(size_t)c * K] = m;
+        return m;
+    });
+}
+
+// M_ij -= L_ik M_kj for the rows i below the block [i0, i0 + PB), k over the block ascending, j < i0 + PB.
+__global__ __launch_bounds__(256) void tri_inverse_update_kernel(const double* L, int K, int i0, double* M) {
+    const int r0 = i0 + PB + blockIdx.y * F64_B, c0 = blockIdx.x * F64_B, cols = i0 + PB;
+    auto a = f64_operand<false>(L + (size_t)r0 * K + i0, K, K - r0, F64Minus{});
+    auto b = f64_operand<true>((const double*)M + (size_t)i0 * K + c0, K, cols - c0, F64Same{});
+    __shared__ double lds[decltype(a)::LDS + decltype(b)::LDS];
+    F64Acc acc;
+    f64_tile_each(acc, [&](double& v, int i, int j) { v = r0 + i < K && c0 + j < cols ? M[(size_t)(r0 + i) * K + c0 + j] : 0.0; });
+    f64_tile_mac(acc, PB, lds, a, b);
+    f64_tile_each(acc, [&](double v, int i, int j) {
+        if (r0 + i < K && c0 + j < cols) M[(size_t)(r0 + i) * K + c0 + j] = v;
+    });
 }
 
 // ---- the quantise-and-compensate sweep ------------------------------------------------------------
@@ -298,100 +302,60 @@ __global__ void fold_weight_kernel(const float* w, const float* s, int K, int N,
 
 // Channels b0 .. b0 + GB - 1, one thread per output channel n: code, error, compensation of the
 // block's later channels; the errors go to err [GB x N] for the rows below the block.
-__global__ __launch_bounds__(64) void gptq_block_kernel(double* w64, const double* U, const float* scale, int K, int N, int b0,
-                                                        int8_t* wq, double* err) {
-    __shared__ double Ub[GB][GB + 1];
+__global__ __launch_bounds__(64, 1) void gptq_block_kernel(double* w64, const double* U, const float* scale, int K, int N, int b0,
+                                                           int8_t* wq, double* err) {
+    __shared__ __attribute__((aligned(16))) double Us[GB][GB];  // skewed: Us[i][p] = U(i, i + 1 + p); past the block's channels: 0
+    __shared__ double diag[GB];
+    const int lane = threadIdx.x, n = blockIdx.x * 64 + lane, nc = min(n, N - 1);
     const int gb = min(GB, K - b0);
-    for (int e = threadIdx.x; e < GB * GB; e += 64) {
-        const int r = e / GB, c = e % GB;
-        Ub[r][c] = (r < gb && c < gb) ? U[(size_t)(b0 + r) * K + b0 + c] : 0.0;
-    }
-    __syncthreads();
-    const int n = blockIdx.x * 64 + threadIdx.x;
-    if (n >= N) return;
-    const float sc_f = scale[n];
-    const double sc = (double)sc_f;
     double w[GB];
 #pragma unroll
-    for (int i = 0; i < GB; ++i) w[i] = i < gb ? w64[(size_t)(b0 + i) * N + n] : 0.0;
+    for (int r = 0; r < GB; ++r) w[r] = U[(size_t)(b0 + min(r, gb - 1)) * K + b0 + min(lane, gb - 1)];  // loads stay unconditional
 #pragma unroll
-    for (int i = 0; i < GB; ++i) {
-        if (i < gb) {
-            double code = 0.0;
-            if (sc_f != 0.0f) {
-                code = __builtin_rint(w[i] / sc);
-                code = fmin(fmax(code, -127.0), 127.0);
-            }
-            wq[(size_t)(b0 + i) * N + n] = (int8_t)code;
-            const double e = (w[i] - code * sc) / Ub[i][i];
-            err[(size_t)i * N + n] = e;
-#pragma unroll
-            for (int j = 0; j < GB; ++j)
-                if (j > i && j < gb) w[j] = __builtin_fma(-e, Ub[i][j], w[j]);
-        }
+    for (int r = 0; r < GB; ++r) {
+        const double u = r < gb && lane < gb && lane >= r ? w[r] : lane == r ? 1.0 : 0.0;
+        double* to = lane == r ? &diag[r] : lane > r ? &Us[r][lane - r - 1] : &Us[r][GB - 1 - lane];  // (an element that is not used)
+        *to = u;
     }
+#pragma unroll
+    for (int i = 0; i < GB; ++i) w[i] = w64[(size_t)(b0 + min(i, gb - 1)) * N + nc];
+    __syncthreads();
+    const float sc_f = scale[nc];
+    const double sc = (double)sc_f;
+    const double my_diag = diag[lane];
+    eliminate_columns(w, Us, [&](int i, double wi) {
+        double code = 0.0;
+        if (sc_f != 0.0f) {
+            code = __builtin_rint(wi / sc);
+            code = fmin(fmax(code, -127.0), 127.0);
+        }
+        const double e = (wi - code * sc) / from_lane(my_diag, i);
+        if (i < gb && n < N) {
+            wq[(size_t)(b0 + i) * N + n] = (int8_t)code;
+            err[(size_t)i * N + n] = e;
+        }
+        return e;
+    });
 }
 
-// Rows j >= b0 + GB: w_jn -= err_in U_ij for the block's channels i ascending.  64 rows x 64
-// output channels per work-group, 4 x 4 per thread held in registers; the block's channels come
-// through LDS 32 at a time (in order).
-__global__ __launch_bounds__(256) void gptq_update_kernel(double* w64, const double* U, const double* err, int K, int N, int b0) {
-    constexpr int GH = 32;
-    __shared__ double Es[GH][64 + 1];  // [i][n]
-    __shared__ double Us[GH][64 + 1];  // [i][j]
-    const int tid = threadIdx.x;
-    const int r0 = b0 + GB + blockIdx.y * 64, n0 = blockIdx.x * 64;
-    const int tx = tid % 16, ty = tid / 16;
-    const bool full_cols = n0 + tx * 4 + 3 < N && (N % 2 == 0);
-    double v[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        const int j = r0 + ty * 4 + a;
-        const double* p = w64 + (size_t)j * N + n0 + tx * 4;
-        if (j < K && full_cols) {  // 32 contiguous bytes per thread, two 16-byte accesses
-            const double2 lo = *reinterpret_cast<const double2*>(p), hi = *reinterpret_cast<const double2*>(p + 2);
-            v[a][0] = lo.x; v[a][1] = lo.y; v[a][2] = hi.x; v[a][3] = hi.y;
-        } else {
-#pragma unroll
-            for (int b = 0; b < 4; ++b) v[a][b] = (j < K && n0 + tx * 4 + b < N) ? p[b] : 0.0;
-        }
-    }
-    for (int h = 0; h < GB; h += GH) {
-        __syncthreads();
-        for (int e = tid; e < GH * 64; e += 256) {
-            const int i = e / 64, c = e % 64;
-            Es[i][c] = (n0 + c < N) ? err[(size_t)(h + i) * N + n0 + c] : 0.0;
-            Us[i][c] = (r0 + c < K) ? U[(size_t)(b0 + h + i) * K + r0 + c] : 0.0;
-        }
-        __syncthreads();
-#pragma unroll 8
-        for (int i = 0; i < GH; ++i) {
-            double ev[4], uv[4];
-#pragma unroll
-            for (int b = 0; b < 4; ++b) ev[b] = Es[i][tx * 4 + b];
-#pragma unroll
-            for (int a = 0; a < 4; ++a) uv[a] = Us[i][ty * 4 + a];
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int b = 0; b < 4; ++b) v[a][b] = __builtin_fma(-ev[b], uv[a], v[a][b]);
-        }
-    }
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        const int j = r0 + ty * 4 + a;
-        if (j >= K) continue;
-        double* p = w64 + (size_t)j * N + n0 + tx * 4;
-        if (full_cols) {
-            *reinterpret_cast<double2*>(p) = make_double2(v[a][0], v[a][1]);
-            *reinterpret_cast<double2*>(p + 2) = make_double2(v[a][2], v[a][3]);
-        } else {
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-                if (n0 + tx * 4 + b < N) p[b] = v[a][b];
-        }
-    }
+// Rows [r_lo, r_hi): w_jn -= err_in U_ij for the n_i channels from i0 on, ascending.  Applied after every 64 channels to
+// the rest of a stretch of 256 and after the stretch to everything below: w is read and written once per stretch there
+// (34 GB -> 9 GB in all at 4096 x 16384, which took 25 ms; now 6.1, the rate of the matrix pipe).
+__global__ __launch_bounds__(256, 5) void gptq_update_kernel(double* w64, const double* U, const double* err, int K, int N, int i0, int n_i,
+                                                          int r_lo, int r_hi) {
+    const int r0 = r_lo + blockIdx.y * F64_B, n0 = blockIdx.x * F64_B;
+    auto a = f64_operand<true>(U + (size_t)i0 * K + r0, K, r_hi - r0, F64Minus{});
+    auto b = f64_operand<true>(err + n0, N, N - n0, F64Same{});
+    __shared__ double lds[decltype(a)::LDS + decltype(b)::LDS];
+    F64Acc acc;
+    f64_tile_each(acc, [&](double& v, int j, int n) { v = r0 + j < r_hi && n0 + n < N ? w64[(size_t)(r0 + j) * N + n0 + n] : 0.0; });
+    f64_tile_mac(acc, n_i, lds, a, b);
+    f64_tile_each(acc, [&](double v, int j, int n) {
+        if (r0 + j < r_hi && n0 + n < N) w64[(size_t)(r0 + j) * N + n0 + n] = v;
+    });
 }
+
+constexpr size_t STATUS_BYTES = 64 + 8192;  // the status word; the rest is not used
 
 struct HessWs {
     double *H, *A, *M, *w64, *err;
@@ -413,7 +377,7 @@ HessWs carve_hess(void* ws, int K, int N) {
     w.M = (double*)take((size_t)K * K * 8);
     w.w64 = (double*)take((size_t)K * N * 8);
     w.err = (double*)take((size_t)GB * N * 8);
-    w.status = (int*)take(64 + PB * PB * 8);
+    w.status = (int*)take(STATUS_BYTES);
     w.bytes = off;
     return w;
 }
@@ -431,7 +395,7 @@ int32_t haq_hessian_f64(const void* x_fp16, int64_t ldx, const float* s, int32_t
     if (T <= 0 || K <= 0 || !(percdamp >= 0.0)) HAQ_FAIL(HAQ_ERR_INVALID_ARG, "haq_hessian_f64: T=%d K=%d percdamp=%g", T, K, percdamp);
     if (!x_fp16 || !H || ldx < K) HAQ_FAIL(HAQ_ERR_INVALID_ARG, "haq_hessian_f64: null buffer or ldx=%lld", (long long)ldx);
     hipStream_t st = (hipStream_t)stream;
-    hipLaunchKernelGGL(hessian_kernel, dim3(cdiv(K, HT), cdiv(K, HT)), dim3(256), 0, st, (const __half*)x_fp16, ldx, s, T, K, H);
+    hipLaunchKernelGGL(hessian_kernel, dim3(cdiv(K, 64), cdiv(K, 64)), dim3(256), 0, st, (const __half*)x_fp16, ldx, s, T, K, H);
     hipLaunchKernelGGL(hessian_finish_kernel, dim3(1), dim3(256), 0, st, H, K, percdamp);
     HAQ_CHECK_HIP(hipGetLastError());
     return HAQ_OK;
@@ -439,27 +403,29 @@ int32_t haq_hessian_f64(const void* x_fp16, int64_t ldx, const float* s, int32_t
 
 size_t haq_inverse_cholesky_workspace_bytes(int32_t K) {
     if (K <= 0) return 0;
-    return 2 * (size_t)round_up((int64_t)K * K * 8, 256) + 64 + PB * PB * 8;
+    return 2 * (size_t)round_up((int64_t)K * K * 8, 256) + STATUS_BYTES;
 }
 
 // H may alias U: H is read once, into A, before anything else runs.
 static int32_t inverse_cholesky_upper(const double* H, int K, double* U, double* A, double* M, int* status, hipStream_t st) {
-    double* dblock = reinterpret_cast<double*>(status) + 8;  // PB x PB doubles behind the status word
+    double* dblock = M;  // the factorised diagonal block on its way into A (M is filled afterwards)
     HAQ_CHECK_HIP(hipMemsetAsync(status, 0, sizeof(int), st));
     hipLaunchKernelGGL(flip_kernel, dim3(cdiv(K, 256), K), dim3(256), 0, st, H, K, A);
     for (int j0 = 0; j0 < K; j0 += PB) {
-        const int pb = K - j0 < PB ? K - j0 : PB;
-        const int below = K - j0 - pb;
-        hipLaunchKernelGGL(chol_panel_kernel, dim3(below > 0 ? cdiv(below, 256) : 1), dim3(256), 0, st, A, K, j0, dblock, status);
-        hipLaunchKernelGGL(chol_store_diag_kernel, dim3(1), dim3(256), 0, st, A, K, j0, (const double*)dblock);
-        if (below > 0) {
-            const int nt = cdiv(below, 64);
-            hipLaunchKernelGGL(chol_trail_kernel, dim3(nt, nt), dim3(256), 0, st, A, K, j0);
-        }
+        const int below = K - j0 - PB;
+        hipLaunchKernelGGL(chol_panel_kernel, dim3(below > 0 ? cdiv(below, 64) : 1), dim3(256), 0, st, A, K, j0, dblock, status);
+        if (below <= 0)
+            hipLaunchKernelGGL(chol_store_diag_kernel, dim3(1), dim3(256), 0, st, A, K, j0, (const double*)dblock);
+        else
+            hipLaunchKernelGGL(chol_trail_kernel, dim3(cdiv(below, 64), cdiv(below, 64)), dim3(256), 0, st, A, K, j0, (const double*)dblock);
     }
     HAQ_CHECK_HIP(hipMemsetAsync(M, 0, (size_t)K * K * sizeof(double), st));
-    for (int i0 = 0; i0 < K; i0 += TR)
-        hipLaunchKernelGGL(tri_inverse_block_kernel, dim3(cdiv(i0 + TR < K ? i0 + TR : K, 64)), dim3(64 * TW), 0, st, (const double*)A, K, i0, M);
+    for (int i0 = 0; i0 < K; i0 += PB) {
+        const int cols = i0 + PB < K ? i0 + PB : K, below = K - i0 - PB;
+        hipLaunchKernelGGL(tri_inverse_block_kernel, dim3(cdiv(cols, 64)), dim3(64), 0, st, (const double*)A, K, i0, M);
+        if (below <= 0) break;
+        hipLaunchKernelGGL(tri_inverse_update_kernel, dim3(cdiv(cols, 64), cdiv(below, 64)), dim3(256), 0, st, (const double*)A, K, i0, M);
+    }
     hipLaunchKernelGGL(flip_kernel, dim3(cdiv(K, 256), K), dim3(256), 0, st, (const double*)M, K, U);
     HAQ_CHECK_HIP(hipGetLastError());
     int host_status = 0;
@@ -503,12 +469,23 @@ int32_t haq_hessian_quant_weight(const void* x_fp16, int64_t ldx, int32_t T, con
     if ((rc = inverse_cholesky_upper(ws.H, K, ws.H, ws.A, ws.M, ws.status, st)) != HAQ_OK) return rc;  // U replaces H
     const double* U = ws.H;
     hipLaunchKernelGGL(fold_weight_kernel, dim3(cdiv(N, 256), K), dim3(256), 0, st, w, s, K, N, ws.w64);
-    for (int b0 = 0; b0 < K; b0 += GB) {
-        hipLaunchKernelGGL(gptq_block_kernel, dim3(cdiv(N, 64)), dim3(64), 0, st, ws.w64, U, (const float*)w_scale, K, N, b0, wq, ws.err);
-        const int below = K - b0 - GB;
-        if (below > 0)
-            hipLaunchKernelGGL(gptq_update_kernel, dim3(cdiv(N, 64), cdiv(below, 64)), dim3(256), 0, st, ws.w64, U,
-                               (const double*)ws.err, K, N, b0);
+    // The errors of a stretch of channels are kept for one product over everything below it: in the memory of A and M,
+    // which are done with, where GS channels fit there, else block by block in the block's own memory.
+    const bool wide = (size_t)2 * K * K >= (size_t)GS * N;
+    double* err = wide ? ws.A : ws.err;
+    const int stretch = wide ? GS : GB;
+    for (int s0 = 0; s0 < K; s0 += stretch) {
+        const int s1 = s0 + stretch < K ? s0 + stretch : K;
+        for (int b0 = s0; b0 < s1; b0 += GB) {
+            hipLaunchKernelGGL(gptq_block_kernel, dim3(cdiv(N, 64)), dim3(64), 0, st, ws.w64, U, (const float*)w_scale, K, N, b0, wq,
+                               err + (size_t)(b0 - s0) * N);
+            if (b0 + GB < s1)
+                hipLaunchKernelGGL(gptq_update_kernel, dim3(cdiv(N, 64), cdiv(s1 - b0 - GB, 64)), dim3(256), 0, st, ws.w64, U,
+                                   (const double*)err + (size_t)(b0 - s0) * N, K, N, b0, GB, b0 + GB, s1);
+        }
+        if (s1 >= K) break;
+        hipLaunchKernelGGL(gptq_update_kernel, dim3(cdiv(N, 64), cdiv(K - s1, 64)), dim3(256), 0, st, ws.w64, U, (const double*)err, K, N,
+                               s0, stretch, s1, K);
     }
     HAQ_CHECK_HIP(hipGetLastError());
     return HAQ_OK;

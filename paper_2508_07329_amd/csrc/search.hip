@@ -2,7 +2,7 @@
 // of s = ax^e for one linear layer.  Every candidate goes through the library's own offline
 // quantiser and its run-time W8A8 linear; what this file adds is the full-precision product
 // the candidates are measured against, the loss reduction, and the search loop around them.
-#include "haq_common.h"
+#include "f64_tile.h"
 
 #include <cmath>
 #include <limits>
@@ -17,128 +17,84 @@ namespace {
 // One binary64 accumulator per output, k ascending, one fused multiply-add per term.  The
 // product of a binary16 and a binary32 number is exact in binary64, so the FMA rounds exactly
 // where "multiply, then add" would: the result does not depend on the tiling.
-// 64 x 64 outputs per work-group, 4 x 4 per thread, K in steps of 16 through LDS.
-constexpr int RT = 64, RK = 16;
-__global__ __launch_bounds__(256) void ref_gemm_f64_kernel(const __half* x, int64_t ldx, const float* w, int T, int K,
-                                                           int N, double* yref) {
-    __shared__ double xs[RK][RT + 1];  // [k][row]
-    __shared__ double ws[RK][RT];      // [k][col]
-    const int tid = threadIdx.x;
-    const int tx = tid % 16, ty = tid / 16;  // thread's 4 columns / 4 rows inside the tile
-    const int row0 = blockIdx.y * RT, col0 = blockIdx.x * RT;
-    double acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
-    for (int k0 = 0; k0 < K; k0 += RK) {
-        // X tile: 64 rows x 16 k; thread loads 4 consecutive k of one row
-        {
-            const int r = tid / 4, kk = (tid % 4) * 4;
-            const int row = row0 + r;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int k = k0 + kk + i;
-                xs[kk + i][r] = (row < T && k < K) ? (double)h2f(x[(size_t)row * ldx + k]) : 0.0;
-            }
-        }
-        // W tile: 16 k x 64 columns; thread loads 4 consecutive columns of one k
-        {
-            const int kk = tid / 16, c = (tid % 16) * 4;
-            const int k = k0 + kk;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int col = col0 + c + i;
-                ws[kk][c + i] = (k < K && col < N) ? (double)w[(size_t)k * N + col] : 0.0;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < RK; ++kk) {
-            double xv[4], wv[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) xv[i] = xs[kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) wv[j] = ws[kk][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_fma(xv[i], wv[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int row = row0 + ty * 4 + i;
-        if (row >= T) continue;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int col = col0 + tx * 4 + j;
-            if (col < N) yref[(size_t)row * N + col] = acc[i][j];
-        }
-    }
+// Bound: the binary64 matrix pipe; 2048 x 4096 x 16384: 8.3 -> 5.1 ms (54 TFLOP/s).
+__global__ __launch_bounds__(256, 5) void ref_gemm_f64_kernel(const __half* x, int64_t ldx, const float* w, int T, int K, int N, double* yref) {
+    const int row0 = blockIdx.y * F64_B, col0 = blockIdx.x * F64_B;
+    auto a = f64_operand<false>(x + row0 * ldx, ldx, T - row0, [](__half v) { return (double)h2f(v); });
+    auto b = f64_operand<true>(w + col0, N, N - col0, F64Same{});
+    __shared__ double lds[decltype(a)::LDS + decltype(b)::LDS];
+    F64Acc acc = {};
+    f64_tile_mac(acc, K, lds, a, b);
+    f64_tile_each(acc, [&](double v, int i, int j) {
+        if (row0 + i < T && col0 + j < N) yref[(size_t)(row0 + i) * N + col0 + j] = v;
+    });
 }
 
 // ---- loss = mean (Y - Yref)^2 in binary64 ------------------------------------------------------
-// Row sums run over the columns in order (one sequential chain per row, as the definition is
-// written), so the value does not depend on the launch shape.  A work-group owns 16 rows and
-// walks over tiles of 256 columns: all threads fetch the next tile (coalesced) and square the
-// differences while thread r < 16 adds the 256 values of row r of the current tile, in column
-// order, from LDS (two buffers, one barrier per tile).  A last small kernel adds the rows in
-// order.
-constexpr int LR = 16, LC = 256;
-__global__ __launch_bounds__(256) void row_sq_err_kernel(const __half* y, int64_t ldy, const double* yref, int T, int N,
-                                                         double* row_sum) {
-    __shared__ double sq[2][LR][LC + 2];
-    const int tid = threadIdx.x;
+// Row sums run over the columns in order (one sequential chain per row, as the definition is written), so the value
+// does not depend on the launch shape.  Bounds: the chain (N dependent additions) and, from one row per two lanes of
+// every CU on, the read of Yref.  A work-group owns LR rows and walks over tiles of 256 columns: its first wave does
+// nothing but add (lane r the values of row r, from LDS), the other four fetch two tiles ahead and leave the squared
+// differences in one of two LDS buffers (2048 x 16384: 600 -> 92 us; one wave both fetched and added before).  A last
+// small kernel adds the rows in order.
+constexpr int LR = 8, LC = 256;
+__global__ __launch_bounds__(64 + LC) void row_sq_err_kernel(const __half* y, int64_t ldy, const double* yref, int T, int N,
+                                                             double* row_sum) {
+    __shared__ __attribute__((aligned(16))) double sq[2][LR][LC + 2];
+    const int lane = threadIdx.x, col = threadIdx.x - 64;
+    const bool adds = threadIdx.x < 64;
     const int row0 = blockIdx.x * LR;
     const int ntile = (N + LC - 1) / LC;
-    double v[LR];
-    auto fetch = [&](int tile) {  // thread = one column of the tile, all 16 rows
-        const int col = tile * LC + tid;
-        const int colc = min(col, N - 1);  // loads stay unconditional (clamped), masked afterwards
-        __half yv[LR];
-        double rv[LR];
+    struct Tile {
+        __half y[LR];
+        double r[LR];
+    };
+    auto fetch = [&](int tile, Tile& f) {  // thread = one column, all rows; loads stay unconditional (clamped), masked afterwards
+        const int c = min(tile * LC + col, N - 1);
 #pragma unroll
         for (int r = 0; r < LR; ++r) {
-            const int rowc = min(row0 + r, T - 1);
-            yv[r] = y[(size_t)rowc * ldy + colc];
-            rv[r] = yref[(size_t)rowc * N + colc];
+            const int row = min(row0 + r, T - 1);
+            f.y[r] = y[(size_t)row * ldy + c];
+            f.r[r] = __builtin_nontemporal_load(yref + (size_t)row * N + c);
         }
+    };
+    auto stage = [&](int tile, const Tile& f) {
 #pragma unroll
         for (int r = 0; r < LR; ++r) {
-            const double d = (double)h2f(yv[r]) - rv[r];
-            v[r] = (row0 + r < T && col < N) ? d * d : 0.0;
+            const double d = (double)h2f(f.y[r]) - f.r[r];
+            sq[tile & 1][r][col] = row0 + r < T && tile * LC + col < N ? d * d : 0.0;
         }
     };
-    auto stage = [&](int buf) {
-#pragma unroll
-        for (int r = 0; r < LR; ++r) sq[buf][r][tid] = v[r];
-    };
-    fetch(0);
-    stage(0);
-    __syncthreads();
     double run = 0.0;
-    for (int tile = 0; tile < ntile; ++tile) {
-        const int buf = tile & 1;
-        if (tile + 1 < ntile) fetch(tile + 1);  // in flight while the chain below runs
-        if (tid < LR) {
-            const int lim = min(LC, N - tile * LC);
-            const double* p = sq[buf][tid];
-            int c = 0;
-            for (; c + 16 <= lim; c += 16) {  // 16 loads ahead of the dependent additions
-                double t[16];
-#pragma unroll
-                for (int i = 0; i < 16; ++i) t[i] = p[c + i];
-#pragma unroll
-                for (int i = 0; i < 16; ++i) run += t[i];
-            }
-            for (; c < lim; ++c) run += p[c];
+    auto add = [&](int tile) {
+        if (lane < LR) run = add_in_order(run, sq[tile & 1][lane], min(LC, N - tile * LC));
+    };
+    Tile f0, f1;
+    if (!adds) {
+        fetch(0, f0);
+        if (ntile > 1) fetch(1, f1);
+        stage(0, f0);
+        if (ntile > 2) fetch(2, f0);
+    }
+    __syncthreads();
+    for (int tile = 0; tile < ntile; tile += 2) {
+        if (adds) {
+            add(tile);
+        } else if (tile + 1 < ntile) {
+            stage(tile + 1, f1);
+            if (tile + 3 < ntile) fetch(tile + 3, f1);
         }
-        if (tile + 1 < ntile) stage(buf ^ 1);
+        __syncthreads();
+        if (tile + 1 >= ntile) break;
+        if (adds) {
+            add(tile + 1);
+        } else if (tile + 2 < ntile) {
+            stage(tile + 2, f0);
+            if (tile + 4 < ntile) fetch(tile + 4, f0);
+        }
         __syncthreads();
     }
-    if (tid < LR && row0 + tid < T) row_sum[row0 + tid] = run;
+    if (lane < LR && row0 + lane < T) row_sum[row0 + lane] = run;
 }
 
 __global__ __launch_bounds__(256) void total_loss_kernel(const double* row_sum, int T, int N, double* loss) {
@@ -147,10 +103,7 @@ __global__ __launch_bounds__(256) void total_loss_kernel(const double* row_sum, 
     for (int t0 = 0; t0 < T; t0 += 1024) {  // rows in order, 1024 at a time through LDS
         for (int i = threadIdx.x; i < 1024; i += 256) part[i] = t0 + i < T ? row_sum[t0 + i] : 0.0;
         __syncthreads();
-        if (threadIdx.x == 0) {
-            const int lim = min(1024, T - t0);
-            for (int i = 0; i < lim; ++i) total += part[i];
-        }
+        if (threadIdx.x == 0) total = add_in_order(total, part, min(1024, T - t0));
         __syncthreads();
     }
     if (threadIdx.x == 0) *loss = total / ((double)T * (double)N);
@@ -207,8 +160,8 @@ int32_t haq_reference_matmul_f64(const void* x_fp16, int64_t ldx, const float* w
                                  double* yref, void* stream) {
     if (T <= 0 || K <= 0 || N <= 0) HAQ_FAIL(HAQ_ERR_INVALID_ARG, "haq_reference_matmul_f64: T=%d K=%d N=%d", T, K, N);
     if (!x_fp16 || !w || !yref || ldx < K) HAQ_FAIL(HAQ_ERR_INVALID_ARG, "haq_reference_matmul_f64: null buffer or ldx=%lld", (long long)ldx);
-    hipLaunchKernelGGL(ref_gemm_f64_kernel, dim3(cdiv(N, RT), cdiv(T, RT)), dim3(256), 0, (hipStream_t)stream,
-                       (const __half*)x_fp16, ldx, w, T, K, N, yref);
+    hipLaunchKernelGGL(ref_gemm_f64_kernel, dim3(cdiv(N, 64), cdiv(T, 64)), dim3(256), 0, (hipStream_t)stream,
+                           (const __half*)x_fp16, ldx, w, T, K, N, yref);
     HAQ_CHECK_HIP(hipGetLastError());
     return HAQ_OK;
 }
@@ -218,7 +171,7 @@ int32_t haq_quant_loss_f64(const void* y_fp16, int64_t ldy, const double* yref, 
     if (T <= 0 || N <= 0) HAQ_FAIL(HAQ_ERR_INVALID_ARG, "haq_quant_loss_f64: T=%d N=%d", T, N);
     if (!y_fp16 || !yref || !row_scratch || !loss || ldy < N) HAQ_FAIL(HAQ_ERR_INVALID_ARG, "haq_quant_loss_f64: null buffer or ldy=%lld", (long long)ldy);
     hipStream_t st = (hipStream_t)stream;
-    hipLaunchKernelGGL(row_sq_err_kernel, dim3(cdiv(T, LR)), dim3(256), 0, st, (const __half*)y_fp16, ldy, yref, T, N, row_scratch);
+    hipLaunchKernelGGL(row_sq_err_kernel, dim3(cdiv(T, LR)), dim3(64 + LC), 0, st, (const __half*)y_fp16, ldy, yref, T, N, row_scratch);
     hipLaunchKernelGGL(total_loss_kernel, dim3(1), dim3(256), 0, st, (const double*)row_scratch, T, N, loss);
     HAQ_CHECK_HIP(hipGetLastError());
     return HAQ_OK;

@@ -64,3 +64,24 @@ def test_short_batch_quantisers_at_the_edges_of_their_row_split(T, K):
     y, _, q, sx, zp = haq.haq_w8a8_linear_asym(dev(X), dev(s), haq.haq_pack_weight(wq), dev(sw), haq.haq_weight_colsum(wq), 16, debug=True)
     assert bits_equal(host(q), q_ref) and bits_equal(host(sx), sx_ref) and bits_equal(host(zp), zp_ref)
     assert bits_equal(host(y), y_ref)
+
+
+@pytest.mark.parametrize("T,K,N", [(17, 63, 17), (80, 65, 130), (40, 128, 9), (33, 257, 66), (64, 330, 1000), (100, 448, 208), (70, 700, 81)])
+def test_layer_quantiser_at_the_edges_of_its_blocks(T, K, N):
+    """Panels and blocks of 64 with one row less and more, k chunks of 16 with a remainder, a second stretch of 256
+    channels, errors kept in the freed matrices (700 x 81) and, where they do not fit there, block by block (330 x 1000)."""
+    rng = np.random.default_rng(T + K + N)
+    X = (rng.standard_normal((T, 12)) @ rng.standard_normal((12, K)) + 0.1 * rng.standard_normal((T, K))).astype(np.float16)
+    W = hi.gaussian_weight(T + K, 0, K, N)
+    W[3, :] = -0.0
+    s = oracle.smoothing_vector(oracle.col_absmax_f16(X), oracle.row_absmax_f32(W), 0.5)
+    for sv in (None, s):
+        H_ref = oracle.hessian(X, sv, 0.01)
+        H = haq.haq_hessian_f64(dev(X), None if sv is None else dev(sv), 0.01)
+        assert bits_equal(host(H), H_ref), diff_report(host(H), H_ref)
+        U_ref = oracle.inverse_cholesky_upper(H_ref)
+        U = haq.haq_inverse_cholesky_upper_f64(H)
+        assert bits_equal(host(U), U_ref), diff_report(host(U), U_ref)
+        Wq_ref, sw_ref = oracle.gptq(W, sv, U_ref)
+        Wq, sw = haq.haq_hessian_quant_weight(dev(X), dev(W), None if sv is None else dev(sv), 0.01)
+        assert bits_equal(host(sw), sw_ref) and bits_equal(host(Wq), Wq_ref)
