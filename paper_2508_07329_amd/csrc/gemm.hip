@@ -48,8 +48,9 @@ int launch_one(const GemmArgs& a, dim3 grid, hipStream_t st) {
 constexpr int SMALL_TILE_LIMIT = HAQ_SMALL_TILE_LIMIT;  // 128 x 256 tiles that would not even give every CU one work-group
 constexpr int BN_S = 128, MINB_S = 3;
 using ShapeS = GemmShape<128, BN_S, 2, 2, 3>;
+template <int EPI>
 int launch_small(const GemmArgs& a, dim3 grid, hipStream_t st) {
-    auto kern = gemm_i8_kernel<128, BN_S, 2, 2, 3, MINB_S, EPI_LINEAR, false>;
+    auto kern = gemm_i8_kernel<128, BN_S, 2, 2, 3, MINB_S, EPI, false>;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [&] {
@@ -67,8 +68,9 @@ int launch_small(const GemmArgs& a, dim3 grid, hipStream_t st) {
 // 2048..8192 x 4096 x 16384, -8 % on a single round, and slower on ragged expert groups (more padding rows).
 constexpr int LARGE_TILE_MIN = 512;
 using ShapeL = GemmShape<256, 256, 4, 2, 3>;
+template <int EPI>
 int launch_large(const GemmArgs& a, dim3 grid, hipStream_t st) {
-    auto kern = gemm_i8_kernel<256, 256, 4, 2, 3, 1, EPI_LINEAR, false>;
+    auto kern = gemm_i8_kernel<256, 256, 4, 2, 3, 1, EPI, false>;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [&] {
@@ -84,8 +86,9 @@ int launch_large(const GemmArgs& a, dim3 grid, hipStream_t st) {
 // one round with most CUs busy (fc2 of the OPT-6.7B block: 8 x 32 tiles on 256 CUs).  A quarter fewer
 // direct-to-LDS bytes per matrix instruction than the 128 x 128 shape such problems would otherwise take: -2 %.
 using ShapeT = GemmShape<256, 128, 4, 2, 3>;
+template <int EPI>
 int launch_tall(const GemmArgs& a, dim3 grid, hipStream_t st) {
-    auto kern = gemm_i8_kernel<256, 128, 4, 2, 3, 1, EPI_LINEAR, false>;
+    auto kern = gemm_i8_kernel<256, 128, 4, 2, 3, 1, EPI, false>;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [&] {
@@ -98,6 +101,29 @@ int launch_tall(const GemmArgs& a, dim3 grid, hipStream_t st) {
 }
 
 }  // namespace
+
+// Row blocks of 16 per tile (4, 6 or 8) with which the streaming kernel (skinny.hip: 64-channel tiles, K split over
+// the waves, operands straight into registers) beats one round of 128 x 128 tiles, or 0.  Such a round costs a
+// work-group 0.3 us for each 64-byte K-step however few of them there are (77 us at K = 16384 for 64 to 256 tiles);
+// a round of streaming tiles costs (4 + RB) / 80 us a K-step, the fragments of a step through a CU's load path, and
+// 4 us to start and finish.  Measured (us, M rows, K x N, streaming against tiled):
+//   16384 x 4096:  129 rows 30 / 78,  333: 37 / 78,  512: 44 / 79,  700: 70 / 82,  1024: 84 / 85
+//   4096 x 4096:   129 rows 10 / 20,  333: 13 / 20,  512: 15 / 20,  700: 25 / 21 (tiled stays)
+//   3072 x 768:    333 rows 9.4 / 15.3,  1024: 9.7 / 15.7;   2048 x 8192: 192 rows 10.3 / 13.1,  333: 18 / 13 (tiled)
+static int stream_row_blocks(const GemmArgs& a, int n_cu) {
+    const int nk = cdiv(a.K, 64);
+    float best = 3.0f + 0.3f * nk;
+    int rb = 0;
+    for (int r = 4; r <= 8; r += 2) {
+        const int64_t tiles = (int64_t)cdiv(a.M, 16 * r) * cdiv(a.N, 64);
+        const float t = (float)((tiles + n_cu - 1) / n_cu) * (4.0f + nk * (4 + r) * (1.0f / 80.0f));
+        if (t < best) {
+            best = t;
+            rb = r;
+        }
+    }
+    return rb;
+}
 
 int cu_count() {
     static const int n_cu = [] {
@@ -114,16 +140,27 @@ int launch_gemm(const GemmArgs& a, int epi, hipStream_t st) {
     // upper bound on the M tiles: exact for one matrix; rows/BM plus one partial tile per group otherwise
     const int mt = a.offsets ? a.max_rows / BM + a.n_sel : cdiv(a.M, BM);
     if (mt <= 0 || ntn <= 0) return HAQ_OK;
-    if (!a.offsets && epi == EPI_LINEAR && !a.acc_dbg) {
-        const int64_t tiles_l = (int64_t)cdiv(a.M, 256) * cdiv(a.N, 256);
-        if (tiles_l >= LARGE_TILE_MIN) return launch_large(a, dim3((unsigned)round_up(tiles_l, 8)), st);
-        const int64_t tiles_t = (int64_t)cdiv(a.M, 256) * cdiv(a.N, 128);
+    if (!a.offsets && !a.acc_dbg && (epi == EPI_LINEAR || epi == EPI_LINEAR_ASYM)) {
+        const bool asym = epi == EPI_LINEAR_ASYM;
         const int n_cu = cu_count();
-        if (tiles_t <= n_cu && 4 * tiles_t > 3 * n_cu) return launch_tall(a, dim3((unsigned)round_up(tiles_t, 8)), st);
-    }
-    if (!a.offsets && epi == EPI_LINEAR && !a.acc_dbg && mt * ntn <= SMALL_TILE_LIMIT) {
-        const int ntn_s = cdiv(a.N, BN_S), mt_s = cdiv(a.M, 128);
-        return launch_small(a, dim3((unsigned)round_up((int64_t)mt_s * ntn_s, 8)), st);
+        const int64_t tiles_l = (int64_t)cdiv(a.M, 256) * cdiv(a.N, 256);
+        if (tiles_l >= LARGE_TILE_MIN) {
+            const dim3 grid((unsigned)round_up(tiles_l, 8));
+            return asym ? launch_large<EPI_LINEAR_ASYM>(a, grid, st) : launch_large<EPI_LINEAR>(a, grid, st);
+        }
+        const int64_t tiles_s = (int64_t)cdiv(a.M, 128) * cdiv(a.N, BN_S);
+        if (tiles_s <= n_cu) {
+            if (const int rb = stream_row_blocks(a, n_cu)) return launch_stream_rows(a, asym, rb, st);
+        }
+        const int64_t tiles_t = (int64_t)cdiv(a.M, 256) * cdiv(a.N, 128);
+        if (tiles_t <= n_cu && 4 * tiles_t > 3 * n_cu) {
+            const dim3 grid((unsigned)round_up(tiles_t, 8));
+            return asym ? launch_tall<EPI_LINEAR_ASYM>(a, grid, st) : launch_tall<EPI_LINEAR>(a, grid, st);
+        }
+        if (mt * ntn <= SMALL_TILE_LIMIT) {
+            const dim3 grid((unsigned)round_up(tiles_s, 8));
+            return asym ? launch_small<EPI_LINEAR_ASYM>(a, grid, st) : launch_small<EPI_LINEAR>(a, grid, st);
+        }
     }
     const dim3 grid((unsigned)round_up((int64_t)mt * ntn, 8));
     if (epi == EPI_SWIGLU) return launch_one<EPI_SWIGLU, false>(a, grid, st);

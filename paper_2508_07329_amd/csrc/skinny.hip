@@ -1,4 +1,4 @@
-// Dense W8A8 linear for short batches (at most 128 token rows): the weights are streamed from HBM
+// Dense W8A8 linear for short batches (at most 128 token rows, and longer ones on few output channels): the weights are streamed from HBM
 // once, straight into MFMA operand registers, as on the decode path of the routed expert FFN.
 //
 // Bound: the weight stream (K N bytes).  The tiled GEMM cannot draw it at these batches: its grid is one
@@ -25,21 +25,20 @@ __device__ __forceinline__ v4i gload16_stream(const int8_t* p) { return __builti
 
 constexpr int SK_WAVES = 8;
 
-// C: blocks of 16 channels per work-group; RB: blocks of 16 token rows; WPS: waves per SIMD (register budget).
-template <int C, int RB, int DEPTH, int WPS, bool ASYM>
-__global__ __launch_bounds__(SK_WAVES * 64, WPS) void skinny_linear_kernel(GemmArgs a) {
-    __shared__ int sum[C * RB][4][64];
+// One tile: channels n0 .. n0 + 16 C - 1, rows row0 .. row0 + rows - 1 (at most 16 RB).  STREAM: no other work-group
+// reads these weights.
+template <int C, int RB, int DEPTH, bool ASYM, bool STREAM>
+__device__ __forceinline__ void stream_tile(const GemmArgs& a, int row0, int rows, int n0, int (*sum)[4][64]) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, q = lane >> 4;
-    const int n0 = blockIdx.x * (16 * C);
     const int nk = (a.K + 63) / 64;  // a last partial K-step reads chunks past K: the weights are zero there
     const int n = nk > wave ? (nk - wave + SK_WAVES - 1) / SK_WAVES : 0;  // this wave's K-steps: wave, wave + 8, ...
     const size_t wstep = (size_t)4 * SK_WAVES * a.Npad * 16, xstep = (size_t)4 * SK_WAVES * a.R * 16;
     const int8_t* pw = a.B + ((size_t)(4 * wave + q) * a.Npad + n0 + l16) * 16;
-    const int8_t* px = a.A + (size_t)(4 * wave + q) * a.R * 16;
+    const int8_t* px = a.A + ((size_t)(4 * wave + q) * a.R + row0) * 16;
     int xoff[RB];  // rows past the last one re-read it (their results are dropped)
 #pragma unroll
-    for (int b = 0; b < RB; ++b) xoff[b] = min(16 * b + l16, a.M - 1) * 16;
+    for (int b = 0; b < RB; ++b) xoff[b] = min(16 * b + l16, rows - 1) * 16;
 
     v4i acc[C][RB];
 #pragma unroll
@@ -51,7 +50,7 @@ __global__ __launch_bounds__(SK_WAVES * 64, WPS) void skinny_linear_kernel(GemmA
     };
     auto fetch = [&](Frag& f) {
 #pragma unroll
-        for (int c = 0; c < C; ++c) f.w[c] = gload16_stream(pw + c * 256);
+        for (int c = 0; c < C; ++c) f.w[c] = STREAM ? gload16_stream(pw + c * 256) : gload16(pw + c * 256);
 #pragma unroll
         for (int b = 0; b < RB; ++b) f.x[b] = gload16(px + xoff[b]);
     };
@@ -99,21 +98,42 @@ __global__ __launch_bounds__(SK_WAVES * 64, WPS) void skinny_linear_kernel(GemmA
     for (int i = tid; i < C * RB * 64; i += SK_WAVES * 64) {
         const int cb = i >> 6, ln = i & 63;
         const int row = 16 * (cb % RB) + (ln & 15), ch = n0 + 16 * (cb / RB) + 4 * (ln >> 4);
-        if (row >= a.M || ch >= a.N) continue;
-        const float sx = a.sx[row];
-        const int zshift = ASYM ? 128 - a.zp[row] : 0;
+        if (row >= rows || ch >= a.N) continue;
+        const float sx = a.sx[row0 + row];
+        const int zshift = ASYM ? 128 - a.zp[row0 + row] : 0;
         __half hv[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             int v = sum[cb][r][ln];
             if (ASYM) v += zshift * a.colsum[ch + r];
-            if (a.acc_dbg) a.acc_dbg[(size_t)row * a.N + ch + r] = v;
+            if (a.acc_dbg) a.acc_dbg[(size_t)(row0 + row) * a.N + ch + r] = v;
             float f = dequant(v, sx, a.sw[ch + r]);
             if (a.act == HAQ_ACT_RELU) f = fmaxf(f, 0.0f);
             hv[r] = f2h(f);
         }
-        *reinterpret_cast<uint2*>(a.Y + (size_t)row * a.ldy + ch) = *reinterpret_cast<const uint2*>(hv);
+        *reinterpret_cast<uint2*>(a.Y + (size_t)(row0 + row) * a.ldy + ch) = *reinterpret_cast<const uint2*>(hv);
     }
+}
+
+// C: blocks of 16 channels per work-group; RB: blocks of 16 token rows; WPS: waves per SIMD (register budget).
+template <int C, int RB, int DEPTH, int WPS, bool ASYM>
+__global__ __launch_bounds__(SK_WAVES * 64, WPS) void skinny_linear_kernel(GemmArgs a) {
+    __shared__ int sum[C * RB][4][64];
+    stream_tile<C, RB, DEPTH, ASYM, true>(a, 0, a.M, blockIdx.x * (16 * C), sum);
+}
+
+// More rows: `mt` row tiles of `tile_rows` rows share a unit of 64 channels.  Work-group ids are dealt round-robin to
+// the eight XCDs; each of them (one L2) takes a contiguous range of tiles, rows fastest, so that a unit's weights cross
+// the fabric once.  Bound: the fragments of a K-step, 1 KB for each block of 16 channels or rows, through a CU's load
+// path (64 B a cycle) against 4 RB matrix instructions; 16384 x 4096 on 333 rows, 256 tiles of 96 x 64: 77.5 -> 36.9 us.
+template <int RB, int DEPTH, bool ASYM>
+__global__ __launch_bounds__(SK_WAVES * 64, 2) void stream_linear_kernel(GemmArgs a, int mt, int tile_rows) {
+    __shared__ int sum[4 * RB][4][64];
+    const int total = mt * ((a.N + 63) / 64), per = (total + 7) / 8, slot = blockIdx.x / 8;
+    const int id = (int)(blockIdx.x % 8) * per + slot;
+    if (slot >= per || id >= total) return;
+    const int row0 = (id % mt) * tile_rows;
+    stream_tile<4, RB, DEPTH, ASYM, false>(a, row0, min(tile_rows, a.M - row0), (id / mt) * 64, sum);
 }
 
 template <int C, int RB, int DEPTH, int WPS>
@@ -123,6 +143,18 @@ int launch_one(const GemmArgs& a, bool asym, hipStream_t st) {
         hipLaunchKernelGGL((skinny_linear_kernel<C, RB, DEPTH, WPS, true>), grid, dim3(SK_WAVES * 64), 0, st, a);
     else
         hipLaunchKernelGGL((skinny_linear_kernel<C, RB, DEPTH, WPS, false>), grid, dim3(SK_WAVES * 64), 0, st, a);
+    HAQ_CHECK_HIP(hipGetLastError());
+    return HAQ_OK;
+}
+
+template <int RB, int DEPTH>
+int launch_rows(const GemmArgs& a, bool asym, hipStream_t st) {
+    const int mt = cdiv(a.M, 16 * RB), tile_rows = 16 * cdiv(cdiv(a.M, mt), 16);
+    const dim3 grid((unsigned)round_up((int64_t)mt * cdiv(a.N, 64), 8));
+    if (asym)
+        hipLaunchKernelGGL((stream_linear_kernel<RB, DEPTH, true>), grid, dim3(SK_WAVES * 64), 0, st, a, mt, tile_rows);
+    else
+        hipLaunchKernelGGL((stream_linear_kernel<RB, DEPTH, false>), grid, dim3(SK_WAVES * 64), 0, st, a, mt, tile_rows);
     HAQ_CHECK_HIP(hipGetLastError());
     return HAQ_OK;
 }
@@ -152,6 +184,14 @@ int launch_skinny(const GemmArgs& a, bool asym, hipStream_t st) {
     HAQ_SKINNY(4, 8, 2, 2);
 #undef HAQ_SKINNY
     return HAQ_ERR_UNSUPPORTED;
+}
+
+int launch_stream_rows(const GemmArgs& a, bool asym, int rb, hipStream_t st) {
+    switch (rb) {
+        case 4: return launch_rows<4, 4>(a, asym, st);
+        case 6: return launch_rows<6, 3>(a, asym, st);
+        default: return launch_rows<8, 2>(a, asym, st);
+    }
 }
 
 }  // namespace haq

@@ -41,8 +41,17 @@ def _linear_both_codes(T, K, N, act):
     (1, 64, 8192, "relu"), (16, 592, 8208, "none"), (31, 208, 8240, "relu"), (64, 1344, 8224, "none"), (90, 912, 8192, "relu"),
     (128, 1104, 8208, "none")])
 def test_short_batch_linear_at_the_edges_of_its_variants(T, K, N, act):
-    """Row blocks of 16 (1, 2, 4, 6, 8 of them; 129 rows take the tiled GEMM), K-steps that do and do not divide among
+    """Row blocks of 16 (1, 2, 4, 6, 8 of them; 129 rows take several row tiles), K-steps that do and do not divide among
     the eight waves and the prefetch depth, a last partial K-step, channel units past the last channel."""
+    _linear_both_codes(T, K, N, act)
+
+
+@pytest.mark.parametrize("T,K,N,act", [
+    # row tiles of the streaming kernel: of 64 (the second ends in one row; one round, and many tiles), of 96 and of 128
+    (129, 1040, 528, "none"), (257, 592, 16, "relu"), (1030, 1104, 272, "none"), (333, 1040, 4096, "relu"), (500, 1088, 4080, "none"),
+    # the tiled GEMM's three dense shapes besides the grouped one: 128 x 128, 256 x 128 and 256 x 256
+    (300, 80, 2064, "relu"), (513, 80, 10240, "none"), (2049, 48, 14352, "none")])
+def test_dense_linear_at_the_edges_of_its_tile_shapes(T, K, N, act):
     _linear_both_codes(T, K, N, act)
 
 
