@@ -283,7 +283,8 @@ __global__ __launch_bounds__(GU_WAVES * 64, 4) void decode_tiny_gate_up_kernel(D
 // division by the row scale goes through its reciprocal (quant_math.h).
 constexpr int RQ_THREADS = 1024;
 __global__ __launch_bounds__(RQ_THREADS) void decode_requant_kernel(DecodeArgs a) {
-    __shared__ float red[RQ_THREADS / 64];
+    __shared__ __attribute__((aligned(16))) float red[16];  // partial maxima of the waves, unused ones 0
+    static_assert(RQ_THREADS / 64 == 16, "one entry per wave");
     const int pos = a.row0 + blockIdx.x;
     int e = 0;
     while (e + 1 < a.E && pos >= a.offsets[e + 1]) ++e;
@@ -311,12 +312,11 @@ __global__ __launch_bounds__(RQ_THREADS) void decode_requant_kernel(DecodeArgs a
     }
     float m = 0.0f;
     for (int i = tid; i < nu; i += nthr) m = fmaxf(m, a.pmax[(size_t)pos * nu + i]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    m = wave_max(m);
+    if (tid >= nwave && tid < 16) red[tid] = 0.0f;
     if ((tid & 63) == 0) red[tid >> 6] = m;
     __syncthreads();
-    m = 0.0f;
-    for (int w = 0; w < nwave; ++w) m = fmaxf(m, red[w]);
+    m = max16(red);
     const float scale = m / 127.0f;
     const float rscale = 1.0f / scale;
     const bool sfast = scale >= 0x1p-100f && scale <= 0x1p100f;
@@ -487,8 +487,7 @@ __device__ __forceinline__ void requant_rows_to_lds(const DecodeArgs& a, const E
         const int pos = lo + row;
         float mx = 0.0f;
         for (int i = tid; i < nu; i += NT) mx = fmaxf(mx, a.pmax[(size_t)pos * nu + i]);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+        mx = wave_max(mx);
         __syncthreads();  // an earlier use of s_red is over
         if ((tid & 63) == 0) s_red[tid >> 6] = mx;
         __syncthreads();

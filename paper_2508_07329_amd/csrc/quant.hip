@@ -162,7 +162,7 @@ __global__ __launch_bounds__(QMAX_THREADS) void smooth_quant_kernel(QuantArgs a,
 // the rounding, so every row is read from memory once.
 template <int RS>
 __global__ __launch_bounds__(QMAX_THREADS) void smooth_quant_reg_kernel(QuantArgs a, int CL) {
-    __shared__ float red[QMAX_THREADS / 64][RS];
+    __shared__ __attribute__((aligned(16))) float red[8][RS][16];  // partial maxima: row group, row, wave of the group
     const int tid = threadIdx.x;
     const int c = tid % CL, g = tid / CL;
     const int brows = (blockDim.x / CL) * RS;  // rows per work-group
@@ -193,6 +193,8 @@ __global__ __launch_bounds__(QMAX_THREADS) void smooth_quant_reg_kernel(QuantArg
     row0 += g * RS;
     const int nrow = min(RS, row_end - row0);  // may be <= 0
     const bool active = c < nchunk;
+    for (int i = tid; i < 8 * RS * 16; i += blockDim.x)
+        if ((i & 15) >= waves_per_group) (&red[0][0][0])[i] = 0.0f;
     uint4 raw[RS][2];
 #pragma unroll
     for (int r = 0; r < RS; ++r) {
@@ -237,13 +239,10 @@ __global__ __launch_bounds__(QMAX_THREADS) void smooth_quant_reg_kernel(QuantArg
         amax[r] = m;
     }
 #pragma unroll
-    for (int r = 0; r < RS; ++r) {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) amax[r] = fmaxf(amax[r], __shfl_xor(amax[r], o));
-    }
+    for (int r = 0; r < RS; ++r) amax[r] = wave_max(amax[r]);
     if ((tid & 63) == 0) {
 #pragma unroll
-        for (int r = 0; r < RS; ++r) red[wave][r] = amax[r];
+        for (int r = 0; r < RS; ++r) red[g][r][wave - g * waves_per_group] = amax[r];
     }
     __syncthreads();
     if (!active) return;
@@ -259,8 +258,7 @@ __global__ __launch_bounds__(QMAX_THREADS) void smooth_quant_reg_kernel(QuantArg
     for (int r = 0; r < RS; ++r) {
         if (r < nrow) {
             // every thread of the row group derives the row's scale from the per-wave maxima
-            float m = 0.0f;
-            for (int w = 0; w < waves_per_group; ++w) m = fmaxf(m, red[g * waves_per_group + w][r]);
+            const float m = max16(red[g][r]);
             const float scale = m / 127.0f;
             const float rscale = 1.0f / scale;
             const bool sfast = scale >= 0x1p-100f && scale <= 0x1p100f;
@@ -333,8 +331,11 @@ __global__ __launch_bounds__(QMAX_THREADS) void smooth_quant_lds_kernel(QuantArg
     const int nchunk = a.K / 16;
     const int slab = G * RS;
     const int srows = qstage_rows(slab), pitch = qstage_pitch(nchunk);
-    float* red = reinterpret_cast<float*>(qlds + (size_t)srows * pitch);  // [2][QMAX_THREADS / 64][RS] maxima (ASYM: then minima)
-    constexpr int RED_HALF = 2 * (QMAX_THREADS / 64) * RS;
+    // partial maxima (ASYM: then negated minima): slab parity, row group, row, wave of the group (16, unused ones 0)
+    float* red = reinterpret_cast<float*>(qlds + (size_t)srows * pitch);
+    constexpr int RED_SLAB = 8 * RS * 16, RED_HALF = 2 * RED_SLAB;
+    for (int i = tid; i < (ASYM ? 2 : 1) * RED_HALF; i += nthr)
+        if ((i & 15) >= waves_per_group) red[i] = 0.0f;
     // Slabs per work-group: the grid is fixed (one work-group per CU); every group (expert)
     // is cut into runs of `nit` slabs, so no work-group does more than nit slabs whatever the
     // group sizes are, and sum_e ceil(slabs_e / nit) <= total / nit + groups <= grid.
@@ -455,18 +456,16 @@ __global__ __launch_bounds__(QMAX_THREADS) void smooth_quant_lds_kernel(QuantArg
         }
 #pragma unroll
         for (int r = 0; r < RS; ++r) {
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                amax[r] = fmaxf(amax[r], __shfl_xor(amax[r], o));
-                if constexpr (ASYM) amin[r] = fminf(amin[r], __shfl_xor(amin[r], o));
-            }
+            amax[r] = wave_max(amax[r]);
+            if constexpr (ASYM) amin[r] = wave_max(-amin[r]);
         }
-        float* redp = red + (size_t)(it & 1) * (QMAX_THREADS / 64) * RS;
+        float* redp = red + (it & 1) * RED_SLAB + g * RS * 16;
+        const int gw = wave - g * waves_per_group;
         if (lane == 0) {
 #pragma unroll
             for (int r = 0; r < RS; ++r) {
-                redp[wave * RS + r] = amax[r];
-                if constexpr (ASYM) redp[RED_HALF + wave * RS + r] = amin[r];
+                redp[r * 16 + gw] = amax[r];
+                if constexpr (ASYM) redp[RED_HALF + r * 16 + gw] = amin[r];
             }
         }
         __syncthreads();
@@ -474,11 +473,8 @@ __global__ __launch_bounds__(QMAX_THREADS) void smooth_quant_lds_kernel(QuantArg
         for (int r = 0; r < RS; ++r) {
             if (src[r] >= 0) {
                 uint32_t w[4] = {0, 0, 0, 0};
-                float m = 0.0f, mlo = 0.0f;
-                for (int w2 = 0; w2 < waves_per_group; ++w2) {
-                    m = fmaxf(m, redp[(g * waves_per_group + w2) * RS + r]);
-                    if constexpr (ASYM) mlo = fminf(mlo, redp[RED_HALF + (g * waves_per_group + w2) * RS + r]);
-                }
+                const float m = max16(redp + r * 16);
+                const float mlo = ASYM ? -max16(redp + RED_HALF + r * 16) : 0.0f;
                 float scale, z = 0.0f;
                 if constexpr (ASYM) {
                     const float range = m - mlo;
@@ -580,8 +576,7 @@ struct AsymQuantArgs {
 
 template <int RS>
 __global__ __launch_bounds__(QMAX_THREADS) void asym_quant_kernel(AsymQuantArgs a, int CL) {
-    __shared__ float red_mn[QMAX_THREADS / 64][RS];
-    __shared__ float red_mx[QMAX_THREADS / 64][RS];
+    __shared__ __attribute__((aligned(16))) float red[2][8][RS][16];  // negated minima, maxima: row group, row, wave of the group
     const int tid = threadIdx.x;
     const int c = tid % CL, g = tid / CL;
     const int brows = (blockDim.x / CL) * RS;
@@ -590,6 +585,8 @@ __global__ __launch_bounds__(QMAX_THREADS) void asym_quant_kernel(AsymQuantArgs 
     const int row0 = blockIdx.x * brows + g * RS;
     const int nrow = min(RS, a.T - row0);
     const bool active = c < nchunk;
+    for (int i = tid; i < 2 * 8 * RS * 16; i += blockDim.x)
+        if ((i & 15) >= waves_per_group) (&red[0][0][0][0])[i] = 0.0f;
     uint4 raw[RS][2];
 #pragma unroll
     for (int r = 0; r < RS; ++r) {
@@ -635,17 +632,14 @@ __global__ __launch_bounds__(QMAX_THREADS) void asym_quant_kernel(AsymQuantArgs 
                 mx[r] = fmaxf(mx[r], x[i]);
             }
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            mn[r] = fminf(mn[r], __shfl_xor(mn[r], o));
-            mx[r] = fmaxf(mx[r], __shfl_xor(mx[r], o));
-        }
+        mn[r] = wave_max(-mn[r]);
+        mx[r] = wave_max(mx[r]);
     }
     if ((tid & 63) == 0) {
 #pragma unroll
         for (int r = 0; r < RS; ++r) {
-            red_mn[wave][r] = mn[r];
-            red_mx[wave][r] = mx[r];
+            red[0][g][r][wave - g * waves_per_group] = mn[r];
+            red[1][g][r][wave - g * waves_per_group] = mx[r];
         }
     }
     __syncthreads();
@@ -659,11 +653,7 @@ __global__ __launch_bounds__(QMAX_THREADS) void asym_quant_kernel(AsymQuantArgs 
 #pragma unroll
     for (int r = 0; r < RS; ++r) {
         if (r < nrow) {
-            float lo = 0.0f, hi = 0.0f;
-            for (int w = 0; w < waves_per_group; ++w) {
-                lo = fminf(lo, red_mn[g * waves_per_group + w][r]);
-                hi = fmaxf(hi, red_mx[g * waves_per_group + w][r]);
-            }
+            const float lo = -max16(red[0][g][r]), hi = max16(red[1][g][r]);
             const float range = hi - lo;
             const int t = row0 + r;
             float scale = 0.0f, z = 0.0f;
@@ -699,7 +689,7 @@ __global__ __launch_bounds__(QMAX_THREADS) void asym_quant_kernel(AsymQuantArgs 
 // routed expert FFN: rows gathered through the permutation, or rows of the sorted intermediate with the
 // smoothing vector of the expert whose group holds the row.
 __global__ __launch_bounds__(QMAX_THREADS) void asym_quant_row_kernel(AsymRowArgs a) {
-    __shared__ float red_mn[QMAX_THREADS / 64], red_mx[QMAX_THREADS / 64];
+    __shared__ __attribute__((aligned(16))) float red_mn[16], red_mx[16];  // negated minima, maxima of the waves
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nwave = blockDim.x >> 6;
     const int row = blockIdx.x;
     const int src = a.gather ? (a.gather[row] >> 1) : row;
@@ -734,21 +724,15 @@ __global__ __launch_bounds__(QMAX_THREADS) void asym_quant_row_kernel(AsymRowArg
         mn = fminf(mn, y[i]);
         mx = fmaxf(mx, y[i]);
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        mn = fminf(mn, __shfl_xor(mn, o));
-        mx = fmaxf(mx, __shfl_xor(mx, o));
-    }
+    mn = wave_max(-mn);
+    mx = wave_max(mx);
+    if (tid >= nwave && tid < 16) red_mn[tid] = red_mx[tid] = 0.0f;
     if (lane == 0) {
         red_mn[wave] = mn;
         red_mx[wave] = mx;
     }
     __syncthreads();
-    float lo = 0.0f, hi = 0.0f;
-    for (int w = 0; w < nwave; ++w) {
-        lo = fminf(lo, red_mn[w]);
-        hi = fmaxf(hi, red_mx[w]);
-    }
+    const float lo = -max16(red_mn), hi = max16(red_mx);
     const float range = hi - lo;
     float scale = 0.0f, z = 0.0f;
     uint32_t w4[4] = {0x80808080u, 0x80808080u, 0x80808080u, 0x80808080u};  // code 0 -> -128
@@ -901,7 +885,7 @@ int launch_quant(const QuantArgs& a, hipStream_t st) {
         const int rows = a.tab ? a.max_rows : a.T;
         const int n_cu = cu_count();
         if (rows / (LRS * G) >= n_cu) {
-            const size_t red_bytes = 4 * (QMAX_THREADS / 64) * LRS * sizeof(float);  // maxima and (asymmetric codes) minima
+            const size_t red_bytes = 4 * 8 * LRS * 16 * sizeof(float);  // maxima and (asymmetric codes) minima
             const size_t lds = (size_t)qstage_rows(LRS * G) * qstage_pitch(nchunk) + red_bytes;
             static std::once_flag once;
             static hipError_t attr_err = hipSuccess;
