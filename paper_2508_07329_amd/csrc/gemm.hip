@@ -26,9 +26,9 @@ namespace {
 constexpr int BM = HAQ_BM, BN = HAQ_BN, WAVES_M = HAQ_WAVES_M, WAVES_N = HAQ_WAVES_N, STAGES = HAQ_STAGES, MINB = HAQ_MINB;
 using Shape = GemmShape<BM, BN, WAVES_M, WAVES_N, STAGES>;
 
-template <int EPI, bool DBG>
+template <int EPI, bool DBG, bool FEW = false>
 int launch_one(const GemmArgs& a, dim3 grid, hipStream_t st) {
-    auto kern = gemm_i8_kernel<BM, BN, WAVES_M, WAVES_N, STAGES, MINB, EPI, DBG>;
+    auto kern = gemm_i8_kernel<BM, BN, WAVES_M, WAVES_N, STAGES, MINB, EPI, DBG, FEW>;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [&] {
@@ -134,6 +134,8 @@ int cu_count() {
     return n_cu;
 }
 
+static constexpr int STREAM_MEAN_ROWS = 48, FEW_MEAN_ROWS = 112;  // rows per selected expert, on average
+
 int launch_gemm(const GemmArgs& a, int epi, hipStream_t st) {
     if (skinny_supported(a) && (epi == EPI_LINEAR || epi == EPI_LINEAR_ASYM)) return launch_skinny(a, epi == EPI_LINEAR_ASYM, st);
     const int ntn = cdiv(a.N, BN);
@@ -160,6 +162,23 @@ int launch_gemm(const GemmArgs& a, int epi, hipStream_t st) {
         if (mt * ntn <= SMALL_TILE_LIMIT) {
             const dim3 grid((unsigned)round_up(tiles_s, 8));
             return asym ? launch_small<EPI_LINEAR_ASYM>(a, grid, st) : launch_small<EPI_LINEAR>(a, grid, st);
+        }
+    }
+    if (a.offsets) {
+        // Few rows per expert: bound by the weight stream, not by the matrix cores.  Measured on a whole layer (us,
+        // 4096 x 14336, 8 experts; streaming kernel / this kernel's FEW form / its form for many rows), rows per expert
+        // 18: 265 / 324 / 340, 32: 283 / 309 / 335, 50: 315 / 312 / 341, 75: 372 / 331 / 354, 112: 445 / 354 / 371,
+        // 150: 666 / 515 / 463; 2048 x 5632, 16 experts: 9: 139 / 150 / 154, 37: 161 / 164 / 168, 75: 195 / 182 / 180.
+        const int mean = a.max_rows / (a.n_sel > 0 ? a.n_sel : 1);
+        if (mean <= STREAM_MEAN_ROWS) return launch_stream_grouped(a, epi, st);
+        if (mean <= FEW_MEAN_ROWS) {
+            const dim3 grid((unsigned)((int64_t)mt * round_up(ntn, 8)));
+            switch (epi) {
+                case EPI_SWIGLU: return launch_one<EPI_SWIGLU, false, true>(a, grid, st);
+                case EPI_SWIGLU_ASYM: return launch_one<EPI_SWIGLU_ASYM, false, true>(a, grid, st);
+                case EPI_LINEAR_ASYM: return launch_one<EPI_LINEAR_ASYM, false, true>(a, grid, st);
+                default: return launch_one<EPI_LINEAR, false, true>(a, grid, st);
+            }
         }
     }
     const dim3 grid((unsigned)round_up((int64_t)mt * ntn, 8));

@@ -43,13 +43,35 @@ struct TileCoord {
 #endif
 constexpr int TILE_BAND = HAQ_TILE_BAND;
 
-template <int BM, int BN>
+// FEW (expert groups of a row tile or so each): every expert's channel tiles go round the XCDs, as work-group ids do, and
+// the row tiles of one channel tile stay on one of them; a contiguous range would give each XCD an expert of its own.
+template <int BM, int BN, bool FEW>
 __device__ __forceinline__ TileCoord decode_tile(const GemmArgs& a) {
     TileCoord tc;
     tc.valid = false;
     tc.e = 0;
     tc.m0 = tc.m_end = tc.n0 = 0;
     const int ntn = (a.N + BN - 1) / BN;
+    if constexpr (FEW) {
+        const int ntp = (ntn + 7) / 8 * 8;
+        int id = blockIdx.x;
+        for (int i = 0; i < a.n_sel; ++i) {
+            const int e = a.sel[i];
+            const int lo = a.offsets[e], hi = a.offsets[e + 1];
+            const int mt = (hi - lo + BM - 1) / BM;
+            if (id < mt * ntp) {
+                const int u = (id / 8 / mt) * 8 + id % 8;
+                tc.e = e;
+                tc.m0 = lo + ((id / 8) % mt) * BM;
+                tc.m_end = hi;
+                tc.n0 = u * BN;
+                tc.valid = u < ntn;
+                return tc;
+            }
+            id -= mt * ntp;
+        }
+        return tc;  // the grid is an upper bound
+    }
     int total_mt = 0;
     if (!a.offsets) {
         total_mt = (a.M + BM - 1) / BM;
@@ -106,7 +128,7 @@ struct GemmShape {
     static constexpr int LDS_BYTES = STAGES * STAGE_BYTES + SCALE_BYTES;
 };
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int MINB, int EPI, bool DBG>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int MINB, int EPI, bool DBG, bool FEW = false>
 __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINB) void gemm_i8_kernel(GemmArgs a) {
     using S = GemmShape<BM, BN, WAVES_M, WAVES_N, STAGES>;
     constexpr int NW = S::NW;
@@ -132,7 +154,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINB) void gemm_i8_kernel(G
     float* sw_s = sx_s + BM;                                             // [BN] channel scales, packed order
     int32_t* cs_s = reinterpret_cast<int32_t*>(sw_s + BN);               // [BN] column sums of the weight codes, packed order (ASYM)
 
-    const TileCoord tc = decode_tile<BM, BN>(a);
+    const TileCoord tc = decode_tile<BM, BN, FEW>(a);
     if (!tc.valid) return;
 
     const int8_t* Bmat = a.B;
@@ -203,7 +225,9 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINB) void gemm_i8_kernel(G
     for (int i = 0; i < LPW; ++i) {
         const int g = wave + i * NW;
         if (g < GA) {
-            const int c = g / (BM / 64), rg = g % (BM / 64);
+            const int c = g / (BM / 64);
+            int rg = g % (BM / 64);
+            if (FEW && rg * 64 >= tc.m_end - m0u) rg = 0;  // 64 rows past the group's last: their results are dropped
             gsrc[i] = Au + ((size_t)c * a.R + m0u + rg * 64) * 16;
             gstep[i] = (size_t)4 * a.R * 16;
         } else {
@@ -221,9 +245,14 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINB) void gemm_i8_kernel(G
 #pragma unroll
         for (int i = 0; i < LPW; ++i) {
             const int8_t* src = gsrc[i] + (size_t)kt * gstep[i] + lo;
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(uintptr_t)src,
-                                             (__attribute__((address_space(3))) void*)(lds + buf * STAGE_BYTES + (wave + i * NW) * 1024),
-                                             16, 0, 0);
+            const auto* gp = (const __attribute__((address_space(1))) void*)(uintptr_t)src;
+            auto* lp = (__attribute__((address_space(3))) void*)(lds + buf * STAGE_BYTES + (wave + i * NW) * 1024);
+            // FEW: the weights are hardly shared and pass the caches by (non-temporal), so that the token rows stay there
+            static_assert(!FEW || GA % NW == 0, "a load slot is of one operand for all waves");
+            if (FEW && i * NW >= GA)
+                __builtin_amdgcn_global_load_lds(gp, lp, 16, 0, 2);
+            else
+                __builtin_amdgcn_global_load_lds(gp, lp, 16, 0, 0);
         }
     };
 

@@ -8,6 +8,7 @@ import oracle
 import paper_2508_07329_amd as haq
 from tests import offline
 from tests.gpu_util import bits_equal, dev, diff_report, host
+from tests.test_gpu_parity import _check_moe, _check_moe_asym
 
 pytestmark = pytest.mark.gpu
 
@@ -94,3 +95,24 @@ def test_layer_quantiser_at_the_edges_of_its_blocks(T, K, N):
         Wq_ref, sw_ref = oracle.gptq(W, sv, U_ref)
         Wq, sw = haq.haq_hessian_quant_weight(dev(X), dev(W), None if sv is None else dev(sv), 0.01)
         assert bits_equal(host(sw), sw_ref) and bits_equal(host(Wq), Wq_ref)
+
+
+@pytest.mark.parametrize("H,I,first,second,E", [
+    # on average at most 48 rows per expert: the streaming kernel, tiles of 32, 64, 96 and 128 rows and one row more
+    (192, 448, (129, 97, 65, 33, 17, 1), (128, 96, 64, 32, 16, 6), 16),
+    (64, 64, (257, 2), (130, 128, 1), 12),
+    # at most 112: the tiled kernel's form for few rows, groups with one row tile, one row more, two tiles, one row, none
+    (320, 448, (129, 64, 65, 84), (256, 1, 0, 85), 8),
+    (128, 704, (100, 28), (127, 1), 4)])
+def test_routed_experts_at_the_edges_of_their_row_tiles(H, I, first, second, E):
+    """Group sizes are set through the logits: every token has one expert of `first` and one of `second`."""
+    T = sum(first)
+    assert T == sum(second) and len(first) + len(second) <= E
+    m = offline.small_moe(seed=T + H, T=T, H=H, I=I, E=E)
+    logits = np.full((T, E), -4.0, np.float16)
+    logits[np.arange(T), np.repeat(np.arange(len(first)), first)] = 2.0
+    logits[np.arange(T), len(first) + np.repeat(np.arange(len(second)), second)[::-1]] = 1.5
+    m["logits"] = logits + (np.arange(T)[:, None] % 7 * 0.0625).astype(np.float16)
+    _check_moe(m)
+    counts = _check_moe_asym(m)
+    assert tuple(counts[:len(first) + len(second)]) == (*first, *second)
