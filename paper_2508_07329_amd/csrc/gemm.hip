@@ -165,12 +165,21 @@ int launch_gemm(const GemmArgs& a, int epi, hipStream_t st) {
         }
     }
     if (a.offsets) {
-        // Few rows per expert: bound by the weight stream, not by the matrix cores.  Measured on a whole layer (us,
-        // 4096 x 14336, 8 experts; streaming kernel / this kernel's FEW form / its form for many rows), rows per expert
-        // 18: 265 / 324 / 340, 32: 283 / 309 / 335, 50: 315 / 312 / 341, 75: 372 / 331 / 354, 112: 445 / 354 / 371,
-        // 150: 666 / 515 / 463; 2048 x 5632, 16 experts: 9: 139 / 150 / 154, 37: 161 / 164 / 168, 75: 195 / 182 / 180.
+        // Few rows per expert: bound by the weight stream, not by the matrix cores.  Measured on whole layers (us) with the
+        // other projection on the 128 x 256 form for many rows, by rows per expert:
+        // gate/up, FEW / many rows (streaming): 4096 x 14336, 8 experts: 18: 310 / 325 (307), 32: 315 / 334 (327),
+        //   75: 340 / 363 (393), 112: 366 / 368, 150: 513 / 441; 2048 x 5632, 16 experts: 37: 159 / 173 (169), 75: 176 / 185.
+        // down, streaming / 128 x 128 / FEW / many rows: 14336 x 4096: 18: 286 / 309 / 324 / 325, 50: 315 / 316 / 329 / 342,
+        //   75: 344 / 331 / 350 / 360, 112: 382 / 378 / 364 / 371; 5632 x 2048: 37: 158 / 162 / 169 / 172;
+        //   3584 x 1024, 8 experts: 25: 52 / 57 / 69 / 68, 75: 63 / 64 / 77 / 75, 256: 105 / 95 / 109 / 105.
         const int mean = a.max_rows / (a.n_sel > 0 ? a.n_sel : 1);
-        if (mean <= STREAM_MEAN_ROWS) return launch_stream_grouped(a, epi, st);
+        const bool down = epi == EPI_LINEAR || epi == EPI_LINEAR_ASYM, asym = epi == EPI_LINEAR_ASYM;
+        if (down && mean <= STREAM_MEAN_ROWS) return launch_stream_grouped(a, asym, st);
+        // few output channels: 128 x 256 tiles (`mt` is an upper bound) would leave CUs without one
+        if (down && 8 * mt * ntn <= 7 * cu_count()) {
+            const dim3 grid((unsigned)round_up((int64_t)mt * cdiv(a.N, BN_S), 8));
+            return asym ? launch_small<EPI_LINEAR_ASYM>(a, grid, st) : launch_small<EPI_LINEAR>(a, grid, st);
+        }
         if (mean <= FEW_MEAN_ROWS) {
             const dim3 grid((unsigned)((int64_t)mt * round_up(ntn, 8)));
             switch (epi) {

@@ -26,20 +26,17 @@ __device__ __forceinline__ v4i gload16_stream(const int8_t* p) { return __builti
 constexpr int SK_WAVES = 8;
 
 struct StreamTile {
-    const int8_t* B;            // packed weights
-    const float *sw_a, *sw_b;   // channel scales (SwiGLU: gate, up)
-    const int32_t *cs_a, *cs_b; // column sums of the weight codes (asymmetric codes)
-    int row0, rows;             // first row and row count (at most 16 RB)
-    int n0;                     // first packed channel
+    const int8_t* B;        // packed weights
+    const float* sw;        // channel scales
+    const int32_t* colsum;  // column sums of the weight codes (asymmetric codes)
+    int row0, rows;         // first row and row count (at most 16 RB)
+    int n0;                 // first channel
 };
 
-// One tile: 16 C packed channels x `rows` token rows, K split over the work-group's NW waves.
-// SwiGLU tiles hold 32 gate channels and their 32 up channels (C = 4).  STREAM: nobody else reads these weights.
-template <int NW, int C, int RB, int DEPTH, int EPI, bool STREAM>
+// One tile: 16 C channels x `rows` token rows, K split over the work-group's NW waves.  STREAM: (nearly) no other
+// work-group reads these weights.
+template <int NW, int C, int RB, int DEPTH, bool ASYM, bool STREAM>
 __device__ __forceinline__ void stream_tile(const GemmArgs& a, const StreamTile& t, int (*sum)[4][64]) {
-    constexpr bool SWIGLU = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_ASYM;
-    constexpr bool ASYM = EPI == EPI_LINEAR_ASYM || EPI == EPI_SWIGLU_ASYM;
-    static_assert(!SWIGLU || C == 4, "two blocks of gate channels, then two of up channels");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, q = lane >> 4;
     const int nk = (a.K + 63) / 64;  // a last partial K-step reads chunks past K: the weights are zero there
@@ -106,65 +103,57 @@ __device__ __forceinline__ void stream_tile(const GemmArgs& a, const StreamTile&
                 for (int r = 0; r < 4; ++r) atomicAdd(&sum[c * RB + b][r][lane], acc[c][b][r]);  // exact: the order is immaterial
     }
     __syncthreads();
-    constexpr int OC = SWIGLU ? C / 2 : C;  // blocks of 16 output channels
-    const int out0 = SWIGLU ? t.n0 / 2 : t.n0, out_n = SWIGLU ? a.N / 2 : a.N;
-    for (int i = tid; i < OC * RB * 64; i += NW * 64) {
+    for (int i = tid; i < C * RB * 64; i += NW * 64) {
         const int cb = i >> 6, ln = i & 63;
-        const int row = 16 * (cb % RB) + (ln & 15), ch = out0 + 16 * (cb / RB) + 4 * (ln >> 4);
-        if (row >= t.rows || ch >= out_n) continue;
+        const int row = 16 * (cb % RB) + (ln & 15), ch = t.n0 + 16 * (cb / RB) + 4 * (ln >> 4);
+        if (row >= t.rows || ch >= a.N) continue;
         const float sx = a.sx[t.row0 + row];
         const int zshift = ASYM ? 128 - a.zp[t.row0 + row] : 0;
         __half hv[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             int v = sum[cb][r][ln];
-            if (ASYM) v += zshift * t.cs_a[ch + r];
-            if constexpr (SWIGLU) {
-                int u = sum[cb + OC * RB][r][ln];
-                if (ASYM) u += zshift * t.cs_b[ch + r];
-                const float g = dequant(v, sx, t.sw_a[ch + r]);
-                hv[r] = f2h(silu(g) * dequant(u, sx, t.sw_b[ch + r]));
-            } else {
-                if (a.acc_dbg) a.acc_dbg[(size_t)(t.row0 + row) * a.N + ch + r] = v;
-                float f = dequant(v, sx, t.sw_a[ch + r]);
-                if (a.act == HAQ_ACT_RELU) f = fmaxf(f, 0.0f);
-                hv[r] = f2h(f);
-            }
+            if (ASYM) v += zshift * t.colsum[ch + r];
+            if (a.acc_dbg) a.acc_dbg[(size_t)(t.row0 + row) * a.N + ch + r] = v;
+            float f = dequant(v, sx, t.sw[ch + r]);
+            if (a.act == HAQ_ACT_RELU) f = fmaxf(f, 0.0f);
+            hv[r] = f2h(f);
         }
         *reinterpret_cast<uint2*>(a.Y + (size_t)(t.row0 + row) * a.ldy + ch) = *reinterpret_cast<const uint2*>(hv);
     }
 }
 
 // C: blocks of 16 channels per work-group; RB: blocks of 16 token rows; WPS: waves per SIMD (register budget).
-template <int C, int RB, int DEPTH, int WPS, int EPI>
+template <int C, int RB, int DEPTH, int WPS, bool ASYM>
 __global__ __launch_bounds__(SK_WAVES * 64, WPS) void skinny_linear_kernel(GemmArgs a) {
     __shared__ int sum[C * RB][4][64];
-    const StreamTile t{a.B, a.sw, nullptr, a.colsum, nullptr, 0, a.M, (int)blockIdx.x * (16 * C)};
-    stream_tile<SK_WAVES, C, RB, DEPTH, EPI, true>(a, t, sum);
+    const StreamTile t{a.B, a.sw, a.colsum, 0, a.M, (int)blockIdx.x * (16 * C)};
+    stream_tile<SK_WAVES, C, RB, DEPTH, ASYM, true>(a, t, sum);
 }
 
 // More rows: `mt` row tiles of `tile_rows` rows share a unit of 64 channels.  Work-group ids are dealt round-robin to
 // the eight XCDs; each of them (one L2) takes a contiguous range of tiles, rows fastest, so that a unit's weights cross
 // the fabric once.  Bound: the fragments of a K-step, 1 KB for each block of 16 channels or rows, through a CU's load
 // path (64 B a cycle) against 4 RB matrix instructions; 16384 x 4096 on 333 rows, 256 tiles of 96 x 64: 77.5 -> 36.9 us.
-template <int RB, int DEPTH, int EPI>
+template <int RB, int DEPTH, bool ASYM>
 __global__ __launch_bounds__(SK_WAVES * 64, 2) void stream_linear_kernel(GemmArgs a, int mt, int tile_rows) {
     __shared__ int sum[4 * RB][4][64];
     const int total = mt * ((a.N + 63) / 64), per = (total + 7) / 8, slot = blockIdx.x / 8;
     const int id = (int)(blockIdx.x % 8) * per + slot;
     if (slot >= per || id >= total) return;
     const int row0 = (id % mt) * tile_rows;
-    const StreamTile t{a.B, a.sw, nullptr, a.colsum, nullptr, row0, min(tile_rows, a.M - row0), (id / mt) * 64};
-    stream_tile<SK_WAVES, 4, RB, DEPTH, EPI, false>(a, t, sum);
+    const StreamTile t{a.B, a.sw, a.colsum, row0, min(tile_rows, a.M - row0), (id / mt) * 64};
+    stream_tile<SK_WAVES, 4, RB, DEPTH, ASYM, false>(a, t, sum);
 }
 
-// Expert groups of few rows.  Bound: the weight stream, each activated expert's once (6 TB/s at best); the tiled kernel
-// draws 4.2 TB/s here, its work-groups starting and ending together in two rounds of long tiles.  An expert's m rows
+// Down projections of expert groups of few rows.  Bound: the weight stream, each activated expert's once; the tiled
+// kernel has one work-group per 256 channels and expert with two K-steps in flight (14336 x 4096, 8 experts of 18 rows:
+// the layer 325 -> 286 us).  An expert's m rows
 // are cut into ceil(m / 128) tiles of equal height; the units of 64 channels go round the XCDs, as work-group ids do, and
 // the row tiles of a unit stay on one of them.  Four waves, so that a CU holds two work-groups, one streaming while the
 // other adds up and stores.
 constexpr int SG_WAVES = 4;
-template <int EPI>
+template <bool ASYM>
 __global__ __launch_bounds__(SG_WAVES * 64, 2) void stream_grouped_kernel(GemmArgs a) {
     __shared__ int sum[4 * 8][4][64];
     const int nu = a.N / 64, nup = (nu + 7) / 8 * 8;
@@ -181,19 +170,15 @@ __global__ __launch_bounds__(SG_WAVES * 64, 2) void stream_grouped_kernel(GemmAr
         const int tile_rows = ((m + mt - 1) / mt + 15) / 16 * 16;  // (mt - 1) tile_rows < m: no tile is empty
         const int r0 = (id / 8) % mt * tile_rows, rows = min(tile_rows, m - r0);
         const ExpertTab& x = a.tab[e];
-        StreamTile t{a.which == 0 ? x.w13 : x.w2, a.which == 0 ? x.sw1 : x.sw2, x.sw3, nullptr, nullptr, lo + r0, rows, unit * 64};
-        if (EPI == EPI_LINEAR_ASYM || EPI == EPI_SWIGLU_ASYM) {
-            t.cs_a = a.which == 0 ? a.cstab[e].cs1 : a.cstab[e].cs2;
-            t.cs_b = a.cstab[e].cs3;
-        }
+        const StreamTile t{x.w2, x.sw2, ASYM ? a.cstab[e].cs2 : nullptr, lo + r0, rows, unit * 64};
         if (rows <= 32)
-            stream_tile<SG_WAVES, 4, 2, 6, EPI, true>(a, t, sum);
+            stream_tile<SG_WAVES, 4, 2, 6, ASYM, true>(a, t, sum);
         else if (rows <= 64)
-            stream_tile<SG_WAVES, 4, 4, 4, EPI, true>(a, t, sum);
+            stream_tile<SG_WAVES, 4, 4, 4, ASYM, true>(a, t, sum);
         else if (rows <= 96)
-            stream_tile<SG_WAVES, 4, 6, 3, EPI, true>(a, t, sum);
+            stream_tile<SG_WAVES, 4, 6, 3, ASYM, true>(a, t, sum);
         else
-            stream_tile<SG_WAVES, 4, 8, 2, EPI, true>(a, t, sum);
+            stream_tile<SG_WAVES, 4, 8, 2, ASYM, true>(a, t, sum);
         return;
     }
 }
@@ -202,9 +187,9 @@ template <int C, int RB, int DEPTH, int WPS>
 int launch_one(const GemmArgs& a, bool asym, hipStream_t st) {
     const dim3 grid(cdiv(a.N, 16 * C));
     if (asym)
-        hipLaunchKernelGGL((skinny_linear_kernel<C, RB, DEPTH, WPS, EPI_LINEAR_ASYM>), grid, dim3(SK_WAVES * 64), 0, st, a);
+        hipLaunchKernelGGL((skinny_linear_kernel<C, RB, DEPTH, WPS, true>), grid, dim3(SK_WAVES * 64), 0, st, a);
     else
-        hipLaunchKernelGGL((skinny_linear_kernel<C, RB, DEPTH, WPS, EPI_LINEAR>), grid, dim3(SK_WAVES * 64), 0, st, a);
+        hipLaunchKernelGGL((skinny_linear_kernel<C, RB, DEPTH, WPS, false>), grid, dim3(SK_WAVES * 64), 0, st, a);
     HAQ_CHECK_HIP(hipGetLastError());
     return HAQ_OK;
 }
@@ -214,9 +199,9 @@ int launch_rows(const GemmArgs& a, bool asym, hipStream_t st) {
     const int mt = cdiv(a.M, 16 * RB), tile_rows = 16 * cdiv(cdiv(a.M, mt), 16);
     const dim3 grid((unsigned)round_up((int64_t)mt * cdiv(a.N, 64), 8));
     if (asym)
-        hipLaunchKernelGGL((stream_linear_kernel<RB, DEPTH, EPI_LINEAR_ASYM>), grid, dim3(SK_WAVES * 64), 0, st, a, mt, tile_rows);
+        hipLaunchKernelGGL((stream_linear_kernel<RB, DEPTH, true>), grid, dim3(SK_WAVES * 64), 0, st, a, mt, tile_rows);
     else
-        hipLaunchKernelGGL((stream_linear_kernel<RB, DEPTH, EPI_LINEAR>), grid, dim3(SK_WAVES * 64), 0, st, a, mt, tile_rows);
+        hipLaunchKernelGGL((stream_linear_kernel<RB, DEPTH, false>), grid, dim3(SK_WAVES * 64), 0, st, a, mt, tile_rows);
     HAQ_CHECK_HIP(hipGetLastError());
     return HAQ_OK;
 }
@@ -256,15 +241,13 @@ int launch_stream_rows(const GemmArgs& a, bool asym, int rb, hipStream_t st) {
     }
 }
 
-int launch_stream_grouped(const GemmArgs& a, int epi, hipStream_t st) {
-    if (a.N % 64) return HAQ_ERR_UNSUPPORTED;  // the expert entry points take multiples of 64 only
+int launch_stream_grouped(const GemmArgs& a, bool asym, hipStream_t st) {
+    if (a.which != 1 || a.N % 64) return HAQ_ERR_UNSUPPORTED;  // the expert entry points take multiples of 64 only
     const dim3 grid((unsigned)((int64_t)(a.max_rows / 128 + a.n_sel) * round_up(a.N / 64, 8))), block(SG_WAVES * 64);
-    switch (epi) {
-        case EPI_LINEAR: hipLaunchKernelGGL(stream_grouped_kernel<EPI_LINEAR>, grid, block, 0, st, a); break;
-        case EPI_SWIGLU: hipLaunchKernelGGL(stream_grouped_kernel<EPI_SWIGLU>, grid, block, 0, st, a); break;
-        case EPI_LINEAR_ASYM: hipLaunchKernelGGL(stream_grouped_kernel<EPI_LINEAR_ASYM>, grid, block, 0, st, a); break;
-        default: hipLaunchKernelGGL(stream_grouped_kernel<EPI_SWIGLU_ASYM>, grid, block, 0, st, a); break;
-    }
+    if (asym)
+        hipLaunchKernelGGL(stream_grouped_kernel<true>, grid, block, 0, st, a);
+    else
+        hipLaunchKernelGGL(stream_grouped_kernel<false>, grid, block, 0, st, a);
     HAQ_CHECK_HIP(hipGetLastError());
     return HAQ_OK;
 }

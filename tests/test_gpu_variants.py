@@ -98,12 +98,15 @@ def test_layer_quantiser_at_the_edges_of_its_blocks(T, K, N):
 
 
 @pytest.mark.parametrize("H,I,first,second,E", [
-    # on average at most 48 rows per expert: the streaming kernel, tiles of 32, 64, 96 and 128 rows and one row more
+    # on average at most 48 rows per expert: the down projection streams in tiles of 32, 64, 96 and 128 rows (and one row
+    # more); the gate/up projection takes the tiled kernel's form for few rows
     (192, 448, (129, 97, 65, 33, 17, 1), (128, 96, 64, 32, 16, 6), 16),
     (64, 64, (257, 2), (130, 128, 1), 12),
-    # at most 112: the tiled kernel's form for few rows, groups with one row tile, one row more, two tiles, one row, none
+    # more rows: the down projection in 128 x 128 tiles; groups with one row tile, one row more, two tiles, one row, none
     (320, 448, (129, 64, 65, 84), (256, 1, 0, 85), 8),
-    (128, 704, (100, 28), (127, 1), 4)])
+    (128, 704, (100, 28), (127, 1), 4),
+    # 56 rows on average and more channel tiles than CUs: the form for few rows in both projections
+    (4096, 64, (300, 148), (1, 447), 16)])
 def test_routed_experts_at_the_edges_of_their_row_tiles(H, I, first, second, E):
     """Group sizes are set through the logits: every token has one expert of `first` and one of `second`."""
     T = sum(first)
