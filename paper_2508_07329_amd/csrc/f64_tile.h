@@ -20,14 +20,15 @@ constexpr int F64_PER = F64_KC * F64_B / 256;  // elements of an operand per thr
 
 // An operand: element (k, i) of the tile's rows i is cvt(p[k ld + i]) (KMAJOR) or cvt(p[i ld + k]), p at the tile's first
 // row.  Rows past n_i re-read the last one: they end in results that nobody stores.  The lane's offsets do not change
-// with k: an address is a scalar base and a 32-bit offset.
+// with k; they are 64-bit, since nothing bounds a stride (63 rows of 2^27 values are past 32 bits).  That costs neither
+// registers nor time: scaled to bytes a 32-bit offset needed 64 bits all the same.
 template <bool KMAJOR, class T, class CVT>
 struct F64Operand {
     static constexpr int LDS = KMAJOR ? F64_KC * (F64_B + 16) : F64_B * (F64_KC + 1);  // doubles; both pitches spread a fragment over the banks
     const T* p;
     int64_t ld;
     CVT cvt;
-    uint32_t off[F64_PER];
+    int64_t off[F64_PER];
     double r[F64_PER];
     static __device__ __forceinline__ int at(int k, int i) { return KMAJOR ? k * (F64_B + 16) + i : i * (F64_KC + 1) + k; }
     static __device__ __forceinline__ int my_k(int n) { return KMAJOR ? threadIdx.x / F64_B + 256 / F64_B * n : threadIdx.x % F64_KC; }
@@ -36,7 +37,7 @@ struct F64Operand {
 #pragma unroll
         for (int n = 0; n < F64_PER; ++n) {
             const int i = min(my_i(n), n_i - 1);
-            off[n] = (uint32_t)(KMAJOR ? my_k(n) * ld + i : i * ld + my_k(n));
+            off[n] = KMAJOR ? my_k(n) * ld + i : i * ld + my_k(n);
         }
     }
     __device__ __forceinline__ void fetch(int k0, int klen) {

@@ -97,6 +97,27 @@ def test_layer_quantiser_at_the_edges_of_its_blocks(T, K, N):
         assert bits_equal(host(sw), sw_ref) and bits_equal(host(Wq), Wq_ref)
 
 
+@pytest.mark.parametrize("rows,cols", [(33, 40), (70, 16)])
+def test_binary64_products_at_strides_past_32_bits(rows, cols):
+    """A tile's offsets from its first element exceed 2^32 elements: rows of x 2^27 apart (reference product), tokens 2^29
+    apart (Hessian), and a weight row of 2^29 values.  What lies between the rows is never read."""
+    rng = np.random.default_rng(rows)
+    X, W = rng.standard_normal((rows, cols)).astype(np.float16), rng.standard_normal((cols, 24)).astype(np.float32)
+    far = lambda n, ld: torch.empty((n - 1) * ld + cols, dtype=torch.float16, device="cuda").as_strided((n, cols), (ld, 1))
+    x = far(rows, 2 ** 27)
+    x.copy_(dev(X))
+    assert bits_equal(host(haq.haq_reference_matmul_f64(x, dev(W))), oracle.matmul_f64(X, W))
+    del x
+    x = far(17, 2 ** 29)
+    x.copy_(dev(X[:17]))
+    assert bits_equal(host(haq.haq_hessian_f64(x, None, 0.01)), oracle.hessian(X[:17], None, 0.01))
+    del x
+    n, k = 2 ** 29, 9
+    w = torch.zeros(k, n, dtype=torch.float32, device="cuda")
+    w[:, -100:] = dev(W[:k, :1])
+    y = haq.haq_reference_matmul_f64(dev(X[:1, :k]), w)
+    assert bits_equal(host(y[:, -100:]), oracle.matmul_f64(X[:1, :k], np.repeat(W[:k, :1], 100, axis=1))) and not bool(y[:, :-100].any())
+
 @pytest.mark.parametrize("H,I,first,second,E", [
     # on average at most 48 rows per expert: the down projection streams in tiles of 32, 64, 96 and 128 rows (and one row
     # more); the gate/up projection takes the tiled kernel's form for few rows
