@@ -10,7 +10,7 @@ namespace {
 
 // 128 x 256 tiles, 4 waves (2 x 2, 64 x 128 each), 3-deep ring: 75 KB of LDS and at most
 // 256 registers per lane, so two work-groups share a CU and fill each other's stalls.
-// (The shape can be overridden at compile time to measure other tilings; the small-problem instantiation below is fixed.)
+// (The shape can be overridden at compile time to measure other tilings; the other shapes below are fixed.)
 #ifndef HAQ_BM
 #define HAQ_BM 128
 #define HAQ_BN 256
@@ -26,8 +26,15 @@ namespace {
 constexpr int BM = HAQ_BM, BN = HAQ_BN, WAVES_M = HAQ_WAVES_M, WAVES_N = HAQ_WAVES_N, STAGES = HAQ_STAGES, MINB = HAQ_MINB;
 using Shape = GemmShape<BM, BN, WAVES_M, WAVES_N, STAGES>;
 
+// Row tiles of `bm` rows: exact for one matrix; an upper bound, rows / bm plus one partial tile per group, otherwise.
+int row_tiles(const GemmArgs& a, int bm) { return a.offsets ? a.max_rows / bm + a.n_sel : cdiv(a.M, bm); }
+// Every launch takes its grid from the tile of its own kernel: at least the tile count, a multiple of 8.
+dim3 tile_grid(const GemmArgs& a, int bm, int bn) { return dim3((unsigned)round_up((int64_t)row_tiles(a, bm) * cdiv(a.N, bn), 8)); }
+
 template <int EPI, bool DBG, bool FEW = false>
-int launch_one(const GemmArgs& a, dim3 grid, hipStream_t st) {
+int launch_one(const GemmArgs& a, hipStream_t st) {
+    // FEW: an expert's channel tiles go round the XCDs (decode_tile), a multiple of 8 of them for each row tile
+    const dim3 grid = FEW ? dim3((unsigned)((int64_t)row_tiles(a, BM) * round_up(cdiv(a.N, BN), 8))) : tile_grid(a, BM, BN);
     auto kern = gemm_i8_kernel<BM, BN, WAVES_M, WAVES_N, STAGES, MINB, EPI, DBG, FEW>;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
@@ -49,7 +56,7 @@ constexpr int SMALL_TILE_LIMIT = HAQ_SMALL_TILE_LIMIT;  // 128 x 256 tiles that 
 constexpr int BN_S = 128, MINB_S = 3;
 using ShapeS = GemmShape<128, BN_S, 2, 2, 3>;
 template <int EPI>
-int launch_small(const GemmArgs& a, dim3 grid, hipStream_t st) {
+int launch_small(const GemmArgs& a, hipStream_t st) {
     auto kern = gemm_i8_kernel<128, BN_S, 2, 2, 3, MINB_S, EPI, false>;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
@@ -57,7 +64,7 @@ int launch_small(const GemmArgs& a, dim3 grid, hipStream_t st) {
         attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, ShapeS::LDS_BYTES);
     });
     HAQ_CHECK_HIP(attr_err);
-    hipLaunchKernelGGL(kern, grid, dim3(ShapeS::THREADS), ShapeS::LDS_BYTES, st, a);
+    hipLaunchKernelGGL(kern, tile_grid(a, 128, BN_S), dim3(ShapeS::THREADS), ShapeS::LDS_BYTES, st, a);
     HAQ_CHECK_HIP(hipGetLastError());
     return HAQ_OK;
 }
@@ -69,7 +76,7 @@ int launch_small(const GemmArgs& a, dim3 grid, hipStream_t st) {
 constexpr int LARGE_TILE_MIN = 512;
 using ShapeL = GemmShape<256, 256, 4, 2, 3>;
 template <int EPI>
-int launch_large(const GemmArgs& a, dim3 grid, hipStream_t st) {
+int launch_large(const GemmArgs& a, hipStream_t st) {
     auto kern = gemm_i8_kernel<256, 256, 4, 2, 3, 1, EPI, false>;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
@@ -77,7 +84,7 @@ int launch_large(const GemmArgs& a, dim3 grid, hipStream_t st) {
         attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, ShapeL::LDS_BYTES);
     });
     HAQ_CHECK_HIP(attr_err);
-    hipLaunchKernelGGL(kern, grid, dim3(ShapeL::THREADS), ShapeL::LDS_BYTES, st, a);
+    hipLaunchKernelGGL(kern, tile_grid(a, 256, 256), dim3(ShapeL::THREADS), ShapeL::LDS_BYTES, st, a);
     HAQ_CHECK_HIP(hipGetLastError());
     return HAQ_OK;
 }
@@ -87,7 +94,7 @@ int launch_large(const GemmArgs& a, dim3 grid, hipStream_t st) {
 // direct-to-LDS bytes per matrix instruction than the 128 x 128 shape such problems would otherwise take: -2 %.
 using ShapeT = GemmShape<256, 128, 4, 2, 3>;
 template <int EPI>
-int launch_tall(const GemmArgs& a, dim3 grid, hipStream_t st) {
+int launch_tall(const GemmArgs& a, hipStream_t st) {
     auto kern = gemm_i8_kernel<256, 128, 4, 2, 3, 1, EPI, false>;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
@@ -95,7 +102,7 @@ int launch_tall(const GemmArgs& a, dim3 grid, hipStream_t st) {
         attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, ShapeT::LDS_BYTES);
     });
     HAQ_CHECK_HIP(attr_err);
-    hipLaunchKernelGGL(kern, grid, dim3(ShapeT::THREADS), ShapeT::LDS_BYTES, st, a);
+    hipLaunchKernelGGL(kern, tile_grid(a, 256, 128), dim3(ShapeT::THREADS), ShapeT::LDS_BYTES, st, a);
     HAQ_CHECK_HIP(hipGetLastError());
     return HAQ_OK;
 }
@@ -139,30 +146,20 @@ static constexpr int STREAM_MEAN_ROWS = 48, FEW_MEAN_ROWS = 112;  // rows per se
 int launch_gemm(const GemmArgs& a, int epi, hipStream_t st) {
     if (skinny_supported(a) && (epi == EPI_LINEAR || epi == EPI_LINEAR_ASYM)) return launch_skinny(a, epi == EPI_LINEAR_ASYM, st);
     const int ntn = cdiv(a.N, BN);
-    // upper bound on the M tiles: exact for one matrix; rows/BM plus one partial tile per group otherwise
-    const int mt = a.offsets ? a.max_rows / BM + a.n_sel : cdiv(a.M, BM);
+    const int mt = row_tiles(a, BM);
     if (mt <= 0 || ntn <= 0) return HAQ_OK;
     if (!a.offsets && !a.acc_dbg && (epi == EPI_LINEAR || epi == EPI_LINEAR_ASYM)) {
         const bool asym = epi == EPI_LINEAR_ASYM;
         const int n_cu = cu_count();
         const int64_t tiles_l = (int64_t)cdiv(a.M, 256) * cdiv(a.N, 256);
-        if (tiles_l >= LARGE_TILE_MIN) {
-            const dim3 grid((unsigned)round_up(tiles_l, 8));
-            return asym ? launch_large<EPI_LINEAR_ASYM>(a, grid, st) : launch_large<EPI_LINEAR>(a, grid, st);
-        }
+        if (tiles_l >= LARGE_TILE_MIN) return asym ? launch_large<EPI_LINEAR_ASYM>(a, st) : launch_large<EPI_LINEAR>(a, st);
         const int64_t tiles_s = (int64_t)cdiv(a.M, 128) * cdiv(a.N, BN_S);
         if (tiles_s <= n_cu) {
             if (const int rb = stream_row_blocks(a, n_cu)) return launch_stream_rows(a, asym, rb, st);
         }
         const int64_t tiles_t = (int64_t)cdiv(a.M, 256) * cdiv(a.N, 128);
-        if (tiles_t <= n_cu && 4 * tiles_t > 3 * n_cu) {
-            const dim3 grid((unsigned)round_up(tiles_t, 8));
-            return asym ? launch_tall<EPI_LINEAR_ASYM>(a, grid, st) : launch_tall<EPI_LINEAR>(a, grid, st);
-        }
-        if (mt * ntn <= SMALL_TILE_LIMIT) {
-            const dim3 grid((unsigned)round_up(tiles_s, 8));
-            return asym ? launch_small<EPI_LINEAR_ASYM>(a, grid, st) : launch_small<EPI_LINEAR>(a, grid, st);
-        }
+        if (tiles_t <= n_cu && 4 * tiles_t > 3 * n_cu) return asym ? launch_tall<EPI_LINEAR_ASYM>(a, st) : launch_tall<EPI_LINEAR>(a, st);
+        if (mt * ntn <= SMALL_TILE_LIMIT) return asym ? launch_small<EPI_LINEAR_ASYM>(a, st) : launch_small<EPI_LINEAR>(a, st);
     }
     if (a.offsets) {
         // Few rows per expert: bound by the weight stream, not by the matrix cores.  Measured on whole layers (us) with the
@@ -176,26 +173,21 @@ int launch_gemm(const GemmArgs& a, int epi, hipStream_t st) {
         const bool down = epi == EPI_LINEAR || epi == EPI_LINEAR_ASYM, asym = epi == EPI_LINEAR_ASYM;
         if (down && mean <= STREAM_MEAN_ROWS) return launch_stream_grouped(a, asym, st);
         // few output channels: 128 x 256 tiles (`mt` is an upper bound) would leave CUs without one
-        if (down && 8 * mt * ntn <= 7 * cu_count()) {
-            const dim3 grid((unsigned)round_up((int64_t)mt * cdiv(a.N, BN_S), 8));
-            return asym ? launch_small<EPI_LINEAR_ASYM>(a, grid, st) : launch_small<EPI_LINEAR>(a, grid, st);
-        }
+        if (down && 8 * mt * ntn <= 7 * cu_count()) return asym ? launch_small<EPI_LINEAR_ASYM>(a, st) : launch_small<EPI_LINEAR>(a, st);
         if (mean <= FEW_MEAN_ROWS) {
-            const dim3 grid((unsigned)((int64_t)mt * round_up(ntn, 8)));
             switch (epi) {
-                case EPI_SWIGLU: return launch_one<EPI_SWIGLU, false, true>(a, grid, st);
-                case EPI_SWIGLU_ASYM: return launch_one<EPI_SWIGLU_ASYM, false, true>(a, grid, st);
-                case EPI_LINEAR_ASYM: return launch_one<EPI_LINEAR_ASYM, false, true>(a, grid, st);
-                default: return launch_one<EPI_LINEAR, false, true>(a, grid, st);
+                case EPI_SWIGLU: return launch_one<EPI_SWIGLU, false, true>(a, st);
+                case EPI_SWIGLU_ASYM: return launch_one<EPI_SWIGLU_ASYM, false, true>(a, st);
+                case EPI_LINEAR_ASYM: return launch_one<EPI_LINEAR_ASYM, false, true>(a, st);
+                default: return launch_one<EPI_LINEAR, false, true>(a, st);
             }
         }
     }
-    const dim3 grid((unsigned)round_up((int64_t)mt * ntn, 8));
-    if (epi == EPI_SWIGLU) return launch_one<EPI_SWIGLU, false>(a, grid, st);
-    if (epi == EPI_SWIGLU_ASYM) return launch_one<EPI_SWIGLU_ASYM, false>(a, grid, st);
-    if (epi == EPI_LINEAR_ASYM) return a.acc_dbg ? launch_one<EPI_LINEAR_ASYM, true>(a, grid, st) : launch_one<EPI_LINEAR_ASYM, false>(a, grid, st);
-    if (a.acc_dbg) return launch_one<EPI_LINEAR, true>(a, grid, st);
-    return launch_one<EPI_LINEAR, false>(a, grid, st);
+    if (epi == EPI_SWIGLU) return launch_one<EPI_SWIGLU, false>(a, st);
+    if (epi == EPI_SWIGLU_ASYM) return launch_one<EPI_SWIGLU_ASYM, false>(a, st);
+    if (epi == EPI_LINEAR_ASYM) return a.acc_dbg ? launch_one<EPI_LINEAR_ASYM, true>(a, st) : launch_one<EPI_LINEAR_ASYM, false>(a, st);
+    if (a.acc_dbg) return launch_one<EPI_LINEAR, true>(a, st);
+    return launch_one<EPI_LINEAR, false>(a, st);
 }
 
 }  // namespace haq

@@ -1,0 +1,83 @@
+"""Which kernel a GEMM takes and with what grid: the launchers' host code over a recording stand-in for the HIP runtime."""
+import os
+import random
+import re
+import subprocess
+
+import pytest
+
+from paper_2508_07329_amd import build as hip_build
+
+LINEAR, SWIGLU, LINEAR_ASYM, SWIGLU_ASYM = range(4)
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    """plan(problems, *defines) -> [(kernel, its integer template arguments, work-groups)]; a problem is
+    (epi, M, N, K, n_sel, max_rows, which, acc_dbg)."""
+    out = tmp_path_factory.mktemp("plan")
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    flags = ["--offload-arch=gfx950", "--offload-host-only", "-O1", "-std=c++17", "-I", os.path.join(hip_build.ROOT, "include"), "-I", hip_build.CSRC]
+    built = {}
+
+    def build(defines):
+        tag, objs = str(len(built)), []
+        for src in (os.path.join(hip_build.CSRC, "gemm.hip"), os.path.join(hip_build.CSRC, "skinny.hip"), os.path.join(HERE, "launch_recorder.cpp")):
+            objs.append(str(out / (os.path.basename(src) + tag + ".o")))
+            subprocess.run([hipcc, *flags, *defines, "-c", "-x", "hip", src, "-o", objs[-1]], check=True)
+        exe = str(out / ("plan" + tag))
+        # the device code that the objects refer to does not exist
+        subprocess.run(["g++", *objs, "-o", exe, "-pthread", "-no-pie", "-Wl,--unresolved-symbols=ignore-all"], check=True)
+        return exe
+
+    def run(problems, *defines):
+        if defines not in built:
+            built[defines] = build(defines)
+        text = "".join(" ".join(map(str, p)) + "\n" for p in problems)
+        lines = subprocess.run([built[defines]], input=text, stdout=subprocess.PIPE, text=True, check=True).stdout.splitlines()
+        assert len(lines) == len(problems)
+        res = []
+        for line in lines:
+            name, grid = line.split()
+            m = re.search(r"(gemm_i8|skinny_linear|stream_linear|stream_grouped)_kernel", name)
+            res.append((m.group(1), [int(v) for v in re.findall(r"L[ib](\d+)E", name)], int(grid)))
+        return res
+
+    return run
+
+
+WIDE_MAIN_TILE = ("-DHAQ_BM=256", "-DHAQ_BN=256", "-DHAQ_MINB=1", "-DHAQ_STAGES=3", "-DHAQ_WAVES_M=4")
+
+
+@pytest.mark.parametrize("defines", [(), WIDE_MAIN_TILE], ids=["default", "256-row main tile"])
+def test_every_tile_has_a_work_group(plan, defines):
+    """Single matrices and expert groups of random sizes, also when the main tile is overridden at compile time."""
+    rng = random.Random(7)
+    problems, groups = [], []
+    for _ in range(600):
+        K = rng.choice((64, 512, 2048, 4096, 14336))
+        if rng.random() < 0.5:
+            M, N = int(2 ** rng.uniform(0, 12.5)), 16 * int(2 ** rng.uniform(0, 12))
+            problems.append((rng.choice((LINEAR, LINEAR_ASYM)), M, N, K, 0, 0, 0, int(rng.random() < 0.1)))
+            groups.append([M])
+        else:
+            which, N = rng.randrange(2), 64 * int(2 ** rng.uniform(0, 8))
+            m = [int(2 ** rng.uniform(0, 9.5)) - 1 for _ in range(rng.randrange(1, 17))]
+            epi = rng.choice((LINEAR, LINEAR_ASYM) if which else (SWIGLU, SWIGLU_ASYM))
+            problems.append((epi, 0, N, K, len(m), sum(m) + rng.randrange(3), which, 0))
+            groups.append(m)
+    for p, m, (kernel, t, grid) in zip(problems, groups, plan(problems, *defines)):
+        N, cd = p[2], lambda a, b: -(-a // b)
+        if kernel == "gemm_i8":
+            bm, bn, few = t[0], t[1], t[8]
+            need = sum(cd(x, bm) for x in m) * (cd(cd(N, bn), 8) * 8 if few else cd(N, bn))
+        elif kernel == "stream_grouped":
+            need = sum(cd(x, 128) for x in m) * cd(N // 64, 8) * 8
+        elif kernel == "stream_linear":
+            need = cd(m[0], 16 * t[0]) * cd(N, 64)
+        else:
+            assert m[0] <= 16 * t[1]
+            need = cd(N, 16 * t[0])
+        assert grid >= need, (p, m, kernel, t, grid, need)
+        assert kernel in ("skinny_linear", "stream_grouped") or grid % 8 == 0
