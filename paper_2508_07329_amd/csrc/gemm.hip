@@ -92,6 +92,7 @@ int launch_large(const GemmArgs& a, hipStream_t st) {
 // 256 x 128 tiles, 8 waves (4 x 2 of 64 x 64), one work-group per CU: for dense problems that this tiling covers in
 // one round with most CUs busy (fc2 of the OPT-6.7B block: 8 x 32 tiles on 256 CUs).  A quarter fewer
 // direct-to-LDS bytes per matrix instruction than the 128 x 128 shape such problems would otherwise take: -2 %.
+// Not for 128 rows and fewer, of which the tile would waste half: 64 rows of 512 x 32768 10.2 us instead of 10.8.
 using ShapeT = GemmShape<256, 128, 4, 2, 3>;
 template <int EPI>
 int launch_tall(const GemmArgs& a, hipStream_t st) {
@@ -122,6 +123,7 @@ static int stream_row_blocks(const GemmArgs& a, int n_cu) {
     float best = 3.0f + 0.3f * nk;
     int rb = 0;
     for (int r = 4; r <= 8; r += 2) {
+        if (a.M <= 16 * r) break;  // a single row tile: skinny_pays has decided
         const int64_t tiles = (int64_t)cdiv(a.M, 16 * r) * cdiv(a.N, 64);
         const float t = (float)((tiles + n_cu - 1) / n_cu) * (4.0f + nk * (4 + r) * (1.0f / 80.0f));
         if (t < best) {
@@ -144,7 +146,7 @@ int cu_count() {
 static constexpr int STREAM_MEAN_ROWS = 48, FEW_MEAN_ROWS = 112;  // rows per selected expert, on average
 
 int launch_gemm(const GemmArgs& a, int epi, hipStream_t st) {
-    if (skinny_supported(a) && (epi == EPI_LINEAR || epi == EPI_LINEAR_ASYM)) return launch_skinny(a, epi == EPI_LINEAR_ASYM, st);
+    if (skinny_pays(a) && (epi == EPI_LINEAR || epi == EPI_LINEAR_ASYM)) return launch_skinny(a, epi == EPI_LINEAR_ASYM, st);
     const int ntn = cdiv(a.N, BN);
     const int mt = row_tiles(a, BM);
     if (mt <= 0 || ntn <= 0) return HAQ_OK;
@@ -158,7 +160,7 @@ int launch_gemm(const GemmArgs& a, int epi, hipStream_t st) {
             if (const int rb = stream_row_blocks(a, n_cu)) return launch_stream_rows(a, asym, rb, st);
         }
         const int64_t tiles_t = (int64_t)cdiv(a.M, 256) * cdiv(a.N, 128);
-        if (tiles_t <= n_cu && 4 * tiles_t > 3 * n_cu) return asym ? launch_tall<EPI_LINEAR_ASYM>(a, st) : launch_tall<EPI_LINEAR>(a, st);
+        if (a.M > 128 && tiles_t <= n_cu && 4 * tiles_t > 3 * n_cu) return asym ? launch_tall<EPI_LINEAR_ASYM>(a, st) : launch_tall<EPI_LINEAR>(a, st);
         if (mt * ntn <= SMALL_TILE_LIMIT) return asym ? launch_small<EPI_LINEAR_ASYM>(a, st) : launch_small<EPI_LINEAR>(a, st);
     }
     if (a.offsets) {

@@ -153,7 +153,7 @@ struct GemmArgs {
 int launch_gemm(const GemmArgs& a, int epi, hipStream_t st);
 // Dense problems of at most SKINNY_MAX_ROWS token rows (skinny.hip): the weights are streamed once into registers.
 constexpr int SKINNY_MAX_ROWS = 128;
-bool skinny_supported(const GemmArgs& a);
+bool skinny_pays(const GemmArgs& a);  // within its limits and not slower than the tiled kernel
 int launch_skinny(const GemmArgs& a, bool asym, hipStream_t st);
 int launch_stream_rows(const GemmArgs& a, bool asym, int rb, hipStream_t st);  // any row count: row tiles of 16 rb rows (rb: 4, 6 or 8)
 int launch_stream_grouped(const GemmArgs& a, bool asym, hipStream_t st);       // expert groups (down projection), row tiles of at most 128 rows

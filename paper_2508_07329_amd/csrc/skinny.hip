@@ -208,14 +208,40 @@ int launch_rows(const GemmArgs& a, bool asym, hipStream_t st) {
 
 }  // namespace
 
-bool skinny_supported(const GemmArgs& a) { return !a.offsets && a.M >= 1 && a.M <= SKINNY_MAX_ROWS; }
+// 64 channels per work-group share every token fragment, but only from 128 such units on do enough CUs draw
+// weights: 12672 channels, 16 rows of 3168: 9.9 us against 13.2 with 16 channels, 64 rows: 13.6 against 22.9;
+// 4096 channels, 16 rows of 4096: 8.3 us against 5.8, 64 rows: 12.0 against 8.0.
+static int channel_blocks(int N) { return N / 64 >= 128 ? 4 : 1; }
+
+// Up to 64 rows the weight stream decides: one round of work-groups always wins; more rounds each pay the start, the sums
+// and the epilogue again and need K to carry them, while the tiled kernel has work-groups enough from 24576 channels on.
+// From 65 rows on a K-step also costs 6 or 8 row fragments, on one work-group per CU.
+// Measured (weights cold, us, this kernel / what launch_gemm takes instead; K x N):
+//   16 rows:  1024 x 65536 19.0 / 19.0, 1024 x 24576 9.3 / 12.4, 512 x 65536 17.7 / 12.9
+//   32 rows:  1536 x 24576 14.1 / 15.7, 1024 x 24576 12.4 / 12.5, 768 x 24576 11.6 / 10.7;  2048 x 65536 32 / 29 to 38 (box to box),
+//             1536 x 50272 25.4 / 22.7
+//   33 rows:  4096 x 65536 53 / 57 to 62, 2048 x 65536 35 / 36;   64 rows: 4096 x 65536 61 / 52, 2048 x 24576 18.1 / 18.8, 1536 x 24576 17.3 / 15.9
+//   96 rows:  768 x 16384 9.9 / 10.2, 512 x 16384 9.3 / 8.7, 4096 x 24576 32.3 / 29.1;  128 rows: 1024 x 16384 11.1 / 11.8, 768 x 16384 10.8 / 10.2
+// Between one round of 16-channel units and 128 units of 64 channels two row tiles of 64 rows (launch_stream_rows) fill the
+// chip: 96 rows of 512 x 8192 8.3 / 7.7, 1536 x 6144 11.5 / 9.1, 4096 x 8192 16.4 / 14.3, 8192 x 8192 28.2 / 22.5.  On fewer
+// channels those are too few work-groups: 128 rows of 4096 x 4096 9.9 / 12.5, 16384 x 4096 34.9 / 35.4.
+bool skinny_pays(const GemmArgs& a) {
+    if (a.offsets || a.M < 1 || a.M > SKINNY_MAX_ROWS) return false;
+    const int n_cu = cu_count(), C = channel_blocks(a.N), RB = (a.M + 15) / 16;
+    const int per_cu = RB == 1 || (C == 1 && RB <= 4) ? 2 : 1;  // work-groups that a CU holds
+    const int rounds = cdiv(cdiv(a.N, 16 * C), per_cu * n_cu);
+    if (RB > 4) {
+        if (a.N <= 16 * n_cu) return true;
+        return 2 * cdiv(a.N, 64) > n_cu && rounds == 1 && a.K >= (RB > 6 ? 1024 : 768);
+    }
+    // least K for two rounds and for more, by blocks of 16 rows
+    constexpr int MIN_K[2][4] = {{1024, 1536, 2048, 2048}, {1024, 2048, 4096, INT32_MAX}};
+    return rounds == 1 || a.K >= MIN_K[rounds > 2][RB - 1];
+}
 
 int launch_skinny(const GemmArgs& a, bool asym, hipStream_t st) {
     static_assert(SKINNY_MAX_ROWS == 128, "eight blocks of 16 rows");
-    // 64 channels per work-group share every token fragment, but only from 128 such units on do enough CUs draw
-    // weights: 12672 channels, 16 rows of 3168: 9.9 us against 13.2 with 16 channels, 64 rows: 13.6 against 22.9;
-    // 4096 channels, 16 rows of 4096: 8.3 us against 5.8, 64 rows: 12.0 against 8.0.
-    const int C = a.N / 64 >= 128 ? 4 : 1;
+    const int C = channel_blocks(a.N);
     const int RB = (a.M + 15) / 16;
 #define HAQ_SKINNY(c, b, d, w) \
     if (C == c && RB <= b) return launch_one<c, b, d, w>(a, asym, st)
