@@ -114,10 +114,13 @@ int launch_tall(const GemmArgs& a, hipStream_t st) {
 // the waves, operands straight into registers) beats one round of 128 x 128 tiles, or 0.  Such a round costs a
 // work-group 0.3 us for each 64-byte K-step however few of them there are (77 us at K = 16384 for 64 to 256 tiles);
 // a round of streaming tiles costs (4 + RB) / 80 us a K-step, the fragments of a step through a CU's load path, and
-// 4 us to start and finish.  Measured (us, M rows, K x N, streaming against tiled):
+// 3.4 + RB / 5 us to start, add up and finish.  Measured (us, M rows, K x N, streaming against tiled):
 //   16384 x 4096:  129 rows 30 / 78,  333: 37 / 78,  512: 44 / 79,  700: 70 / 82,  1024: 84 / 85
 //   4096 x 4096:   129 rows 10 / 20,  333: 13 / 20,  512: 15 / 20,  700: 25 / 21 (tiled stays)
 //   3072 x 768:    333 rows 9.4 / 15.3,  1024: 9.7 / 15.7;   2048 x 8192: 192 rows 10.3 / 13.1,  333: 18 / 13 (tiled)
+// and where few K-steps leave the start and the end to decide (weights cold):
+//   512 x 4096:    256 rows 7.6 / 8.5,  333: 9.2 / 8.6 (tiled);   768 x 3072: 400 rows 9.6 / 9.9,  512: 10.3 / 10.0 (tiled)
+//   1024 x 4096:   512 rows 10.7 / 11.2
 static int stream_row_blocks(const GemmArgs& a, int n_cu) {
     const int nk = cdiv(a.K, 64);
     float best = 3.0f + 0.3f * nk;
@@ -125,7 +128,7 @@ static int stream_row_blocks(const GemmArgs& a, int n_cu) {
     for (int r = 4; r <= 8; r += 2) {
         if (a.M <= 16 * r) break;  // a single row tile: skinny_pays has decided
         const int64_t tiles = (int64_t)cdiv(a.M, 16 * r) * cdiv(a.N, 64);
-        const float t = (float)((tiles + n_cu - 1) / n_cu) * (4.0f + nk * (4 + r) * (1.0f / 80.0f));
+        const float t = (float)((tiles + n_cu - 1) / n_cu) * (3.4f + 0.2f * r + nk * (4 + r) * (1.0f / 80.0f));
         if (t < best) {
             best = t;
             rb = r;

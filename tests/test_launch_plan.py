@@ -97,3 +97,11 @@ def test_short_batches_leave_the_streaming_kernel_where_it_was_slower(plan):
             assert kernel == "gemm_i8" and t[0] == 128, (p, kernel, t)  # 256-row tiles would be half empty
         assert all(kernel == "skinny_linear" for kernel, _, _ in of(skinny)), of(skinny)
         assert all(kernel == "stream_linear" and t[0] == 4 for kernel, t, _ in of(rows64)), of(rows64)
+
+
+def test_streaming_row_tiles_only_where_k_steps_carry_their_start_and_end(plan):
+    tiled = [(333, 512, 4096), (512, 512, 4096), (512, 768, 3072), (640, 768, 3072), (777, 4096, 4096), (333, 2048, 8192)]
+    stream = [(256, 512, 4096), (400, 768, 3072), (512, 1024, 4096), (333, 16384, 4096), (700, 16384, 4096), (1024, 3072, 768)]
+    for epi in (LINEAR, LINEAR_ASYM):
+        of = lambda sizes: [k for k, _, _ in plan([(epi, M, N, K, 0, 0, 0, 0) for M, K, N in sizes])]
+        assert set(of(tiled)) == {"gemm_i8"} and set(of(stream)) == {"stream_linear"}, (of(tiled), of(stream))
