@@ -14,6 +14,7 @@
 // channels; the epilogue dequantises, applies the activation, stages fp16 rows in LDS
 // and writes 16 bytes per lane.
 #pragma once
+#include "group_tiles.h"
 #include "haq_common.h"
 
 namespace haq {
@@ -43,8 +44,6 @@ struct TileCoord {
 #endif
 constexpr int TILE_BAND = HAQ_TILE_BAND;
 
-// FEW (expert groups of a row tile or so each): every expert's channel tiles go round the XCDs, as work-group ids do, and
-// the row tiles of one channel tile stay on one of them; a contiguous range would give each XCD an expert of its own.
 template <int BM, int BN, bool FEW>
 __device__ __forceinline__ TileCoord decode_tile(const GemmArgs& a) {
     TileCoord tc;
@@ -53,22 +52,14 @@ __device__ __forceinline__ TileCoord decode_tile(const GemmArgs& a) {
     tc.m0 = tc.m_end = tc.n0 = 0;
     const int ntn = (a.N + BN - 1) / BN;
     if constexpr (FEW) {
-        const int ntp = (ntn + 7) / 8 * 8;
-        int id = blockIdx.x;
-        for (int i = 0; i < a.n_sel; ++i) {
-            const int e = a.sel[i];
-            const int lo = a.offsets[e], hi = a.offsets[e + 1];
-            const int mt = (hi - lo + BM - 1) / BM;
-            if (id < mt * ntp) {
-                const int u = (id / 8 / mt) * 8 + id % 8;
-                tc.e = e;
-                tc.m0 = lo + ((id / 8) % mt) * BM;
-                tc.m_end = hi;
-                tc.n0 = u * BN;
-                tc.valid = u < ntn;
-                return tc;
-            }
-            id -= mt * ntp;
+        const GroupLanes g(a);
+        GroupTile t;
+        if (g.template deal<BM>(a, ntn, t)) {
+            tc.e = g.of(g.e, t.i);
+            tc.m0 = g.of(g.lo, t.i) + t.mi * BM;
+            tc.m_end = g.of(g.hi, t.i);
+            tc.n0 = t.u * BN;
+            tc.valid = true;
         }
         return tc;  // the grid is an upper bound
     }

@@ -12,6 +12,7 @@
 //   4096 x 16384   27.8-12.6   27.8-12.9   28.0-14.4   28.4-15.7   28.7-21.3   (13.2 at the rate of a large copy)
 //   16384 x 4096   81.0-14.1   80.4-14.8   80.8-19.1   81.3-25.5   80.6-36.5   (13.2; the token rows are re-read per unit)
 //   768 x 3072      7.4- 3.3    7.5- 3.4    7.5- 4.2    7.8- 4.4    7.7- 6.3
+#include "group_tiles.h"
 #include "haq_common.h"
 
 namespace haq {
@@ -23,7 +24,7 @@ typedef const __attribute__((address_space(1))) v4i* gptr_v4i;
 __device__ __forceinline__ v4i gload16(const int8_t* p) { return *(gptr_v4i)(uintptr_t)p; }
 __device__ __forceinline__ v4i gload16_stream(const int8_t* p) { return __builtin_nontemporal_load((gptr_v4i)(uintptr_t)p); }
 
-constexpr int SK_WAVES = 8;
+constexpr int SK_WAVES = 8, SG_WAVES = 4;  // waves of a work-group: dense, expert groups
 
 struct StreamTile {
     const int8_t* B;        // packed weights
@@ -90,6 +91,10 @@ __device__ __forceinline__ void stream_tile(const GemmArgs& a, const StreamTile&
             for (int i = 0; i < DEPTH; ++i) {
                 mac(fr[i]);
                 next(fr[i]);
+                // Expert groups: without it the loads sink below the next steps' MFMAs (two groups of 112 rows of
+                // 1024 x 3584: 57.4 -> 55.6 us a layer).  The dense forms, eight waves that cover for each other, are
+                // faster as the compiler places them (400 rows of 16384 x 4096: 42.6 against 44.0).
+                if (NW == SG_WAVES) __builtin_amdgcn_sched_barrier(0);
             }
         }
 #pragma unroll
@@ -152,35 +157,25 @@ __global__ __launch_bounds__(SK_WAVES * 64, 2) void stream_linear_kernel(GemmArg
 // are cut into ceil(m / 128) tiles of equal height; the units of 64 channels go round the XCDs, as work-group ids do, and
 // the row tiles of a unit stay on one of them.  Four waves, so that a CU holds two work-groups, one streaming while the
 // other adds up and stores.
-constexpr int SG_WAVES = 4;
 template <bool ASYM>
 __global__ __launch_bounds__(SG_WAVES * 64, 2) void stream_grouped_kernel(GemmArgs a) {
     __shared__ int sum[4 * 8][4][64];
-    const int nu = a.N / 64, nup = (nu + 7) / 8 * 8;
-    int id = blockIdx.x;
-    for (int i = 0; i < a.n_sel; ++i) {
-        const int e = a.sel[i], lo = a.offsets[e], m = a.offsets[e + 1] - lo;
-        const int mt = (m + 127) / 128;
-        if (id >= mt * nup) {
-            id -= mt * nup;
-            continue;
-        }
-        const int unit = (id / 8 / mt) * 8 + id % 8;
-        if (unit >= nu) return;
-        const int tile_rows = ((m + mt - 1) / mt + 15) / 16 * 16;  // (mt - 1) tile_rows < m: no tile is empty
-        const int r0 = (id / 8) % mt * tile_rows, rows = min(tile_rows, m - r0);
-        const ExpertTab& x = a.tab[e];
-        const StreamTile t{x.w2, x.sw2, ASYM ? a.cstab[e].cs2 : nullptr, lo + r0, rows, unit * 64};
-        if (rows <= 32)
-            stream_tile<SG_WAVES, 4, 2, 6, ASYM, true>(a, t, sum);
-        else if (rows <= 64)
-            stream_tile<SG_WAVES, 4, 4, 4, ASYM, true>(a, t, sum);
-        else if (rows <= 96)
-            stream_tile<SG_WAVES, 4, 6, 3, ASYM, true>(a, t, sum);
-        else
-            stream_tile<SG_WAVES, 4, 8, 2, ASYM, true>(a, t, sum);
-        return;
-    }
+    const GroupLanes g(a);
+    GroupTile gt;
+    if (!g.deal<128>(a, a.N / 64, gt)) return;
+    const int e = g.of(g.e, gt.i), lo = g.of(g.lo, gt.i), m = g.of(g.hi, gt.i) - lo;
+    const int tile_rows = ((m + gt.mt - 1) / gt.mt + 15) / 16 * 16;  // (mt - 1) tile_rows < m: no tile is empty
+    const int r0 = gt.mi * tile_rows, rows = min(tile_rows, m - r0);
+    const ExpertTab& x = a.tab[e];
+    const StreamTile t{x.w2, x.sw2, ASYM ? a.cstab[e].cs2 : nullptr, lo + r0, rows, gt.u * 64};
+    if (rows <= 32)
+        stream_tile<SG_WAVES, 4, 2, 6, ASYM, true>(a, t, sum);
+    else if (rows <= 64)
+        stream_tile<SG_WAVES, 4, 4, 4, ASYM, true>(a, t, sum);
+    else if (rows <= 96)
+        stream_tile<SG_WAVES, 4, 6, 3, ASYM, true>(a, t, sum);
+    else
+        stream_tile<SG_WAVES, 4, 8, 2, ASYM, true>(a, t, sum);
 }
 
 template <int C, int RB, int DEPTH, int WPS>

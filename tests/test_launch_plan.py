@@ -10,6 +10,19 @@ from paper_2508_07329_amd import build as hip_build
 
 LINEAR, SWIGLU, LINEAR_ASYM, SWIGLU_ASYM = range(4)
 HERE = os.path.dirname(os.path.abspath(__file__))
+HIPCC = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-arch=gfx950", "--offload-host-only", "-O1", "-std=c++17",
+         "-I", os.path.join(hip_build.ROOT, "include"), "-I", hip_build.CSRC]
+
+
+def _host_program(out, tag, sources, defines=()):
+    """An executable of the sources' host code; the device code and the HIP runtime that it refers to do not exist."""
+    objs = []
+    for src in sources:
+        objs.append(str(out / (os.path.basename(src) + tag + ".o")))
+        subprocess.run([*HIPCC, *defines, "-c", "-x", "hip", src, "-o", objs[-1]], check=True)
+    exe = str(out / ("prog" + tag))
+    subprocess.run(["g++", *objs, "-o", exe, "-pthread", "-no-pie", "-Wl,--unresolved-symbols=ignore-all"], check=True)
+    return exe
 
 
 @pytest.fixture(scope="module")
@@ -17,23 +30,12 @@ def plan(tmp_path_factory):
     """plan(problems, *defines) -> [(kernel, its integer template arguments, work-groups)]; a problem is
     (epi, M, N, K, n_sel, max_rows, which, acc_dbg)."""
     out = tmp_path_factory.mktemp("plan")
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    flags = ["--offload-arch=gfx950", "--offload-host-only", "-O1", "-std=c++17", "-I", os.path.join(hip_build.ROOT, "include"), "-I", hip_build.CSRC]
+    sources = [os.path.join(hip_build.CSRC, "gemm.hip"), os.path.join(hip_build.CSRC, "skinny.hip"), os.path.join(HERE, "launch_recorder.cpp")]
     built = {}
-
-    def build(defines):
-        tag, objs = str(len(built)), []
-        for src in (os.path.join(hip_build.CSRC, "gemm.hip"), os.path.join(hip_build.CSRC, "skinny.hip"), os.path.join(HERE, "launch_recorder.cpp")):
-            objs.append(str(out / (os.path.basename(src) + tag + ".o")))
-            subprocess.run([hipcc, *flags, *defines, "-c", "-x", "hip", src, "-o", objs[-1]], check=True)
-        exe = str(out / ("plan" + tag))
-        # the device code that the objects refer to does not exist
-        subprocess.run(["g++", *objs, "-o", exe, "-pthread", "-no-pie", "-Wl,--unresolved-symbols=ignore-all"], check=True)
-        return exe
 
     def run(problems, *defines):
         if defines not in built:
-            built[defines] = build(defines)
+            built[defines] = _host_program(out, str(len(built)), sources, defines)
         text = "".join(" ".join(map(str, p)) + "\n" for p in problems)
         lines = subprocess.run([built[defines]], input=text, stdout=subprocess.PIPE, text=True, check=True).stdout.splitlines()
         assert len(lines) == len(problems)
@@ -105,3 +107,21 @@ def test_streaming_row_tiles_only_where_k_steps_carry_their_start_and_end(plan):
     for epi in (LINEAR, LINEAR_ASYM):
         of = lambda sizes: [k for k, _, _ in plan([(epi, M, N, K, 0, 0, 0, 0) for M, K, N in sizes])]
         assert set(of(tiled)) == {"gemm_i8"} and set(of(stream)) == {"stream_linear"}, (of(tiled), of(stream))
+
+
+def test_group_tiles_are_dealt_once_and_evenly(tmp_path):
+    """Every tile of every group once, all row tiles of a channel tile on one XCD; with one row tile for each group the
+    XCDs differ by one tile at most, whatever the number of channel tiles is."""
+    exe = _host_program(tmp_path, "deal", [os.path.join(HERE, "group_tiles_check.cpp")])
+    rng = random.Random(11)
+    even = [(128, ntn, [rng.randrange(1, 129) for _ in range(n)]) for ntn in (1, 5, 7, 8, 9, 12, 14, 44, 64) for n in (1, 4, 8, 17, 32)]
+    mixed = [(rng.choice((128, 256)), rng.randrange(1, 113), [rng.choice((0, 1, rng.randrange(700))) for _ in range(rng.randrange(1, 33))])
+             for _ in range(300)]
+    text = "".join(f"{bm} {ntn} {len(rows)} {' '.join(map(str, rows))}\n" for bm, ntn, rows in even + mixed)
+    lines = subprocess.run([exe], input=text, stdout=subprocess.PIPE, text=True, check=True).stdout.splitlines()
+    assert len(lines) == len(even + mixed)
+    for p, line in zip(even + mixed, lines):
+        assert line.startswith("covered"), (p, line)
+    for p, line in zip(even, lines):
+        lo, hi = map(int, line.split()[1:])
+        assert hi - lo <= 1, (p, lo, hi)
