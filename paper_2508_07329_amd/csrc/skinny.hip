@@ -34,8 +34,8 @@ struct StreamTile {
     int n0;                 // first channel
 };
 
-// One tile: 16 C channels x `rows` token rows, K split over the work-group's NW waves.  STREAM: (nearly) no other
-// work-group reads these weights.
+// One tile: 16 C channels x `rows` token rows, K split over the work-group's NW waves.  STREAM: no other work-group
+// reads these weights.
 template <int NW, int C, int RB, int DEPTH, bool ASYM, bool STREAM>
 __device__ __forceinline__ void stream_tile(const GemmArgs& a, const StreamTile& t, int (*sum)[4][64]) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -168,14 +168,24 @@ __global__ __launch_bounds__(SG_WAVES * 64, 2) void stream_grouped_kernel(GemmAr
     const int r0 = gt.mi * tile_rows, rows = min(tile_rows, m - r0);
     const ExpertTab& x = a.tab[e];
     const StreamTile t{x.w2, x.sw2, ASYM ? a.cstab[e].cs2 : nullptr, lo + r0, rows, gt.u * 64};
-    if (rows <= 32)
+    // Row tiles that share their weights read them through the caches (4096 x 14336, 8 experts of 76 rows, skewed: the layer
+    // 339 -> 333 us; two of 192 rows: 161 -> 152); two and more have over 32 rows each.
+    if (gt.mt > 1) {
+        if (rows <= 64)
+            stream_tile<SG_WAVES, 4, 4, 4, ASYM, false>(a, t, sum);
+        else if (rows <= 96)
+            stream_tile<SG_WAVES, 4, 6, 3, ASYM, false>(a, t, sum);
+        else
+            stream_tile<SG_WAVES, 4, 8, 2, ASYM, false>(a, t, sum);
+    } else if (rows <= 32) {
         stream_tile<SG_WAVES, 4, 2, 6, ASYM, true>(a, t, sum);
-    else if (rows <= 64)
+    } else if (rows <= 64) {
         stream_tile<SG_WAVES, 4, 4, 4, ASYM, true>(a, t, sum);
-    else if (rows <= 96)
+    } else if (rows <= 96) {
         stream_tile<SG_WAVES, 4, 6, 3, ASYM, true>(a, t, sum);
-    else
+    } else {
         stream_tile<SG_WAVES, 4, 8, 2, ASYM, true>(a, t, sum);
+    }
 }
 
 template <int C, int RB, int DEPTH, int WPS>
