@@ -146,7 +146,26 @@ int cu_count() {
     return n_cu;
 }
 
-static constexpr int STREAM_MEAN_ROWS = 48, FEW_MEAN_ROWS = 112;  // rows per selected expert, on average
+// Down projections of expert groups: rows per selected expert, on average, up to which the streaming kernel is taken.
+// Units of 64 channels, one row tile each, are its work-groups, of which a CU holds two.  Measured on whole layers (us,
+// weights cold, tokens spread evenly, then by 1 / rank^1.1; streaming / 128 x 128 tiles / FEW / many rows):
+//   units 128 (1024 x 3584, 8 experts), 100 rows: 71 / 77 / 82 / 86, 75 / 82 / 86 / 92
+//         256 (4096 x 14336, 4), 100: 171 / 184 / 216 / 214, 197 / 201 / 233 / 232;  (2048 x 8192, 8), 100: 124 / 135 / 147 / 151, 137 / 144 / 155 / 160
+//         384 (3072 x 14336, 8), 100: 275 / 271 / 286 / 294, 308 / 341 / 312 / 321
+//         448 (3584 x 8192, 8), 48: 165 / 161 / 180 / 174, 170 / 161 / 182 / 173;  76: 179 / 167 / 189 / 180, 187 / 182 / 199 / 192
+//         512 (4096 x 14336, 8), 56: 289 / 295 / 306 / 317, 306 / 334 / 308 / 319;  76: 312 / 313 / 325 / 333, 333 / 347 / 320 / 332;
+//              100: 318 / 316 / 328 / 338, 363 / 388 / 363 / 375
+//         512 (2048 x 5632, 16), 64: 160 / 161 / 166 / 171, 177 / 184 / 172 / 179;  100: 169 / 166 / 172 / 176, 194 / 197 / 185 / 192
+// More units than two for each CU: FEW, unless its own 128 x 256 tiles fill the chip and a second row tile starts a round:
+//         768 (3072 x 8192, 16), 20: 238 / 265 / 241 / 255;  36: 266 / 277 / 253 / 268, 269 / 287 / 263 / 278
+//         1024 (4096 x 7168, 16), 36: 294 / 297 / 290 / 297, 288 / 322 / 317 / 335;  56: 311 / 306 / 299 / 306, 331 / 352 / 349 / 364
+static int stream_mean_rows(const GemmArgs& a, int n_cu) {
+    const int units = a.n_sel * (a.N / 64);
+    if (2 * units <= 3 * n_cu) return 112;
+    if (units <= 2 * n_cu) return 64;
+    return a.n_sel * cdiv(a.N, BN) >= n_cu ? 48 : 24;
+}
+static constexpr int FEW_MEAN_ROWS = 112;  // likewise for the form for few rows
 
 int launch_gemm(const GemmArgs& a, int epi, hipStream_t st) {
     if (skinny_pays(a) && (epi == EPI_LINEAR || epi == EPI_LINEAR_ASYM)) return launch_skinny(a, epi == EPI_LINEAR_ASYM, st);
@@ -167,18 +186,16 @@ int launch_gemm(const GemmArgs& a, int epi, hipStream_t st) {
         if (mt * ntn <= SMALL_TILE_LIMIT) return asym ? launch_small<EPI_LINEAR_ASYM>(a, st) : launch_small<EPI_LINEAR>(a, st);
     }
     if (a.offsets) {
-        // Few rows per expert: bound by the weight stream, not by the matrix cores.  Measured on whole layers (us) with the
-        // other projection on the 128 x 256 form for many rows, by rows per expert:
-        // gate/up, FEW / many rows (streaming): 4096 x 14336, 8 experts: 18: 310 / 325 (307), 32: 315 / 334 (327),
-        //   75: 340 / 363 (393), 112: 366 / 368, 150: 513 / 441; 2048 x 5632, 16 experts: 37: 159 / 173 (169), 75: 176 / 185.
-        // down, streaming / 128 x 128 / FEW / many rows: 14336 x 4096: 18: 286 / 309 / 324 / 325, 50: 315 / 316 / 329 / 342,
-        //   75: 344 / 331 / 350 / 360, 112: 382 / 378 / 364 / 371; 5632 x 2048: 37: 158 / 162 / 169 / 172;
-        //   3584 x 1024, 8 experts: 25: 52 / 57 / 69 / 68, 75: 63 / 64 / 77 / 75, 256: 105 / 95 / 109 / 105.
+        // Few rows per expert: bound by the weight stream, not by the matrix cores.  Gate/up, FEW / many rows, whole layers (us)
+        // by rows per expert: 4096 x 14336, 8 experts: 18: 310 / 325, 32: 315 / 334, 75: 340 / 363, 112: 366 / 368, 150: 513 / 441;
+        // 2048 x 5632, 16 experts: 37: 159 / 173, 75: 176 / 185.  (The streaming kernel there: 307, 327, 393; 169.)
         const int mean = a.max_rows / (a.n_sel > 0 ? a.n_sel : 1);
         const bool down = epi == EPI_LINEAR || epi == EPI_LINEAR_ASYM, asym = epi == EPI_LINEAR_ASYM;
-        if (down && mean <= STREAM_MEAN_ROWS) return launch_stream_grouped(a, asym, st);
-        // few output channels: 128 x 256 tiles (`mt` is an upper bound) would leave CUs without one
-        if (down && 8 * mt * ntn <= 7 * cu_count()) return asym ? launch_small<EPI_LINEAR_ASYM>(a, st) : launch_small<EPI_LINEAR>(a, st);
+        if (down && mean <= stream_mean_rows(a, cu_count())) return launch_stream_grouped(a, asym, st);
+        // 128 x 128 tiles where they cover the groups in one round (a CU with two of them takes 1.4 times as long: 14336 x 4096,
+        // 8 experts, 256 tiles 99 us, 288 tiles 137): at one row tile for each group while few have more, else by the upper bound
+        const int row_tiles_s = mean <= 104 ? a.n_sel : mean <= FEW_MEAN_ROWS ? a.n_sel + cdiv(a.n_sel, 8) : row_tiles(a, 128);
+        if (down && row_tiles_s * cdiv(a.N, BN_S) <= cu_count()) return asym ? launch_small<EPI_LINEAR_ASYM>(a, st) : launch_small<EPI_LINEAR>(a, st);
         if (mean <= FEW_MEAN_ROWS) {
             switch (epi) {
                 case EPI_SWIGLU: return launch_one<EPI_SWIGLU, false, true>(a, st);

@@ -121,15 +121,19 @@ def test_binary64_products_at_strides_past_32_bits(rows, cols):
     assert bits_equal(host(y[:, -100:]), oracle.matmul_f64(X[:1, :k], np.repeat(W[:k, :1], 100, axis=1))) and not bool(y[:, :-100].any())
 
 @pytest.mark.parametrize("H,I,first,second,E", [
-    # on average at most 48 rows per expert: the down projection streams in tiles of 32, 64, 96 and 128 rows (and one row
-    # more); the gate/up projection takes the tiled kernel's form for few rows
+    # few channels: the down projection streams in tiles of 32, 64, 96 and 128 rows (and one row more, and groups of two and
+    # three tiles, which share their weights); the gate/up projection takes the tiled kernel's form for few rows; groups
+    # with one row tile, one row more, two tiles, one row, none
     (192, 448, (129, 97, 65, 33, 17, 1), (128, 96, 64, 32, 16, 6), 16),
     (64, 64, (257, 2), (130, 128, 1), 12),
-    # more rows: the down projection in 128 x 128 tiles; groups with one row tile, one row more, two tiles, one row, none
     (320, 448, (129, 64, 65, 84), (256, 1, 0, 85), 8),
     (128, 704, (100, 28), (127, 1), 4),
-    # 56 rows on average and more channel tiles than CUs: the form for few rows in both projections
-    (4096, 64, (300, 148), (1, 447), 16)])
+    # 80 rows on average and 512 units of 64 channels: the down projection in 128 x 128 tiles
+    (4096, 64, (129, 64, 65, 62), (256, 1, 0, 63), 8),
+    # 56 rows on average and more channel tiles than CUs: the form for few rows in both projections; channel tiles that are
+    # no multiple of 8 (the count goes on from group to group)
+    (4096, 64, (300, 148), (1, 447), 16),
+    (2624, 192, (130, 70, 1, 199), (128, 129, 0, 143), 16)])
 def test_routed_experts_at_the_edges_of_their_row_tiles(H, I, first, second, E):
     """Group sizes are set through the logits: every token has one expert of `first` and one of `second`."""
     T = sum(first)

@@ -125,3 +125,19 @@ def test_group_tiles_are_dealt_once_and_evenly(tmp_path):
     for p, line in zip(even, lines):
         lo, hi = map(int, line.split()[1:])
         assert hi - lo <= 1, (p, lo, hi)
+
+
+def test_down_projections_of_expert_groups_by_units_and_rows(plan):
+    """(experts, channels, K, rows for each) on both sides of the lines between the streaming kernel, 128 x 128 tiles and the
+    tiled form for few rows; each projection's epilogue in both codes."""
+    stream = [(8, 4096, 14336, 64), (16, 2048, 5632, 64), (4, 4096, 14336, 112), (8, 3072, 14336, 112), (8, 1024, 3584, 112),
+              (16, 3072, 8192, 24), (16, 4096, 7168, 48), (1, 4096, 14336, 100)]
+    small = [(8, 4096, 14336, 65), (8, 4096, 14336, 104), (8, 3584, 8192, 112), (16, 2048, 5632, 80), (4, 4096, 14336, 128)]
+    few = [(8, 4096, 14336, 105), (16, 3072, 8192, 25), (16, 2560, 5632, 112), (16, 4096, 7168, 49), (16, 2112, 3008, 56)]
+    many = [(8, 3584, 8192, 128), (8, 3072, 14336, 113), (16, 1536, 6144, 128), (8, 4096, 14336, 113)]
+    for epi in (LINEAR, LINEAR_ASYM):
+        of = lambda sizes: plan([(epi, 0, N, K, n, n * rows, 1, 0) for n, N, K, rows in sizes])
+        assert {k for k, _, _ in of(stream)} == {"stream_grouped"}, of(stream)
+        for sizes, bn, is_few in ((small, 128, 0), (few, 256, 1), (many, 256, 0)):
+            for p, (kernel, t, _) in zip(sizes, of(sizes)):
+                assert (kernel, t[:2], t[8]) == ("gemm_i8", [128, bn], is_few), (p, kernel, t)
