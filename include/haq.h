@@ -451,8 +451,10 @@ size_t haq_moe_workspace_bytes(int32_t T, int32_t H, int32_t I, int32_t E);
  * everything else of the call is enqueued as usual.
  * Launch shapes (same results on every path): more than 64 tokens or any
  * host-resident expert -> grouped GEMMs (on average at most 112 rows per expert:
- * tiles that read the weights past the caches, the down projection streamed at
- * most 48 rows; a streamed expert with at most 64 rows runs on the weight-streaming kernels when H and I allow); up to 64 tokens, all experts
+ * tiles that read the weights past the caches; the down projection straight
+ * into registers up to 24 to 112 rows, the fewer channels and experts the more;
+ * an expert streamed from the host with at most 64 rows runs on the
+ * weight-streaming kernels when H and I allow); up to 64 tokens, all experts
  * resident, H % 128 == 0 and I % 256 == 0 -> weight-streaming kernels (five
  * launches); one or two tokens with H <= 8192, I <= 16384 and none of q, sx, hq,
  * sh asked for in dbg -> three launches (those four stay on chip on that path). */

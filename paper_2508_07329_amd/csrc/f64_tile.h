@@ -4,9 +4,11 @@
 //
 // A work-group of 4 waves (2 x 2) owns a 64 x 64 tile, a wave 32 x 32 of it; k comes through LDS in chunks of 16, the
 // next chunk held in registers meanwhile.  Bound: the binary64 matrix pipe, an instruction of 1024 multiply-adds every
-// 91 cycles with several waves on a SIMD (138 with one: hence a small tile, five waves to a SIMD; 128 x 128 tiles, two
-// waves, took 424 us where four 64 x 64 ones take 400), 45 TFLOP/s.  The 4 x 4 register tiles of the vector unit that
-// these products used before were bound by LDS, 8 reads for 16 multiply-adds.
+// 91 cycles with several waves on a SIMD (138 with one: hence a small tile, four to seven waves to a SIMD; 128 x 128
+// tiles, two waves, took 424 us where four 64 x 64 ones take 400), which is 55 TFLOP/s at 2.4 GHz.  The reference product
+// (4096 links a tile) reaches 54, the compensation's products, which load and store their tile for 64 to 256 links, 44.
+// The 4 x 4 register tiles of the vector unit that these products used before were bound by LDS, 8 reads for 16
+// multiply-adds.
 #pragma once
 #include "haq_common.h"
 

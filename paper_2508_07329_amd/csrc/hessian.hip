@@ -27,7 +27,8 @@ constexpr int GS = 256;   // input channels per rank-GS compensation of everythi
 // v_l -= e C(c, l) for l > c, with skew[c][p] = C(c, c + 1 + p).  The current value is always v[0]: the array moves down
 // by one with each column (the multiply-add's destination is its neighbour's register), so that the columns are a
 // loop of short code; what moves in from beyond value 63 is never used.  Written out as 64 different columns the loop
-// is longer than the instruction cache, and the compiler spills.
+// is longer than the instruction cache, and the compiler spills vector registers.  (Scalar registers, the addresses of
+// 64 rows, spill into vector lanes in the callers' prologues and in chol_panel_kernel's turns; not in these loops.)
 // One wave runs alone on its SIMD: the coefficients come out of LDS in chunks of eight, three chunks ahead of their use
 // (the asm keeps reads and values with their chunk: left alone, the compiler fetches everything first and spills).
 template <class F>
@@ -340,7 +341,7 @@ __global__ __launch_bounds__(64, 1) void gptq_block_kernel(double* w64, const do
 
 // Rows [r_lo, r_hi): w_jn -= err_in U_ij for the n_i channels from i0 on, ascending.  Applied after every 64 channels to
 // the rest of a stretch of 256 and after the stretch to everything below: w is read and written once per stretch there
-// (34 GB -> 9 GB in all at 4096 x 16384, which took 25 ms; now 6.1, the rate of the matrix pipe).
+// (34 GB -> 9 GB in all at 4096 x 16384, which took 25 ms; now 6.3, 44 TFLOP/s of the matrix pipe's 55).
 __global__ __launch_bounds__(256, 5) void gptq_update_kernel(double* w64, const double* U, const double* err, int K, int N, int i0, int n_i,
                                                           int r_lo, int r_hi) {
     const int r0 = r_lo + blockIdx.y * F64_B, n0 = blockIdx.x * F64_B;
@@ -355,7 +356,7 @@ __global__ __launch_bounds__(256, 5) void gptq_update_kernel(double* w64, const 
     });
 }
 
-constexpr size_t STATUS_BYTES = 64 + 8192;  // the status word; the rest is not used
+constexpr size_t STATUS_BYTES = 64 + 8192;  // the status word; the rest keeps the workspace sizes that callers have stored
 
 struct HessWs {
     double *H, *A, *M, *w64, *err;

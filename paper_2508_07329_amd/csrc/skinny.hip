@@ -1,10 +1,11 @@
-// Dense W8A8 linear for short batches (at most 128 token rows, and longer ones on few output channels): the weights are streamed from HBM
-// once, straight into MFMA operand registers, as on the decode path of the routed expert FFN.
+// W8A8 linear for short batches (at most 128 token rows, longer ones on few output channels, the down projections of expert
+// groups of few rows): the weights are streamed from HBM once, straight into MFMA operand registers, as on the decode path
+// of the routed expert FFN.
 //
 // Bound: the weight stream (K N bytes).  The tiled GEMM cannot draw it at these batches: its grid is one
 // work-group per 128 or 256 channels (32 on a 4096-channel layer), with two K-steps of 16 KB in flight each.
 // Here a work-group owns 16 C channels and splits K over its 8 waves (a 64-byte K-step each in turn), every wave
-// keeps DEPTH K-steps of fragments in flight, and the exact int32 partial sums are added in LDS.
+// holds the fragments of DEPTH K-steps, and the exact int32 partial sums are added in LDS.
 // v_mfma_i32_16x16x64_i8: the weights are the first operand (16 channels x 64 k, lane = channel, 16-byte chunk), a
 // block of 16 token rows the second, so a lane ends up with four consecutive channels of one row.
 // Measured (weights cold, us; before = the tiled GEMM):
