@@ -263,7 +263,7 @@ __global__ __launch_bounds__(QMAX_THREADS) void smooth_quant_reg_kernel(QuantArg
             const float rscale = 1.0f / scale;
             const bool sfast = scale >= 0x1p-100f && scale <= 0x1p100f;
             const int t = row0 + r;
-            if (c == r) {
+            if (c == min(r, nchunk - 1)) {  // one thread for each row, also where a row has fewer chunks than the thread rows
                 if (a.scale_dest) a.scale_dest[t] = scale;
                 if (a.scale) a.scale[a.gather ? (a.gather[t] >> 1) : t] = scale;
             }
@@ -512,7 +512,7 @@ __global__ __launch_bounds__(QMAX_THREADS) void smooth_quant_lds_kernel(QuantArg
                 }
                 const uint4 code = make_uint4(w[0], w[1], w[2], w[3]);
                 const int t = base + g * RS + r;
-                if (c == r) {
+                if (c == min(r, nchunk - 1)) {  // one thread for each row, also where a row has fewer chunks than the thread rows
                     if (a.scale_dest) a.scale_dest[t] = scale;
                     if (a.scale) a.scale[src[r]] = scale;
                     if constexpr (ASYM) {
@@ -675,7 +675,7 @@ __global__ __launch_bounds__(QMAX_THREADS) void asym_quant_kernel(AsymQuantArgs 
 #pragma unroll
                 for (int i = 0; i < 4; ++i) w4[i] = u4[i] ^ 0x80808080u;  // code - 128 as a signed byte
             }
-            if (c == r) {
+            if (c == min(r, nchunk - 1)) {  // one thread for each row, also where a row has fewer chunks than the thread rows
                 a.scale[t] = scale;
                 a.zp[t] = (int32_t)z;
             }

@@ -78,6 +78,13 @@ def test_short_batch_quantisers_at_the_edges_of_their_row_split(T, K):
     assert bits_equal(host(y), y_ref)
 
 
+@pytest.mark.parametrize("T", [257, 1030, 4100])
+@pytest.mark.parametrize("K", [16, 32, 48])
+def test_quantisers_on_rows_of_fewer_chunks_than_a_thread_has_rows(T, K):
+    """Two or four rows to a thread and one to three chunks of 16 channels to a row: every row's scale is written."""
+    _linear_both_codes(T, K, 16, "none")
+
+
 @pytest.mark.parametrize("T,K,N", [(17, 63, 17), (80, 65, 130), (40, 128, 9), (33, 257, 66), (64, 330, 1000), (100, 448, 208), (70, 700, 81)])
 def test_layer_quantiser_at_the_edges_of_its_blocks(T, K, N):
     """Panels and blocks of 64 with one row less and more, k chunks of 16 with a remainder, a second stretch of 256
