@@ -31,89 +31,102 @@ int row_tiles(const GemmArgs& a, int bm) { return a.offsets ? a.max_rows / bm + 
 // Every launch takes its grid from the tile of its own kernel: at least the tile count, a multiple of 8.
 dim3 tile_grid(const GemmArgs& a, int bm, int bn) { return dim3((unsigned)round_up((int64_t)row_tiles(a, bm) * cdiv(a.N, bn), 8)); }
 
-template <int EPI, bool DBG, bool FEW = false>
+template <int BM_, int BN_, int WM_, int WN_, int STAGES_, int MINB_, int EPI, bool DBG, bool FEW, bool WIDE>
+int launch_tiles(const GemmArgs& a, dim3 grid, hipStream_t st) {
+    using S = GemmShape<BM_, BN_, WM_, WN_, STAGES_>;
+    static_assert(MINB_ * S::LDS_BYTES <= 160 * 1024, "the LDS of a CU");
+    auto kern = gemm_i8_kernel<BM_, BN_, WM_, WN_, STAGES_, MINB_, EPI, DBG, FEW, WIDE>;
+    static std::once_flag once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(once, [&] { attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS_BYTES); });
+    HAQ_CHECK_HIP(attr_err);
+    hipLaunchKernelGGL(kern, grid, dim3(S::THREADS), S::LDS_BYTES, st, a);
+    HAQ_CHECK_HIP(hipGetLastError());
+    return HAQ_OK;
+}
+
+template <int EPI, bool DBG, bool FEW = false, bool WIDE = false>
 int launch_one(const GemmArgs& a, hipStream_t st) {
     // FEW: an expert's channel tiles go round the XCDs (decode_tile), a multiple of 8 of them for each row tile
     const dim3 grid = FEW ? dim3((unsigned)((int64_t)row_tiles(a, BM) * round_up(cdiv(a.N, BN), 8))) : tile_grid(a, BM, BN);
-    auto kern = gemm_i8_kernel<BM, BN, WAVES_M, WAVES_N, STAGES, MINB, EPI, DBG, FEW>;
-    static std::once_flag once;
-    static hipError_t attr_err = hipSuccess;
-    std::call_once(once, [&] {
-        attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, Shape::LDS_BYTES);
-    });
-    HAQ_CHECK_HIP(attr_err);
-    hipLaunchKernelGGL(kern, grid, dim3(Shape::THREADS), Shape::LDS_BYTES, st, a);
-    HAQ_CHECK_HIP(hipGetLastError());
-    return HAQ_OK;
+    return launch_tiles<BM, BN, WAVES_M, WAVES_N, STAGES, MINB, EPI, DBG, FEW, WIDE>(a, grid, st);
 }
 
-// 128 x 128 tiles (wave tile 64 x 64) for problems whose 128 x 256 tiling would leave half of the
-// work-group slots empty: twice the tiles, 49 KB of LDS, three work-groups per CU.
-#ifndef HAQ_SMALL_TILE_LIMIT
-#define HAQ_SMALL_TILE_LIMIT 256
-#endif
-constexpr int SMALL_TILE_LIMIT = HAQ_SMALL_TILE_LIMIT;  // 128 x 256 tiles that would not even give every CU one work-group
-constexpr int BN_S = 128, MINB_S = 3;
-using ShapeS = GemmShape<128, BN_S, 2, 2, 3>;
-template <int EPI>
-int launch_small(const GemmArgs& a, hipStream_t st) {
-    auto kern = gemm_i8_kernel<128, BN_S, 2, 2, 3, MINB_S, EPI, false>;
-    static std::once_flag once;
-    static hipError_t attr_err = hipSuccess;
-    std::call_once(once, [&] {
-        attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, ShapeS::LDS_BYTES);
-    });
-    HAQ_CHECK_HIP(attr_err);
-    hipLaunchKernelGGL(kern, tile_grid(a, 128, BN_S), dim3(ShapeS::THREADS), ShapeS::LDS_BYTES, st, a);
-    HAQ_CHECK_HIP(hipGetLastError());
-    return HAQ_OK;
+// The other tile shapes.  Dense linears take the one that the estimate below finds fastest.
+struct TileShape {
+    int bm, bn, per_cu;  // tile, work-groups that a CU holds
+    // Estimated us of a launch of T tiles on C compute units: c0 + per full round of per_cu C tiles (fix + K-steps step[per_cu-1][1])
+    // + for a last round of rem tiles, k = ceil(rem / C) to a CU, (fix + K-steps step), step between step[k-1][0] (a CU alone)
+    // and step[k-1][1] (every CU busy: the caches and the chip's power are shared) in proportion to rem / (k C).
+    float c0, fix, step[2][2];
+};
+enum { T128x256, T128x128, T192x128, T192x256, T256x256, N_TILES };
+// Fitted to 195 launches of each shape (129 to 4096 rows, 13 layers between 768 x 3072 and 16384 x 4096, weights cold; mean
+// deviation 3 to 6 %).  The shape with the lowest estimate is on average 1.1 % slower than the fastest of these and four
+// more (256 x 128, 128 x 256 alone on its CU, 192 x 128 and 128 x 128 with two and three to a CU); one shape fewer costs
+// another 0.3 to 1.5 %.  Against the two thresholds on tile counts before (us, with the kernel before and now):
+//   4096 x 16384:  333 rows 38.8 / 34.0,  600: 60 / 51,  777: 65 / 61,  2048: 124 / 118;   16384 x 4096:  777: 86 / 72,  1300: 120 / 87
+//   8192 x 8192:  333: 48 / 41,  600: 71 / 52,  1300: 108 / 81,  4096: 228 / 213;   5120 x 13824:  256: 35.6 / 30.7,  1024: 79 / 66
+//   4096 x 11008:  1024: 64 / 51;   2064 x 8208:  777: 25.2 / 24.6;   768 x 3072:  1024: 10.3 / 9.5
+constexpr TileShape TILES[N_TILES] = {
+    {128, 256, 2, 0.64f, 8.13f, {{0.369f, 0.461f}, {0.608f, 0.846f}}},
+    {128, 128, 2, 1.95f, 4.77f, {{0.216f, 0.280f}, {0.421f, 0.502f}}},
+    {192, 128, 1, 2.90f, 5.46f, {{0.242f, 0.340f}}},
+    {192, 256, 1, 2.08f, 9.20f, {{0.402f, 0.563f}}},
+    {256, 256, 1, 0.00f, 9.61f, {{0.452f, 0.745f}}},
+};
+float tile_us(const TileShape& t, int M, int N, int nk, int n_cu) {
+    const int64_t tiles = (int64_t)cdiv(M, t.bm) * cdiv(N, t.bn), round = (int64_t)t.per_cu * n_cu;
+    const int rem = (int)(tiles % round), k = cdiv(rem, n_cu);
+    float us = t.c0 + (float)(tiles / round) * (t.fix + (float)nk * t.step[t.per_cu - 1][1]);
+    if (rem) {
+        const float* step = t.step[k - 1];
+        us += t.fix + (float)nk * (step[0] + (step[1] - step[0]) * (float)rem / (float)(k * n_cu));
+    }
+    return us;
+}
+// More than half a 192- or 256-row tile would be empty on at most 128 rows.
+int fastest_tile(int M, int N, int nk, int n_cu, float& us) {
+    int best = 0;
+    for (int i = 0; i < (M <= 128 ? T192x128 : N_TILES); ++i) {
+        const float t = tile_us(TILES[i], M, N, nk, n_cu);
+        if (i == 0 || t < us) us = t, best = i;
+    }
+    return best;
 }
 
-// 256 x 256 tiles, 8 waves (4 x 2, the same 64 x 128 wave tile and per-wave code as the main shape), one
-// work-group per CU: a third fewer direct-to-LDS bytes per matrix instruction, which is what limits the K loop.
-// For dense problems with at least two full rounds of such tiles (one per CU and round); measured +3 % on
-// 2048..8192 x 4096 x 16384, -8 % on a single round, and slower on ragged expert groups (more padding rows).
-constexpr int LARGE_TILE_MIN = 512;
-using ShapeL = GemmShape<256, 256, 4, 2, 3>;
 template <int EPI>
-int launch_large(const GemmArgs& a, hipStream_t st) {
-    auto kern = gemm_i8_kernel<256, 256, 4, 2, 3, 1, EPI, false>;
-    static std::once_flag once;
-    static hipError_t attr_err = hipSuccess;
-    std::call_once(once, [&] {
-        attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, ShapeL::LDS_BYTES);
-    });
-    HAQ_CHECK_HIP(attr_err);
-    hipLaunchKernelGGL(kern, tile_grid(a, 256, 256), dim3(ShapeL::THREADS), ShapeL::LDS_BYTES, st, a);
-    HAQ_CHECK_HIP(hipGetLastError());
-    return HAQ_OK;
+int launch_shape(const GemmArgs& a, int shape, hipStream_t st) {
+    const dim3 grid = tile_grid(a, TILES[shape].bm, TILES[shape].bn);
+    switch (shape) {
+        case T128x128: return launch_tiles<128, 128, 2, 2, 4, 2, EPI, false, false, false>(a, grid, st);  // wave tile 64 x 64
+        case T192x128: return launch_tiles<192, 128, 2, 2, 7, 1, EPI, false, false, false>(a, grid, st);  // 96 x 64
+        case T192x256: return launch_tiles<192, 256, 2, 2, 5, 1, EPI, false, false, false>(a, grid, st);  // 96 x 128
+        case T256x256: return launch_tiles<256, 256, 4, 2, 4, 1, EPI, false, false, false>(a, grid, st);  // 64 x 128, eight waves
+        default: return launch_one<EPI, false>(a, st);
+    }
 }
 
-// 256 x 128 tiles, 8 waves (4 x 2 of 64 x 64), one work-group per CU: for dense problems that this tiling covers in
-// one round with most CUs busy (fc2 of the OPT-6.7B block: 8 x 32 tiles on 256 CUs).  A quarter fewer
-// direct-to-LDS bytes per matrix instruction than the 128 x 128 shape such problems would otherwise take: -2 %.
-// Not for 128 rows and fewer, of which the tile would waste half: 64 rows of 512 x 32768 10.2 us instead of 10.8.
-using ShapeT = GemmShape<256, 128, 4, 2, 3>;
-template <int EPI>
-int launch_tall(const GemmArgs& a, hipStream_t st) {
-    auto kern = gemm_i8_kernel<256, 128, 4, 2, 3, 1, EPI, false>;
-    static std::once_flag once;
-    static hipError_t attr_err = hipSuccess;
-    std::call_once(once, [&] {
-        attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, ShapeT::LDS_BYTES);
-    });
-    HAQ_CHECK_HIP(attr_err);
-    hipLaunchKernelGGL(kern, tile_grid(a, 256, 128), dim3(ShapeT::THREADS), ShapeT::LDS_BYTES, st, a);
-    HAQ_CHECK_HIP(hipGetLastError());
-    return HAQ_OK;
+// Operands whose offsets need more than 32 bits (4 GB): the tiled kernel computes its addresses in 64.
+bool wide_operands(const GemmArgs& a) {
+    const int64_t rows = a.R > a.Npad ? a.R : a.Npad;
+    return rows > INT64_C(0xFFFFFFFF) / (64 * (int64_t)cdiv(a.K, 64));
+}
+template <bool DBG>
+int launch_wide(const GemmArgs& a, int epi, hipStream_t st) {
+    switch (epi) {
+        case EPI_SWIGLU: return launch_one<EPI_SWIGLU, false, false, true>(a, st);
+        case EPI_SWIGLU_ASYM: return launch_one<EPI_SWIGLU_ASYM, false, false, true>(a, st);
+        case EPI_LINEAR_ASYM: return launch_one<EPI_LINEAR_ASYM, DBG, false, true>(a, st);
+        default: return launch_one<EPI_LINEAR, DBG, false, true>(a, st);
+    }
 }
 
 }  // namespace
 
 // Row blocks of 16 per tile (4, 6 or 8) with which the streaming kernel (skinny.hip: 64-channel tiles, K split over
-// the waves, operands straight into registers) beats one round of 128 x 128 tiles, or 0.  Such a round costs a
-// work-group 0.3 us for each 64-byte K-step however few of them there are (77 us at K = 16384 for 64 to 256 tiles);
-// a round of streaming tiles costs (4 + RB) / 80 us a K-step, the fragments of a step through a CU's load path, and
+// the waves, operands straight into registers) beats the tiled kernel, whose fastest shape takes `tiled_us`, or 0.  A
+// round of streaming tiles costs (4 + RB) / 80 us a K-step, the fragments of a step through a CU's load path, and
 // 3.4 + RB / 5 us to start, add up and finish.  Measured (us, M rows, K x N, streaming against tiled):
 //   16384 x 4096:  129 rows 30 / 78,  333: 37 / 78,  512: 44 / 79,  700: 70 / 82,  1024: 84 / 85
 //   4096 x 4096:   129 rows 10 / 20,  333: 13 / 20,  512: 15 / 20,  700: 25 / 21 (tiled stays)
@@ -121,9 +134,13 @@ int launch_tall(const GemmArgs& a, hipStream_t st) {
 // and where few K-steps leave the start and the end to decide (weights cold):
 //   512 x 4096:    256 rows 7.6 / 8.5,  333: 9.2 / 8.6 (tiled);   768 x 3072: 400 rows 9.6 / 9.9,  512: 10.3 / 10.0 (tiled)
 //   1024 x 4096:   512 rows 10.7 / 11.2
-static int stream_row_blocks(const GemmArgs& a, int n_cu) {
+// Two bounds: a round of 128 x 128 tiles at 0.3 us a K-step, which keeps the tiled kernel on short K (its estimate counts
+// the start of a launch, some 3 us, and the streaming tiles' terms do not), and the estimate, less what evens out where the
+// two measure the same (700 rows of 16384 x 4096: 71 / 71).  300 rows of 8192 x 8192: 48 / 41 (tiled).
+static int stream_row_blocks(const GemmArgs& a, int n_cu, float tiled_us) {
     const int nk = cdiv(a.K, 64);
-    float best = 3.0f + 0.3f * nk;
+    const float before = 3.0f + 0.3f * nk, now = tiled_us - 1.0f;
+    float best = before < now ? before : now;
     int rb = 0;
     for (int r = 4; r <= 8; r += 2) {
         if (a.M <= 16 * r) break;  // a single row tile: skinny_pays has decided
@@ -169,21 +186,17 @@ static constexpr int FEW_MEAN_ROWS = 112;  // likewise for the form for few rows
 
 int launch_gemm(const GemmArgs& a, int epi, hipStream_t st) {
     if (skinny_pays(a) && (epi == EPI_LINEAR || epi == EPI_LINEAR_ASYM)) return launch_skinny(a, epi == EPI_LINEAR_ASYM, st);
-    const int ntn = cdiv(a.N, BN);
-    const int mt = row_tiles(a, BM);
-    if (mt <= 0 || ntn <= 0) return HAQ_OK;
+    if (row_tiles(a, BM) <= 0 || a.N <= 0) return HAQ_OK;
+    if (wide_operands(a)) return a.acc_dbg ? launch_wide<true>(a, epi, st) : launch_wide<false>(a, epi, st);
     if (!a.offsets && !a.acc_dbg && (epi == EPI_LINEAR || epi == EPI_LINEAR_ASYM)) {
         const bool asym = epi == EPI_LINEAR_ASYM;
         const int n_cu = cu_count();
-        const int64_t tiles_l = (int64_t)cdiv(a.M, 256) * cdiv(a.N, 256);
-        if (tiles_l >= LARGE_TILE_MIN) return asym ? launch_large<EPI_LINEAR_ASYM>(a, st) : launch_large<EPI_LINEAR>(a, st);
-        const int64_t tiles_s = (int64_t)cdiv(a.M, 128) * cdiv(a.N, BN_S);
-        if (tiles_s <= n_cu) {
-            if (const int rb = stream_row_blocks(a, n_cu)) return launch_stream_rows(a, asym, rb, st);
+        float us = 0.0f;
+        const int shape = fastest_tile(a.M, a.N, cdiv(a.K, 64), n_cu, us);
+        if ((int64_t)cdiv(a.M, 128) * cdiv(a.N, 128) <= n_cu) {
+            if (const int rb = stream_row_blocks(a, n_cu, us)) return launch_stream_rows(a, asym, rb, st);
         }
-        const int64_t tiles_t = (int64_t)cdiv(a.M, 256) * cdiv(a.N, 128);
-        if (a.M > 128 && tiles_t <= n_cu && 4 * tiles_t > 3 * n_cu) return asym ? launch_tall<EPI_LINEAR_ASYM>(a, st) : launch_tall<EPI_LINEAR>(a, st);
-        if (mt * ntn <= SMALL_TILE_LIMIT) return asym ? launch_small<EPI_LINEAR_ASYM>(a, st) : launch_small<EPI_LINEAR>(a, st);
+        return asym ? launch_shape<EPI_LINEAR_ASYM>(a, shape, st) : launch_shape<EPI_LINEAR>(a, shape, st);
     }
     if (a.offsets) {
         // Few rows per expert: bound by the weight stream, not by the matrix cores.  Gate/up, FEW / many rows, whole layers (us)
@@ -195,7 +208,8 @@ int launch_gemm(const GemmArgs& a, int epi, hipStream_t st) {
         // 128 x 128 tiles where they cover the groups in one round (a CU with two of them takes 1.4 times as long: 14336 x 4096,
         // 8 experts, 256 tiles 99 us, 288 tiles 137): at one row tile for each group while few have more, else by the upper bound
         const int row_tiles_s = mean <= 104 ? a.n_sel : mean <= FEW_MEAN_ROWS ? a.n_sel + cdiv(a.n_sel, 8) : row_tiles(a, 128);
-        if (down && row_tiles_s * cdiv(a.N, BN_S) <= cu_count()) return asym ? launch_small<EPI_LINEAR_ASYM>(a, st) : launch_small<EPI_LINEAR>(a, st);
+        if (down && row_tiles_s * cdiv(a.N, 128) <= cu_count())
+            return asym ? launch_shape<EPI_LINEAR_ASYM>(a, T128x128, st) : launch_shape<EPI_LINEAR>(a, T128x128, st);
         if (mean <= FEW_MEAN_ROWS) {
             switch (epi) {
                 case EPI_SWIGLU: return launch_one<EPI_SWIGLU, false, true>(a, st);

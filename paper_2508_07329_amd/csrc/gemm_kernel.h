@@ -4,8 +4,8 @@
 // sorted by expert.
 //
 // Data flow of a work-group (BM x BN output tile, WAVES_M x WAVES_N waves):
-//   HBM/L2 --global_load_lds (16 B/lane, no VGPR staging)--> LDS ring of STAGES K-steps
-//   (64 bytes of k each) --ds_read_b128--> fragment registers, one whole K-step ahead
+//   HBM/L2 --buffer_load ... lds (16 B/lane, no VGPR staging)--> LDS ring of STAGES K-steps
+//   (64 bytes of k each) --ds_read_b128--> fragment registers, half a K-step ahead
 //   --> v_mfma_i32_32x32x32_i8 (16 bytes of k per lane per operand).
 // Both operands are chunk-major ([K/16][rows][16]), so a K-step of a tile is four
 // contiguous row segments per operand, lands in LDS in fragment order and is read back
@@ -13,9 +13,22 @@
 // transposed (weights as first operand) so that a lane owns four consecutive output
 // channels; the epilogue dequantises, applies the activation, stages fp16 rows in LDS
 // and writes 16 bytes per lane.
+//
+// What bounds the K loop: a matrix instruction holds its pipe for 32 cycles, and a wave issues in order, so whatever
+// stands between two of them and takes longer stops the pipe.  A K-step of a 128 x 128 tile, whose matrix instructions
+// take 256 cycles, took 550 on a CU of its own (128 x 256: 963 for 512; 256 x 256: 1450 for 1024), however deep the ring
+// and with every load served by L2: the loads stood in a block behind the barrier, each with its scalar address
+// arithmetic, and every LDS read was waited for in front of it.  With one load or one read behind a matrix instruction,
+// loads whose address costs nothing but the write of m0, and reads half a K-step ahead it takes 385 (655, 1170); what is
+// left over the matrix instructions, some 140 cycles for any tile, is the barrier and the instructions around it.
+// Whole launches (us, weights cold): 2048 x 4096 x 16384 122 -> 115, 2048 x 16384 x 4096 126 -> 118, 4096 x 8192 x 8192
+// 228 -> 213: from some 2.4 POP/s on the chip's power management slows the clock (1.6 GHz under nothing but matrix
+// instructions and LDS reads).
 #pragma once
 #include "group_tiles.h"
 #include "haq_common.h"
+
+#include <type_traits>
 
 namespace haq {
 
@@ -26,6 +39,22 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 #define HAQ_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 0xF) | (((n) >> 4) << 14) | (0x7 << 4) | (0xF << 8))
 #define HAQ_WAIT_LGKM0() __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4) | (0x0 << 8))
 #define HAQ_CFENCE() asm volatile("" ::: "memory")
+
+// Buffer resources: the address of a lane's 16 bytes is a scalar base, a lane offset and a scalar offset, 32 bits each
+// but the base, and only the scalar offset changes with the K-step.  (The builtins exist on the device side only.)
+#ifdef __HIP_DEVICE_COMPILE__
+typedef __amdgpu_buffer_rsrc_t BufferRsrc;
+__device__ __forceinline__ BufferRsrc buffer_rsrc(const int8_t* p) { return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, 0xFFFFFFFF, 0x00027000); }
+template <int AUX>
+__device__ __forceinline__ void buffer_to_lds(BufferRsrc r, int8_t* to, uint32_t lane_off, uint32_t off) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)to, 16, lane_off, off, 0, AUX);
+}
+#else
+typedef const int8_t* BufferRsrc;
+__device__ __forceinline__ BufferRsrc buffer_rsrc(const int8_t* p) { return p; }
+template <int AUX>
+__device__ __forceinline__ void buffer_to_lds(BufferRsrc, int8_t*, uint32_t, uint32_t) {}
+#endif
 
 struct TileCoord {
     int m0;     // first (sorted) row of the tile
@@ -119,7 +148,7 @@ struct GemmShape {
     static constexpr int LDS_BYTES = STAGES * STAGE_BYTES + SCALE_BYTES;
 };
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int MINB, int EPI, bool DBG, bool FEW = false>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int MINB, int EPI, bool DBG, bool FEW = false, bool WIDE = false>
 __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINB) void gemm_i8_kernel(GemmArgs a) {
     using S = GemmShape<BM, BN, WAVES_M, WAVES_N, STAGES>;
     constexpr int NW = S::NW;
@@ -128,7 +157,8 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINB) void gemm_i8_kernel(G
     constexpr int STAGE_BYTES = S::STAGE_BYTES;
     constexpr int GA = 4 * BM / 64, GB = 4 * BN / 64;  // 1 KB (64 rows x 16 B) load groups per K-step
     constexpr int LPW = (GA + GB) / NW;                // direct-to-LDS loads per wave per K-step
-    static_assert((GA + GB) % NW == 0, "load groups must divide among the waves");
+    static_assert(GA % NW == 0 && GB % NW == 0, "a load slot is of one operand for all waves");
+    static_assert(LPW * STAGES <= 63, "s_waitcnt counts the loads of a whole ring");
     // a tile's loads cover BM rows and BN channels whatever the problem size: the packed operands are padded for that
     static_assert(NPAD % BN == 0, "a channel tile must not reach past the padded width of the packed weights");
     static_assert(BM <= 256, "packed activations carry 256 rows of padding");
@@ -197,10 +227,9 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINB) void gemm_i8_kernel(G
         if (ASYM) cs_s[i] = cs;
     }
 
-    // direct-to-LDS load descriptors: group g = wave + i*NW covers 64 rows of one 16-byte chunk.  The base of a
-    // group is the same for all lanes of the wave (scalar registers; the tile origin and the expert's matrix come
-    // out of memory and are made wave-uniform explicitly), the lane adds 16 bytes per row: the loads then use the
-    // scalar-base + 32-bit lane-offset form and their addresses cost no vector instructions in the K loop.
+    // Direct-to-LDS loads: group g = wave + i*NW covers 64 rows of one 16-byte chunk.  The tile's origin in either operand
+    // is the same for all lanes of the wave (the tile coordinates and the expert's matrix come out of memory and are made
+    // wave-uniform explicitly).
     auto uniform_ptr = [](const int8_t* p) {
         const uint64_t v = (uint64_t)(uintptr_t)p;
         const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
@@ -209,44 +238,46 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINB) void gemm_i8_kernel(G
     const int m0u = __builtin_amdgcn_readfirstlane(tc.m0), n0u = __builtin_amdgcn_readfirstlane(tc.n0);
     const int8_t* Au = uniform_ptr(a.A);
     const int8_t* Bu = uniform_ptr(Bmat);
-    const uint32_t lane_off = (uint32_t)lane * 16u;
-    const int8_t* gsrc[LPW];
-    size_t gstep[LPW];
+    const int8_t* Ag = Au + (size_t)m0u * 16;
+    const int8_t* Bg = Bu + (size_t)n0u * 16;
+    const BufferRsrc rsrc_a = buffer_rsrc(Ag), rsrc_b = buffer_rsrc(Bg);
+    using Off = std::conditional_t<WIDE, size_t, uint32_t>;  // WIDE: operands of 4 GB and more
+    const Off step_a = (Off)4 * a.R * 16, step_b = (Off)4 * a.Npad * 16;
+    Off off[LPW];  // of this lane's 16 bytes from the tile's origin, at K-step 0
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
         const int g = wave + i * NW;
-        if (g < GA) {
-            const int c = g / (BM / 64);
+        if (i * NW < GA) {
             int rg = g % (BM / 64);
             if (FEW && rg * 64 >= tc.m_end - m0u) rg = 0;  // 64 rows past the group's last: their results are dropped
-            gsrc[i] = Au + ((size_t)c * a.R + m0u + rg * 64) * 16;
-            gstep[i] = (size_t)4 * a.R * 16;
+            off[i] = ((Off)(g / (BM / 64)) * a.R + rg * 64 + lane) * 16;
         } else {
             const int g2 = g - GA;
-            const int c = g2 / (BN / 64), rg = g2 % (BN / 64);
-            gsrc[i] = Bu + ((size_t)c * a.Npad + n0u + rg * 64) * 16;
-            gstep[i] = (size_t)4 * a.Npad * 16;
+            off[i] = ((Off)(g2 / (BN / 64)) * a.Npad + g2 % (BN / 64) * 64 + lane) * 16;
         }
     }
-    auto load_stage = [&](int buf, int kt) {
-        // (the empty asm keeps the widening of the lane offset next to its use: hoisted out of the loop as a 64-bit
-        // vector value it would turn every address back into a vector add)
-        uint32_t lo = lane_off;
-        asm volatile("" : "+v"(lo));
-#pragma unroll
-        for (int i = 0; i < LPW; ++i) {
-            const int8_t* src = gsrc[i] + (size_t)kt * gstep[i] + lo;
-            const auto* gp = (const __attribute__((address_space(1))) void*)(uintptr_t)src;
-            auto* lp = (__attribute__((address_space(3))) void*)(lds + buf * STAGE_BYTES + (wave + i * NW) * 1024);
-            // FEW: the weights are hardly shared and pass the caches by (non-temporal), so that the token rows stay there;
-            // for a group's second row tile too (cached from there on: two experts of 256 rows of 4096 x 14336 172 -> 188 us
-            // a layer, eight of 10 to 183 rows 364 -> 363)
-            static_assert(!FEW || GA % NW == 0, "a load slot is of one operand for all waves");
-            if (FEW && i * NW >= GA)
-                __builtin_amdgcn_global_load_lds(gp, lp, 16, 0, 2);
-            else
-                __builtin_amdgcn_global_load_lds(gp, lp, 16, 0, 0);
+    // FEW: the weights are hardly shared and pass the caches by (non-temporal), so that the token rows stay there;
+    // for a group's second row tile too (cached from there on: two experts of 256 rows of 4096 x 14336 172 -> 188 us
+    // a layer, eight of 10 to 183 rows 364 -> 363)
+    constexpr int NT = FEW ? 2 : 0;
+    Off next_a = 0, next_b = 0;  // of the next K-step to request
+    auto load = [&](int buf, int i) __attribute__((always_inline)) {
+        int8_t* to = lds + buf * STAGE_BYTES + (wave + i * NW) * 1024;
+        if constexpr (WIDE) {
+            const int8_t* src = i * NW < GA ? Ag + next_a + off[i] : Bg + next_b + off[i];
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(uintptr_t)src,
+                                             (__attribute__((address_space(3))) void*)to, 16, 0, 0);
+        } else if (i * NW < GA) {
+            buffer_to_lds<0>(rsrc_a, to, off[i], next_a);
+        } else {
+            buffer_to_lds<NT>(rsrc_b, to, off[i], next_b);
         }
+    };
+    // K-step kt has been requested.  Past the last one it is requested again, into a stage that nobody reads any more:
+    // the loads of every K-step are then the same code and the same count for s_waitcnt.
+    auto advance = [&](int kt) __attribute__((always_inline)) {
+        next_a += kt + 1 < nkt ? step_a : 0;
+        next_b += kt + 1 < nkt ? step_b : 0;
     };
 
     v16i acc[MI][NI];
@@ -260,112 +291,87 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINB) void gemm_i8_kernel(G
     // fragment address inside a stage: chunk = 2*half + lane/32, row = wave base + 32*tile + lane%32
     const int frag_a = ((lane >> 5) * BM + wm * WM + (lane & 31)) * 16;
     const int frag_b = BM * 64 + ((lane >> 5) * BN + wn * WN + (lane & 31)) * 16;
-    v4i fa[2][2][MI], fb[2][2][NI];  // [register buffer][k half][tile]
+    v4i fa[2][MI], fb[2][NI];  // fragments of either half (32 bytes of k) of a K-step
 
-    auto read_frags = [&](int buf, int kk, v4i(&xa)[MI], v4i(&xb)[NI]) {
-        const int8_t* sb = lds + buf * STAGE_BYTES;
+    // The matrix instructions on half KK of a K-step; behind them, one at a time, the LDS reads of the next half (half
+    // 1 - KK of stage `rbuf`) and, spread over both halves, the loads into stage `lbuf`.
+    auto half = [&](auto kk, auto reads, auto loads, int rbuf, int lbuf) __attribute__((always_inline)) {
+        constexpr int KK = decltype(kk)::value, M = MI * NI, R = MI + NI;
+        static_assert(M >= R, "one read behind each of the first matrix instructions");
+        const int8_t* sb = lds + rbuf * STAGE_BYTES;
 #pragma unroll
-        for (int i = 0; i < MI; ++i) xa[i] = *reinterpret_cast<const v4i*>(sb + frag_a + (kk * 2 * BM + i * 32) * 16);
+        for (int m = 0; m < M; ++m) {
+            // channel block outermost: consecutive MFMAs keep the weight fragment and change the (fewer)
+            // token fragments -- measured 2.4 % faster than the other nesting on 64 x 128 wave tiles
+            const int j = m / MI, i = m % MI;
+            acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[KK][j], fa[KK][i], acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (decltype(reads)::value) {
 #pragma unroll
-        for (int j = 0; j < NI; ++j) xb[j] = *reinterpret_cast<const v4i*>(sb + frag_b + (kk * 2 * BN + j * 32) * 16);
-    };
-    auto mfmas = [&](v4i(&xa)[MI], v4i(&xb)[NI]) {
-        // channel block outermost: consecutive MFMAs keep the weight fragment and change the (fewer)
-        // token fragments -- measured 2.4 % faster than the other nesting on 64 x 128 wave tiles
+                for (int r = 0; r < R; ++r) {
+                    if (r != m) continue;
+                    if (r < NI)
+                        fb[1 - KK][r] = *reinterpret_cast<const v4i*>(sb + frag_b + ((1 - KK) * 2 * BN + r * 32) * 16);
+                    else
+                        fa[1 - KK][r - NI] = *reinterpret_cast<const v4i*>(sb + frag_a + ((1 - KK) * 2 * BM + (r - NI) * 32) * 16);
+                }
+            }
+            if (decltype(loads)::value) {
 #pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-                acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(xb[j], xa[i], acc[i][j], 0, 0, 0);
-    };
-#ifndef HAQ_ILV
-#define HAQ_ILV 0
-#endif
-    auto interleave = [&]() {
-#if HAQ_ILV == 0
-        // one LDS read behind each of the first MFMAs of the group
-#pragma unroll
-        for (int i = 0; i < MI + NI; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                for (int l = 0; l < LPW; ++l)
+                    if ((2 * l + 1) * M / LPW == (1 - KK) * M + m) load(lbuf, l);
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_sched_group_barrier(0x008, MI * NI - (MI + NI), 0);
-#elif HAQ_ILV == 1
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, MI + NI, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, MI * NI - 1, 0);
-#elif HAQ_ILV == 2
-        __builtin_amdgcn_sched_group_barrier(0x100, MI + NI, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, MI * NI, 0);
-#elif HAQ_ILV == 3
-        // two reads behind each of the first MFMAs
-#pragma unroll
-        for (int i = 0; i < (MI + NI) / 2; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, MI * NI - (MI + NI) / 2, 0);
-#endif
     };
+    using H0 = std::integral_constant<int, 0>;
+    using H1 = std::integral_constant<int, 1>;
+    using Yes = std::true_type;
+    using No = std::false_type;
 
-    // prologue: request every ring buffer (K-steps 0..STAGES-1); K-step 0 landed -> its fragments
+    // prologue: request every stage (K-steps 0..STAGES-1); K-step 0 landed -> the first half of it
 #pragma unroll
-    for (int s = 0; s < STAGES; ++s)
-        if (s < nkt) load_stage(s, s);
-    if (nkt >= STAGES) {
-        HAQ_WAIT_VMCNT(LPW * (STAGES - 1));
-    } else {
-        HAQ_WAIT_VMCNT(0);
+    for (int s = 0; s < STAGES; ++s) {
+#pragma unroll
+        for (int i = 0; i < LPW; ++i) load(s, i);
+        advance(s);
     }
+    HAQ_WAIT_VMCNT(LPW * (STAGES - 1));
     HAQ_CFENCE();
     __builtin_amdgcn_s_barrier();
     HAQ_CFENCE();
-    read_frags(0, 0, fa[0][0], fb[0][0]);
-    read_frags(0, 1, fa[0][1], fb[0][1]);
+#pragma unroll
+    for (int i = 0; i < MI; ++i) fa[0][i] = *reinterpret_cast<const v4i*>(lds + frag_a + i * 32 * 16);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) fb[0][j] = *reinterpret_cast<const v4i*>(lds + frag_b + j * 32 * 16);
+    half(H0{}, Yes{}, No{}, 0, 0);
 
-    // iteration kt: MFMAs on K-step kt (registers), LDS reads of K-step kt+1, global loads of
-    // K-step kt+STAGES into the buffer K-step kt has vacated.
-    auto body = [&](int kt, int cur, v4i(&ca)[2][MI], v4i(&cb)[2][NI], v4i(&na)[2][MI], v4i(&nb)[2][NI]) {
-        int nxt = cur + 1;
-        if (nxt >= STAGES) nxt -= STAGES;
-        // K-step kt+1 has landed for this wave and its reads of K-step kt are complete; after
-        // the barrier that holds for every wave, so the buffer of K-step kt may be overwritten.
-        if (nkt - 2 - kt >= STAGES - 2) {
-            HAQ_WAIT_VMCNT(LPW * (STAGES - 2));
-        } else {
-            HAQ_WAIT_VMCNT(0);
-        }
+    // iteration kt: the second half of K-step kt and the first of kt+1 (registers), the LDS reads of K-step kt+1, the
+    // loads of K-step kt+STAGES into the stage that K-step kt has left.
+    int cur = 0;
+    for (int kt = 0; kt + 1 < nkt; ++kt) {
+        const int nxt = cur + 1 >= STAGES ? 0 : cur + 1;
+        // K-step kt+1 has landed for this wave and its reads of K-step kt (issued with the half before) are complete;
+        // after the barrier that holds for every wave, so the stage of K-step kt may be overwritten.
+        HAQ_WAIT_VMCNT(LPW * (STAGES - 2));
         HAQ_WAIT_LGKM0();
         HAQ_CFENCE();
         __builtin_amdgcn_s_barrier();
         HAQ_CFENCE();
         __builtin_amdgcn_sched_barrier(0);
-        if (kt + STAGES < nkt) load_stage(cur, kt + STAGES);
-        read_frags(nxt, 0, na[0], nb[0]);  // past the last K-step this reads a stale buffer; unused
-        mfmas(ca[0], cb[0]);
-        interleave();
-        __builtin_amdgcn_sched_barrier(0);
-        read_frags(nxt, 1, na[1], nb[1]);
-        mfmas(ca[1], cb[1]);
-        interleave();
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    {
-        int st = 0, kt = 0;
-        for (; kt + 1 < nkt; kt += 2) {
-            body(kt, st, fa[0], fb[0], fa[1], fb[1]);
-            st = st + 1 >= STAGES ? 0 : st + 1;
-            body(kt + 1, st, fa[1], fb[1], fa[0], fb[0]);
-            st = st + 1 >= STAGES ? 0 : st + 1;
-        }
-        if (kt < nkt) body(kt, st, fa[0], fb[0], fa[1], fb[1]);
+        half(H1{}, Yes{}, Yes{}, nxt, cur);
+        half(H0{}, Yes{}, Yes{}, nxt, cur);
+        advance(kt + STAGES);
+        cur = nxt;
     }
+    half(H1{}, No{}, No{}, 0, 0);
 
     // ---- epilogue.  Lane l, register r of acc[i][j] holds token row i*32 + l%32 and packed
     // channel j*32 + 8*(r/4) + 4*(l/32) + r%4 of the wave tile.
+    HAQ_WAIT_VMCNT(0);  // the loads past the last K-step
     HAQ_WAIT_LGKM0();
     HAQ_CFENCE();
-    __builtin_amdgcn_s_barrier();  // all reads of the ring are complete: it becomes the staging area
+    __builtin_amdgcn_s_barrier();  // all reads and writes of the ring are complete: it becomes the staging area
     HAQ_CFENCE();
     int8_t* stage = lds + wave * (32 * PITCH);  // private to the wave, 32 rows at a time
     const int m_l = lane & 31, n_l = (lane >> 5) * 4;

@@ -58,6 +58,37 @@ def test_dense_linear_at_the_edges_of_its_tile_shapes(T, K, N, act):
     _linear_both_codes(T, K, N, act)
 
 
+@pytest.mark.parametrize("T,K,N,act", [
+    # K-steps: one, as many as the ring of 128 x 128 tiles has stages, one more and one less; the last one partial
+    (300, 16, 272, "relu"), (300, 208, 272, "none"), (257, 256, 400, "none"), (300, 272, 2064, "relu"), (300, 336, 2064, "none"),
+    # 192 x 128 (one tile and a row; a row short of one), 192 x 256 and 256 x 256 tiles, the last channel tile in 16 channels
+    (385, 1040, 8208, "relu"), (191, 592, 16400, "none"), (513, 1040, 16400, "none"), (385, 400, 16400, "relu")])
+def test_dense_linear_at_the_edges_of_its_rings_and_tiles(T, K, N, act):
+    _linear_both_codes(T, K, N, act)
+
+
+@pytest.mark.parametrize("T,N", [(130, 4_000_016), (4_000_016, 32)])
+def test_tiled_linear_on_operands_past_4_gb(T, N):
+    """Byte offsets that need more than 32 bits: in the weights, then in the codes.  Every output of the rows or channels
+    checked (the first, the last, those on both sides of an offset of 2^32) is an exact sum and two roundings."""
+    K, g = 1088, torch.Generator("cuda").manual_seed(T)
+    code = lambda n: torch.randint(-127, 128, (n,), dtype=torch.int8, device="cuda", generator=g)
+    q, w = code(haq.haq_packed_act_bytes(T, K)), code(haq.haq_packed_bytes(K, N))
+    assert max(q.numel(), w.numel()) > 2 ** 32
+    sx, sw = (torch.rand(n, device="cuda", generator=g) * 1e-3 + 1e-3 for n in (T, N))
+    y = haq.haq_gemm_w8a8_packed(q, sx, w, sw, T, K, N)
+
+    def some(n):
+        near = 2 ** 32 // K  # the offset of row i in the last chunk is near i * K
+        return torch.tensor(sorted({i for i in [0, 1, n - 2, n - 1, *range(near - 40, near + 300)] if 0 <= i < n} if n > 200 else range(n)))
+
+    t, n = some(T), some(N)
+    rows = lambda p, i: p.view(K // 16, -1, 16)[:, i.to(p.device)].permute(1, 0, 2).reshape(len(i), K).cpu().double()
+    acc = rows(q, t) @ rows(w, n).T  # below 2^53: exact in any order
+    ref = ((acc.float() * sx.cpu()[t, None]) * sw.cpu()[None, n]).half()
+    assert torch.equal(y[t.to(y.device)][:, n.to(y.device)].cpu().view(torch.int16), ref.view(torch.int16))
+
+
 @pytest.mark.parametrize("T,K", [(256, 816), (257, 80), (511, 4112), (1024, 528), (1025, 336), (256, 16384), (257, 8208), (1030, 1040)])
 def test_short_batch_quantisers_at_the_edges_of_their_row_split(T, K):
     """One, two and eight rows per work-group (the line lies at one and at four rows per compute unit, 256 of them)."""
