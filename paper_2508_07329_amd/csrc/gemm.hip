@@ -31,11 +31,11 @@ int row_tiles(const GemmArgs& a, int bm) { return a.offsets ? a.max_rows / bm + 
 // Every launch takes its grid from the tile of its own kernel: at least the tile count, a multiple of 8.
 dim3 tile_grid(const GemmArgs& a, int bm, int bn) { return dim3((unsigned)round_up((int64_t)row_tiles(a, bm) * cdiv(a.N, bn), 8)); }
 
-template <int BM_, int BN_, int WM_, int WN_, int STAGES_, int MINB_, int EPI, bool DBG, bool FEW, bool WIDE>
+template <int BM_, int BN_, int WM_, int WN_, int STAGES_, int MINB_, int EPI, bool DBG, bool FEW, int FETCH>
 int launch_tiles(const GemmArgs& a, dim3 grid, hipStream_t st) {
     using S = GemmShape<BM_, BN_, WM_, WN_, STAGES_>;
     static_assert(MINB_ * S::LDS_BYTES <= 160 * 1024, "the LDS of a CU");
-    auto kern = gemm_i8_kernel<BM_, BN_, WM_, WN_, STAGES_, MINB_, EPI, DBG, FEW, WIDE>;
+    auto kern = gemm_i8_kernel<BM_, BN_, WM_, WN_, STAGES_, MINB_, EPI, DBG, FEW, FETCH>;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [&] { attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS_BYTES); });
@@ -45,110 +45,130 @@ int launch_tiles(const GemmArgs& a, dim3 grid, hipStream_t st) {
     return HAQ_OK;
 }
 
-template <int EPI, bool DBG, bool FEW = false, bool WIDE = false>
+template <int EPI, bool DBG, bool FEW = false, int FETCH = FETCH_PLAIN>
 int launch_one(const GemmArgs& a, hipStream_t st) {
     // FEW: an expert's channel tiles go round the XCDs (decode_tile), a multiple of 8 of them for each row tile
     const dim3 grid = FEW ? dim3((unsigned)((int64_t)row_tiles(a, BM) * round_up(cdiv(a.N, BN), 8))) : tile_grid(a, BM, BN);
-    return launch_tiles<BM, BN, WAVES_M, WAVES_N, STAGES, MINB, EPI, DBG, FEW, WIDE>(a, grid, st);
+    return launch_tiles<BM, BN, WAVES_M, WAVES_N, STAGES, MINB, EPI, DBG, FEW, FETCH>(a, grid, st);
 }
 
 // The other tile shapes.  Dense linears take the one that the estimate below finds fastest.
 struct TileShape {
     int bm, bn, per_cu;  // tile, work-groups that a CU holds
-    // Estimated us of a launch of T tiles on C compute units: c0 + per full round of per_cu C tiles (fix + K-steps step[per_cu-1][1])
-    // + for a last round of rem tiles, k = ceil(rem / C) to a CU, (fix + K-steps step), step between step[k-1][0] (a CU alone)
-    // and step[k-1][1] (every CU busy: the caches and the chip's power are shared) in proportion to rem / (k C).
-    float c0, fix, step[2][2];
+    // Estimated us of a launch of T tiles on C compute units.  A round is per_cu C tiles; one of n tiles, k = ceil(n / C) to a
+    // CU, takes fix + K-steps step: fix between fix[0] and fix[1] in proportion to n / (per_cu C), step between step[k-1][0] (a
+    // CU alone) and step[k-1][1] (every CU busy: the caches and the chip's power are shared) in proportion to n / (k C).  Full
+    // rounds before the last one overlap (`round` of that each); the last one costs its share of a full round and, as far as
+    // `tail` goes, what it takes alone.
+    float fix[2], step[2][2], round, tail;
 };
 enum { T128x256, T128x128, T192x128, T192x256, T256x256, N_TILES };
-// Fitted to 195 launches of each shape (129 to 4096 rows, 13 layers between 768 x 3072 and 16384 x 4096, weights cold; mean
-// deviation 3 to 6 %).  The shape with the lowest estimate is on average 1.1 % slower than the fastest of these and four
-// more (256 x 128, 128 x 256 alone on its CU, 192 x 128 and 128 x 128 with two and three to a CU); one shape fewer costs
-// another 0.3 to 1.5 %.  Against the two thresholds on tile counts before (us, with the kernel before and now):
+// Fitted to 419 launches of each shape (129 to 4096 rows, layers of 512 to 16384 input and output channels, weights cold;
+// mean deviation 3 to 5 %).  The shape with the lowest estimate is on average 0.6 % slower than the fastest of the five; four
+// more (256 x 128, 128 x 256 alone on its CU, 192 x 128 and 128 x 128 with two and three to a CU) would win another 1 %.
+// Against the two thresholds on tile counts before (us, with the kernel before and now):
 //   4096 x 16384:  333 rows 38.8 / 34.0,  600: 60 / 51,  777: 65 / 61,  2048: 124 / 118;   16384 x 4096:  777: 86 / 72,  1300: 120 / 87
 //   8192 x 8192:  333: 48 / 41,  600: 71 / 52,  1300: 108 / 81,  4096: 228 / 213;   5120 x 13824:  256: 35.6 / 30.7,  1024: 79 / 66
 //   4096 x 11008:  1024: 64 / 51;   2064 x 8208:  777: 25.2 / 24.6;   768 x 3072:  1024: 10.3 / 9.5
 constexpr TileShape TILES[N_TILES] = {
-    {128, 256, 2, 0.64f, 8.13f, {{0.369f, 0.461f}, {0.608f, 0.846f}}},
-    {128, 128, 2, 1.95f, 4.77f, {{0.216f, 0.280f}, {0.421f, 0.502f}}},
-    {192, 128, 1, 2.90f, 5.46f, {{0.242f, 0.340f}}},
-    {192, 256, 1, 2.08f, 9.20f, {{0.402f, 0.563f}}},
-    {256, 256, 1, 0.00f, 9.61f, {{0.452f, 0.745f}}},
+    {128, 256, 2, {7.37f, 11.46f}, {{0.3905f, 0.4527f}, {0.3685f, 0.8805f}}, 0.912f, 0.474f},
+    {128, 128, 2, {5.56f, 7.78f}, {{0.2365f, 0.2676f}, {0.2595f, 0.5308f}}, 0.891f, 0.467f},
+    {192, 128, 1, {7.10f, 7.04f}, {{0.2505f, 0.3565f}}, 0.894f, 0.876f},
+    {192, 256, 1, {10.02f, 11.39f}, {{0.3990f, 0.5617f}}, 0.929f, 0.930f},
+    {256, 256, 1, {7.91f, 11.54f}, {{0.4647f, 0.7081f}}, 0.952f, 0.991f},
 };
+constexpr int ONE_ROUND_MIN_K_STEPS = 16;
 float tile_us(const TileShape& t, int M, int N, int nk, int n_cu) {
     const int64_t tiles = (int64_t)cdiv(M, t.bm) * cdiv(N, t.bn), round = (int64_t)t.per_cu * n_cu;
-    const int rem = (int)(tiles % round), k = cdiv(rem, n_cu);
-    float us = t.c0 + (float)(tiles / round) * (t.fix + (float)nk * t.step[t.per_cu - 1][1]);
-    if (rem) {
+    auto one_round = [&](int n) {
+        const int k = cdiv(n, n_cu);
         const float* step = t.step[k - 1];
-        us += t.fix + (float)nk * (step[0] + (step[1] - step[0]) * (float)rem / (float)(k * n_cu));
-    }
-    return us;
+        return t.fix[0] + (t.fix[1] - t.fix[0]) * (float)n / (float)round +
+               (float)nk * (step[0] + (step[1] - step[0]) * (float)n / (float)(k * n_cu));
+    };
+    if (tiles <= round) return one_round((int)tiles);
+    const float full_us = one_round((int)round);
+    const int rem = (int)(tiles % round);
+    const float share = full_us * (float)rem / (float)round;
+    return (float)(tiles / round) * full_us * t.round + share + (rem ? t.tail * (one_round(rem) - share) : 0.0f);
 }
-// More than half a 192- or 256-row tile would be empty on at most 128 rows.
+// More than half a 192- or 256-row tile would be empty on at most 128 rows.  One round of 256 x 256 tiles, one to a CU, has
+// nothing to cover its stores with, and on few K-steps they decide: 1024 rows of 512 x 16384 19.9 to 26 us against 18.6 with
+// 128 x 256, of 768 x 16384 23.4 / 22.3 (in four rounds, 4096 rows of 512 x 16384, 60 / 67).
 int fastest_tile(int M, int N, int nk, int n_cu, float& us) {
     int best = 0;
     for (int i = 0; i < (M <= 128 ? T192x128 : N_TILES); ++i) {
+        if (i == T256x256 && nk < ONE_ROUND_MIN_K_STEPS && (int64_t)cdiv(M, 256) * cdiv(N, 256) <= n_cu) continue;
         const float t = tile_us(TILES[i], M, N, nk, n_cu);
         if (i == 0 || t < us) us = t, best = i;
     }
     return best;
 }
 
-template <int EPI>
+// FETCH_ONCE: 128 x 128 and 192 x 128 tiles whose weights one row tile reads, or most of whose weights.  As many weights
+// pass the caches by, and the token rows stay there: 128 rows of 2048 x 32768 21.4 -> 18.0 us, of 512 x 16384 8.2 -> 7.9, 192
+// rows of 4096 x 16384 29.5 -> 27.9; 8 experts of 75 rows of 14336 x 4096, the layer 308 -> 298.  With several row tiles it
+// depends on who comes first (256 rows of 4096 x 16384 31.6 -> 30.5, of 2048 x 32768 32.6 -> 34.2): left as it is.
+template <int EPI, int FETCH = FETCH_PLAIN>
 int launch_shape(const GemmArgs& a, int shape, hipStream_t st) {
     const dim3 grid = tile_grid(a, TILES[shape].bm, TILES[shape].bn);
     switch (shape) {
-        case T128x128: return launch_tiles<128, 128, 2, 2, 4, 2, EPI, false, false, false>(a, grid, st);  // wave tile 64 x 64
-        case T192x128: return launch_tiles<192, 128, 2, 2, 7, 1, EPI, false, false, false>(a, grid, st);  // 96 x 64
-        case T192x256: return launch_tiles<192, 256, 2, 2, 5, 1, EPI, false, false, false>(a, grid, st);  // 96 x 128
-        case T256x256: return launch_tiles<256, 256, 4, 2, 4, 1, EPI, false, false, false>(a, grid, st);  // 64 x 128, eight waves
+        case T128x128: return launch_tiles<128, 128, 2, 2, 4, 2, EPI, false, false, FETCH>(a, grid, st);  // wave tile 64 x 64
+        case T192x128: return launch_tiles<192, 128, 2, 2, 7, 1, EPI, false, false, FETCH>(a, grid, st);  // 96 x 64
+        case T192x256: return launch_tiles<192, 256, 2, 2, 5, 1, EPI, false, false, FETCH_PLAIN>(a, grid, st);  // 96 x 128
+        case T256x256: return launch_tiles<256, 256, 4, 2, 4, 1, EPI, false, false, FETCH_PLAIN>(a, grid, st);  // 64 x 128, eight waves
         default: return launch_one<EPI, false>(a, st);
     }
+}
+
+// 128 x 128 tiles dealt over the XCDs, for the gate/up projection of very few rows.
+template <int EPI>
+int launch_few_narrow(const GemmArgs& a, hipStream_t st) {
+    const dim3 grid((unsigned)((int64_t)row_tiles(a, 128) * round_up(cdiv(a.N, 128), 8)));
+    return launch_tiles<128, 128, 2, 2, 4, 2, EPI, false, true, FETCH_PLAIN>(a, grid, st);
 }
 
 // Operands whose offsets need more than 32 bits (4 GB): the tiled kernel computes its addresses in 64.
 bool wide_operands(const GemmArgs& a) {
     const int64_t rows = a.R > a.Npad ? a.R : a.Npad;
-    return rows > INT64_C(0xFFFFFFFF) / (64 * (int64_t)cdiv(a.K, 64));
+    return rows > (int64_t)PAST_END / (64 * (int64_t)cdiv(a.K, 64));
 }
 template <bool DBG>
 int launch_wide(const GemmArgs& a, int epi, hipStream_t st) {
     switch (epi) {
-        case EPI_SWIGLU: return launch_one<EPI_SWIGLU, false, false, true>(a, st);
-        case EPI_SWIGLU_ASYM: return launch_one<EPI_SWIGLU_ASYM, false, false, true>(a, st);
-        case EPI_LINEAR_ASYM: return launch_one<EPI_LINEAR_ASYM, DBG, false, true>(a, st);
-        default: return launch_one<EPI_LINEAR, DBG, false, true>(a, st);
+        case EPI_SWIGLU: return launch_one<EPI_SWIGLU, false, false, FETCH_WIDE>(a, st);
+        case EPI_SWIGLU_ASYM: return launch_one<EPI_SWIGLU_ASYM, false, false, FETCH_WIDE>(a, st);
+        case EPI_LINEAR_ASYM: return launch_one<EPI_LINEAR_ASYM, DBG, false, FETCH_WIDE>(a, st);
+        default: return launch_one<EPI_LINEAR, DBG, false, FETCH_WIDE>(a, st);
     }
 }
 
 }  // namespace
 
 // Row blocks of 16 per tile (4, 6 or 8) with which the streaming kernel (skinny.hip: 64-channel tiles, K split over
-// the waves, operands straight into registers) beats the tiled kernel, whose fastest shape takes `tiled_us`, or 0.  A
-// round of streaming tiles costs (4 + RB) / 80 us a K-step, the fragments of a step through a CU's load path, and
-// 3.4 + RB / 5 us to start, add up and finish.  Measured (us, M rows, K x N, streaming against tiled):
-//   16384 x 4096:  129 rows 30 / 78,  333: 37 / 78,  512: 44 / 79,  700: 70 / 82,  1024: 84 / 85
-//   4096 x 4096:   129 rows 10 / 20,  333: 13 / 20,  512: 15 / 20,  700: 25 / 21 (tiled stays)
-//   3072 x 768:    333 rows 9.4 / 15.3,  1024: 9.7 / 15.7;   2048 x 8192: 192 rows 10.3 / 13.1,  333: 18 / 13 (tiled)
-// and where few K-steps leave the start and the end to decide (weights cold):
-//   512 x 4096:    256 rows 7.6 / 8.5,  333: 9.2 / 8.6 (tiled);   768 x 3072: 400 rows 9.6 / 9.9,  512: 10.3 / 10.0 (tiled)
-//   1024 x 4096:   512 rows 10.7 / 11.2
-// Two bounds: a round of 128 x 128 tiles at 0.3 us a K-step, which keeps the tiled kernel on short K (its estimate counts
-// the start of a launch, some 3 us, and the streaming tiles' terms do not), and the estimate, less what evens out where the
-// two measure the same (700 rows of 16384 x 4096: 71 / 71).  300 rows of 8192 x 8192: 48 / 41 (tiled).
+// the waves, operands straight into registers) beats the tiled kernel, whose fastest shape takes `tiled_us`, or 0.  Its
+// three tiles are estimated alike (fitted to 174 launches of each with at most 300 tiles of 128 x 128; mean deviation 4 to 5 %):
+// a K-step costs them a third to a half of the others', which pays where few of either fit and K is long.  Within 9 % of
+// each other the streaming tiles are taken: the estimates cannot tell them apart.  Measured (us, M rows, K x N, streaming against tiled):
+//   16384 x 4096:  129 rows 30 / 69,  333: 37 / 69,  512: 44 / 70,  600: 70 / 70;   4096 x 4096:  129: 12 / 22,  512: 18 / 22
+//   3072 x 768:    1024 rows 12 / 18;   2048 x 8192:  256 rows 13.4 / 14.6,  300: 16.8 / 14.7 (tiled)
+//   8192 x 8192:   300 rows 48 / 41 (tiled);   4352 x 10304:  170 rows 29.2 / 24.5 (tiled);   5872 x 8800:  185: 35.5 / 30.8 (tiled)
+// and where few K-steps leave the start and the end to decide:
+//   512 x 4096:    256 rows 7.6 / 8.5,  333: 9.2 / 8.6 (tiled);   768 x 3072: 400 rows 9.6 / 8.9,  512: 10.3 / 9.0 (tiled)
 static int stream_row_blocks(const GemmArgs& a, int n_cu, float tiled_us) {
-    const int nk = cdiv(a.K, 64);
-    const float before = 3.0f + 0.3f * nk, now = tiled_us - 1.0f;
-    float best = before < now ? before : now;
+    static constexpr TileShape STREAM[3] = {
+        {64, 64, 1, {6.18f, 6.08f}, {{0.0968f, 0.1246f}}, 0.812f, 0.738f},
+        {96, 64, 1, {7.34f, 7.85f}, {{0.1166f, 0.1374f}}, 0.817f, 0.843f},
+        {128, 64, 1, {7.46f, 8.28f}, {{0.1430f, 0.1627f}}, 0.890f, 0.788f},
+    };
+    float best = 1.09f * tiled_us;
     int rb = 0;
-    for (int r = 4; r <= 8; r += 2) {
-        if (a.M <= 16 * r) break;  // a single row tile: skinny_pays has decided
-        const int64_t tiles = (int64_t)cdiv(a.M, 16 * r) * cdiv(a.N, 64);
-        const float t = (float)((tiles + n_cu - 1) / n_cu) * (3.4f + 0.2f * r + nk * (4 + r) * (1.0f / 80.0f));
-        if (t < best) {
-            best = t;
-            rb = r;
+    for (const TileShape& t : STREAM) {
+        if (a.M <= t.bm) break;  // a single row tile: skinny_pays has decided
+        const float us = tile_us(t, a.M, a.N, cdiv(a.K, 64), n_cu);
+        if (us <= best) {
+            best = us;
+            rb = t.bm / 16;
         }
     }
     return rb;
@@ -183,6 +203,28 @@ static int stream_mean_rows(const GemmArgs& a, int n_cu) {
     return a.n_sel * cdiv(a.N, BN) >= n_cu ? 48 : 24;
 }
 static constexpr int FEW_MEAN_ROWS = 112;  // likewise for the form for few rows
+// ... and for its 128 x 128 tiles on the gate/up projection: with two work-groups of four stages to a CU more of the weight
+// stream is in flight than with 128 x 256 tiles, which fetch the token rows half as often.  Whole layers (us, 128 x 256 / 128 x 128):
+//   4096 x 14336, 8 experts:  17 rows 260 / 247,  25: 264 / 253,  50: 286 / 289,  75: 309 / 318;   2048 x 5632, 16:  18: 138 / 137,  37: 145 / 146
+static constexpr int NARROW_MEAN_ROWS = 32;
+
+// Down projections of more than 128 rows per expert: 192 x 256 tiles (a tenth less time for the same work than 128 x 256,
+// more rows of padding) where they fill most of a round and no more, or one and a half rounds and more.  The tiles are
+// counted for experts between half and one and a half times the average.  Whole layers (us, tokens even, then by
+// 1 / rank^1.1; 128 x 256 / 192 x 256):
+//   4096 x 14336, 8 experts:  194 rows 441 / 457, 457 / 463 (no);  256: 583 / 528, 603 / 536;  512: 903 / 879, 919 / 887;  1024: 1515 / 1470, 1521 / 1469
+//   2048 x 5632, 16:  300: 332 / 315, 328 / 355 (no);  512: 456 / 451, 460 / 454;   1024 x 3584, 8:  600: 153 / 158, 154 / 158 (no)
+static bool tall_group_tiles(const GemmArgs& a, int n_cu) {
+    const int mean = a.max_rows / a.n_sel, nk = cdiv(a.K, 64), ntn = cdiv(a.N, 256);
+    auto count = [&](int bm) {  // tiles, and estimated us as a dense launch
+        int n = 0;
+        for (int f = 2; f <= 6; ++f) n += cdiv((int64_t)mean * f, 4 * bm);
+        return (int)((int64_t)n * a.n_sel * ntn / 5);
+    };
+    const int tall = count(192);
+    if (2 * tall >= 3 * n_cu) return true;
+    return 20 * tall <= 17 * n_cu && tile_us(TILES[T192x256], 1, tall * 256, nk, n_cu) < tile_us(TILES[T128x256], 1, count(128) * 256, nk, n_cu);
+}
 
 int launch_gemm(const GemmArgs& a, int epi, hipStream_t st) {
     if (skinny_pays(a) && (epi == EPI_LINEAR || epi == EPI_LINEAR_ASYM)) return launch_skinny(a, epi == EPI_LINEAR_ASYM, st);
@@ -196,6 +238,7 @@ int launch_gemm(const GemmArgs& a, int epi, hipStream_t st) {
         if ((int64_t)cdiv(a.M, 128) * cdiv(a.N, 128) <= n_cu) {
             if (const int rb = stream_row_blocks(a, n_cu, us)) return launch_stream_rows(a, asym, rb, st);
         }
+        if (a.M <= TILES[shape].bm) return asym ? launch_shape<EPI_LINEAR_ASYM, FETCH_ONCE>(a, shape, st) : launch_shape<EPI_LINEAR, FETCH_ONCE>(a, shape, st);
         return asym ? launch_shape<EPI_LINEAR_ASYM>(a, shape, st) : launch_shape<EPI_LINEAR>(a, shape, st);
     }
     if (a.offsets) {
@@ -208,8 +251,10 @@ int launch_gemm(const GemmArgs& a, int epi, hipStream_t st) {
         // 128 x 128 tiles where they cover the groups in one round (a CU with two of them takes 1.4 times as long: 14336 x 4096,
         // 8 experts, 256 tiles 99 us, 288 tiles 137): at one row tile for each group while few have more, else by the upper bound
         const int row_tiles_s = mean <= 104 ? a.n_sel : mean <= FEW_MEAN_ROWS ? a.n_sel + cdiv(a.n_sel, 8) : row_tiles(a, 128);
-        if (down && row_tiles_s * cdiv(a.N, 128) <= cu_count())
-            return asym ? launch_shape<EPI_LINEAR_ASYM>(a, T128x128, st) : launch_shape<EPI_LINEAR>(a, T128x128, st);
+        if (down && row_tiles_s * cdiv(a.N, 128) <= cu_count()) return asym ? launch_shape<EPI_LINEAR_ASYM, FETCH_ONCE>(a, T128x128, st) : launch_shape<EPI_LINEAR, FETCH_ONCE>(a, T128x128, st);
+        if (!down && mean <= NARROW_MEAN_ROWS)
+            return epi == EPI_SWIGLU_ASYM ? launch_few_narrow<EPI_SWIGLU_ASYM>(a, st) : launch_few_narrow<EPI_SWIGLU>(a, st);
+        if (down && mean > 128 && tall_group_tiles(a, cu_count())) return asym ? launch_shape<EPI_LINEAR_ASYM>(a, T192x256, st) : launch_shape<EPI_LINEAR>(a, T192x256, st);
         if (mean <= FEW_MEAN_ROWS) {
             switch (epi) {
                 case EPI_SWIGLU: return launch_one<EPI_SWIGLU, false, true>(a, st);

@@ -41,20 +41,31 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 #define HAQ_CFENCE() asm volatile("" ::: "memory")
 
 // Buffer resources: the address of a lane's 16 bytes is a scalar base, a lane offset and a scalar offset, 32 bits each
-// but the base, and only the scalar offset changes with the K-step.  (The builtins exist on the device side only.)
+// but the base, and only the scalar offset changes with the K-step; a lane whose offset lies past the resource's bytes
+// fetches nothing and gets zeros.  (The builtins exist on the device side only.)
 #ifdef __HIP_DEVICE_COMPILE__
 typedef __amdgpu_buffer_rsrc_t BufferRsrc;
-__device__ __forceinline__ BufferRsrc buffer_rsrc(const int8_t* p) { return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, 0xFFFFFFFF, 0x00027000); }
+__device__ __forceinline__ BufferRsrc buffer_rsrc(const int8_t* p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, bytes, 0x00027000);
+}
 template <int AUX>
 __device__ __forceinline__ void buffer_to_lds(BufferRsrc r, int8_t* to, uint32_t lane_off, uint32_t off) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)to, 16, lane_off, off, 0, AUX);
 }
 #else
 typedef const int8_t* BufferRsrc;
-__device__ __forceinline__ BufferRsrc buffer_rsrc(const int8_t* p) { return p; }
+__device__ __forceinline__ BufferRsrc buffer_rsrc(const int8_t* p, uint32_t) { return p; }
 template <int AUX>
 __device__ __forceinline__ void buffer_to_lds(BufferRsrc, int8_t*, uint32_t, uint32_t) {}
 #endif
+
+// How a launch fetches its operands.
+enum {
+    FETCH_PLAIN = 0,
+    FETCH_WIDE = 1,   // offsets of 64 bits: operands of 4 GB and more
+    FETCH_ONCE = 2,   // weights that hardly any other tile reads pass the caches by (non-temporal)
+};
+constexpr uint32_t PAST_END = 0xFFFF0000u;  // an offset past every resource's bytes
 
 struct TileCoord {
     int m0;     // first (sorted) row of the tile
@@ -148,7 +159,7 @@ struct GemmShape {
     static constexpr int LDS_BYTES = STAGES * STAGE_BYTES + SCALE_BYTES;
 };
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int MINB, int EPI, bool DBG, bool FEW = false, bool WIDE = false>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int MINB, int EPI, bool DBG, bool FEW = false, int FETCH = FETCH_PLAIN>
 __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINB) void gemm_i8_kernel(GemmArgs a) {
     using S = GemmShape<BM, BN, WAVES_M, WAVES_N, STAGES>;
     constexpr int NW = S::NW;
@@ -162,6 +173,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINB) void gemm_i8_kernel(G
     // a tile's loads cover BM rows and BN channels whatever the problem size: the packed operands are padded for that
     static_assert(NPAD % BN == 0, "a channel tile must not reach past the padded width of the packed weights");
     static_assert(BM <= 256, "packed activations carry 256 rows of padding");
+    constexpr bool WIDE = FETCH == FETCH_WIDE;
     constexpr bool SWIGLU = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_ASYM;
     constexpr bool ASYM = EPI == EPI_LINEAR_ASYM || EPI == EPI_SWIGLU_ASYM;
     static_assert(!SWIGLU || NI % 2 == 0, "gate/up blocks come in pairs");
@@ -240,26 +252,25 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINB) void gemm_i8_kernel(G
     const int8_t* Bu = uniform_ptr(Bmat);
     const int8_t* Ag = Au + (size_t)m0u * 16;
     const int8_t* Bg = Bu + (size_t)n0u * 16;
-    const BufferRsrc rsrc_a = buffer_rsrc(Ag), rsrc_b = buffer_rsrc(Bg);
-    using Off = std::conditional_t<WIDE, size_t, uint32_t>;  // WIDE: operands of 4 GB and more
+    using Off = std::conditional_t<WIDE, size_t, uint32_t>;
+    uint32_t bytes_a = (uint32_t)(((size_t)nkt * 4 * a.R - m0u) * 16), bytes_b = PAST_END;  // of the buffer resources
     const Off step_a = (Off)4 * a.R * 16, step_b = (Off)4 * a.Npad * 16;
     Off off[LPW];  // of this lane's 16 bytes from the tile's origin, at K-step 0
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
         const int g = wave + i * NW;
         if (i * NW < GA) {
-            int rg = g % (BM / 64);
-            if (FEW && rg * 64 >= tc.m_end - m0u) rg = 0;  // 64 rows past the group's last: their results are dropped
-            off[i] = ((Off)(g / (BM / 64)) * a.R + rg * 64 + lane) * 16;
+            const int row = g % (BM / 64) * 64 + lane;
+            off[i] = ((Off)(g / (BM / 64)) * a.R + row) * 16;
+            if (!WIDE && m0u + row >= tc.m_end) off[i] = PAST_END;  // a row past the last one: its results are dropped
         } else {
             const int g2 = g - GA;
             off[i] = ((Off)(g2 / (BN / 64)) * a.Npad + g2 % (BN / 64) * 64 + lane) * 16;
         }
     }
-    // FEW: the weights are hardly shared and pass the caches by (non-temporal), so that the token rows stay there;
-    // for a group's second row tile too (cached from there on: two experts of 256 rows of 4096 x 14336 172 -> 188 us
+    // FEW: for a group's second row tile too (cached from there on: two experts of 256 rows of 4096 x 14336 172 -> 188 us
     // a layer, eight of 10 to 183 rows 364 -> 363)
-    constexpr int NT = FEW ? 2 : 0;
+    constexpr int NT = FEW || FETCH == FETCH_ONCE ? 2 : 0;
     Off next_a = 0, next_b = 0;  // of the next K-step to request
     auto load = [&](int buf, int i) __attribute__((always_inline)) {
         int8_t* to = lds + buf * STAGE_BYTES + (wave + i * NW) * 1024;
@@ -268,16 +279,19 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINB) void gemm_i8_kernel(G
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(uintptr_t)src,
                                              (__attribute__((address_space(3))) void*)to, 16, 0, 0);
         } else if (i * NW < GA) {
-            buffer_to_lds<0>(rsrc_a, to, off[i], next_a);
+            buffer_to_lds<0>(buffer_rsrc(Ag, bytes_a), to, off[i], next_a);
         } else {
-            buffer_to_lds<NT>(rsrc_b, to, off[i], next_b);
+            buffer_to_lds<NT>(buffer_rsrc(Bg, bytes_b), to, off[i], next_b);
         }
     };
-    // K-step kt has been requested.  Past the last one it is requested again, into a stage that nobody reads any more:
-    // the loads of every K-step are then the same code and the same count for s_waitcnt.
+    // K-step kt has been requested.  Past the last one the loads go on, into stages that nobody reads any more, so that every
+    // K-step is the same code and the same count for s_waitcnt; their resources are empty then and nothing is fetched
+    // (with the last K-step requested again 2339 rows of 720 x 6464 took 24.3 us instead of 23.4).  64-bit offsets: it is.
     auto advance = [&](int kt) __attribute__((always_inline)) {
-        next_a += kt + 1 < nkt ? step_a : 0;
-        next_b += kt + 1 < nkt ? step_b : 0;
+        const bool more = kt + 1 < nkt;
+        next_a = more ? next_a + step_a : WIDE ? next_a : 0;  // (0: nothing is in range of an empty resource at scalar offset 0)
+        next_b = more ? next_b + step_b : WIDE ? next_b : 0;
+        if (!more) bytes_a = bytes_b = 0;
     };
 
     v16i acc[MI][NI];

@@ -120,9 +120,26 @@ def test_dense_tile_shapes_by_rows_channels_and_k(plan):
         for shape, sizes in best.items():
             for p, (kernel, t, _) in zip(sizes, plan([(epi, M, N, K, 0, 0, 0, 0) for M, K, N in sizes])):
                 assert (kernel, tuple(t[:2]), t[9]) == ("gemm_i8", shape, 0), (p, kernel, t)
+        assert [t[9] for _, t, _ in plan([(epi, M, N, K, 0, 0, 0, 0) for M, N, K in [(128, 16384, 512), (192, 24576, 4096), (193, 24576, 4096)]])] == [2, 2, 0]
         edge = [(300, 2 ** 22 - 256, 1024), (300, 2 ** 22, 1024), (2 ** 22, 300, 1024), (2 ** 22 - 1024, 300, 1024), (300, 2 ** 22, 1025)]
         assert [t[9] for _, t, _ in plan([(epi, M, N, K, 0, 0, 0, 0) for M, N, K in edge])] == [0, 1, 1, 0, 1]
         assert [t[9] for _, t, _ in plan([(epi, M, N, K, 0, 0, 0, 1) for M, N, K in edge])] == [0, 1, 1, 0, 1]  # with the accumulators
+
+
+def test_projections_of_expert_groups_on_either_side_of_their_lines(plan):
+    """(experts, channels, K, rows for each): 192 x 256 tiles of down projections, 128 x 128 tiles of gate/up projections and
+    weights that pass the caches by."""
+    tall = [(8, 4096, 14336, 256), (8, 4096, 14336, 512), (8, 4096, 14336, 1024), (16, 2048, 5632, 512)]
+    flat = [(8, 4096, 14336, 128), (8, 4096, 14336, 194), (16, 2048, 5632, 300), (8, 1024, 3584, 600)]
+    for epi in (LINEAR, LINEAR_ASYM):
+        of = lambda sizes: [(k, t[:2], t[8:10]) for k, t, _ in plan([(epi, 0, N, K, n, n * rows, 1, 0) for n, N, K, rows in sizes])]
+        assert all(r == ("gemm_i8", [192, 256], [0, 0]) for r in of(tall)), of(tall)
+        assert all(r == ("gemm_i8", [128, 256], [0, 0]) for r in of(flat)), of(flat)
+        assert of([(8, 4096, 14336, 75)]) == [("gemm_i8", [128, 128], [0, 2])]
+    for epi in (SWIGLU, SWIGLU_ASYM):
+        of = lambda rows: [(k, t[:2], t[8:10]) for k, t, _ in plan([(epi, 0, 28672, 4096, 8, 8 * r, 0, 0) for r in rows])]
+        assert of([9, 32]) == [("gemm_i8", [128, 128], [1, 0])] * 2 and of([33, 112]) == [("gemm_i8", [128, 256], [1, 0])] * 2
+        assert of([113, 1024]) == [("gemm_i8", [128, 256], [0, 0])] * 2
 
 
 def test_group_tiles_are_dealt_once_and_evenly(tmp_path):
