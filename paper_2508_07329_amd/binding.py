@@ -73,6 +73,20 @@ class _MoeDebug(C.Structure):
     _fields_ = [(n, C.c_void_p) for n in _DBG_FIELDS]
 
 
+# Argument types of the calls that a serving loop makes: tensors' addresses and sizes then go over as plain integers (a
+# ctypes object for each of them, and a stream object, took half of a linear's 6 us in Python).
+_P, _I, _L, _Z = C.c_void_p, C.c_int32, C.c_int64, C.c_size_t
+_CALLS = {
+    "haq_quant_act_packed": (_P, _L, _P, _I, _I, _P, _P, _P),
+    "haq_gemm_w8a8_packed": (_P, _P, _P, _P, _I, _I, _I, _I, _P, _L, _P, _P),
+    "haq_w8a8_linear": (_P, _L, _P, _P, _P, _I, _I, _I, _I, _P, _L, _P, _P, _P, _P, _Z, _P),
+    "haq_w8a8_linear_asym": (_P, _L, _P, _P, _P, _P, _I, _I, _I, _I, _P, _L, _P, _P, _P, _P, _P, _Z, _P),
+    "haq_w8a8_ffn": (_P, _L, _P, _P, _P, _I, _P, _P, _P, _I, _I, _I, _I, _P, _L, _P, _P, _Z, _P),
+    "haq_moe_w8a8_ffn": (_P, _P, _L, _P, _L, _P, _P, _I, _I, _I, _I, _I, _P, _L, _P, _P, _Z, _P),
+    "haq_moe_w8a8_ffn_static": (_P, _L, _P, _L, _P, _P, _I, _I, _I, _I, _I, _P, _L, _P),
+    "haq_moe_w8a8_ffn_asym": (_P, _L, _P, _L, _P, _P, _P, _I, _I, _I, _I, _I, _P, _L, _P, _P, _Z, _P),
+}
+
 _lib = None
 
 
@@ -91,6 +105,8 @@ def lib() -> C.CDLL:
                   "haq_quantize_layer_workspace_bytes", "haq_moe_asym_workspace_bytes", "haq_linear_kn_workspace_bytes"):
             getattr(L, n).restype = C.c_size_t
         L.haq_packed_act_rows.restype = C.c_int64
+        for n, types in _CALLS.items():
+            getattr(L, n).argtypes = types
         _lib = L
     return _lib
 
@@ -108,6 +124,20 @@ def _ptr(t):
 
 def _stream():
     return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+
+
+# The same as plain integers: for the calls in _CALLS only, any other would take them for 32-bit ints.
+def _adr(t):
+    return None if t is None else t.data_ptr()
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream_adr():
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _ws(nbytes: int, device) -> torch.Tensor:
@@ -197,9 +227,9 @@ def haq_w8a8_linear(x, s, w_packed, w_scale, N: int, act: int = HAQ_ACT_NONE, *,
         acc = torch.empty((T, N), dtype=torch.int32, device=dev)
         q = torch.empty((T, K), dtype=torch.int8, device=dev)
         sx = torch.empty((T,), dtype=torch.float32, device=dev)
-    _check(lib().haq_w8a8_linear(_ptr(x), C.c_int64(x.stride(0)), _ptr(s), _ptr(w_packed), _ptr(w_scale), T, K, N, act,
-                                 _ptr(y), C.c_int64(y.stride(0)), _ptr(acc), _ptr(q), _ptr(sx), _ptr(workspace),
-                                 C.c_size_t(workspace.numel()), _stream()))
+    _check(lib().haq_w8a8_linear(_adr(x), x.stride(0), _adr(s), _adr(w_packed), _adr(w_scale), T, K, N, act,
+                                 _adr(y), y.stride(0), _adr(acc), _adr(q), _adr(sx), _adr(workspace),
+                                 workspace.numel(), _stream_adr()))
     return (y, acc, q, sx) if debug else y
 
 
@@ -234,16 +264,16 @@ def haq_quant_act_packed(x, s, *, q_packed=None, row_scale=None):
         q_packed = torch.empty((haq_packed_act_bytes(T, K),), dtype=torch.int8, device=x.device)
     if row_scale is None:
         row_scale = torch.empty((T,), dtype=torch.float32, device=x.device)
-    _check(lib().haq_quant_act_packed(_ptr(x), C.c_int64(x.stride(0)), _ptr(s), T, K, _ptr(q_packed), _ptr(row_scale),
-                                      _stream()))
+    _check(lib().haq_quant_act_packed(_adr(x), x.stride(0), _adr(s), T, K, _adr(q_packed), _adr(row_scale),
+                                      _stream_adr()))
     return q_packed, row_scale
 
 
 def haq_gemm_w8a8_packed(q_packed, row_scale, w_packed, w_scale, T: int, K: int, N: int, act: int = HAQ_ACT_NONE, *,
                          out=None):
     y = out if out is not None else torch.empty((T, N), dtype=torch.float16, device=q_packed.device)
-    _check(lib().haq_gemm_w8a8_packed(_ptr(q_packed), _ptr(row_scale), _ptr(w_packed), _ptr(w_scale), T, K, N, act,
-                                      _ptr(y), C.c_int64(y.stride(0)), None, _stream()))
+    _check(lib().haq_gemm_w8a8_packed(_adr(q_packed), _adr(row_scale), _adr(w_packed), _adr(w_scale), T, K, N, act,
+                                      _adr(y), y.stride(0), None, _stream_adr()))
     return y
 
 
@@ -260,9 +290,9 @@ def haq_w8a8_ffn(x, s1, w1_packed, w1_scale, F: int, act: int, s2, w2_packed, w2
     if workspace is None:
         workspace = _ws(haq_ffn_workspace_bytes(T, K, F, N), dev)
     h = torch.empty((T, F), dtype=torch.float16, device=dev) if debug else None
-    _check(lib().haq_w8a8_ffn(_ptr(x), C.c_int64(x.stride(0)), _ptr(s1), _ptr(w1_packed), _ptr(w1_scale), act, _ptr(s2),
-                              _ptr(w2_packed), _ptr(w2_scale), T, K, F, N, _ptr(y), C.c_int64(y.stride(0)), _ptr(h),
-                              _ptr(workspace), C.c_size_t(workspace.numel()), _stream()))
+    _check(lib().haq_w8a8_ffn(_adr(x), x.stride(0), _adr(s1), _adr(w1_packed), _adr(w1_scale), act, _adr(s2),
+                              _adr(w2_packed), _adr(w2_scale), T, K, F, N, _adr(y), y.stride(0), _adr(h),
+                              _adr(workspace), workspace.numel(), _stream_adr()))
     return (y, h) if debug else y
 
 
@@ -276,6 +306,16 @@ class ExpertWeights:
     sw2: torch.Tensor
     s_mid: torch.Tensor
     location: int = HAQ_LOC_DEVICE
+
+
+def _expert_descs(experts):
+    """haq_expert_desc[E] (_ExpertDesc: six addresses, then location and reserved in one word) as 64-bit words in one go:
+    field by field it took 8 us for eight experts, a third of a decode call on small layers."""
+    words = []
+    for e in experts:
+        words += (e.w13.data_ptr(), e.w2.data_ptr(), e.sw1.data_ptr(), e.sw3.data_ptr(), e.sw2.data_ptr(), e.s_mid.data_ptr(),
+                  e.location & 0xFFFFFFFF)
+    return (C.c_uint64 * len(words))(*words)
 
 
 @dataclass
@@ -318,11 +358,7 @@ def haq_moe_w8a8_ffn(x, logits, s_in, experts: list[ExpertWeights], I: int, *, c
     y = out if out is not None else torch.empty((T, H), dtype=torch.float16, device=dev)
     if workspace is None:
         workspace = _ws(haq_moe_workspace_bytes(T, H, I, E), dev)
-    descs = (_ExpertDesc * E)()
-    for i, e in enumerate(experts):
-        descs[i].w13, descs[i].w2 = e.w13.data_ptr(), e.w2.data_ptr()
-        descs[i].sw1, descs[i].sw3, descs[i].sw2 = e.sw1.data_ptr(), e.sw3.data_ptr(), e.sw2.data_ptr()
-        descs[i].s_mid, descs[i].location = e.s_mid.data_ptr(), e.location
+    descs = _expert_descs(experts)
     dbg = None
     dbg_c = None
     if debug:
@@ -336,10 +372,10 @@ def haq_moe_w8a8_ffn(x, logits, s_in, experts: list[ExpertWeights], I: int, *, c
             raise ValueError(f"unknown debug fields {sorted(set(want) - set(_DBG_FIELDS))}")
         dbg = MoeDebug(*[mk(*sp) if n in want else None for n, sp in zip(_DBG_FIELDS, spec)])
         dbg_c = _MoeDebug(*[getattr(dbg, n).data_ptr() if n in want else None for n in _DBG_FIELDS])
-    _check(lib().haq_moe_w8a8_ffn(ctx, _ptr(x), C.c_int64(x.stride(0)), _ptr(logits), C.c_int64(logits.stride(0)),
-                                  _ptr(s_in), descs, T, H, I, E, 2, _ptr(y), C.c_int64(y.stride(0)),
-                                  C.byref(dbg_c) if dbg_c is not None else None, _ptr(workspace),
-                                  C.c_size_t(workspace.numel()), _stream()))
+    _check(lib().haq_moe_w8a8_ffn(ctx, _adr(x), x.stride(0), _adr(logits), logits.stride(0),
+                                  _adr(s_in), descs, T, H, I, E, 2, _adr(y), y.stride(0),
+                                  C.byref(dbg_c) if dbg_c is not None else None, _adr(workspace),
+                                  workspace.numel(), _stream_adr()))
     return (y, dbg) if debug else y
 
 
@@ -347,18 +383,10 @@ def haq_moe_w8a8_ffn_static(x, logits, s_in, experts, I: int, *, out):
     """haq_moe_w8a8_ffn on the library's built-in scratch array: nothing is allocated, so `out` is required."""
     T, H = x.shape
     E = len(experts)
-    descs = (_ExpertDesc * E)()
-    for i, e in enumerate(experts):
-        descs[i].w13, descs[i].w2 = e.w13.data_ptr(), e.w2.data_ptr()
-        descs[i].sw1, descs[i].sw3, descs[i].sw2 = e.sw1.data_ptr(), e.sw3.data_ptr(), e.sw2.data_ptr()
-        descs[i].s_mid, descs[i].location = e.s_mid.data_ptr(), e.location
-    _check(lib().haq_moe_w8a8_ffn_static(_ptr(x), C.c_int64(x.stride(0)), _ptr(logits), C.c_int64(logits.stride(0)), _ptr(s_in),
-                                         descs, T, H, I, E, 2, _ptr(out), C.c_int64(out.stride(0)), _stream()))
+    descs = _expert_descs(experts)
+    _check(lib().haq_moe_w8a8_ffn_static(_adr(x), x.stride(0), _adr(logits), logits.stride(0), _adr(s_in),
+                                         descs, T, H, I, E, 2, _adr(out), out.stride(0), _stream_adr()))
     return out
-
-
-class _ExpertColsum(C.Structure):
-    _fields_ = [("cs1", C.c_void_p), ("cs3", C.c_void_p), ("cs2", C.c_void_p)]
 
 
 class _MoeDebugAsym(C.Structure):
@@ -378,13 +406,8 @@ def haq_moe_w8a8_ffn_asym(x, logits, s_in, experts, colsums, I: int, *, out=None
     y = out if out is not None else torch.empty((T, H), dtype=torch.float16, device=dev)
     if workspace is None:
         workspace = _ws(haq_moe_asym_workspace_bytes(T, H, I, E), dev)
-    descs = (_ExpertDesc * E)()
-    cs = (_ExpertColsum * E)()
-    for i, (e, c) in enumerate(zip(experts, colsums)):
-        descs[i].w13, descs[i].w2 = e.w13.data_ptr(), e.w2.data_ptr()
-        descs[i].sw1, descs[i].sw3, descs[i].sw2 = e.sw1.data_ptr(), e.sw3.data_ptr(), e.sw2.data_ptr()
-        descs[i].s_mid, descs[i].location = e.s_mid.data_ptr(), e.location
-        cs[i].cs1, cs[i].cs3, cs[i].cs2 = c[0].data_ptr(), c[1].data_ptr(), c[2].data_ptr()
+    descs = _expert_descs(experts)
+    cs = (C.c_uint64 * (3 * E))(*[c.data_ptr() for _, (c1, c3, c2) in zip(experts, colsums) for c in (c1, c3, c2)])
     dbg = zx = zh = None
     dbg_c = None
     if debug:
@@ -396,10 +419,10 @@ def haq_moe_w8a8_ffn_asym(x, logits, s_in, experts, colsums, I: int, *, out=None
         dbg = MoeDebug(*[mk(*sp) for sp in spec])
         zx, zh = mk((T,), i32), mk((P,), i32)
         dbg_c = _MoeDebugAsym(_MoeDebug(*[getattr(dbg, n).data_ptr() for n in _DBG_FIELDS]), zx.data_ptr(), zh.data_ptr())
-    _check(lib().haq_moe_w8a8_ffn_asym(_ptr(x), C.c_int64(x.stride(0)), _ptr(logits), C.c_int64(logits.stride(0)), _ptr(s_in),
-                                       descs, cs, T, H, I, E, 2, _ptr(y), C.c_int64(y.stride(0)),
-                                       C.byref(dbg_c) if dbg_c is not None else None, _ptr(workspace),
-                                       C.c_size_t(workspace.numel()), _stream()))
+    _check(lib().haq_moe_w8a8_ffn_asym(_adr(x), x.stride(0), _adr(logits), logits.stride(0), _adr(s_in),
+                                       descs, cs, T, H, I, E, 2, _adr(y), y.stride(0),
+                                       C.byref(dbg_c) if dbg_c is not None else None, _adr(workspace),
+                                       workspace.numel(), _stream_adr()))
     return (y, dbg, zx, zh) if debug else y
 
 
@@ -652,9 +675,9 @@ def haq_w8a8_linear_asym(x, s, w_packed, w_scale, w_colsum, N: int, act: int = H
         q = torch.empty((T, K), dtype=torch.uint8, device=dev)
         sx = torch.empty((T,), dtype=torch.float32, device=dev)
         zp = torch.empty((T,), dtype=torch.int32, device=dev)
-    _check(lib().haq_w8a8_linear_asym(_ptr(x), C.c_int64(x.stride(0)), _ptr(s), _ptr(w_packed), _ptr(w_scale), _ptr(w_colsum),
-                                      T, K, N, act, _ptr(y), C.c_int64(y.stride(0)), _ptr(acc), _ptr(q), _ptr(sx), _ptr(zp),
-                                      _ptr(workspace), C.c_size_t(workspace.numel()), _stream()))
+    _check(lib().haq_w8a8_linear_asym(_adr(x), x.stride(0), _adr(s), _adr(w_packed), _adr(w_scale), _adr(w_colsum),
+                                      T, K, N, act, _adr(y), y.stride(0), _adr(acc), _adr(q), _adr(sx), _adr(zp),
+                                      _adr(workspace), workspace.numel(), _stream_adr()))
     return (y, acc, q, sx, zp) if debug else y
 
 
