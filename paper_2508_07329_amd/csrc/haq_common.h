@@ -112,6 +112,12 @@ struct QuantArgs {
     int32_t* zp;
 };
 int launch_quant(const QuantArgs& a, hipStream_t st);
+// Q(W s) for several smoothing vectors (quant.hip).  colmax[c N + n] = max_k |s[c K + k] w[k N + n]| for nc <= WEIGHT_NC
+// vectors (s null: one vector of ones); then the codes of one of them in the packed layout, and their scales.
+constexpr int WEIGHT_NC = 16;
+int launch_weight_colmax(const float* w, const float* s, int nc, int K, int N, float* colmax, hipStream_t st);
+int launch_weight_scale(float* colmax, int N, hipStream_t st);  // column maxima to scales, in place
+int launch_weight_pack(const float* w, const float* s, int K, int N, const float* colmax, int8_t* packed, float* scale, hipStream_t st);
 int cu_count();  // compute units of the current device (256 if that cannot be asked)
 
 enum { EPI_LINEAR = 0, EPI_SWIGLU = 1, EPI_LINEAR_ASYM = 2, EPI_SWIGLU_ASYM = 3 };

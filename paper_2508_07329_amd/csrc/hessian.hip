@@ -464,8 +464,8 @@ int32_t haq_hessian_quant_weight(const void* x_fp16, int64_t ldx, int32_t T, con
     hipStream_t st = (hipStream_t)stream;
     HessWs ws = carve_hess(workspace, K, N);
     int rc;
-    // the per-output-channel grid is the one of plain rounding (its codes are overwritten below)
-    if ((rc = haq_quant_weight(w, s, K, N, wq, w_scale, stream)) != HAQ_OK) return rc;
+    // the per-output-channel grid is the one of plain rounding
+    if ((rc = launch_weight_colmax(w, s, 1, K, N, w_scale, st)) != HAQ_OK || (rc = launch_weight_scale(w_scale, N, st)) != HAQ_OK) return rc;
     if ((rc = haq_hessian_f64(x_fp16, ldx, s, T, K, percdamp, ws.H, stream)) != HAQ_OK) return rc;
     if ((rc = inverse_cholesky_upper(ws.H, K, ws.H, ws.A, ws.M, ws.status, st)) != HAQ_OK) return rc;  // U replaces H
     const double* U = ws.H;

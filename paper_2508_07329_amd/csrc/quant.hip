@@ -795,15 +795,57 @@ __global__ void weight_row_absmax_kernel(const float* w, int K, int N, float* aw
 }
 
 // ---- offline: Q(W s), scale per output channel -------------------------------
-__global__ void weight_col_absmax_kernel(const float* w, const float* s, int K, int N, float* colmax) {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N) return;
-    float m = 0.0f;
-    for (int k = blockIdx.y; k < K; k += gridDim.y) {
-        const float sk = s ? s[k] : 1.0f;
-        m = fmaxf(m, fabsf(sk * w[(size_t)k * N + n]));
+// Bound: the read of W.  NC smoothing vectors in one pass (their entries are the same for the whole work-group: scalar
+// registers), eight rows in flight per thread: 4096 x 16384, eleven vectors 980 -> 148 us
+// (the eleven products and maxima of an element are two thirds of that), one 80 -> 54.
+template <int NC>
+__global__ __launch_bounds__(256) void weight_col_absmax_kernel(const float* w, const float* s, int nc, int K, int N, float* colmax) {
+    const int n = blockIdx.x * blockDim.x + threadIdx.x, nn = min(n, N - 1);
+    float m[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) m[c] = 0.0f;
+    const int rows = (K + gridDim.y - 1) / gridDim.y, k0 = blockIdx.y * rows, k1 = min(K, k0 + rows);
+    for (int k = k0; k < k1; k += 8) {
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = w[(size_t)min(k + i, k1 - 1) * N + nn];  // past the last row it counts twice
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            if (c >= nc) continue;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) m[c] = fmaxf(m[c], fabsf((s ? s[(size_t)c * K + min(k + i, k1 - 1)] : 1.0f) * v[i]));
+        }
     }
-    atomicMax(reinterpret_cast<unsigned int*>(colmax) + n, __float_as_uint(m));
+    if (n >= N) return;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+        if (c < nc) atomicMax(reinterpret_cast<unsigned int*>(colmax) + (size_t)c * N + n, __float_as_uint(m[c]));
+}
+
+// Codes of 16 rows of one channel per thread, stored where the packed layout wants them.  Bound: the read of W and the
+// write of the codes: 4096 x 16384 with the codes in rows and a second kernel that packed them 189 us, now 62
+// (5.4 TB/s).
+__global__ __launch_bounds__(256) void weight_pack_kernel(const float* w, const float* s, int K, int N, int Npad, const float* colmax,
+                                                          int8_t* out, float* scale_out) {
+    const int n = blockIdx.x * blockDim.x + threadIdx.x, kc = blockIdx.y;
+    uint32_t wv[4] = {0, 0, 0, 0};
+    if (n < N) {
+        const float a = colmax[n], scale = a / 127.0f, rscale = 1.0f / scale;
+        if (kc == 0) scale_out[n] = scale;
+        if (a != 0.0f && kc * 16 < K) {  // chunks past K (the pad up to a whole 64-byte k-step) stay zero
+            const bool fast = scale >= 0x1p-100f && scale <= 0x1p100f;
+            float v[16];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) v[j] = w[(size_t)(kc * 16 + j) * N + n];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const float y = (s ? s[kc * 16 + j] : 1.0f) * v[j];
+                const float q = fast ? div_by(y, scale, rscale, true) : y / scale;
+                wv[j / 4] |= (uint32_t)((int)fminf(fmaxf(rintf(q), -127.0f), 127.0f) & 0xff) << (8 * (j % 4));
+            }
+        }
+    }
+    *reinterpret_cast<uint4*>(out + ((size_t)kc * Npad + n) * 16) = make_uint4(wv[0], wv[1], wv[2], wv[3]);
 }
 
 __global__ void weight_codes_kernel(const float* w, const float* s, int K, int N, const float* colmax, int8_t* wq) {
@@ -927,6 +969,31 @@ int launch_quant(const QuantArgs& a, hipStream_t st) {
     return HAQ_OK;
 }
 
+int launch_weight_colmax(const float* w, const float* s, int nc, int K, int N, float* colmax, hipStream_t st) {
+    const size_t n = (size_t)nc * N;
+    hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, (uint32_t*)colmax, n);
+    const dim3 grid(cdiv(N, 256), cdiv(K, 64));  // 64 rows to a work-group
+    if (nc == 1)
+        hipLaunchKernelGGL(weight_col_absmax_kernel<1>, grid, dim3(256), 0, st, w, s, nc, K, N, colmax);
+    else
+        hipLaunchKernelGGL(weight_col_absmax_kernel<WEIGHT_NC>, grid, dim3(256), 0, st, w, s, nc, K, N, colmax);
+    HAQ_CHECK_HIP(hipGetLastError());
+    return HAQ_OK;
+}
+
+int launch_weight_scale(float* colmax, int N, hipStream_t st) {
+    hipLaunchKernelGGL(absmax_to_scale_kernel, dim3(cdiv(N, 256)), dim3(256), 0, st, colmax, N);
+    HAQ_CHECK_HIP(hipGetLastError());
+    return HAQ_OK;
+}
+
+int launch_weight_pack(const float* w, const float* s, int K, int N, const float* colmax, int8_t* packed, float* scale, hipStream_t st) {
+    const int Npad = (int)round_up(N, NPAD);
+    hipLaunchKernelGGL(weight_pack_kernel, dim3(Npad / 256, (unsigned)(round_up(K, 64) / 16)), dim3(256), 0, st, w, s, K, N, Npad, colmax, packed, scale);
+    HAQ_CHECK_HIP(hipGetLastError());
+    return HAQ_OK;
+}
+
 int launch_asym_quant(const __half* x, int64_t ldx, const float* s, int T, int K, int8_t* q_cm, int64_t R, uint8_t* q_rm,
                       int64_t ldq, float* scale, int32_t* zp, hipStream_t st) {
     if (T <= 0) return HAQ_OK;
@@ -1009,13 +1076,9 @@ int32_t haq_quant_weight(const float* w, const float* s, int32_t K, int32_t N, i
     if (!w || !wq || !w_scale) HAQ_FAIL(HAQ_ERR_INVALID_ARG, "haq_quant_weight: null buffer");
     hipStream_t st = (hipStream_t)stream;
     // w_scale first holds the column absmax, then is turned into the scale in place
-    hipLaunchKernelGGL(fill_zero_kernel, dim3(cdiv(N, 256)), dim3(256), 0, st, (uint32_t*)w_scale, (size_t)N);
-    const int ky = K < 64 ? K : 64;
-    hipLaunchKernelGGL(weight_col_absmax_kernel, dim3(cdiv(N, 256), ky), dim3(256), 0, st, w, s, K, N, w_scale);
+    if (const int rc = launch_weight_colmax(w, s, 1, K, N, w_scale, st)) return rc;
     hipLaunchKernelGGL(weight_codes_kernel, dim3(cdiv(N, 256), K), dim3(256), 0, st, w, s, K, N, (const float*)w_scale, wq);
-    hipLaunchKernelGGL(absmax_to_scale_kernel, dim3(cdiv(N, 256)), dim3(256), 0, st, w_scale, N);
-    HAQ_CHECK_HIP(hipGetLastError());
-    return HAQ_OK;
+    return launch_weight_scale(w_scale, N, st);
 }
 
 int32_t haq_weight_colsum(const int8_t* wq, int32_t K, int32_t N, int32_t* colsum, void* stream) {

@@ -220,10 +220,14 @@ int32_t haq_smoothing_search(const void* x_fp16, int64_t ldx, const float* w, in
     HAQ_CHECK_HIP(hipStreamSynchronize(st));  // s_all is pageable host memory: the copy has landed before any return below
 
     if ((rc = haq_reference_matmul_f64(x_fp16, ldx, w, T, K, N, ws.yref, stream)) != HAQ_OK) return rc;
+    // The column maxima of WEIGHT_NC candidates at a time, in the memory of the unpacked codes (K N bytes, K >= 4 WEIGHT_NC),
+    // which this path does not need: the codes go straight into the packed layout.
+    float* colmax = (float*)ws.wq;
+    static_assert(4 * WEIGHT_NC <= 64, "K is a multiple of 64");
     for (int i = 0; i < n_e; ++i) {
         const float* s = ws.s_all + (size_t)i * K;
-        if ((rc = haq_quant_weight(w, s, K, N, ws.wq, ws.sw, stream)) != HAQ_OK) return rc;
-        if ((rc = haq_pack_weight(ws.wq, K, N, ws.packed, stream)) != HAQ_OK) return rc;
+        if (i % WEIGHT_NC == 0 && (rc = launch_weight_colmax(w, s, n_e - i < WEIGHT_NC ? n_e - i : WEIGHT_NC, K, N, colmax, st)) != HAQ_OK) return rc;
+        if ((rc = launch_weight_pack(w, s, K, N, colmax + (size_t)(i % WEIGHT_NC) * N, ws.packed, ws.sw, st)) != HAQ_OK) return rc;
         if ((rc = haq_w8a8_linear(x_fp16, ldx, s, ws.packed, ws.sw, T, K, N, HAQ_ACT_NONE, ws.y, N, nullptr, nullptr, nullptr,
                                   ws.lin, ws.lin_bytes, stream)) != HAQ_OK)
             return rc;

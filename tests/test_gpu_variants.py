@@ -116,6 +116,21 @@ def test_quantisers_on_rows_of_fewer_chunks_than_a_thread_has_rows(T, K):
     _linear_both_codes(T, K, 16, "none")
 
 
+@pytest.mark.parametrize("T,K,N,n_e", [(40, 64, 16, 37), (33, 128, 272, 16), (24, 192, 528, 17)])
+def test_smoothing_search_on_more_candidates_than_one_pass_over_the_weights_takes(T, K, N, n_e):
+    """16 candidates to a pass: one, one and a single one, two and a rest; a channel of zeros, one below the range in which a
+    code is formed by the scale's reciprocal, one of which only a single weight is not zero."""
+    X, _, _ = hi.hidden_states(T + K, T, K, n_outlier=2)
+    W = hi.gaussian_weight(T + K, 0, K, N)
+    W[:, 3], W[:, 5], W[:, 7] = 0.0, W[:, 5] * np.float32(2.0 ** -110), 0.0
+    W[K - 1, 7] = -0.75
+    grid = [i / (n_e - 1) for i in range(n_e)]
+    losses_ref, best_ref, s_ref = oracle.smoothing_search(X, W, grid, True)
+    losses, best, s = haq.haq_smoothing_search(dev(X), dev(W), grid, True)
+    assert np.array_equal(np.asarray(losses), losses_ref), diff_report(np.asarray(losses), losses_ref)
+    assert best == best_ref and bits_equal(host(s), s_ref)
+
+
 @pytest.mark.parametrize("T,K,N", [(17, 63, 17), (80, 65, 130), (40, 128, 9), (33, 257, 66), (64, 330, 1000), (100, 448, 208), (70, 700, 81)])
 def test_layer_quantiser_at_the_edges_of_its_blocks(T, K, N):
     """Panels and blocks of 64 with one row less and more, k chunks of 16 with a remainder, a second stretch of 256
