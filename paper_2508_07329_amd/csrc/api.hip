@@ -1095,9 +1095,6 @@ int32_t haq_moe_w8a8_ffn_asym(const void* x_fp16, int64_t ldx, const void* logit
     int32_t* zh = d.zh ? d.zh : zh_ws;
 
     int rc;
-    if ((rc = launch_route_permute((const __half*)logits_fp16, ldl, T, E, tab, w.tab, idx, gw, counts, offsets, perm, inv, w.blk_counts,
-                                   st, cst, cstab)) != HAQ_OK)
-        return rc;
     // tokens: one row of codes per (token, expert) pair in sorted order, zero point and scale with it
     AsymRowArgs qa{};
     qa.x = (const __half*)x_fp16;
@@ -1130,8 +1127,15 @@ int32_t haq_moe_w8a8_ffn_asym(const void* x_fp16, int64_t ldx, const void* logit
     pa.scale_dest = w.sx_sorted;
     pa.zp = d.zx;
     pa.zp_dest = zx_sorted;
-    rc = launch_quant(pa, st);
-    if (rc == HAQ_ERR_UNSUPPORTED) rc = launch_asym_quant_rows(qa, st);
+    if (decode_prologue_asym_supported(T, H)) {  // routing, permutation and tokens in one launch
+        rc = launch_decode_prologue_asym((const __half*)logits_fp16, ldl, T, E, tab, w.tab, cst, cstab, idx, gw, counts, offsets, perm, inv, qa, st);
+    } else {
+        if ((rc = launch_route_permute((const __half*)logits_fp16, ldl, T, E, tab, w.tab, idx, gw, counts, offsets, perm, inv, w.blk_counts,
+                                       st, cst, cstab)) != HAQ_OK)
+            return rc;
+        rc = launch_quant(pa, st);
+        if (rc == HAQ_ERR_UNSUPPORTED) rc = launch_asym_quant_rows(qa, st);
+    }
     if (rc != HAQ_OK) return rc;
 
     // At most 64 tokens: every activated expert's weights are streamed once by the weight-streaming kernels

@@ -101,6 +101,62 @@ __device__ __forceinline__ float max16(const float* p) {
     return fmaxf(ab, cd);
 }
 
+// One row in asymmetric codes by a whole work-group, one 16-channel chunk per thread: range of x / s widened to contain 0,
+// scale = range / 255, zero point rne(-min / scale).  `red` is LDS scratch of 2 x 16 floats, 16-byte aligned; returns the
+// scale, `z` the zero point, `u` this thread's codes (0 past the row's last chunk).
+__device__ __forceinline__ float asym_quantise_row(const __half* xrow, const float* s, int nchunk, float (*red)[16], float& z, uint32_t (&u)[4]) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nwave = blockDim.x >> 6;
+    float y[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) y[i] = 0.0f;
+    if (tid < nchunk) {
+        load_x16(xrow, tid, y);
+        if (s) {
+            float sv[16], rv[16];
+            const bool fast = load_s16(s, tid, sv, rv);
+            if (fast) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) y[i] = div_by(y[i], sv[i], rv[i], true);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) y[i] = y[i] / sv[i];
+            }
+        }
+    }
+    float mn = 0.0f, mx = 0.0f;  // the range always contains 0
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        mn = fminf(mn, y[i]);
+        mx = fmaxf(mx, y[i]);
+    }
+    mn = wave_max(-mn);
+    mx = wave_max(mx);
+    if (tid >= nwave && tid < 16) red[0][tid] = red[1][tid] = 0.0f;
+    if (lane == 0) {
+        red[0][wave] = mn;
+        red[1][wave] = mx;
+    }
+    __syncthreads();
+    const float lo = -max16(red[0]), hi = max16(red[1]);
+    const float range = hi - lo;
+    float scale = 0.0f;
+    z = 0.0f;
+    u[0] = u[1] = u[2] = u[3] = 0;
+    if (range != 0.0f) {
+        scale = range / 255.0f;
+        z = fminf(fmaxf(rintf(-lo / scale), 0.0f), 255.0f);
+        const float rscale = 1.0f / scale;
+        const bool sfast = scale >= 0x1p-100f && scale <= 0x1p100f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const float qv = sfast ? div_by(y[i], scale, rscale, true) : y[i] / scale;
+            const float cf = fminf(fmaxf(rintf(qv) + z, 0.0f), 255.0f);
+            u[i / 4] |= (uint32_t)(int)cf << (8 * (i % 4));
+        }
+    }
+    return scale;
+}
+
 // One row of Q(s^-1 x) by a whole work-group of NT threads (NCH 16-channel chunks per thread, so up
 // to NT * NCH chunks): raw halves stay in registers between the absmax reduction and the rounding.
 // `red` is LDS scratch of NT / 64 floats; `store(chunk, codes)` receives each finished chunk.  Every

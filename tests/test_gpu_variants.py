@@ -199,3 +199,28 @@ def test_routed_experts_at_the_edges_of_their_row_tiles(H, I, first, second, E):
     _check_moe(m)
     counts = _check_moe_asym(m)
     assert tuple(counts[:len(first) + len(second)]) == (*first, *second)
+
+
+@pytest.mark.parametrize("T,H,I,E", [(1, 64, 64, 2), (63, 2048, 64, 32), (64, 2112, 128, 3), (65, 192, 128, 8), (33, 16384, 64, 4)])
+def test_asymmetric_tokens_and_routing_in_one_launch(T, H, I, E):
+    """Work-groups of as many threads as pairs need, as chunks of 16 channels need, one chunk more than whole waves, and the
+    largest; one token more than the launch takes; all 32 experts."""
+    _check_moe_asym(offline.small_moe(seed=T + H, T=T, H=H, I=I, E=E))
+
+
+@pytest.mark.parametrize("H,I,E,rows", [(256, 192, 4, 300), (128, 64, 8, 500), (4096, 64, 8, 257)])
+def test_large_expert_groups_at_the_edges_of_192_row_tiles(H, I, E, rows):
+    """More than 128 rows per expert on average: groups of one and two rows more than whole tiles of 128, 192 and 256 rows."""
+    T = E * rows // 2
+    m = offline.small_moe(seed=rows + H, T=T, H=H, I=I, E=E)
+    first, second = np.arange(T) % E, (np.arange(T) // E) % E
+    second = np.where(second == first, (first + 1) % E, second)
+    for e, n in enumerate((193, 129)):  # tokens past these go to the last expert
+        first[np.flatnonzero(first == e)[n:]] = E - 1
+    second = np.where(second == first, (first + 1) % E, second)
+    logits = np.full((T, E), -4.0, np.float16)
+    logits[np.arange(T), second] = 1.5
+    logits[np.arange(T), first] = 2.0
+    m["logits"] = logits
+    _check_moe(m)
+    _check_moe_asym(m)
