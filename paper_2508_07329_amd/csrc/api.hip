@@ -194,6 +194,33 @@ inline void prof_mark(hipStream_t st, const char* name) {  // the stage `name` e
     }
     g_prof.name[g_prof.n++] = name;
 }
+
+// One linear on fp16 rows: a few rows of short K in one launch, whose work-groups all read x and s while others store y, so
+// not where y overlaps them (the two launches allow that); anything else as codes in q_cm, row scales in sx, and the linear.
+int linear_f16(const void* x_fp16, int64_t ldx, const float* s, int T, int K, int8_t* q_cm, float* sx, const int8_t* w_packed,
+               const float* w_scale, int N, int act, void* y_fp16, int64_t ldy, hipStream_t st, const char* mark) {
+    auto apart = [&](const void* p, size_t bytes) {
+        const uintptr_t a = (uintptr_t)p, y = (uintptr_t)y_fp16, y_bytes = ((uintptr_t)(T - 1) * ldy + N) * 2;
+        return a + bytes <= y || y + y_bytes <= a;
+    };
+    if (fused_linear_fits(T, K, N) && apart(x_fp16, ((size_t)(T - 1) * ldx + K) * 2) && (!s || apart(s, (size_t)K * 4))) {
+        GemmArgs ga{};
+        ga.K = K;
+        ga.N = N;
+        ga.Npad = round_up(N, NPAD);
+        ga.M = T;
+        ga.B = w_packed;
+        ga.sw = w_scale;
+        ga.act = act;
+        ga.Y = (__half*)y_fp16;
+        ga.ldy = ldy;
+        if (mark) prof_mark(st, mark);
+        return launch_fused_linear(ga, (const __half*)x_fp16, ldx, s, st);
+    }
+    if (const int rc = quant_packed(x_fp16, ldx, s, T, K, q_cm, sx, nullptr, st)) return rc;
+    if (mark) prof_mark(st, mark);
+    return gemm_packed(q_cm, sx, w_packed, w_scale, T, K, N, act, y_fp16, ldy, nullptr, st);
+}
 }  // namespace
 
 // Context of layers with host-resident experts: staging slots in HBM, the copy stream and the
@@ -282,6 +309,7 @@ int32_t haq_w8a8_linear(const void* x_fp16, int64_t ldx, const float* s, const i
         HAQ_FAIL(HAQ_ERR_WORKSPACE, "haq_w8a8_linear: workspace of %zu bytes (256-byte aligned) needed, got %zu", need, workspace_bytes);
     hipStream_t st = (hipStream_t)stream;
     const LinearWs w = carve_linear(workspace, T, K);
+    if (!acc_dbg && !q_dbg && !sx_dbg) return linear_f16(x_fp16, ldx, s, T, K, w.q_cm, w.sx, w_packed, w_scale, N, act, y_fp16, ldy, st, nullptr);
     int rc = quant_packed(x_fp16, ldx, s, T, K, w.q_cm, w.sx, q_dbg, st);
     if (rc != HAQ_OK) return rc;
     if (sx_dbg) HAQ_CHECK_HIP(hipMemcpyAsync(sx_dbg, w.sx, (size_t)T * sizeof(float), hipMemcpyDeviceToDevice, st));
@@ -402,14 +430,10 @@ int32_t haq_w8a8_ffn(const void* x_fp16, int64_t ldx, const float* s1, const int
     const FfnWs w = carve_ffn(workspace, T, K, F);
     __half* h = h_dbg_fp16 ? (__half*)h_dbg_fp16 : w.h;
     prof_begin(st);
-    int rc = quant_packed(x_fp16, ldx, s1, T, K, w.q1, w.sx1, nullptr, st);
+    int rc = linear_f16(x_fp16, ldx, s1, T, K, w.q1, w.sx1, w1_packed, w1_scale, F, act, h, F, st, "quantise X");
     if (rc != HAQ_OK) return rc;
-    prof_mark(st, "quantise X");
-    if ((rc = gemm_packed(w.q1, w.sx1, w1_packed, w1_scale, T, K, F, act, h, F, nullptr, st)) != HAQ_OK) return rc;
     prof_mark(st, "GEMM 1 + activation");
-    if ((rc = quant_packed(h, F, s2, T, F, w.q2, w.sx2, nullptr, st)) != HAQ_OK) return rc;
-    prof_mark(st, "requantise H");
-    rc = gemm_packed(w.q2, w.sx2, w2_packed, w2_scale, T, F, N, HAQ_ACT_NONE, y_fp16, ldy, nullptr, st);
+    rc = linear_f16(h, F, s2, T, F, w.q2, w.sx2, w2_packed, w2_scale, N, HAQ_ACT_NONE, y_fp16, ldy, st, "requantise H");
     prof_mark(st, "GEMM 2");
     return rc;
 }

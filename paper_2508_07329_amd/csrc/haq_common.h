@@ -161,6 +161,8 @@ int launch_gemm(const GemmArgs& a, int epi, hipStream_t st);
 constexpr int SKINNY_MAX_ROWS = 128;
 bool skinny_pays(const GemmArgs& a);  // within its limits and not slower than the tiled kernel
 int launch_skinny(const GemmArgs& a, bool asym, hipStream_t st);
+bool fused_linear_fits(int M, int K, int N);  // a few rows of short K: token codes and linear in one launch (A and sx of `a` not used)
+int launch_fused_linear(const GemmArgs& a, const __half* x, int64_t ldx, const float* s, hipStream_t st);
 int launch_stream_rows(const GemmArgs& a, bool asym, int rb, hipStream_t st);  // any row count: row tiles of 16 rb rows (rb: 4, 6 or 8)
 int launch_stream_grouped(const GemmArgs& a, bool asym, hipStream_t st);       // expert groups (down projection), row tiles of at most 128 rows
 int launch_asym_quant(const __half* x, int64_t ldx, const float* s, int T, int K, int8_t* q_cm, int64_t R, uint8_t* q_rm,

@@ -15,6 +15,7 @@
 //   768 x 3072      7.4- 3.3    7.5- 3.4    7.5- 4.2    7.8- 4.4    7.7- 6.3
 #include "group_tiles.h"
 #include "haq_common.h"
+#include "quant_math.h"
 
 namespace haq {
 
@@ -189,6 +190,147 @@ __global__ __launch_bounds__(SG_WAVES * 64, 2) void stream_grouped_kernel(GemmAr
     }
 }
 
+// A few rows of short K: every work-group forms the codes itself, so that the layer is one launch.  WPR waves share a
+// row (a chunk of 16 channels to each lane, K <= 1024 WPR), 8 / WPR rows at a time, at most two to a lane, which shares the
+// reciprocals of the smoothing vector between them; the codes (16 KB, chunk-major) and the row scales stay in LDS.
+// Bound: latency, of the loads, of the row maximum and of the weight stream, one after another; the first weights are
+// fetched behind the rows' loads and in front of their use.  us a call on the GPU, the quantiser's launch and the linear's / this:
+//   512 x 512, 16 rows 7.8 / 6.5;  768 x 3072, 1: 7.4 / 6.6, 16: 7.8 / 6.7;  1024 x 16384, 16: 10.3 / 9.1;  2048 x 8192, 8: 10.1 / 9.5
+//   4096 x 4096, 4: 9.7 / 9.1;  4096 x 16384, 4: 16.6 / 16.1;  8192 x 1024, 2: 11.4 / 9.3;  8192 x 16384, 2: 26.9 / 25.6
+// and the host launches once: 768 x 3072 on 16 rows, back to back, 9.8 -> 7.5.
+template <int C, int WPR>
+__global__ __launch_bounds__(SK_WAVES * 64, C == 1 ? 4 : 2) void fused_linear_kernel(GemmArgs a, const __half* x, int64_t ldx, const float* s) {
+    constexpr int RG = SK_WAVES / WPR, ROWS = 2 * RG, DEPTH = WPR == 1 ? 2 : 4;
+    __shared__ __attribute__((aligned(16))) uint4 codes[64 * WPR][ROWS];
+    __shared__ float red[ROWS][WPR], scale_s[ROWS];
+    __shared__ int sum[C][4][64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nchunk = a.K / 16, c = (wave % WPR) * 64 + lane, cc = min(c, nchunk - 1), g = wave / WPR;
+    uint4 raw[2][2];  // loads stay unconditional: rows and chunks past the last re-read it
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const uint4* px = reinterpret_cast<const uint4*>(x + (size_t)min(g + j * RG, a.M - 1) * ldx + cc * 16);
+        raw[j][0] = px[0];
+        raw[j][1] = px[1];
+    }
+    float4 s4[4];
+    if (s) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s4[i] = reinterpret_cast<const float4*>(s + cc * 16)[i];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    const int l16 = lane & 15, q = lane >> 4, n0 = (int)blockIdx.x * (16 * C);
+    const int nk = (a.K + 63) / 64, n = nk > wave ? (nk - wave + SK_WAVES - 1) / SK_WAVES : 0;  // this wave's K-steps: wave, wave + 8, ...
+    const int8_t* pw = a.B + ((size_t)(4 * wave + q) * a.Npad + n0 + l16) * 16;
+    const size_t wstep = (size_t)4 * SK_WAVES * a.Npad * 16;
+    v4i w[DEPTH][C];
+    int fetched = 0;
+    auto next = [&](v4i(&f)[C]) {  // past this wave's last K-step it is fetched again
+#pragma unroll
+        for (int b = 0; b < C; ++b) f[b] = gload16_stream(pw + b * 256);
+        if (++fetched < n) pw += wstep;
+    };
+    if (n > 0) {
+#pragma unroll
+        for (int i = 0; i < DEPTH; ++i) next(w[i]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    float y[2][16], sv[16], rv[16], amax[2];
+    bool fast = true;
+    if (s) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            sv[i] = i % 4 == 0 ? s4[i / 4].x : i % 4 == 1 ? s4[i / 4].y : i % 4 == 2 ? s4[i / 4].z : s4[i / 4].w;
+            rv[i] = 1.0f / sv[i];
+            fast = fast & safe_divisor(sv[i]);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        Half8 h0, h1;
+        *reinterpret_cast<uint4*>(&h0) = raw[j][0];
+        *reinterpret_cast<uint4*>(&h1) = raw[j][1];
+        amax[j] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const float v = h2f(i < 8 ? h0.v[i] : h1.v[i - 8]);
+            y[j][i] = !s ? v : fast ? div_by(v, sv[i], rv[i], true) : v / sv[i];
+            amax[j] = fmaxf(amax[j], fabsf(y[j][i]));
+        }
+        amax[j] = wave_max(c < nchunk ? amax[j] : 0.0f);
+        if (lane == 0) red[g + j * RG][wave % WPR] = amax[j];
+    }
+    for (int i = tid; i < C * 256; i += SK_WAVES * 64) (&sum[0][0][0])[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int row = g + j * RG;
+        float m = 0.0f;
+#pragma unroll
+        for (int i = 0; i < WPR; ++i) m = fmaxf(m, red[row][i]);
+        const float scale = m / 127.0f, rscale = 1.0f / scale;
+        const bool sfast = scale >= 0x1p-100f && scale <= 0x1p100f;
+        uint32_t u[4] = {0, 0, 0, 0};
+        if (m != 0.0f) {
+            if (fast && sfast) {
+                float v[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) v[i] = div_by(y[j][i], scale, rscale, true);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) u[i] = round_pack4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) u[i / 4] |= (uint32_t)(code_of(y[j][i], scale) & 0xff) << (8 * (i % 4));
+            }
+        }
+        if (c < nchunk) codes[c][row] = make_uint4(u[0], u[1], u[2], u[3]);
+        if (c == 0) scale_s[row] = scale;
+    }
+    __syncthreads();
+
+    if (n > 0) {
+        v4i acc[C];
+#pragma unroll
+        for (int b = 0; b < C; ++b) acc[b] = v4i{0, 0, 0, 0};
+        const int xr = min(l16, a.M - 1);
+        auto mac = [&](const v4i(&f)[C], int k) {  // a last partial K-step reads chunks past K: the weights are zero there
+            const v4i xv = *reinterpret_cast<const v4i*>(&codes[4 * (wave + SK_WAVES * k) + q][xr]);
+#pragma unroll
+            for (int b = 0; b < C; ++b) acc[b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[b], xv, acc[b], 0, 0, 0);
+        };
+        int k = 0;
+        for (; k + DEPTH < n; k += DEPTH) {
+#pragma unroll
+            for (int i = 0; i < DEPTH; ++i) {
+                mac(w[i], k + i);
+                next(w[i]);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < DEPTH; ++i)
+            if (k + i < n) mac(w[i], k + i);
+#pragma unroll
+        for (int b = 0; b < C; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) atomicAdd(&sum[b][r][lane], acc[b][r]);  // exact: the order is immaterial
+    }
+    __syncthreads();
+    for (int i = tid; i < C * 64; i += SK_WAVES * 64) {
+        const int b = i >> 6, ln = i & 63, row = ln & 15, ch = n0 + 16 * b + 4 * (ln >> 4);
+        if (row >= a.M || ch >= a.N) continue;
+        __half hv[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            float f = dequant(sum[b][r][ln], scale_s[row], a.sw[ch + r]);
+            if (a.act == HAQ_ACT_RELU) f = fmaxf(f, 0.0f);
+            hv[r] = f2h(f);
+        }
+        *reinterpret_cast<uint2*>(a.Y + (size_t)row * a.ldy + ch) = *reinterpret_cast<const uint2*>(hv);
+    }
+}
+
 template <int C, int RB, int DEPTH, int WPS>
 int launch_one(const GemmArgs& a, bool asym, hipStream_t st) {
     const dim3 grid(cdiv(a.N, 16 * C));
@@ -243,6 +385,33 @@ bool skinny_pays(const GemmArgs& a) {
     // least K for two rounds and for more, by blocks of 16 rows
     constexpr int MIN_K[2][4] = {{1024, 1536, 2048, 2048}, {1024, 2048, 4096, INT32_MAX}};
     return rounds == 1 || a.K >= MIN_K[rounds > 2][RB - 1];
+}
+
+// Rows and channels that one round of its work-groups covers: 16 rows up to K = 1024, 8 to 2048, 4 to 4096, 2 to 8192.
+bool fused_linear_fits(int M, int K, int N) {
+    if (M < 1 || K > 8192 || M * (K <= 1024 ? 1 : K <= 2048 ? 2 : K <= 4096 ? 4 : 8) > 16) return false;
+    return cdiv(N, 16 * channel_blocks(N)) <= 2 * cu_count();
+}
+
+int launch_fused_linear(const GemmArgs& a, const __half* x, int64_t ldx, const float* s, hipStream_t st) {
+    const int C = channel_blocks(a.N);
+    const dim3 grid(cdiv(a.N, 16 * C)), block(SK_WAVES * 64);
+#define HAQ_FUSED(c, wpr)                                                                            \
+    if (C == c && a.K <= 1024 * wpr) {                                                               \
+        hipLaunchKernelGGL((fused_linear_kernel<c, wpr>), grid, block, 0, st, a, x, ldx, s);         \
+        HAQ_CHECK_HIP(hipGetLastError());                                                            \
+        return HAQ_OK;                                                                               \
+    }
+    HAQ_FUSED(1, 1)
+    HAQ_FUSED(1, 2)
+    HAQ_FUSED(1, 4)
+    HAQ_FUSED(1, 8)
+    HAQ_FUSED(4, 1)
+    HAQ_FUSED(4, 2)
+    HAQ_FUSED(4, 4)
+    HAQ_FUSED(4, 8)
+#undef HAQ_FUSED
+    return HAQ_ERR_UNSUPPORTED;
 }
 
 int launch_skinny(const GemmArgs& a, bool asym, hipStream_t st) {

@@ -224,3 +224,44 @@ def test_large_expert_groups_at_the_edges_of_192_row_tiles(H, I, E, rows):
     m["logits"] = logits
     _check_moe(m)
     _check_moe_asym(m)
+
+
+@pytest.mark.parametrize("T,K,N,act", [
+    # one, two, four and eight waves to a row: the most rows and channels of each, one row and one channel chunk more
+    (16, 1024, 48, "relu"), (17, 1024, 16, "none"), (8, 1040, 272, "none"), (8, 2048, 16, "relu"), (9, 2048, 32, "none"), (4, 2064, 80, "none"),
+    (4, 4096, 16, "relu"), (2, 4112, 144, "none"), (2, 8192, 16, "relu"), (3, 8192, 16, "none"), (1, 8208, 16, "none"), (1, 16, 16, "relu"),
+    # units of 64 channels, the last one partly past the last channel
+    (16, 592, 8208, "none"), (5, 1552, 8224, "relu"), (3, 4096, 8240, "none"), (1, 6160, 8192, "none")])
+def test_few_rows_of_short_k_in_one_launch(T, K, N, act):
+    """The calls without debug outputs; those with them take the two launches."""
+    _linear_both_codes(T, K, N, act)
+
+
+@pytest.mark.parametrize("T,K", [(16, 1008), (7, 2048), (4, 3088), (2, 8192)])
+def test_one_launch_linear_without_smoothing_on_odd_rows_and_in_place(T, K):
+    """No smoothing vector; entries whose reciprocal is not used; a row of zeros, one of tiny and one of large values; rows
+    with a gap between them; and outputs over the inputs, which only the two launches allow."""
+    X, _, _ = hi.hidden_states(T + K, T, K, n_outlier=2)
+    X[0] = 0
+    X[T - 1] *= np.float16(2.0 ** -12)
+    s, Wq, sw = offline.quantize_linear(X, hi.gaussian_weight(T + K, 0, K, K))
+    s[3], s[K - 1] = 2.0 ** 50, 2.0 ** -45
+    wp, sw_d = haq.haq_pack_weight(dev(Wq)), dev(sw)
+    for sv in (None, s):
+        ref = oracle.w8a8_linear(X, sv if sv is not None else np.ones(K, np.float32), Wq, sw, "none")
+        sd = dev(sv) if sv is not None else None
+        x = torch.full((T, K + 8), 3.0, dtype=torch.float16, device="cuda")
+        x[:, :K] = dev(X)
+        assert bits_equal(host(haq.haq_w8a8_linear(x[:, :K], sd, wp, sw_d, K)), ref)
+        both = dev(X)
+        assert bits_equal(host(haq.haq_w8a8_linear(both, sd, wp, sw_d, K, out=both)), ref)
+
+
+def test_ffn_of_few_rows_in_two_launches():
+    for T, K, F, N in ((16, 320, 1024, 80), (8, 1024, 2048, 1024), (2, 2048, 8192, 2048), (4, 1024, 8192, 512)):
+        X, _, _ = hi.hidden_states(T + K, T, K, n_outlier=2)
+        s1, W1, sw1 = offline.quantize_linear(X, hi.gaussian_weight(T + K, 0, K, F))
+        h = oracle.w8a8_linear(X, s1, W1, sw1, "relu")
+        s2, W2, sw2 = offline.quantize_linear(h, hi.gaussian_weight(T + K, 1, F, N))
+        y = haq.haq_w8a8_ffn(dev(X), dev(s1), haq.haq_pack_weight(dev(W1)), dev(sw1), F, oracle.ACT["relu"], dev(s2), haq.haq_pack_weight(dev(W2)), dev(sw2), N)
+        assert bits_equal(host(y), oracle.w8a8_linear(h, s2, W2, sw2, "none"))
