@@ -50,10 +50,10 @@ QUANT_VALU_PER_ELEMENT = 24.0
 # 256 MiB device copy); the counters cannot be read from inside this process, so the figure is the one
 # of the committed summary profiles/gemm_i8_kernel__opt6.7b_ffn.md and only applies to that workload.
 GEMM_TRAFFIC_BYTES_OPT67B_FFN = 2.77e+08
-# The same for the single GEMM launch of the small linear (16 x 768 x 3072: 3.29 MB read, 0.10 MB written) and for the
+# The same for the single GEMM launch of the small linear (16 x 768 x 3072: 2.53 MB read, 0.10 MB written) and for the
 # grouped gate/up and down launches of the prefill layer (profiles/gemm_i8_kernel__mixtral_prefill.md).
-GEMM_TRAFFIC_BYTES_OPT125M_LINEAR = 3.39e+06
-PREFILL_TRAFFIC_BYTES = {"gate_up": 3.12e+09, "down": 1.93e+09}
+GEMM_TRAFFIC_BYTES_OPT125M_LINEAR = 2.63e+06
+PREFILL_TRAFFIC_BYTES = {"gate_up": 3.38e+09, "down": 1.45e+09}
 # The same for one call of the decode layer (all its kernels; reads only, the writes are a few MB), from
 # profiles/decode_kernels__mixtral_decode.md: within 0.3-2 % of the algorithmic weight bytes.
 DECODE_TRAFFIC_BYTES = {"moe_decode_b1": 3.55e+08, "moe_decode_b8": 1.063e+09, "moe_decode_b64": 1.440e+09}
@@ -257,7 +257,7 @@ def bench_ffn(args, torch, haq, hi, cpu_seconds=10.0):
     if two:
         quant.append(_quant_record("requantisation of the fp16 intermediate", T, F, span(2)))
 
-    roof = {"bound": "mfma", "kernel": "gemm_i8_kernel (int8 MFMA GEMM + dequant epilogue)",
+    roof = {"bound": "mfma", "kernel": ("gemm_i8_kernel" if wl is not None else "skinny_linear_kernel") + " (int8 MFMA GEMM + dequant epilogue)",
             "achieved": achieved, "peak": PEAK_INT8_TOPS, "unit": "TOP/s", "frac": achieved / PEAK_INT8_TOPS,
             "avg_launch_ms": gemm_avg * 1e3, "launch_ms": gemm_ms, "ops_per_launch": ops_per_gemm,
             "traffic": GEMM_TRAFFIC_BYTES_OPT67B_FFN if wl is not None else GEMM_TRAFFIC_BYTES_OPT125M_LINEAR,

@@ -478,8 +478,9 @@ int32_t haq_moe_w8a8_ffn(haq_ctx* ctx, const void* x_fp16, int64_t ldx, const vo
  * colsums_host [E] (HOST array) points at int32 device vectors cs1 [I], cs3 [I]
  * (of the w1 and w3 codes) and cs2 [H] (of the w2 codes) from haq_weight_colsum.
  * Every expert must be device resident.  More than 64 tokens -> grouped
- * GEMMs (as above); up to 64 tokens with H % 128 == 0 and I % 256 == 0 -> the
- * weight-streaming kernels for the two projections.  2 <= E <= 32, top_k = 2, H % 64 == 0, I % 64 == 0, both <= 16384.
+ * GEMMs (as above); up to 64 tokens -> routing and token codes in one launch, and
+ * with H % 128 == 0 and I % 256 == 0 the weight-streaming kernels for the two
+ * projections (five launches).  2 <= E <= 32, top_k = 2, H % 64 == 0, I % 64 == 0, both <= 16384.
  * dbg: the fields of haq_moe_debug (q and hq receive the uint8 codes) plus the zero
  * points zx [T] and zh [2T] (sorted order); every field optional.               */
 typedef struct haq_expert_colsum {
