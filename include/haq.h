@@ -240,7 +240,8 @@ int32_t haq_smoothing_search(const void* x_fp16, int64_t ldx, const float* w, in
  * x_fp16 [T x K] device, w fp32 [K x N] device, s [K] device or NULL.  Outputs
  * wq int8 [K x N] dense and w_scale [N] (device), to be packed with
  * haq_pack_weight.  K < 65536.  The calls synchronise the stream once (the
- * factorisation reports a non-positive pivot as HAQ_ERR_INVALID_ARG).
+ * factorisation reports a non-positive pivot as HAQ_ERR_INVALID_ARG; wq and
+ * w_scale then hold plain rounding, as from haq_quant_weight).
  * Workspace: haq_hessian_quant_workspace_bytes(K, N) bytes, 256-byte aligned
  * (three K x K and one K x N binary64 matrices).
  * Building blocks: haq_hessian_f64 (H [K x K] device), and

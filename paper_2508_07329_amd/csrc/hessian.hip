@@ -467,7 +467,11 @@ int32_t haq_hessian_quant_weight(const void* x_fp16, int64_t ldx, int32_t T, con
     // the per-output-channel grid is the one of plain rounding
     if ((rc = launch_weight_colmax(w, s, 1, K, N, w_scale, st)) != HAQ_OK || (rc = launch_weight_scale(w_scale, N, st)) != HAQ_OK) return rc;
     if ((rc = haq_hessian_f64(x_fp16, ldx, s, T, K, percdamp, ws.H, stream)) != HAQ_OK) return rc;
-    if ((rc = inverse_cholesky_upper(ws.H, K, ws.H, ws.A, ws.M, ws.status, st)) != HAQ_OK) return rc;  // U replaces H
+    if ((rc = inverse_cholesky_upper(ws.H, K, ws.H, ws.A, ws.M, ws.status, st)) != HAQ_OK) {  // U replaces H
+        // an indefinite Hessian leaves the codes of plain rounding, which belong to the scales above
+        if (rc == HAQ_ERR_INVALID_ARG) (void)haq_quant_weight(w, s, K, N, wq, w_scale, stream);
+        return rc;
+    }
     const double* U = ws.H;
     hipLaunchKernelGGL(fold_weight_kernel, dim3(cdiv(N, 256), K), dim3(256), 0, st, w, s, K, N, ws.w64);
     // The errors of a stretch of channels are kept for one product over everything below it: in the memory of A and M,

@@ -1,4 +1,6 @@
 """Kernel variants that a rule on sizes picks: each at the edges of its range, against the CPU oracle, bit for bit."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -6,6 +8,7 @@ import torch
 import haq_inputs as hi
 import oracle
 import paper_2508_07329_amd as haq
+from paper_2508_07329_amd.binding import lib
 from tests import offline
 from tests.gpu_util import bits_equal, dev, diff_report, host
 from tests.test_gpu_parity import _check_moe, _check_moe_asym
@@ -150,6 +153,20 @@ def test_layer_quantiser_at_the_edges_of_its_blocks(T, K, N):
         Wq_ref, sw_ref = oracle.gptq(W, sv, U_ref)
         Wq, sw = haq.haq_hessian_quant_weight(dev(X), dev(W), None if sv is None else dev(sv), 0.01)
         assert bits_equal(host(sw), sw_ref) and bits_equal(host(Wq), Wq_ref)
+
+
+def test_an_indefinite_hessian_leaves_plain_rounding():
+    """Equal channels without damping: the second pivot is exactly zero."""
+    K, N = 64, 48
+    x, W = torch.ones(4, K, dtype=torch.float16, device="cuda"), hi.gaussian_weight(5, 0, K, N)
+    w, wq, sw = dev(W), torch.full((K, N), 85, dtype=torch.int8, device="cuda"), torch.empty(N, device="cuda")
+    ws = torch.empty(int(lib().haq_hessian_quant_workspace_bytes(K, N)), dtype=torch.uint8, device="cuda")
+    p = lambda t: ctypes.c_void_p(t.data_ptr())
+    rc = lib().haq_hessian_quant_weight(p(x), ctypes.c_int64(K), 4, p(w), None, K, N, ctypes.c_double(0.0), p(wq), p(sw), p(ws),
+                                        ctypes.c_size_t(ws.numel()), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == -1 and b"not positive definite" in lib().haq_last_error()
+    Wq_ref, sw_ref = oracle.quant_weight(W, None)
+    assert bits_equal(host(wq), Wq_ref) and bits_equal(host(sw), sw_ref)
 
 
 @pytest.mark.parametrize("rows,cols", [(33, 40), (70, 16)])
