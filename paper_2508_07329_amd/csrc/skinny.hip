@@ -387,10 +387,17 @@ bool skinny_pays(const GemmArgs& a) {
     return rounds == 1 || a.K >= MIN_K[rounds > 2][RB - 1];
 }
 
-// Rows and channels that one round of its work-groups covers: 16 rows up to K = 1024, 8 to 2048, 4 to 4096, 2 to 8192.
+// 16 rows up to K = 1024, 8 to 2048, 4 to 4096, 2 to 8192, and a work-group for each CU at most: 3 to 23 % faster there at
+// every one of 70 sizes.  A second work-group on a CU forms the codes again, on vector units that are busy with the first
+// one's: that pays where the weight stream is long enough to hide it.  us on the GPU, two launches / this:
+//   16-channel units:  K = 48: 7.1 / 7.8,  144: 7.2 / 8.1,  256: 7.6 / 8.1,  384: 8.3 / 8.3,  848: 8.9 / 8.7,  1392: 8.8 / 9.1,
+//                      2240: 9.8 / 9.8,  3472: 11.1 / 10.6,  4336: 13.1 / 10.8,  7280: 17.9 / 14.0
+//   64-channel units (past 16384 channels):  K = 16: 7.2 / 8.5,  128: 8.0 / 8.7,  288: 9.2 / 9.2,  400: 11.0 / 9.9,  992: 12.4 / 11.4,
+//                      1056: 12.2 / 15.8,  1536: 13.9 / 17.5,  2400: 18.3 / 21.2,  5488: 26.2 / 28.4
 bool fused_linear_fits(int M, int K, int N) {
     if (M < 1 || K > 8192 || M * (K <= 1024 ? 1 : K <= 2048 ? 2 : K <= 4096 ? 4 : 8) > 16) return false;
-    return cdiv(N, 16 * channel_blocks(N)) <= 2 * cu_count();
+    const int C = channel_blocks(N), groups = cdiv(N, 16 * C), n_cu = cu_count();
+    return groups <= n_cu || (groups <= 2 * n_cu && K >= 288 && (C == 1 || K <= 1024));
 }
 
 int launch_fused_linear(const GemmArgs& a, const __half* x, int64_t ldx, const float* s, hipStream_t st) {

@@ -1,5 +1,6 @@
 // Stands in for the HIP runtime under the host code of the GEMM launchers: kernels are not run, the name and the grid of
-// each launch are printed.  Reads one problem per line: epi M N K n_sel max_rows which acc_dbg (n_sel 0: a single matrix).
+// each launch are printed.  Reads one problem per line: epi M N K n_sel max_rows which acc_dbg (n_sel 0: a single matrix;
+// epi -1: whether a linear on fp16 rows takes the one launch that forms its own codes).
 #include <cstdarg>
 #include <cstdio>
 #include <map>
@@ -63,6 +64,10 @@ int main() {
     static int32_t some;
     haq::GemmArgs a{};
     while (scanf("%d %d %d %d %d %d %d %d", &epi, &a.M, &a.N, &a.K, &a.n_sel, &a.max_rows, &a.which, &dbg) == 8) {
+        if (epi == -1) {
+            printf("%s 0\n", haq::fused_linear_fits(a.M, a.K, a.N) ? "fused_linear_kernel" : "none_kernel");
+            continue;
+        }
         a.Npad = haq::round_up(a.N, haq::NPAD);
         a.R = 256 + haq::round_up(a.M > a.max_rows ? a.M : a.max_rows, 16);
         a.offsets = a.n_sel ? &some : nullptr;

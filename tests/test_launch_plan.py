@@ -9,6 +9,7 @@ import pytest
 from paper_2508_07329_amd import build as hip_build
 
 LINEAR, SWIGLU, LINEAR_ASYM, SWIGLU_ASYM = range(4)
+F16_ROWS = -1
 HERE = os.path.dirname(os.path.abspath(__file__))
 HIPCC = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-arch=gfx950", "--offload-host-only", "-O1", "-std=c++17",
          "-I", os.path.join(hip_build.ROOT, "include"), "-I", hip_build.CSRC]
@@ -42,7 +43,7 @@ def plan(tmp_path_factory):
         res = []
         for line in lines:
             name, grid = line.split()
-            m = re.search(r"(gemm_i8|skinny_linear|stream_linear|stream_grouped)_kernel", name)
+            m = re.search(r"(gemm_i8|skinny_linear|stream_linear|stream_grouped|fused_linear|none)_kernel", name)
             res.append((m.group(1), [int(v) for v in re.findall(r"L[ib](\d+)E", name)], int(grid)))
         return res
 
@@ -99,6 +100,16 @@ def test_short_batches_leave_the_streaming_kernel_where_it_was_slower(plan):
             assert kernel == "gemm_i8" and t[0] == 128, (p, kernel, t)  # 256-row tiles would be half empty
         assert all(kernel == "skinny_linear" for kernel, _, _ in of(skinny)), of(skinny)
         assert all(kernel == "stream_linear" and t[0] == 4 for kernel, t, _ in of(rows64)), of(rows64)
+
+
+def test_one_launch_linears_only_where_a_second_work_group_on_a_cu_pays(plan):
+    """(rows, K, channels): up to 26 % slower than the two launches where it did not."""
+    one = [(16, 768, 3072), (16, 1024, 16384), (1, 8192, 4096), (16, 16, 4096), (2, 8192, 8192),  # a work-group for each CU
+           (16, 288, 8176), (8, 2048, 8176), (2, 8192, 8176), (16, 288, 32768), (16, 1024, 32768)]
+    two = [(16, 16, 4112), (1, 16, 8176), (8, 272, 8176), (8, 1040, 16400), (8, 2048, 32768), (2, 8192, 32768), (16, 272, 16400),
+           (17, 768, 3072), (9, 1040, 512), (3, 4112, 512), (1, 8208, 512), (16, 1024, 32784)]
+    of = lambda sizes: [k for k, _, _ in plan([(F16_ROWS, M, N, K, 0, 0, 0, 0) for M, K, N in sizes])]
+    assert set(of(one)) == {"fused_linear"} and set(of(two)) == {"none"}, (of(one), of(two))
 
 
 def test_streaming_row_tiles_only_where_k_steps_carry_their_start_and_end(plan):
