@@ -3,6 +3,7 @@
 #include "haq_common.h"
 #include "quant_math.h"
 
+#include <algorithm>
 #include <mutex>
 
 namespace haq {
@@ -925,7 +926,10 @@ int launch_quant(const QuantArgs& a, hipStream_t st) {
 int launch_weight_colmax(const float* w, const float* s, int nc, int K, int N, float* colmax, hipStream_t st) {
     const size_t n = (size_t)nc * N;
     hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, (uint32_t*)colmax, n);
-    const dim3 grid(cdiv(N, 256), cdiv(K, 64));  // 64 rows to a work-group
+    // 64 rows to a work-group, down to the 8 that a thread has in flight where that makes fewer than two for each CU (us a call of
+    // haq_quant_weight, 64 rows always / now: 64 x 16 9.6 / 7.5, 64 x 4096 10.5 / 8.2, 256 x 256 9.9 / 7.9, 768 x 768 10.9 / 10.1)
+    const int cols = cdiv(N, 256), most = cdiv(K, 8), wanted = cdiv(2 * cu_count(), cols);
+    const dim3 grid(cols, std::max(cdiv(K, 64), std::min(most, wanted)));
     if (nc == 1)
         hipLaunchKernelGGL(weight_col_absmax_kernel<1>, grid, dim3(256), 0, st, w, s, nc, K, N, colmax);
     else

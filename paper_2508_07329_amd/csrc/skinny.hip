@@ -391,7 +391,8 @@ bool skinny_pays(const GemmArgs& a) {
 // every one of 70 sizes.  A second work-group on a CU forms the codes again, on vector units that are busy with the first
 // one's: that pays where the weight stream is long enough to hide it.  us on the GPU, two launches / this:
 //   16-channel units:  K = 48: 7.1 / 7.8,  144: 7.2 / 8.1,  256: 7.6 / 8.1,  384: 8.3 / 8.3,  848: 8.9 / 8.7,  1392: 8.8 / 9.1,
-//                      2240: 9.8 / 9.8,  3472: 11.1 / 10.6,  4336: 13.1 / 10.8,  7280: 17.9 / 14.0
+//                      1984: 9.6 / 10.3,  2240: 9.8 / 9.8,  3472: 11.1 / 10.6,  4336: 13.1 / 10.8,  7280: 17.9 / 14.0
+//                      (what is lost from 1040 to 2112 the host's second launch costs: 8 rows of 1984 x 7936 back to back 11.1 / 8.7)
 //   64-channel units (past 16384 channels):  K = 16: 7.2 / 8.5,  128: 8.0 / 8.7,  288: 9.2 / 9.2,  400: 11.0 / 9.9,  992: 12.4 / 11.4,
 //                      1056: 12.2 / 15.8,  1536: 13.9 / 17.5,  2400: 18.3 / 21.2,  5488: 26.2 / 28.4
 bool fused_linear_fits(int M, int K, int N) {

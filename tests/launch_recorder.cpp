@@ -1,6 +1,6 @@
 // Stands in for the HIP runtime under the host code of the GEMM launchers: kernels are not run, the name and the grid of
 // each launch are printed.  Reads one problem per line: epi M N K n_sel max_rows which acc_dbg (n_sel 0: a single matrix;
-// epi -1: whether a linear on fp16 rows takes the one launch that forms its own codes).
+// epi -1: whether a linear on fp16 rows takes the one launch that forms its own codes; epi -2: column maxima of K x N weights).
 #include <cstdarg>
 #include <cstdio>
 #include <map>
@@ -34,7 +34,7 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
     return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void**, size_t, hipStream_t) {
-    printf("%s %u\n", kernels()[f].c_str(), grid.x);
+    if (kernels()[f].find("fill_zero") == std::string::npos) printf("%s %u\n", kernels()[f].c_str(), grid.x * grid.y);
     return hipSuccess;
 }
 hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
@@ -66,6 +66,10 @@ int main() {
     while (scanf("%d %d %d %d %d %d %d %d", &epi, &a.M, &a.N, &a.K, &a.n_sel, &a.max_rows, &a.which, &dbg) == 8) {
         if (epi == -1) {
             printf("%s 0\n", haq::fused_linear_fits(a.M, a.K, a.N) ? "fused_linear_kernel" : "none_kernel");
+            continue;
+        }
+        if (epi == -2) {
+            haq::launch_weight_colmax(nullptr, nullptr, 1, a.K, a.N, nullptr, nullptr);
             continue;
         }
         a.Npad = haq::round_up(a.N, haq::NPAD);

@@ -9,7 +9,7 @@ import pytest
 from paper_2508_07329_amd import build as hip_build
 
 LINEAR, SWIGLU, LINEAR_ASYM, SWIGLU_ASYM = range(4)
-F16_ROWS = -1
+F16_ROWS, COLUMN_MAXIMA = -1, -2
 HERE = os.path.dirname(os.path.abspath(__file__))
 HIPCC = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-arch=gfx950", "--offload-host-only", "-O1", "-std=c++17",
          "-I", os.path.join(hip_build.ROOT, "include"), "-I", hip_build.CSRC]
@@ -31,7 +31,8 @@ def plan(tmp_path_factory):
     """plan(problems, *defines) -> [(kernel, its integer template arguments, work-groups)]; a problem is
     (epi, M, N, K, n_sel, max_rows, which, acc_dbg)."""
     out = tmp_path_factory.mktemp("plan")
-    sources = [os.path.join(hip_build.CSRC, "gemm.hip"), os.path.join(hip_build.CSRC, "skinny.hip"), os.path.join(HERE, "launch_recorder.cpp")]
+    sources = [os.path.join(hip_build.CSRC, "gemm.hip"), os.path.join(hip_build.CSRC, "skinny.hip"), os.path.join(hip_build.CSRC, "quant.hip"),
+               os.path.join(HERE, "launch_recorder.cpp")]
     built = {}
 
     def run(problems, *defines):
@@ -43,7 +44,7 @@ def plan(tmp_path_factory):
         res = []
         for line in lines:
             name, grid = line.split()
-            m = re.search(r"(gemm_i8|skinny_linear|stream_linear|stream_grouped|fused_linear|none)_kernel", name)
+            m = re.search(r"(gemm_i8|skinny_linear|stream_linear|stream_grouped|fused_linear|weight_col_absmax|none)_kernel", name)
             res.append((m.group(1), [int(v) for v in re.findall(r"L[ib](\d+)E", name)], int(grid)))
         return res
 
@@ -110,6 +111,12 @@ def test_one_launch_linears_only_where_a_second_work_group_on_a_cu_pays(plan):
            (17, 768, 3072), (9, 1040, 512), (3, 4112, 512), (1, 8208, 512), (16, 1024, 32784)]
     of = lambda sizes: [k for k, _, _ in plan([(F16_ROWS, M, N, K, 0, 0, 0, 0) for M, K, N in sizes])]
     assert set(of(one)) == {"fused_linear"} and set(of(two)) == {"none"}, (of(one), of(two))
+
+
+def test_column_maxima_of_small_weights_in_short_stretches(plan):
+    """(K, channels, work-groups): eight rows to each where there are few, 64 where there are two for each CU."""
+    sizes = [(64, 16, 8), (63, 16, 8), (8, 16, 1), (1, 16, 1), (256, 256, 32), (768, 768, 3 * 96), (4096, 4096, 16 * 64), (64, 65536, 256 * 2), (65535, 16, 1024)]
+    assert [g for _, _, g in plan([(COLUMN_MAXIMA, 0, N, K, 0, 0, 0, 0) for K, N, _ in sizes])] == [g for _, _, g in sizes]
 
 
 def test_streaming_row_tiles_only_where_k_steps_carry_their_start_and_end(plan):
