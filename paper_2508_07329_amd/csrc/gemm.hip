@@ -24,7 +24,6 @@ namespace {
 #define HAQ_WAVES_N 2
 #endif
 constexpr int BM = HAQ_BM, BN = HAQ_BN, WAVES_M = HAQ_WAVES_M, WAVES_N = HAQ_WAVES_N, STAGES = HAQ_STAGES, MINB = HAQ_MINB;
-using Shape = GemmShape<BM, BN, WAVES_M, WAVES_N, STAGES>;
 
 // Row tiles of `bm` rows: exact for one matrix; an upper bound, rows / bm plus one partial tile per group, otherwise.
 int row_tiles(const GemmArgs& a, int bm) { return a.offsets ? a.max_rows / bm + a.n_sel : cdiv(a.M, bm); }
@@ -60,24 +59,25 @@ struct TileShape {
     // CU alone) and step[k-1][1] (every CU busy: the caches and the chip's power are shared) in proportion to n / (k C).  Full
     // rounds before the last one overlap (`round` of that each); the last one costs its share of a full round and, as far as
     // `tail` goes, what it takes alone.
-    float fix[2], step[2][2], round, tail;
+    float fix[2], step[3][2], round, tail;
 };
-enum { T128x256, T128x128, T192x128, T192x256, T256x256, N_TILES };
-// Fitted to 419 launches of each shape (129 to 4096 rows, layers of 512 to 16384 input and output channels, weights cold;
-// mean deviation 3 to 5 %).  The shape with the lowest estimate is on average 0.6 % slower than the fastest of the five; four
-// more (256 x 128, 128 x 256 alone on its CU, 192 x 128 and 128 x 128 with two and three to a CU) would win another 1 %.
+enum { T128x256, T128x128, T128x128x3, T192x128, T192x256, T256x128, T256x256, N_TILES };  // x3: three work-groups to a CU
+// Fitted to 1013 launches of each shape (129 to 4096 rows, layers of 64 to 16384 input and 256 to 24576 output channels,
+// weights cold; mean deviation 2.5 to 5 %).  The shape with the lowest estimate is on average 0.6 % slower than the fastest of
+// these and the streaming tiles; without 256 x 128 1.2 %, without 128 x 128 thrice to a CU either 1.8 %.
 // Against the two thresholds on tile counts before (us, with the kernel before and now):
 //   4096 x 16384:  333 rows 38.8 / 34.0,  600: 60 / 51,  777: 65 / 61,  2048: 124 / 118;   16384 x 4096:  777: 86 / 72,  1300: 120 / 87
 //   8192 x 8192:  333: 48 / 41,  600: 71 / 52,  1300: 108 / 81,  4096: 228 / 213;   5120 x 13824:  256: 35.6 / 30.7,  1024: 79 / 66
 //   4096 x 11008:  1024: 64 / 51;   2064 x 8208:  777: 25.2 / 24.6;   768 x 3072:  1024: 10.3 / 9.5
 constexpr TileShape TILES[N_TILES] = {
-    {128, 256, 2, {7.37f, 11.46f}, {{0.3905f, 0.4527f}, {0.3685f, 0.8805f}}, 0.912f, 0.474f},
-    {128, 128, 2, {5.56f, 7.78f}, {{0.2365f, 0.2676f}, {0.2595f, 0.5308f}}, 0.891f, 0.467f},
-    {192, 128, 1, {7.10f, 7.04f}, {{0.2505f, 0.3565f}}, 0.894f, 0.876f},
-    {192, 256, 1, {10.02f, 11.39f}, {{0.3990f, 0.5617f}}, 0.929f, 0.930f},
-    {256, 256, 1, {7.91f, 11.54f}, {{0.4647f, 0.7081f}}, 0.952f, 0.991f},
+    {128, 256, 2, {7.124f, 11.452f}, {{0.3870f, 0.4429f}, {0.2890f, 0.9518f}}, 0.739f, 0.860f},
+    {128, 128, 2, {5.525f, 7.425f}, {{0.2289f, 0.2627f}, {0.2244f, 0.5726f}}, 0.751f, 0.849f},
+    {128, 128, 3, {5.182f, 8.845f}, {{0.3202f, 0.3366f}, {0.2670f, 0.5116f}, {0.2578f, 0.8466f}}, 0.757f, 0.860f},
+    {192, 128, 1, {6.834f, 7.508f}, {{0.2366f, 0.3556f}}, 0.833f, 0.925f},
+    {192, 256, 1, {9.965f, 12.135f}, {{0.3701f, 0.5695f}}, 0.867f, 0.986f},
+    {256, 128, 1, {5.927f, 6.946f}, {{0.2777f, 0.4440f}}, 0.862f, 0.956f},
+    {256, 256, 1, {7.974f, 10.957f}, {{0.4511f, 0.7185f}}, 0.895f, 0.977f},
 };
-constexpr int ONE_ROUND_MIN_K_STEPS = 16;
 float tile_us(const TileShape& t, int M, int N, int nk, int n_cu) {
     const int64_t tiles = (int64_t)cdiv(M, t.bm) * cdiv(N, t.bn), round = (int64_t)t.per_cu * n_cu;
     auto one_round = [&](int n) {
@@ -92,13 +92,21 @@ float tile_us(const TileShape& t, int M, int N, int nk, int n_cu) {
     const float share = full_us * (float)rem / (float)round;
     return (float)(tiles / round) * full_us * t.round + share + (rem ? t.tail * (one_round(rem) - share) : 0.0f);
 }
-// More than half a 192- or 256-row tile would be empty on at most 128 rows.  One round of 256 x 256 tiles, one to a CU, has
-// nothing to cover its stores with, and on few K-steps they decide: 1024 rows of 512 x 16384 19.9 to 26 us against 18.6 with
-// 128 x 256, of 768 x 16384 23.4 / 22.3 (in four rounds, 4096 rows of 512 x 16384, 60 / 67).
+// On at most 128 rows every taller tile is half empty, and the weights are read once: 128 x 128 (with FETCH_ONCE) there.
+// One round of 256 x 256 tiles, one to a CU, that fills the chip stores everything at its end, and on few K-steps that is what
+// counts, which the estimate does not know: 1024 rows of 512 x 16384 26.1 us against 20.2, of 768 x 16384 29.3 / 24.9; 3856 of
+// 880 x 4048 22.0 / 24.4, 913 of 784 x 15088 21.1 / 24.2 (236 tiles).
 int fastest_tile(int M, int N, int nk, int n_cu, float& us) {
+    if (M <= 128) {
+        us = tile_us(TILES[T128x128], M, N, nk, n_cu);
+        return T128x128;
+    }
     int best = 0;
-    for (int i = 0; i < (M <= 128 ? T192x128 : N_TILES); ++i) {
-        if (i == T256x256 && nk < ONE_ROUND_MIN_K_STEPS && (int64_t)cdiv(M, 256) * cdiv(N, 256) <= n_cu) continue;
+    for (int i = 0; i < N_TILES; ++i) {
+        if (i == T256x256 && nk <= 12) {
+            const int64_t tiles = (int64_t)cdiv(M, 256) * cdiv(N, 256);
+            if (tiles <= n_cu && 10 * tiles > 9 * n_cu) continue;
+        }
         const float t = tile_us(TILES[i], M, N, nk, n_cu);
         if (i == 0 || t < us) us = t, best = i;
     }
@@ -114,6 +122,8 @@ int launch_shape(const GemmArgs& a, int shape, hipStream_t st) {
     const dim3 grid = tile_grid(a, TILES[shape].bm, TILES[shape].bn);
     switch (shape) {
         case T128x128: return launch_tiles<128, 128, 2, 2, 4, 2, EPI, false, false, FETCH>(a, grid, st);  // wave tile 64 x 64
+        case T128x128x3: return launch_tiles<128, 128, 2, 2, 3, 3, EPI, false, false, FETCH_PLAIN>(a, grid, st);
+        case T256x128: return launch_tiles<256, 128, 4, 2, 5, 1, EPI, false, false, FETCH_PLAIN>(a, grid, st);  // 64 x 64, eight waves
         case T192x128: return launch_tiles<192, 128, 2, 2, 7, 1, EPI, false, false, FETCH>(a, grid, st);  // 96 x 64
         case T192x256: return launch_tiles<192, 256, 2, 2, 5, 1, EPI, false, false, FETCH_PLAIN>(a, grid, st);  // 96 x 128
         case T256x256: return launch_tiles<256, 256, 4, 2, 4, 1, EPI, false, false, FETCH_PLAIN>(a, grid, st);  // 64 x 128, eight waves

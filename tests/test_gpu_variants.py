@@ -12,6 +12,7 @@ from paper_2508_07329_amd.binding import lib
 from tests import offline
 from tests.gpu_util import bits_equal, dev, diff_report, host
 from tests.test_gpu_parity import _check_moe, _check_moe_asym
+from tests.tile_sizes import DENSE_TILES
 
 pytestmark = pytest.mark.gpu
 
@@ -68,6 +69,12 @@ def test_dense_linear_at_the_edges_of_its_tile_shapes(T, K, N, act):
     (385, 1040, 8208, "relu"), (191, 592, 16400, "none"), (513, 1040, 16400, "none"), (385, 400, 16400, "relu")])
 def test_dense_linear_at_the_edges_of_its_rings_and_tiles(T, K, N, act):
     _linear_both_codes(T, K, N, act)
+
+
+@pytest.mark.parametrize("T,K,N", [size for sizes in DENSE_TILES.values() for size in sizes])
+def test_dense_linear_on_each_tile_shape(T, K, N):
+    """Both codes; the accumulator dump takes 128 x 256 tiles, the calls without it the shape that the size is listed under."""
+    _linear_both_codes(T, K, N, "relu" if T % 2 else "none")
 
 
 @pytest.mark.parametrize("T,N", [(130, 4_000_016), (4_000_016, 32)])

@@ -7,6 +7,7 @@ import subprocess
 import pytest
 
 from paper_2508_07329_amd import build as hip_build
+from tests.tile_sizes import DENSE_TILES
 
 LINEAR, SWIGLU, LINEAR_ASYM, SWIGLU_ASYM = range(4)
 F16_ROWS, COLUMN_MAXIMA = -1, -2
@@ -120,8 +121,8 @@ def test_column_maxima_of_small_weights_in_short_stretches(plan):
 
 
 def test_streaming_row_tiles_only_where_k_steps_carry_their_start_and_end(plan):
-    tiled = [(333, 512, 4096), (512, 512, 4096), (512, 768, 3072), (640, 768, 3072), (777, 4096, 4096), (333, 2048, 8192)]
-    stream = [(256, 512, 4096), (400, 768, 3072), (512, 1024, 4096), (333, 16384, 4096), (700, 16384, 4096), (1024, 3072, 768)]
+    tiled = [(333, 512, 4096), (512, 512, 4096), (512, 768, 3072), (640, 768, 3072), (777, 4096, 4096), (333, 2048, 8192), (512, 1024, 4096)]
+    stream = [(256, 512, 4096), (400, 768, 3072), (333, 16384, 4096), (700, 16384, 4096), (1024, 3072, 768)]
     for epi in (LINEAR, LINEAR_ASYM):
         of = lambda sizes: [k for k, _, _ in plan([(epi, M, N, K, 0, 0, 0, 0) for M, K, N in sizes])]
         assert set(of(tiled)) == {"gemm_i8"} and set(of(stream)) == {"stream_linear"}, (of(tiled), of(stream))
@@ -133,15 +134,25 @@ def test_dense_tile_shapes_by_rows_channels_and_k(plan):
             (192, 128): [(333, 4096, 16384), (600, 8192, 8192), (1300, 16384, 4096), (1536, 4096, 4096)],
             (192, 256): [(1300, 2048, 8192), (600, 4096, 16384), (3000, 16384, 4096), (777, 4096, 11008)],
             (256, 256): [(2048, 4096, 16384), (1024, 5120, 13824), (4096, 8192, 8192), (4096, 4096, 4096)],
-            (128, 256): [(2048, 16384, 4096)]}
+            (128, 256): [(1306, 6672, 11472), (529, 1024, 23264)],
+            (256, 128): [(2048, 16384, 4096), (418, 864, 10352), (708, 1328, 9312), (2559, 816, 2160), (1130, 3456, 5424), (3887, 7808, 1552)]}
+    thrice = [(617, 608, 13936), (879, 544, 12704), (1366, 576, 8112)]  # 128 x 128, three work-groups to a CU
     for epi in (LINEAR, LINEAR_ASYM):
         for shape, sizes in best.items():
             for p, (kernel, t, _) in zip(sizes, plan([(epi, M, N, K, 0, 0, 0, 0) for M, K, N in sizes])):
                 assert (kernel, tuple(t[:2]), t[9]) == ("gemm_i8", shape, 0), (p, kernel, t)
+        assert [t[:2] + [t[5]] for _, t, _ in plan([(epi, M, N, K, 0, 0, 0, 0) for M, K, N in thrice])] == [[128, 128, 3]] * 3
         assert [t[9] for _, t, _ in plan([(epi, M, N, K, 0, 0, 0, 0) for M, N, K in [(128, 16384, 512), (192, 24576, 4096), (193, 24576, 4096)]])] == [2, 2, 0]
         edge = [(300, 2 ** 22 - 256, 1024), (300, 2 ** 22, 1024), (2 ** 22, 300, 1024), (2 ** 22 - 1024, 300, 1024), (300, 2 ** 22, 1025)]
         assert [t[9] for _, t, _ in plan([(epi, M, N, K, 0, 0, 0, 0) for M, N, K in edge])] == [0, 1, 1, 0, 1]
         assert [t[9] for _, t, _ in plan([(epi, M, N, K, 0, 0, 0, 1) for M, N, K in edge])] == [0, 1, 1, 0, 1]  # with the accumulators
+
+
+def test_sizes_of_the_gpu_tests_take_the_tiles_that_they_are_for(plan):
+    for epi in (LINEAR, LINEAR_ASYM):
+        for shape, sizes in DENSE_TILES.items():
+            for p, (kernel, t, _) in zip(sizes, plan([(epi, M, N, K, 0, 0, 0, 0) for M, K, N in sizes])):
+                assert (kernel, t[0], t[1], t[5]) == ("gemm_i8", *shape), (p, kernel, t)
 
 
 def test_projections_of_expert_groups_on_either_side_of_their_lines(plan):
