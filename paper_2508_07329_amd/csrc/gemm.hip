@@ -157,21 +157,22 @@ int launch_wide(const GemmArgs& a, int epi, hipStream_t st) {
 
 // Row blocks of 16 per tile (4, 6 or 8) with which the streaming kernel (skinny.hip: 64-channel tiles, K split over
 // the waves, operands straight into registers) beats the tiled kernel, whose fastest shape takes `tiled_us`, or 0.  Its
-// three tiles are estimated alike (fitted to 174 launches of each with at most 300 tiles of 128 x 128; mean deviation 4 to 5 %):
-// a K-step costs them a third to a half of the others', which pays where few of either fit and K is long.  Within 9 % of
-// each other the streaming tiles are taken: the estimates cannot tell them apart.  Measured (us, M rows, K x N, streaming against tiled):
-//   16384 x 4096:  129 rows 30 / 69,  333: 37 / 69,  512: 44 / 70,  600: 70 / 70;   4096 x 4096:  129: 12 / 22,  512: 18 / 22
-//   3072 x 768:    1024 rows 12 / 18;   2048 x 8192:  256 rows 13.4 / 14.6,  300: 16.8 / 14.7 (tiled)
-//   8192 x 8192:   300 rows 48 / 41 (tiled);   4352 x 10304:  170 rows 29.2 / 24.5 (tiled);   5872 x 8800:  185: 35.5 / 30.8 (tiled)
+// three tiles are estimated alike (fitted to the 470 to 562 launches of each with at most 256 tiles of 128 x 128 and between 0.6 and
+// 1.6 times the fastest tiled shape; mean deviation 6 to 8 %): a K-step costs them a third to a half of the others', which pays
+// where few of either fit and K is long.  Of 1013 sizes the estimates choose the slower kernel, by 4 to 12 %, at 10.
+// Measured (us, M rows, K x N, streaming against tiled):
+//   16384 x 4096:  129 rows 30 / 69,  333: 39 / 62,  600: 68 / 62 (tiled),  700: 70 / 63 (tiled);   4096 x 4096:  129: 12 / 20,  512: 18 / 22
+//   3072 x 768:    1024 rows 12 / 18;   2048 x 8192:  256 rows 13.5 / 14.5,  300: 22 / 13.9 (tiled)
+//   8192 x 8192:   300 rows 47 / 36 (tiled);   4352 x 10304:  170 rows 28.0 / 23.4 (tiled);   5872 x 8800:  185: 33.4 / 29.0 (tiled)
 // and where few K-steps leave the start and the end to decide:
-//   512 x 4096:    256 rows 7.6 / 8.5,  333: 9.2 / 8.6 (tiled);   768 x 3072: 400 rows 9.6 / 8.9,  512: 10.3 / 9.0 (tiled)
+//   512 x 4096:    256 rows 7.5 / 7.8,  333: 9.1 / 7.9 (tiled);   768 x 3072: 400 rows 9.6 / 8.6 (tiled);   1024 x 4096: 512 rows 10.7 / 10.0 (tiled)
 static int stream_row_blocks(const GemmArgs& a, int n_cu, float tiled_us) {
     static constexpr TileShape STREAM[3] = {
-        {64, 64, 1, {6.18f, 6.08f}, {{0.0968f, 0.1246f}}, 0.812f, 0.738f},
-        {96, 64, 1, {7.34f, 7.85f}, {{0.1166f, 0.1374f}}, 0.817f, 0.843f},
-        {128, 64, 1, {7.46f, 8.28f}, {{0.1430f, 0.1627f}}, 0.890f, 0.788f},
+        {64, 64, 1, {5.130f, 5.486f}, {{0.1169f, 0.1422f}}, 0.701f, 0.910f},
+        {96, 64, 1, {6.364f, 7.031f}, {{0.1287f, 0.1512f}}, 0.782f, 0.866f},
+        {128, 64, 1, {6.776f, 7.347f}, {{0.1461f, 0.1791f}}, 0.869f, 0.792f},
     };
-    float best = 1.09f * tiled_us;
+    float best = tiled_us;
     int rb = 0;
     for (const TileShape& t : STREAM) {
         if (a.M <= t.bm) break;  // a single row tile: skinny_pays has decided

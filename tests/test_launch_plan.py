@@ -121,8 +121,9 @@ def test_column_maxima_of_small_weights_in_short_stretches(plan):
 
 
 def test_streaming_row_tiles_only_where_k_steps_carry_their_start_and_end(plan):
-    tiled = [(333, 512, 4096), (512, 512, 4096), (512, 768, 3072), (640, 768, 3072), (777, 4096, 4096), (333, 2048, 8192), (512, 1024, 4096)]
-    stream = [(256, 512, 4096), (400, 768, 3072), (333, 16384, 4096), (700, 16384, 4096), (1024, 3072, 768)]
+    tiled = [(333, 512, 4096), (512, 512, 4096), (512, 768, 3072), (640, 768, 3072), (777, 4096, 4096), (333, 2048, 8192),
+             (400, 768, 3072), (512, 1024, 4096), (300, 8192, 8192), (170, 4352, 10304), (185, 5872, 8800), (700, 16384, 4096)]
+    stream = [(256, 512, 4096), (333, 16384, 4096), (512, 16384, 4096), (1024, 3072, 768)]
     for epi in (LINEAR, LINEAR_ASYM):
         of = lambda sizes: [k for k, _, _ in plan([(epi, M, N, K, 0, 0, 0, 0) for M, K, N in sizes])]
         assert set(of(tiled)) == {"gemm_i8"} and set(of(stream)) == {"stream_linear"}, (of(tiled), of(stream))
@@ -152,7 +153,7 @@ def test_sizes_of_the_gpu_tests_take_the_tiles_that_they_are_for(plan):
     for epi in (LINEAR, LINEAR_ASYM):
         for shape, sizes in DENSE_TILES.items():
             for p, (kernel, t, _) in zip(sizes, plan([(epi, M, N, K, 0, 0, 0, 0) for M, K, N in sizes])):
-                assert (kernel, t[0], t[1], t[5]) == ("gemm_i8", *shape), (p, kernel, t)
+                assert kernel == "gemm_i8" and (t[0], t[1], t[5]) == shape, (p, kernel, t)
 
 
 def test_projections_of_expert_groups_on_either_side_of_their_lines(plan):
