@@ -217,7 +217,13 @@ static constexpr int FEW_MEAN_ROWS = 112;  // likewise for the form for few rows
 // ... and for its 128 x 128 tiles on the gate/up projection: with two work-groups of four stages to a CU more of the weight
 // stream is in flight than with 128 x 256 tiles, which fetch the token rows half as often.  Whole layers (us, 128 x 256 / 128 x 128):
 //   4096 x 14336, 8 experts:  17 rows 260 / 247,  25: 264 / 253,  50: 286 / 289,  75: 309 / 318;   2048 x 5632, 16:  18: 138 / 137,  37: 145 / 146
-static constexpr int NARROW_MEAN_ROWS = 32;
+// Twice the work-groups also start, store and (experts without rows) end twice as often, which few K-steps in many tiles do not
+// carry: 128 x 12672, 32 experts, 4 rows 144 / 167, 512 x 9984, 32: 7 rows 156 / 176, 384 x 4032, 32: 14 rows 86 / 95, 1472 x 11648, 32:
+// 1 token 76 / 91, 1024 x 3840, 32: 12 rows 116 / 122, 768 x 1536, 32: 67 / 70;  and 768 x 1216, 16 (160 tiles of 128 x 256): 47 / 44,
+// 1472 x 11648, 8 (728): 109 / 110, 2112 x 5696, 16 (720): 134 / 135.
+static bool narrow_gate_up(const GemmArgs& a, int mean, int n_cu) {
+    return mean <= 32 && (a.K >= 32 * 64 || 4 * a.n_sel * cdiv(a.N, BN) <= 5 * n_cu);
+}
 
 // Down projections of more than 128 rows per expert: 192 x 256 tiles (a tenth less time for the same work than 128 x 256,
 // more rows of padding) where they fill most of a round and no more, or one and a half rounds and more.  The tiles are
@@ -263,7 +269,7 @@ int launch_gemm(const GemmArgs& a, int epi, hipStream_t st) {
         // 8 experts, 256 tiles 99 us, 288 tiles 137): at one row tile for each group while few have more, else by the upper bound
         const int row_tiles_s = mean <= 104 ? a.n_sel : mean <= FEW_MEAN_ROWS ? a.n_sel + cdiv(a.n_sel, 8) : row_tiles(a, 128);
         if (down && row_tiles_s * cdiv(a.N, 128) <= cu_count()) return asym ? launch_shape<EPI_LINEAR_ASYM, FETCH_ONCE>(a, T128x128, st) : launch_shape<EPI_LINEAR, FETCH_ONCE>(a, T128x128, st);
-        if (!down && mean <= NARROW_MEAN_ROWS)
+        if (!down && narrow_gate_up(a, mean, cu_count()))
             return epi == EPI_SWIGLU_ASYM ? launch_few_narrow<EPI_SWIGLU_ASYM>(a, st) : launch_few_narrow<EPI_SWIGLU>(a, st);
         if (down && mean > 128 && tall_group_tiles(a, cu_count())) return asym ? launch_shape<EPI_LINEAR_ASYM>(a, T192x256, st) : launch_shape<EPI_LINEAR>(a, T192x256, st);
         if (mean <= FEW_MEAN_ROWS) {
