@@ -226,21 +226,27 @@ static bool narrow_gate_up(const GemmArgs& a, int mean, int n_cu) {
 }
 
 // Down projections of more than 128 rows per expert: 192 x 256 tiles (a tenth less time for the same work than 128 x 256,
-// more rows of padding) where they fill most of a round and no more, or one and a half rounds and more.  The tiles are
-// counted for experts between half and one and a half times the average.  Whole layers (us, tokens even, then by
-// 1 / rank^1.1; 128 x 256 / 192 x 256):
-//   4096 x 14336, 8 experts:  194 rows 441 / 457, 457 / 463 (no);  256: 583 / 528, 603 / 536;  512: 903 / 879, 919 / 887;  1024: 1515 / 1470, 1521 / 1469
-//   2048 x 5632, 16:  300: 332 / 315, 328 / 355 (no);  512: 456 / 451, 460 / 454;   1024 x 3584, 8:  600: 153 / 158, 154 / 158 (no)
+// more rows of padding) by the estimates of dense launches, where they fill most of a round and no more, or one and a half
+// rounds and more.  Rounds of uneven groups run into each other, which over 64 K-steps and more makes up for an estimate that is a fifth
+// higher.  The tiles are counted for experts between half and one and a half times the average.  Of 320 layers 32 would be more
+// than 3 % faster with the other tiles (74 with 192 x 256 from one and a half rounds on whatever K is).  Whole layers (us,
+// tokens even, then by 1 / rank^1.1; 128 x 256 / 192 x 256):
+//   4096 x 14336, 8 experts:  194 rows 431 / 451, 456 / 469 (no);  256: 579 / 528, 587 / 535;  512: 908 / 875, 885 / 854;  1024: 1565 / 1515, 1529 / 1493
+//   2048 x 5632, 16:  300: 321 / 305, 321 / 334 (no);  512: 442 / 436, 438 / 434;   1024 x 3584, 8:  600: 149 / 152, 148 / 152 (no)
+//   few K-steps in several rounds:  6016 x 704, 16: 177 rows 148 / 152, 150 / 167 (no);  5952 x 3712, 8: 437: 322 / 353, 337 / 363 (no);
+//   3648 x 832, 8: 930: 166 / 182, 169 / 184 (no);  5184 x 7168, 8: 751: 791 / 762, 800 / 772
 static bool tall_group_tiles(const GemmArgs& a, int n_cu) {
     const int mean = a.max_rows / a.n_sel, nk = cdiv(a.K, 64), ntn = cdiv(a.N, 256);
-    auto count = [&](int bm) {  // tiles, and estimated us as a dense launch
+    auto count = [&](int bm) {
         int n = 0;
         for (int f = 2; f <= 6; ++f) n += cdiv((int64_t)mean * f, 4 * bm);
         return (int)((int64_t)n * a.n_sel * ntn / 5);
     };
     const int tall = count(192);
-    if (2 * tall >= 3 * n_cu) return true;
-    return 20 * tall <= 17 * n_cu && tile_us(TILES[T192x256], 1, tall * 256, nk, n_cu) < tile_us(TILES[T128x256], 1, count(128) * 256, nk, n_cu);
+    const bool rounds = 2 * tall >= 3 * n_cu;
+    if (!rounds && 20 * tall > 17 * n_cu) return false;
+    return tile_us(TILES[T192x256], 1, tall * 256, nk, n_cu) <
+           (rounds && nk >= 64 ? 1.2f : 1.0f) * tile_us(TILES[T128x256], 1, count(128) * 256, nk, n_cu);
 }
 
 int launch_gemm(const GemmArgs& a, int epi, hipStream_t st) {

@@ -160,7 +160,9 @@ def test_projections_of_expert_groups_on_either_side_of_their_lines(plan):
     """(experts, channels, K, rows for each): 192 x 256 tiles of down projections, 128 x 128 tiles of gate/up projections and
     weights that pass the caches by."""
     tall = [(8, 4096, 14336, 256), (8, 4096, 14336, 512), (8, 4096, 14336, 1024), (16, 2048, 5632, 512)]
-    flat = [(8, 4096, 14336, 128), (8, 4096, 14336, 194), (16, 2048, 5632, 300), (8, 1024, 3584, 600)]
+    flat = [(8, 4096, 14336, 128), (8, 4096, 14336, 194), (16, 2048, 5632, 300), (8, 1024, 3584, 600),
+            # few K-steps in several rounds
+            (16, 6016, 704, 177), (8, 5952, 3712, 437), (8, 3648, 832, 930), (16, 5184, 512, 316), (16, 5888, 1728, 428)]
     for epi in (LINEAR, LINEAR_ASYM):
         of = lambda sizes: [(k, t[:2], t[8:10]) for k, t, _ in plan([(epi, 0, N, K, n, n * rows, 1, 0) for n, N, K, rows in sizes])]
         assert all(r == ("gemm_i8", [192, 256], [0, 0]) for r in of(tall)), of(tall)
