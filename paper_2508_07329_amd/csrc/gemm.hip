@@ -274,7 +274,12 @@ int launch_gemm(const GemmArgs& a, int epi, hipStream_t st) {
         // 128 x 128 tiles where they cover the groups in one round (a CU with two of them takes 1.4 times as long: 14336 x 4096,
         // 8 experts, 256 tiles 99 us, 288 tiles 137): at one row tile for each group while few have more, else by the upper bound
         const int row_tiles_s = mean <= 104 ? a.n_sel : mean <= FEW_MEAN_ROWS ? a.n_sel + cdiv(a.n_sel, 8) : row_tiles(a, 128);
-        if (down && row_tiles_s * cdiv(a.N, 128) <= cu_count()) return asym ? launch_shape<EPI_LINEAR_ASYM, FETCH_ONCE>(a, T128x128, st) : launch_shape<EPI_LINEAR, FETCH_ONCE>(a, T128x128, st);
+        if (down && row_tiles_s * cdiv(a.N, 128) <= cu_count()) {
+            // several row tiles to a group: the caches keep its weights (whole layers, FETCH_ONCE / plain: 2048 x 8192, 4 experts, 300
+            // rows 137 / 135, 256 rows skewed 137 / 133; 1024 x 3584, 8: 300 rows 104 / 103)
+            if (mean > FEW_MEAN_ROWS) return asym ? launch_shape<EPI_LINEAR_ASYM>(a, T128x128, st) : launch_shape<EPI_LINEAR>(a, T128x128, st);
+            return asym ? launch_shape<EPI_LINEAR_ASYM, FETCH_ONCE>(a, T128x128, st) : launch_shape<EPI_LINEAR, FETCH_ONCE>(a, T128x128, st);
+        }
         if (!down && narrow_gate_up(a, mean, cu_count()))
             return epi == EPI_SWIGLU_ASYM ? launch_few_narrow<EPI_SWIGLU_ASYM>(a, st) : launch_few_narrow<EPI_SWIGLU>(a, st);
         if (down && mean > 128 && tall_group_tiles(a, cu_count())) return asym ? launch_shape<EPI_LINEAR_ASYM>(a, T192x256, st) : launch_shape<EPI_LINEAR>(a, T192x256, st);

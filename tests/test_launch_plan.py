@@ -168,6 +168,7 @@ def test_projections_of_expert_groups_on_either_side_of_their_lines(plan):
         assert all(r == ("gemm_i8", [192, 256], [0, 0]) for r in of(tall)), of(tall)
         assert all(r == ("gemm_i8", [128, 256], [0, 0]) for r in of(flat)), of(flat)
         assert of([(8, 4096, 14336, 75)]) == [("gemm_i8", [128, 128], [0, 2])]
+        assert of([(4, 2048, 8192, 300), (4, 4096, 14336, 128)]) == [("gemm_i8", [128, 128], [0, 0])] * 2  # several row tiles to a group
     for epi in (SWIGLU, SWIGLU_ASYM):
         of = lambda rows: [(k, t[:2], t[8:10]) for k, t, _ in plan([(epi, 0, 28672, 4096, 8, 8 * r, 0, 0) for r in rows])]
         assert of([9, 32]) == [("gemm_i8", [128, 128], [1, 0])] * 2 and of([33, 112]) == [("gemm_i8", [128, 256], [1, 0])] * 2
