@@ -361,18 +361,19 @@ int launch_rows(const GemmArgs& a, bool asym, hipStream_t st) {
 // 4096 channels, 16 rows of 4096: 8.3 us against 5.8, 64 rows: 12.0 against 8.0.
 static int channel_blocks(int N) { return N / 64 >= 128 ? 4 : 1; }
 
-// Up to 64 rows the weight stream decides: one round of work-groups always wins; more rounds each pay the start, the sums
-// and the epilogue again and need K to carry them, while the tiled kernel has work-groups enough from 24576 channels on.
-// From 65 rows on a K-step also costs 6 or 8 row fragments, on one work-group per CU.
-// Measured (weights cold, us, this kernel / what launch_gemm takes instead; K x N):
-//   16 rows:  1024 x 65536 19.0 / 19.0, 1024 x 24576 9.3 / 12.4, 512 x 65536 17.7 / 12.9
-//   32 rows:  1536 x 24576 14.1 / 15.7, 1024 x 24576 12.4 / 12.5, 768 x 24576 11.6 / 10.7;  2048 x 65536 32 / 29 to 38 (box to box),
-//             1536 x 50272 25.4 / 22.7
-//   33 rows:  4096 x 65536 53 / 57 to 62, 2048 x 65536 35 / 36;   64 rows: 4096 x 65536 61 / 52, 2048 x 24576 18.1 / 18.8, 1536 x 24576 17.3 / 15.9
-//   96 rows:  768 x 16384 9.9 / 10.2, 512 x 16384 9.3 / 8.7, 4096 x 24576 32.3 / 29.1;  128 rows: 1024 x 16384 11.1 / 11.8, 768 x 16384 10.8 / 10.2
+// Up to 64 rows the weight stream decides: one round of work-groups wins; more rounds each pay the start, the sums and the
+// epilogue again, while 128 x 128 tiles have work-groups enough and fetch every weight once past the caches: further rounds are
+// level with them on few rows of long K only.  From 65 rows on a K-step also costs 6 or 8 row fragments, on one work-group per CU.
+// Measured (weights cold, us, this kernel / 128 x 128 tiles; K x N):
+//   one round:   1 row:  512 x 16384 5.6 / 7.3;  13 rows:  848 x 25600 9.2 / 9.3, 528 x 27888 8.5 / 7.9;  15: 2416 x 24528 15.0 / 15.6;  41: 672 x 14000 7.9 / 8.3
+//   two rounds:  10 rows:  352 x 49072 10.6 / 8.9;  16: 1024 x 65536 19.0 / 15.3, 3904 x 46272 28.9 / 35.0, 4688 x 57456 48.6 / 44.9;  9: 1680 x 41760 17.0 / 18.5
+//                32 rows:  768 x 24576 11.6 / 8.7, 1536 x 24576 14.0 / 12.0;  17: 2528 x 23152 15.2 / 16.0, 5920 x 30336 33.0 / 31.6;  22: 9104 x 22016 41.2 / 42.3
+//                33 rows:  1232 x 24656 15.3 / 11.2;  48: 7040 x 23680 41.0 / 34.9;   64: 2048 x 24576 17.9 / 14.8, 11264 x 24048 65 / 54
+//   more:        32 rows:  2048 x 65536 31.7 / 24.5;  25: 2000 x 43376 23.3 / 21.5;  23: 3712 x 47184 34.3 / 33.8;  19: 5008 x 41616 39.4 / 44.7;  33: 4096 x 65536 53 / 43;   64: 4096 x 65536 62 / 45
+//   96 rows:  512 x 16384 9.1 / 7.7, 768 x 16384 9.9 / 8.8;  79: 1104 x 11280 9.6 / 10.2;   128: 1024 x 16384 11.1 / 10.2, 1168 x 15264 11.3 / 11.2;  117: 2448 x 11632 15.2 / 16.3
 // Between one round of 16-channel units and 128 units of 64 channels two row tiles of 64 rows (launch_stream_rows) fill the
-// chip: 96 rows of 512 x 8192 8.3 / 7.7, 1536 x 6144 11.5 / 9.1, 4096 x 8192 16.4 / 14.3, 8192 x 8192 28.2 / 22.5.  On fewer
-// channels those are too few work-groups: 128 rows of 4096 x 4096 9.9 / 12.5, 16384 x 4096 34.9 / 35.4.
+// chip (this kernel / those): 96 rows of 512 x 8192 8.1 / 7.6, 1536 x 6144 11.4 / 9.0, 4096 x 8192 16.4 / 14.2, 8192 x 8192 28.2 / 22.5.  On fewer
+// channels those are too few work-groups: 128 rows of 4096 x 4096 11.2 / 13.3, 16384 x 4096 36.2 / 36.7.
 bool skinny_pays(const GemmArgs& a) {
     if (a.offsets || a.M < 1 || a.M > SKINNY_MAX_ROWS) return false;
     const int n_cu = cu_count(), C = channel_blocks(a.N), RB = (a.M + 15) / 16;
@@ -380,11 +381,9 @@ bool skinny_pays(const GemmArgs& a) {
     const int rounds = cdiv(cdiv(a.N, 16 * C), per_cu * n_cu);
     if (RB > 4) {
         if (a.N <= 16 * n_cu) return true;
-        return 2 * cdiv(a.N, 64) > n_cu && rounds == 1 && a.K >= (RB > 6 ? 1024 : 768);
+        return 2 * cdiv(a.N, 64) > n_cu && rounds == 1 && a.K >= (RB > 6 ? 1152 : 1024);
     }
-    // least K for two rounds and for more, by blocks of 16 rows
-    constexpr int MIN_K[2][4] = {{1024, 1536, 2048, 2048}, {1024, 2048, 4096, INT32_MAX}};
-    return rounds == 1 || a.K >= MIN_K[rounds > 2][RB - 1];
+    return rounds == 1 || (rounds == 2 && RB <= 2 && a.K >= (RB == 1 ? 1536 : 2304)) || (rounds == 3 && RB == 2 && a.K >= 3584);
 }
 
 // 16 rows up to K = 1024, 8 to 2048, 4 to 4096, 2 to 8192, and a work-group for each CU at most: 3 to 23 % faster there at

@@ -44,7 +44,7 @@ def _linear_both_codes(T, K, N, act):
     (128, 4112, 272, "relu"), (129, 528, 272, "none"),
     # 128 units of 64 channels and more: four channel blocks per work-group, the last unit partly past the last channel
     (1, 64, 8192, "relu"), (16, 592, 8208, "none"), (31, 208, 8240, "relu"), (64, 1344, 8224, "none"), (90, 912, 8192, "relu"),
-    (90, 912, 8208, "relu"), (128, 1104, 8208, "none"),
+    (90, 912, 8208, "relu"), (128, 1104, 8208, "none"), (90, 1040, 8208, "relu"), (128, 1168, 8208, "none"),
     # wide layers of few K-steps: the tiled kernel, most of its rows past the last one
     (40, 80, 24592, "none"), (128, 272, 8224, "relu")])
 def test_short_batch_linear_at_the_edges_of_its_variants(T, K, N, act):

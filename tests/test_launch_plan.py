@@ -90,11 +90,12 @@ def test_every_tile_has_a_work_group(plan, defines):
 
 def test_short_batches_leave_the_streaming_kernel_where_it_was_slower(plan):
     """Layers whose 64-channel units need several rounds of work-groups with too few K-steps, or too many rows, to carry
-    them: up to 2.3 times slower there than the tiled kernel.  And the sizes next to them, where it is faster."""
+    them: up to 2.2 times slower there than the tiled kernel.  And the sizes next to them, where it is faster."""
     tiled = [(16, 768, 65536), (17, 768, 24576), (32, 1536, 65536), (33, 1536, 24576), (64, 1024, 50272), (64, 4096, 50272),
-             (65, 512, 16384), (128, 768, 16384), (96, 4096, 24576), (96, 8192, 24576), (128, 512, 16384), (128, 1024, 65536), (100, 768, 50272)]
-    skinny = [(1, 512, 16384), (16, 1024, 50272), (32, 2048, 65536), (33, 4096, 50272), (64, 512, 16384), (64, 2048, 32768), (96, 768, 16384),
-              (128, 1024, 16384), (128, 16384, 4096), (128, 4096, 4096), (1, 768, 3072), (128, 512, 512)]
+             (65, 512, 16384), (128, 768, 16384), (96, 4096, 24576), (96, 8192, 24576), (128, 512, 16384), (128, 1024, 65536), (100, 768, 50272),
+             (16, 1024, 50272), (32, 2048, 24576), (32, 2048, 65536), (33, 4096, 50272), (64, 2048, 32768), (96, 768, 16384), (128, 1024, 16384)]
+    skinny = [(1, 512, 16384), (16, 1024, 32768), (16, 1536, 50272), (32, 2304, 24576), (19, 5008, 41616), (33, 4096, 16384), (64, 512, 16384), (96, 1104, 16384),
+              (128, 1168, 16384), (128, 16384, 4096), (128, 4096, 4096), (1, 768, 3072), (128, 512, 512)]
     rows64 = [(65, 512, 6144), (128, 1024, 8176), (96, 4096, 8192), (128, 8192, 8192)]  # two row tiles of 64 rows, one round
     for epi in (LINEAR, LINEAR_ASYM):
         of = lambda sizes: plan([(epi, M, N, K, 0, 0, 0, 0) for M, K, N in sizes])
