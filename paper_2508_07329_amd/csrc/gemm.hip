@@ -197,26 +197,37 @@ int cu_count() {
 // Down projections of expert groups: rows per selected expert, on average, up to which the streaming kernel is taken.
 // Units of 64 channels, one row tile each, are its work-groups, of which a CU holds two.  Measured on whole layers (us,
 // weights cold, tokens spread evenly, then by 1 / rank^1.1; streaming / 128 x 128 tiles / FEW / many rows):
-//   units 128 (1024 x 3584, 8 experts), 100 rows: 71 / 77 / 82 / 86, 75 / 82 / 86 / 92
-//         256 (4096 x 14336, 4), 100: 171 / 184 / 216 / 214, 197 / 201 / 233 / 232;  (2048 x 8192, 8), 100: 124 / 135 / 147 / 151, 137 / 144 / 155 / 160
-//         384 (3072 x 14336, 8), 100: 275 / 271 / 286 / 294, 308 / 341 / 312 / 321
-//         448 (3584 x 8192, 8), 48: 165 / 161 / 180 / 174, 170 / 161 / 182 / 173;  76: 179 / 167 / 189 / 180, 187 / 182 / 199 / 192
-//         512 (4096 x 14336, 8), 56: 289 / 295 / 306 / 317, 306 / 334 / 308 / 319;  76: 312 / 313 / 325 / 333, 333 / 347 / 320 / 332;
-//              100: 318 / 316 / 328 / 338, 363 / 388 / 363 / 375
-//         512 (2048 x 5632, 16), 64: 160 / 161 / 166 / 171, 177 / 184 / 172 / 179;  100: 169 / 166 / 172 / 176, 194 / 197 / 185 / 192
-// More units than two for each CU: FEW, unless its own 128 x 256 tiles fill the chip and a second row tile starts a round:
-//         768 (3072 x 8192, 16), 20: 238 / 265 / 241 / 255;  36: 266 / 277 / 253 / 268, 269 / 287 / 263 / 278
-//         1024 (4096 x 7168, 16), 36: 294 / 297 / 290 / 297, 288 / 322 / 317 / 335;  56: 311 / 306 / 299 / 306, 331 / 352 / 349 / 364
+//   units 128 (1024 x 3584, 8 experts), 100 rows: 68 / 68 / 79 / 82, 73 / 74 / 84 / 88;  132 (704 x 11008, 12), 109: 146 / 155, 152 / 159 (first two)
+//         256 (4096 x 14336, 4), 100: 176 / 178 / 212 / 219, 212 / 203 / 240 / 246;  112: 180 / 180 / 216 / 222, 218 / 210 / 247 / 253
+//             (2048 x 8192, 8), 100: 127 / 128 / 149 / 155, 146 / 140 / 163 / 168;  112: 157 / 141 / 162 / 168, 148 / 139 / 162 / 168
+//         384 (3072 x 14336, 8), 20: 208 / 204 / 239 / 246, 207 / 206 / 240 / 248;  76: 266 / 250 / 281 / 288, 274 / 264 / 292 / 301;
+//              100: 285 / 263 / 292 / 300, 320 / 340 / 315 / 324
+//         448 (3584 x 8192, 8), 36: 160 / 154 / 177 / 182, 165 / 157 / 178 / 183;  76: 180 / 169 / 187 / 192, 188 / 182 / 199 / 205
+//         512 (4096 x 14336, 8), 20: 248 / 247 / 271 / 280, 251 / 249 / 274 / 282;  56: 284 / 275 / 298 / 311, 294 / 280 / 304 / 314;
+//              64: 302 / 285 / 309 / 321, 321 / 347 / 317 / 333;  76: 314 / 292 / 318 / 329, 351 / 354 / 329 / 343
+//         512 (2048 x 5632, 16), 20: 138 / 135 / 144 / 149, 138 / 135 / 143 / 148;  36: 146 / 144 / 154 / 160, 149 / 160 / 153 / 160;
+//              64: 163 / 156 / 167 / 173, 184 / 185 / 176 / 181;  100: 174 / 165 / 176 / 182, 201 / 200 / 191 / 196
+//         between 256 and 384 (first two):  336 (1344 x 4416, 16), 29: 102 / 107, 104 / 106;  294 (3136 x 7616, 6), 60: 137 / 136, 127 / 130
+// One and a half to two units for each CU: one round of 128 x 128 tiles from 24 rows on, as long as few rows in all keep the
+// largest group of skewed routing within one row tile (192 tokens; at 224 a draw of the 56 rows above with 130 in one group: 301 / 332),
+// or within two where the round has room for another row tile (304 tokens).  More units than two for each CU: FEW, unless its own 128 x 256 tiles fill the chip and a second row tile
+// starts a round:
+//         768 (3072 x 8192, 16), 20: 235 / 239 / 233 / 247, 241 / 246 / 234 / 248;  36: 264 / 256 / 250 / 263, 274 / 280 / 263 / 276
+//         1024 (4096 x 7168, 16), 36: 289 / 282 / 281 / 291, 290 / 301 / 314 / 325;  56: 305 / 293 / 292 / 301, 312 / 316 / 325 / 336
 static int stream_mean_rows(const GemmArgs& a, int n_cu) {
-    const int units = a.n_sel * (a.N / 64);
-    if (2 * units <= 3 * n_cu) return 112;
-    if (units <= 2 * n_cu) return 64;
+    const int units = a.n_sel * (a.N / 64), ntn = cdiv(a.N, 128);
+    if (units <= n_cu) return 4 * units <= 3 * n_cu ? 112 : 104;
+    if (2 * units < 3 * n_cu) return 112;
+    if (units <= 2 * n_cu) {
+        if (a.n_sel * ntn <= n_cu && a.max_rows <= 2 * ((a.n_sel + 1) * ntn <= n_cu ? 304 : 192)) return 24;
+        return 2 * units == 3 * n_cu ? 112 : 64;
+    }
     return a.n_sel * cdiv(a.N, BN) >= n_cu ? 48 : 24;
 }
 static constexpr int FEW_MEAN_ROWS = 112;  // likewise for the form for few rows
 // ... and for its 128 x 128 tiles on the gate/up projection: with two work-groups of four stages to a CU more of the weight
 // stream is in flight than with 128 x 256 tiles, which fetch the token rows half as often.  Whole layers (us, 128 x 256 / 128 x 128):
-//   4096 x 14336, 8 experts:  17 rows 260 / 247,  25: 264 / 253,  50: 286 / 289,  75: 309 / 318;   2048 x 5632, 16:  18: 138 / 137,  37: 145 / 146
+//   4096 x 14336, 8 experts:  18 rows 256 / 246,  24: 258 / 250,  32: 269 / 264,  56: 288 / 298,  76: 293 / 308;   2048 x 5632, 16:  18: 137 / 136,  40: 147 / 148
 // Twice the work-groups also start, store and (experts without rows) end twice as often, which few K-steps in many tiles do not
 // carry: 128 x 12672, 32 experts, 4 rows 144 / 167, 512 x 9984, 32: 7 rows 156 / 176, 384 x 4032, 32: 14 rows 86 / 95, 1472 x 11648, 32:
 // 1 token 76 / 91, 1024 x 3840, 32: 12 rows 116 / 122, 768 x 1536, 32: 67 / 70;  and 768 x 1216, 16 (160 tiles of 128 x 256): 47 / 44,
@@ -266,13 +277,13 @@ int launch_gemm(const GemmArgs& a, int epi, hipStream_t st) {
     }
     if (a.offsets) {
         // Few rows per expert: bound by the weight stream, not by the matrix cores.  Gate/up, FEW / many rows, whole layers (us)
-        // by rows per expert: 4096 x 14336, 8 experts: 18: 310 / 325, 32: 315 / 334, 75: 340 / 363, 112: 366 / 368, 150: 513 / 441;
-        // 2048 x 5632, 16 experts: 37: 159 / 173, 75: 176 / 185.  (The streaming kernel there: 307, 327, 393; 169.)
+        // by rows per expert: 4096 x 14336, 8 experts: 40: 274 / 301, 76: 293 / 317, 112: 338 / 365, 124: 449 / 421, 150: 503 / 414;
+        // 2048 x 5632, 16 experts: 40: 147 / 159, 76: 160 / 171, 112: 182 / 197, 124: 204 / 206, 150: 243 / 235.
         const int mean = a.max_rows / (a.n_sel > 0 ? a.n_sel : 1);
         const bool down = epi == EPI_LINEAR || epi == EPI_LINEAR_ASYM, asym = epi == EPI_LINEAR_ASYM;
         if (down && mean <= stream_mean_rows(a, cu_count())) return launch_stream_grouped(a, asym, st);
-        // 128 x 128 tiles where they cover the groups in one round (a CU with two of them takes 1.4 times as long: 14336 x 4096,
-        // 8 experts, 256 tiles 99 us, 288 tiles 137): at one row tile for each group while few have more, else by the upper bound
+        // 128 x 128 tiles where they cover the groups in one round (a CU with two of them takes 1.6 times as long: 1024 rows of
+        // 14336 x 4096, 256 tiles 66 us, 1152 rows, 288 tiles 103): at one row tile for each group while few have more, else by the upper bound
         const int row_tiles_s = mean <= 104 ? a.n_sel : mean <= FEW_MEAN_ROWS ? a.n_sel + cdiv(a.n_sel, 8) : row_tiles(a, 128);
         if (down && row_tiles_s * cdiv(a.N, 128) <= cu_count()) {
             // several row tiles to a group: the caches keep its weights (whole layers, FETCH_ONCE / plain: 2048 x 8192, 4 experts, 300

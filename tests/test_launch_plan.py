@@ -202,9 +202,11 @@ def test_group_tiles_are_dealt_once_and_evenly(tmp_path):
 def test_down_projections_of_expert_groups_by_units_and_rows(plan):
     """(experts, channels, K, rows for each) on both sides of the lines between the streaming kernel, 128 x 128 tiles and the
     tiled form for few rows; each projection's epilogue in both codes."""
-    stream = [(8, 4096, 14336, 64), (16, 2048, 5632, 64), (4, 4096, 14336, 112), (8, 3072, 14336, 112), (8, 1024, 3584, 112),
+    stream = [(8, 4096, 14336, 64), (16, 2048, 5632, 64), (4, 4096, 14336, 104), (8, 3072, 14336, 112), (8, 1024, 3584, 112),
+              (8, 4096, 14336, 24), (8, 4096, 14336, 49), (16, 2048, 5632, 25), (16, 1344, 4416, 29), (8, 3072, 14336, 77), (8, 2048, 8192, 104),
               (16, 3072, 8192, 24), (16, 4096, 7168, 48), (1, 4096, 14336, 100)]
-    small = [(8, 4096, 14336, 65), (8, 4096, 14336, 104), (8, 3584, 8192, 112), (16, 2048, 5632, 80), (4, 4096, 14336, 128)]
+    small = [(8, 4096, 14336, 65), (8, 4096, 14336, 104), (8, 3584, 8192, 112), (16, 2048, 5632, 80), (4, 4096, 14336, 128),
+             (4, 4096, 14336, 112), (8, 2048, 8192, 112), (8, 4096, 14336, 25), (8, 4096, 14336, 48), (8, 3072, 14336, 76), (8, 3584, 8192, 36)]
     few = [(8, 4096, 14336, 105), (16, 3072, 8192, 25), (16, 2560, 5632, 112), (16, 4096, 7168, 49), (16, 2112, 3008, 56)]
     many = [(8, 3584, 8192, 128), (8, 3072, 14336, 113), (16, 1536, 6144, 128), (8, 4096, 14336, 113)]
     for epi in (LINEAR, LINEAR_ASYM):
