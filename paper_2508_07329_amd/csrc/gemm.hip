@@ -231,9 +231,9 @@ static constexpr int FEW_MEAN_ROWS = 112;  // likewise for the form for few rows
 // Twice the work-groups also start, store and (experts without rows) end twice as often, which few K-steps in many tiles do not
 // carry: 128 x 12672, 32 experts, 4 rows 144 / 167, 512 x 9984, 32: 7 rows 156 / 176, 384 x 4032, 32: 14 rows 86 / 95, 1472 x 11648, 32:
 // 1 token 76 / 91, 1024 x 3840, 32: 12 rows 116 / 122, 768 x 1536, 32: 67 / 70;  and 768 x 1216, 16 (160 tiles of 128 x 256): 47 / 44,
-// 1472 x 11648, 8 (728): 109 / 110, 2112 x 5696, 16 (720): 134 / 135.
+// 1472 x 11648, 8 (728): 109 / 110, 1792 x 6464, 12 (612), 26 rows: 123 / 118, 1408 x 4864, 16 (608): 111 / 107, 2112 x 5696, 16 (720): 134 / 135.
 static bool narrow_gate_up(const GemmArgs& a, int mean, int n_cu) {
-    return mean <= 32 && (a.K >= 32 * 64 || 4 * a.n_sel * cdiv(a.N, BN) <= 5 * n_cu);
+    return mean <= 32 && (a.K >= 32 * 64 || 4 * a.n_sel * cdiv(a.N, BN) <= (a.K >= 20 * 64 ? 12 : 5) * n_cu);
 }
 
 // Down projections of more than 128 rows per expert: 192 x 256 tiles (a tenth less time for the same work than 128 x 256,

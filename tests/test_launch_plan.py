@@ -176,7 +176,7 @@ def test_projections_of_expert_groups_on_either_side_of_their_lines(plan):
         assert of([113, 1024]) == [("gemm_i8", [128, 256], [0, 0])] * 2
         # (experts, hidden and intermediate channels, rows for each): few K-steps carry 128 x 128 tiles where they are few
         few_k = [(32, 128, 12672, 4), (32, 512, 9984, 7), (32, 384, 4032, 14), (32, 1472, 11648, 1), (16, 1984, 11648, 8), (16, 128, 2624, 8)]
-        short = [(8, 2048, 10944, 16), (16, 768, 1216, 10), (4, 64, 576, 32), (16, 128, 2560, 8), (32, 2112, 5696, 4)]
+        short = [(8, 2048, 10944, 16), (16, 768, 1216, 10), (4, 64, 576, 32), (16, 128, 2560, 8), (12, 1792, 6464, 26), (32, 2112, 5696, 4)]
         of = lambda sizes: [t[:2] + t[8:9] for _, t, _ in plan([(epi, 0, 2 * I, H, n, n * r, 0, 0) for n, H, I, r in sizes])]
         assert of(few_k) == [[128, 256, 1]] * len(few_k) and of(short) == [[128, 128, 1]] * len(short)
 
