@@ -28,6 +28,43 @@ def test_every_declared_symbol_is_exported():
     assert haq.haq_version() == 1
 
 
+def _header():
+    return re.sub(r"/\*.*?\*/", "", open(os.path.join(ROOT, "include", "haq.h")).read(), flags=re.S)
+
+
+def test_declared_argument_types_are_those_of_the_header():
+    """Calls in _CALLS pass plain integers: a type narrower than the header's would cut an address or a size."""
+    of = lambda p: C.c_void_p if "*" in p or "[" in p else {"int32_t": C.c_int32, "int64_t": C.c_int64, "size_t": C.c_size_t}[p.split()[-2]]
+    for name, types in binding._CALLS.items():
+        params = re.search(rf"\bint32_t\s+{name}\s*\(([^)]*)\)", _header()).group(1).split(",")
+        assert list(types) == [of(p) for p in params], name
+        assert list(getattr(haq.lib(), name).argtypes) == list(types)
+
+
+def test_expert_descriptors_have_the_layout_of_the_header():
+    fields = re.search(r"struct haq_expert_desc \{(.*?)\}", _header(), flags=re.S).group(1).split(";")[:-1]
+    names = [f.replace("*", " ").split()[-1] for f in fields]
+    assert [n for n, _ in binding._ExpertDesc._fields_] == names
+    assert [t for _, t in binding._ExpertDesc._fields_] == [C.c_void_p if "*" in f else C.c_int32 for f in fields]
+
+    class Tensor:
+        def __init__(self, address):
+            self.data_ptr = lambda: address
+
+    experts = []
+    for i in range(3):
+        at = {n: Tensor(0x7F0000000000 + 256 * (16 * i + k)) for k, n in enumerate(names[:6])}
+        experts.append(haq.ExpertWeights(**at, location=i % 2))
+    words = binding._expert_descs(experts)
+    descs = C.cast(words, C.POINTER(binding._ExpertDesc))
+    assert C.sizeof(words) == 3 * C.sizeof(binding._ExpertDesc)
+    for i, e in enumerate(experts):
+        assert [getattr(descs[i], n) for n in names[:6]] == [getattr(e, n).data_ptr() for n in names[:6]]
+        assert (descs[i].location, descs[i].reserved) == (i % 2, 0)
+    columns = re.search(r"struct haq_expert_colsum \{(.*?)\}", _header(), flags=re.S).group(1).split(";")[:-1]
+    assert [f.replace("*", " ").split()[-1] for f in columns] == ["cs1", "cs3", "cs2"]  # three addresses in this order
+
+
 def test_sizes_and_layout_queries():
     assert haq.haq_packed_bytes(768, 3072) == 768 * 3072
     assert haq.haq_packed_bytes(64, 48) == 64 * 256          # output channels padded to 256
