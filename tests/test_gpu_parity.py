@@ -137,9 +137,7 @@ def test_linear_opt125m_config():
                                         (2000, 64, 3984, "relu"), (1600, 128, 4000, "none")])
 def test_linear_ragged_shapes(T, K, N, act):
     """Two are long enough for the pipelined quantisation kernel (its transposed write-out of the packed codes ends
-    in a partial block of rows); two have at least 512 tiles of 256 x 256 and take the large-tile instantiation of
-    the GEMM, the last two fill one round of 256 x 128 tiles and take that instantiation (ragged last row and
-    channel tiles), each on the call without debug outputs."""
+    in a partial block of rows); the last four are many row tiles of few K-steps, the last row and channel tiles ragged."""
     X, _, _ = hi.hidden_states(T + K, T, K, n_outlier=3)
     _linear_case(X, hi.gaussian_weight(T + K, 0, K, N), act)
 

@@ -12,7 +12,7 @@ from paper_2508_07329_amd.binding import lib
 from tests import offline
 from tests.gpu_util import bits_equal, dev, diff_report, host
 from tests.test_gpu_parity import _check_moe, _check_moe_asym
-from tests.tile_sizes import DENSE_TILES
+from tests.tile_sizes import DENSE_TILES, STREAM_ROWS, TALL_GROUPS
 
 pytestmark = pytest.mark.gpu
 
@@ -54,26 +54,26 @@ def test_short_batch_linear_at_the_edges_of_its_variants(T, K, N, act):
 
 
 @pytest.mark.parametrize("T,K,N,act", [
-    # row tiles of the streaming kernel: of 64 (the second ends in one row; one round, and many tiles), of 96 and of 128
+    # row tiles of the streaming kernel, of 64 (the second ends in one row; one round, and many tiles) and of 96 rows; many rows
     (129, 1040, 528, "none"), (257, 592, 16, "relu"), (1030, 1104, 272, "none"), (333, 1040, 4096, "relu"), (500, 1088, 4080, "none"),
-    # the tiled GEMM's three dense shapes besides the grouped one: 128 x 128, 256 x 128 and 256 x 256
+    # tiles of 128 and 256 rows, and many of them
     (300, 80, 2064, "relu"), (513, 80, 10240, "none"), (2049, 48, 14352, "none")])
 def test_dense_linear_at_the_edges_of_its_tile_shapes(T, K, N, act):
     _linear_both_codes(T, K, N, act)
 
 
 @pytest.mark.parametrize("T,K,N,act", [
-    # K-steps: one, as many as the ring of 128 x 128 tiles has stages, one more and one less; the last one partial
+    # K-steps: one to six, the last one partial, in the streaming kernel and (with the accumulator dump) 128 x 256 tiles
     (300, 16, 272, "relu"), (300, 208, 272, "none"), (257, 256, 400, "none"), (300, 272, 2064, "relu"), (300, 336, 2064, "none"),
-    # 192 x 128 (one tile and a row; a row short of one), 192 x 256 and 256 x 256 tiles, the last channel tile in 16 channels
+    # 192-row tiles (one tile and a row; a row short of one) and others, the last channel tile in 16 channels
     (385, 1040, 8208, "relu"), (191, 592, 16400, "none"), (513, 1040, 16400, "none"), (385, 400, 16400, "relu")])
 def test_dense_linear_at_the_edges_of_its_rings_and_tiles(T, K, N, act):
     _linear_both_codes(T, K, N, act)
 
 
-@pytest.mark.parametrize("T,K,N", [size for sizes in DENSE_TILES.values() for size in sizes])
+@pytest.mark.parametrize("T,K,N", [size for shapes in (DENSE_TILES, STREAM_ROWS) for sizes in shapes.values() for size in sizes])
 def test_dense_linear_on_each_tile_shape(T, K, N):
-    """Both codes; the accumulator dump takes 128 x 256 tiles, the calls without it the shape that the size is listed under."""
+    """Both codes; the accumulator dump takes 128 x 256 tiles, the calls without it the tiles that the size is listed under."""
     _linear_both_codes(T, K, N, "relu" if T % 2 else "none")
 
 
@@ -210,7 +210,9 @@ def test_binary64_products_at_strides_past_32_bits(rows, cols):
     # 56 rows on average and more channel tiles than CUs: the form for few rows in both projections; channel tiles that are
     # no multiple of 8 (the count goes on from group to group)
     (4096, 64, (300, 148), (1, 447), 16),
-    (2624, 192, (130, 70, 1, 199), (128, 129, 0, 143), 16)])
+    (2624, 192, (130, 70, 1, 199), (128, 129, 0, 143), 16),
+    # 192 x 256 tiles of the down projection
+    *[(H, I, first, second, len(first) + len(second)) for H, I, first, second in TALL_GROUPS]])
 def test_routed_experts_at_the_edges_of_their_row_tiles(H, I, first, second, E):
     """Group sizes are set through the logits: every token has one expert of `first` and one of `second`."""
     T = sum(first)
@@ -233,8 +235,8 @@ def test_asymmetric_tokens_and_routing_in_one_launch(T, H, I, E):
 
 
 @pytest.mark.parametrize("H,I,E,rows", [(256, 192, 4, 300), (128, 64, 8, 500), (4096, 64, 8, 257)])
-def test_large_expert_groups_at_the_edges_of_192_row_tiles(H, I, E, rows):
-    """More than 128 rows per expert on average: groups of one and two rows more than whole tiles of 128, 192 and 256 rows."""
+def test_large_expert_groups(H, I, E, rows):
+    """More than 128 rows per expert on average, several row tiles of 128 rows to a group, the last group the longest."""
     T = E * rows // 2
     m = offline.small_moe(seed=rows + H, T=T, H=H, I=I, E=E)
     first, second = np.arange(T) % E, (np.arange(T) // E) % E
@@ -279,6 +281,28 @@ def test_one_launch_linear_without_smoothing_on_odd_rows_and_in_place(T, K):
         assert bits_equal(host(haq.haq_w8a8_linear(x[:, :K], sd, wp, sw_d, K)), ref)
         both = dev(X)
         assert bits_equal(host(haq.haq_w8a8_linear(both, sd, wp, sw_d, K, out=both)), ref)
+
+
+@pytest.mark.parametrize("T,K,N", [(16, 1008, 48), (7, 2048, 16), (4, 3088, 80), (2, 8192, 16)])
+def test_one_launch_linear_on_infinities_and_nan(T, K, N):
+    """The same bits as the two launches, which the calls with debug outputs take: rows with an infinity of either sign, with a
+    NaN, with both, with nothing else; a zero, an infinite and a NaN entry of the smoothing vector."""
+    rng = np.random.default_rng(T + K)
+    X = rng.standard_normal((T, K)).astype(np.float16)
+    X[0, [1, 40]], X[0, 7] = np.inf, -np.inf
+    X[1, [3, K - 1]] = np.nan
+    if T > 2:
+        X[2, 5], X[2, 6], X[3] = np.nan, -np.inf, np.nan
+    _, Wq, sw = offline.quantize_linear(np.ones((1, K), np.float16), hi.gaussian_weight(T + K, 0, K, N))
+    s = (rng.random(K) + 0.5).astype(np.float32)
+    wp, sw_d, x = haq.haq_pack_weight(dev(Wq)), dev(sw), dev(X)
+    for bad in (None, 0.0, np.inf, np.nan):
+        if bad is not None:
+            s[K // 2] = bad
+        for sv in (dev(s), None):
+            y = haq.haq_w8a8_linear(x, sv, wp, sw_d, N)
+            two = haq.haq_w8a8_linear(x, sv, wp, sw_d, N, debug=True)[0]
+            assert bool((y.view(torch.int16) == two.view(torch.int16)).all())
 
 
 def test_ffn_of_few_rows_in_two_launches():

@@ -7,7 +7,7 @@ import subprocess
 import pytest
 
 from paper_2508_07329_amd import build as hip_build
-from tests.tile_sizes import DENSE_TILES
+from tests.tile_sizes import DENSE_TILES, STREAM_ROWS, TALL_GROUPS
 
 LINEAR, SWIGLU, LINEAR_ASYM, SWIGLU_ASYM = range(4)
 F16_ROWS, COLUMN_MAXIMA = -1, -2
@@ -155,6 +155,12 @@ def test_sizes_of_the_gpu_tests_take_the_tiles_that_they_are_for(plan):
         for shape, sizes in DENSE_TILES.items():
             for p, (kernel, t, _) in zip(sizes, plan([(epi, M, N, K, 0, 0, 0, 0) for M, K, N in sizes])):
                 assert kernel == "gemm_i8" and (t[0], t[1], t[5]) == shape, (p, kernel, t)
+        for rb, sizes in STREAM_ROWS.items():
+            for p, (kernel, t, _) in zip(sizes, plan([(epi, M, N, K, 0, 0, 0, 0) for M, K, N in sizes])):
+                assert kernel == "stream_linear" and t[0] == rb, (p, kernel, t)
+        groups = [(epi, 0, H, I, len(first) + len(second), sum(first) + sum(second), 1, 0) for H, I, first, second in TALL_GROUPS]
+        for p, (kernel, t, _) in zip(groups, plan(groups)):
+            assert kernel == "gemm_i8" and t[:2] == [192, 256], (p, kernel, t)
 
 
 def test_projections_of_expert_groups_on_either_side_of_their_lines(plan):
