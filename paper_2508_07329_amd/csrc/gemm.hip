@@ -65,10 +65,11 @@ enum { T128x256, T128x128, T128x128x3, T192x128, T192x256, T256x128, T256x256, N
 // Fitted to 1013 launches of each shape (129 to 4096 rows, layers of 64 to 16384 input and 256 to 24576 output channels,
 // weights cold; mean deviation 2.5 to 5 %).  The shape with the lowest estimate is on average 0.6 % slower than the fastest of
 // these and the streaming tiles; without 256 x 128 1.2 %, without 128 x 128 thrice to a CU either 1.8 %.
-// Against the two thresholds on tile counts before (us, with the kernel before and now):
-//   4096 x 16384:  333 rows 38.8 / 34.0,  600: 60 / 51,  777: 65 / 61,  2048: 124 / 118;   16384 x 4096:  777: 86 / 72,  1300: 120 / 87
-//   8192 x 8192:  333: 48 / 41,  600: 71 / 52,  1300: 108 / 81,  4096: 228 / 213;   5120 x 13824:  256: 35.6 / 30.7,  1024: 79 / 66
-//   4096 x 11008:  1024: 64 / 51;   2064 x 8208:  777: 25.2 / 24.6;   768 x 3072:  1024: 10.3 / 9.5
+// Against two thresholds on tile counts (us, with the kernel of that time and now):
+//   4096 x 16384:  333 rows 41.7 / 31.3,  600: 59 / 45,  777: 64 / 53,  2048: 121 / 113;   16384 x 4096:  777: 87 / 64,  1300: 121 / 83
+//   8192 x 8192:  333: 47 / 38,  600: 69 / 45,  1300: 106 / 77,  4096: 223 / 208;   5120 x 13824:  256: 35.8 / 30.0,  1024: 78 / 64
+//   4096 x 11008:  1024: 62 / 46;   2064 x 8208:  777: 24.2 / 21.7;   768 x 3072:  1024: 10.3 / 9.5
+// and without the last two shapes named (with all seven / without them): 879 rows of 544 x 12704 15.5 / 26.6, 418 of 864 x 10352 11.9 / 15.6
 constexpr TileShape TILES[N_TILES] = {
     {128, 256, 2, {7.124f, 11.452f}, {{0.3870f, 0.4429f}, {0.2890f, 0.9518f}}, 0.739f, 0.860f},
     {128, 128, 2, {5.525f, 7.425f}, {{0.2289f, 0.2627f}, {0.2244f, 0.5726f}}, 0.751f, 0.849f},

@@ -8,11 +8,11 @@
 // holds the fragments of DEPTH K-steps, and the exact int32 partial sums are added in LDS.
 // v_mfma_i32_16x16x64_i8: the weights are the first operand (16 channels x 64 k, lane = channel, 16-byte chunk), a
 // block of 16 token rows the second, so a lane ends up with four consecutive channels of one row.
-// Measured (weights cold, us; before = the tiled GEMM):
+// Measured (weights cold, us; 128 x 128 tiles of the GEMM - this kernel):
 //   rows             1          16          32          64         128
-//   4096 x 16384   27.8-12.6   27.8-12.9   28.0-14.4   28.4-15.7   28.7-21.3   (13.2 at the rate of a large copy)
-//   16384 x 4096   81.0-14.1   80.4-14.8   80.8-19.1   81.3-25.5   80.6-36.5   (13.2; the token rows are re-read per unit)
-//   768 x 3072      7.4- 3.3    7.5- 3.4    7.5- 4.2    7.8- 4.4    7.7- 6.3
+//   4096 x 16384   20.7-12.3   20.9-12.4   20.8-14.1   21.5-15.4   23.6-21.0   (13.2 at the rate of a large copy)
+//   16384 x 4096   57.5-13.3   57.8-14.7   57.7-18.7   59.3-25.3   66.1-36.3   (13.2; the token rows are re-read per unit)
+//   768 x 3072      7.6- 3.6    7.9- 3.7    7.9- 4.3    8.2- 4.6    8.4- 6.5
 #include "group_tiles.h"
 #include "haq_common.h"
 #include "quant_math.h"
@@ -141,7 +141,8 @@ __global__ __launch_bounds__(SK_WAVES * 64, WPS) void skinny_linear_kernel(GemmA
 // More rows: `mt` row tiles of `tile_rows` rows share a unit of 64 channels.  Work-group ids are dealt round-robin to
 // the eight XCDs; each of them (one L2) takes a contiguous range of tiles, rows fastest, so that a unit's weights cross
 // the fabric once.  Bound: the fragments of a K-step, 1 KB for each block of 16 channels or rows, through a CU's load
-// path (64 B a cycle) against 4 RB matrix instructions; 16384 x 4096 on 333 rows, 256 tiles of 96 x 64: 77.5 -> 36.9 us.
+// path (64 B a cycle) against 4 RB matrix instructions; 16384 x 4096 on 333 rows, 256 tiles of 96 x 64
+// 39.2 us, 128 x 128 tiles 62.5.
 template <int RB, int DEPTH, bool ASYM>
 __global__ __launch_bounds__(SK_WAVES * 64, 2) void stream_linear_kernel(GemmArgs a, int mt, int tile_rows) {
     __shared__ int sum[4 * RB][4][64];
@@ -154,8 +155,8 @@ __global__ __launch_bounds__(SK_WAVES * 64, 2) void stream_linear_kernel(GemmArg
 }
 
 // Down projections of expert groups of few rows.  Bound: the weight stream, each activated expert's once; the tiled
-// kernel has one work-group per 256 channels and expert with two K-steps in flight (14336 x 4096, 8 experts of 18 rows:
-// the layer 325 -> 286 us).  An expert's m rows
+// kernel has one work-group per 256 channels and expert with two K-steps in flight (14336 x 4096, 8 experts of 20 rows:
+// the layer 280 us, 248 here).  An expert's m rows
 // are cut into ceil(m / 128) tiles of equal height; the units of 64 channels go round the XCDs, as work-group ids do, and
 // the row tiles of a unit stay on one of them.  Four waves, so that a CU holds two work-groups, one streaming while the
 // other adds up and stores.
