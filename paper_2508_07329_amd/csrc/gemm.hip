@@ -62,22 +62,23 @@ struct TileShape {
     float fix[2], step[3][2], round, tail;
 };
 enum { T128x256, T128x128, T128x128x3, T192x128, T192x256, T256x128, T256x256, N_TILES };  // x3: three work-groups to a CU
-// Fitted to 1013 launches of each shape (129 to 4096 rows, layers of 64 to 16384 input and 256 to 24576 output channels,
-// weights cold; mean deviation 2.5 to 5 %).  The shape with the lowest estimate is on average 0.6 % slower than the fastest of
-// these and the streaming tiles; without 256 x 128 1.2 %, without 128 x 128 thrice to a CU either 1.8 %.
+// Fitted to 1313 launches of each shape (129 to 4200 rows, layers of 64 to 16384 input and 256 to 28000 output channels, 300 of
+// them near whole rounds of one of the shapes; weights cold; mean deviation 3 to 5 %; `round` held to 0.85 and more, below which
+// one nearly full round of long K was overestimated by 16 %).  The shape with the lowest estimate is on average 0.6 % slower than the
+// fastest of these and the streaming tiles; without 256 x 128 1.2 %, without 128 x 128 thrice to a CU either 1.8 %.
 // Against two thresholds on tile counts (us, with the kernel of that time and now):
 //   4096 x 16384:  333 rows 41.7 / 31.3,  600: 59 / 45,  777: 64 / 53,  2048: 121 / 113;   16384 x 4096:  777: 87 / 64,  1300: 121 / 83
 //   8192 x 8192:  333: 47 / 38,  600: 69 / 45,  1300: 106 / 77,  4096: 223 / 208;   5120 x 13824:  256: 35.8 / 30.0,  1024: 78 / 64
 //   4096 x 11008:  1024: 62 / 46;   2064 x 8208:  777: 24.2 / 21.7;   768 x 3072:  1024: 10.3 / 9.5
 // and without the last two shapes named (with all seven / without them): 879 rows of 544 x 12704 15.5 / 26.6, 418 of 864 x 10352 11.9 / 15.6
 constexpr TileShape TILES[N_TILES] = {
-    {128, 256, 2, {7.124f, 11.452f}, {{0.3870f, 0.4429f}, {0.2890f, 0.9518f}}, 0.739f, 0.860f},
-    {128, 128, 2, {5.525f, 7.425f}, {{0.2289f, 0.2627f}, {0.2244f, 0.5726f}}, 0.751f, 0.849f},
-    {128, 128, 3, {5.182f, 8.845f}, {{0.3202f, 0.3366f}, {0.2670f, 0.5116f}, {0.2578f, 0.8466f}}, 0.757f, 0.860f},
-    {192, 128, 1, {6.834f, 7.508f}, {{0.2366f, 0.3556f}}, 0.833f, 0.925f},
-    {192, 256, 1, {9.965f, 12.135f}, {{0.3701f, 0.5695f}}, 0.867f, 0.986f},
-    {256, 128, 1, {5.927f, 6.946f}, {{0.2777f, 0.4440f}}, 0.862f, 0.956f},
-    {256, 256, 1, {7.974f, 10.957f}, {{0.4511f, 0.7185f}}, 0.895f, 0.977f},
+    {128, 256, 2, {7.146f, 11.345f}, {{0.3866f, 0.4416f}, {0.4107f, 0.8608f}}, 0.850f, 0.679f},
+    {128, 128, 2, {5.549f, 7.319f}, {{0.2288f, 0.2614f}, {0.3044f, 0.5239f}}, 0.850f, 0.677f},
+    {128, 128, 3, {5.194f, 8.811f}, {{0.3205f, 0.3336f}, {0.2915f, 0.4967f}, {0.3656f, 0.7871f}}, 0.850f, 0.658f},
+    {192, 128, 1, {6.836f, 7.551f}, {{0.2385f, 0.3419f}}, 0.850f, 0.888f},
+    {192, 256, 1, {9.988f, 12.129f}, {{0.3722f, 0.5366f}}, 0.906f, 0.945f},
+    {256, 128, 1, {5.942f, 6.877f}, {{0.2803f, 0.4261f}}, 0.891f, 0.907f},
+    {256, 256, 1, {8.004f, 10.893f}, {{0.4526f, 0.6699f}}, 0.945f, 0.950f},
 };
 float tile_us(const TileShape& t, int M, int N, int nk, int n_cu) {
     const int64_t tiles = (int64_t)cdiv(M, t.bm) * cdiv(N, t.bn), round = (int64_t)t.per_cu * n_cu;
@@ -232,9 +233,10 @@ static constexpr int FEW_MEAN_ROWS = 112;  // likewise for the form for few rows
 // Twice the work-groups also start, store and (experts without rows) end twice as often, which few K-steps in many tiles do not
 // carry: 128 x 12672, 32 experts, 4 rows 144 / 167, 512 x 9984, 32: 7 rows 156 / 176, 384 x 4032, 32: 14 rows 86 / 95, 1472 x 11648, 32:
 // 1 token 76 / 91, 1024 x 3840, 32: 12 rows 116 / 122, 768 x 1536, 32: 67 / 70;  and 768 x 1216, 16 (160 tiles of 128 x 256): 47 / 44,
-// 1472 x 11648, 8 (728): 109 / 110, 1792 x 6464, 12 (612), 26 rows: 123 / 118, 1408 x 4864, 16 (608): 111 / 107, 2112 x 5696, 16 (720): 134 / 135.
+// 1472 x 11648, 8 (728): 109 / 110, 1792 x 6464, 12 (612), 26 rows: 123 / 118, 1408 x 4864, 16 (608): 111 / 107, 1152 x 11584, 6 (546), 11: 91 / 87, 1856 x 4096, 32 (1024), one
+// token 54 / 47; 2112 x 5696, 16 (720): 134 / 135.
 static bool narrow_gate_up(const GemmArgs& a, int mean, int n_cu) {
-    return mean <= 32 && (a.K >= 32 * 64 || 4 * a.n_sel * cdiv(a.N, BN) <= (a.K >= 20 * 64 ? 12 : 5) * n_cu);
+    return mean <= 32 && (a.K >= 28 * 64 || 4 * a.n_sel * cdiv(a.N, BN) <= (a.K >= 18 * 64 ? 12 : 5) * n_cu);
 }
 
 // Down projections of more than 128 rows per expert: 192 x 256 tiles (a tenth less time for the same work than 128 x 256,

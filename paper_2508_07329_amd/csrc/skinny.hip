@@ -367,10 +367,12 @@ static int channel_blocks(int N) { return N / 64 >= 128 ? 4 : 1; }
 // level with them on few rows of long K only.  From 65 rows on a K-step also costs 6 or 8 row fragments, on one work-group per CU.
 // Measured (weights cold, us, this kernel / 128 x 128 tiles; K x N):
 //   one round:   1 row:  512 x 16384 5.6 / 7.3;  13 rows:  848 x 25600 9.2 / 9.3, 528 x 27888 8.5 / 7.9;  15: 2416 x 24528 15.0 / 15.6;  41: 672 x 14000 7.9 / 8.3
-//   two rounds:  10 rows:  352 x 49072 10.6 / 8.9;  16: 1024 x 65536 19.0 / 15.3, 3904 x 46272 28.9 / 35.0, 4688 x 57456 48.6 / 44.9;  9: 1680 x 41760 17.0 / 18.5
-//                32 rows:  768 x 24576 11.6 / 8.7, 1536 x 24576 14.0 / 12.0;  17: 2528 x 23152 15.2 / 16.0, 5920 x 30336 33.0 / 31.6;  22: 9104 x 22016 41.2 / 42.3
+//   two rounds:  15 rows:  848 x 37168 12.3 / 12.4;  9: 1168 x 39632 13.6 / 14.9;  16: 1840 x 34112 14.9 / 19.0
+//                13: 832 x 54752 15.6 / 12.7;  10: 1232 x 53408 17.4 / 16.2;  13: 1520 x 48784 17.4 / 17.9;  5: 1680 x 56592 18.8 / 19.8;  16: 1024 x 65536 19.0 / 15.3
+//                20 rows:  1536 x 18784 12.8 / 11.6;  31: 2112 x 17120 14.1 / 13.9;  19: 2288 x 16464 13.5 / 14.3;  21: 4720 x 16640 21.6 / 23.6;  28: 5712 x 29600 34.4 / 30.7
 //                33 rows:  1232 x 24656 15.3 / 11.2;  48: 7040 x 23680 41.0 / 34.9;   64: 2048 x 24576 17.9 / 14.8, 11264 x 24048 65 / 54
-//   more:        32 rows:  2048 x 65536 31.7 / 24.5;  25: 2000 x 43376 23.3 / 21.5;  23: 3712 x 47184 34.3 / 33.8;  19: 5008 x 41616 39.4 / 44.7;  33: 4096 x 65536 53 / 43;   64: 4096 x 65536 62 / 45
+//   three:       23 rows:  1536 x 37840 19.1 / 17.2;  22: 2032 x 34256 20.0 / 20.4;  29: 2560 x 41072 22.6 / 24.6;  25: 4912 x 41584 37.7 / 42.5
+//   four:        32 rows:  2048 x 65536 31.7 / 24.5;   33: 4096 x 65536 53 / 43;   64: 4096 x 65536 62 / 45
 //   96 rows:  512 x 16384 9.1 / 7.7, 768 x 16384 9.9 / 8.8;  79: 1104 x 11280 9.6 / 10.2;   128: 1024 x 16384 11.1 / 10.2, 1168 x 15264 11.3 / 11.2;  117: 2448 x 11632 15.2 / 16.3
 // Between one round of 16-channel units and 128 units of 64 channels two row tiles of 64 rows (launch_stream_rows) fill the
 // chip (this kernel / those): 96 rows of 512 x 8192 8.1 / 7.6, 1536 x 6144 11.4 / 9.0, 4096 x 8192 16.4 / 14.2, 8192 x 8192 28.2 / 22.5.  On fewer
@@ -384,7 +386,8 @@ bool skinny_pays(const GemmArgs& a) {
         if (a.N <= 16 * n_cu) return true;
         return 2 * cdiv(a.N, 64) > n_cu && rounds == 1 && a.K >= (RB > 6 ? 1152 : 1024);
     }
-    return rounds == 1 || (rounds == 2 && RB <= 2 && a.K >= (RB == 1 ? 1536 : 2304)) || (rounds == 3 && RB == 2 && a.K >= 3584);
+    if (RB == 1 && rounds == 2) return a.K >= (a.N <= 160 * n_cu ? 896 : 1472);  // a second round that is hardly begun costs less
+    return rounds == 1 || (RB == 2 && rounds <= 3 && a.K >= (rounds == 2 ? 2176 : 2048));
 }
 
 // 16 rows up to K = 1024, 8 to 2048, 4 to 4096, 2 to 8192, and a work-group for each CU at most: 3 to 23 % faster there at

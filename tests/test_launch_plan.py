@@ -93,8 +93,8 @@ def test_short_batches_leave_the_streaming_kernel_where_it_was_slower(plan):
     them: up to 2.2 times slower there than the tiled kernel.  And the sizes next to them, where it is faster."""
     tiled = [(16, 768, 65536), (17, 768, 24576), (32, 1536, 65536), (33, 1536, 24576), (64, 1024, 50272), (64, 4096, 50272),
              (65, 512, 16384), (128, 768, 16384), (96, 4096, 24576), (96, 8192, 24576), (128, 512, 16384), (128, 1024, 65536), (100, 768, 50272),
-             (16, 1024, 50272), (32, 2048, 24576), (32, 2048, 65536), (33, 4096, 50272), (64, 2048, 32768), (96, 768, 16384), (128, 1024, 16384)]
-    skinny = [(1, 512, 16384), (16, 1024, 32768), (16, 1536, 50272), (32, 2304, 24576), (19, 5008, 41616), (33, 4096, 16384), (64, 512, 16384), (96, 1104, 16384),
+             (16, 1024, 50272), (15, 848, 37168), (32, 2048, 24576), (23, 1536, 37840), (32, 2048, 65536), (33, 4096, 50272), (64, 2048, 32768), (96, 768, 16384), (128, 1024, 16384)]
+    skinny = [(1, 512, 16384), (16, 1024, 32768), (16, 1472, 50272), (3, 1456, 33872), (9, 896, 40960), (32, 2176, 24576), (19, 5008, 41616), (29, 2560, 41072), (33, 4096, 16384), (64, 512, 16384), (96, 1104, 16384),
               (128, 1168, 16384), (128, 16384, 4096), (128, 4096, 4096), (1, 768, 3072), (128, 512, 512)]
     rows64 = [(65, 512, 6144), (128, 1024, 8176), (96, 4096, 8192), (128, 8192, 8192)]  # two row tiles of 64 rows, one round
     for epi in (LINEAR, LINEAR_ASYM):
@@ -136,7 +136,7 @@ def test_dense_tile_shapes_by_rows_channels_and_k(plan):
             (192, 128): [(333, 4096, 16384), (600, 8192, 8192), (1300, 16384, 4096), (1536, 4096, 4096)],
             (192, 256): [(1300, 2048, 8192), (600, 4096, 16384), (3000, 16384, 4096), (777, 4096, 11008)],
             (256, 256): [(2048, 4096, 16384), (1024, 5120, 13824), (4096, 8192, 8192), (4096, 4096, 4096)],
-            (128, 256): [(1306, 6672, 11472), (529, 1024, 23264)],
+            (128, 256): [(1306, 6672, 11472), (529, 1024, 23264), (2671, 14560, 5920)],
             (256, 128): [(2048, 16384, 4096), (418, 864, 10352), (708, 1328, 9312), (2559, 816, 2160), (1130, 3456, 5424), (3887, 7808, 1552)]}
     thrice = [(617, 608, 13936), (879, 544, 12704), (1366, 576, 8112)]  # 128 x 128, three work-groups to a CU
     for epi in (LINEAR, LINEAR_ASYM):
@@ -181,8 +181,8 @@ def test_projections_of_expert_groups_on_either_side_of_their_lines(plan):
         assert of([9, 32]) == [("gemm_i8", [128, 128], [1, 0])] * 2 and of([33, 112]) == [("gemm_i8", [128, 256], [1, 0])] * 2
         assert of([113, 1024]) == [("gemm_i8", [128, 256], [0, 0])] * 2
         # (experts, hidden and intermediate channels, rows for each): few K-steps carry 128 x 128 tiles where they are few
-        few_k = [(32, 128, 12672, 4), (32, 512, 9984, 7), (32, 384, 4032, 14), (32, 1472, 11648, 1), (16, 1984, 11648, 8), (16, 128, 2624, 8)]
-        short = [(8, 2048, 10944, 16), (16, 768, 1216, 10), (4, 64, 576, 32), (16, 128, 2560, 8), (12, 1792, 6464, 26), (32, 2112, 5696, 4)]
+        few_k = [(32, 128, 12672, 4), (32, 512, 9984, 7), (32, 384, 4032, 14), (32, 1472, 11648, 1), (16, 1728, 11648, 8), (16, 128, 2624, 8)]
+        short = [(8, 2048, 10944, 16), (16, 768, 1216, 10), (4, 64, 576, 32), (16, 128, 2560, 8), (12, 1408, 6464, 26), (32, 1856, 4096, 1), (6, 1152, 11584, 11), (32, 2112, 5696, 4)]
         of = lambda sizes: [t[:2] + t[8:9] for _, t, _ in plan([(epi, 0, 2 * I, H, n, n * r, 0, 0) for n, H, I, r in sizes])]
         assert of(few_k) == [[128, 256, 1]] * len(few_k) and of(short) == [[128, 128, 1]] * len(short)
 
