@@ -161,7 +161,7 @@ int launch_wide(const GemmArgs& a, int epi, hipStream_t st) {
 // the waves, operands straight into registers) beats the tiled kernel, whose fastest shape takes `tiled_us`, or 0.  Its
 // three tiles are estimated alike (fitted to the 470 to 562 launches of each with at most 256 tiles of 128 x 128 and between 0.6 and
 // 1.6 times the fastest tiled shape; mean deviation 6 to 8 %): a K-step costs them a third to a half of the others', which pays
-// where few of either fit and K is long.  Of 1013 sizes the estimates choose the slower kernel, by 4 to 12 %, at 10.
+// where few of either fit and K is long.  Of 1313 sizes the estimates choose the slower kernel, by 4 to 11 %, at 10.
 // Measured (us, M rows, K x N, streaming against tiled):
 //   16384 x 4096:  129 rows 30 / 69,  333: 39 / 62,  600: 68 / 62 (tiled),  700: 70 / 63 (tiled);   4096 x 4096:  129: 12 / 20,  512: 18 / 22
 //   3072 x 768:    1024 rows 12 / 18;   2048 x 8192:  256 rows 13.5 / 14.5,  300: 22 / 13.9 (tiled)
@@ -242,7 +242,7 @@ static bool narrow_gate_up(const GemmArgs& a, int mean, int n_cu) {
 // Down projections of more than 128 rows per expert: 192 x 256 tiles (a tenth less time for the same work than 128 x 256,
 // more rows of padding) by the estimates of dense launches, where they fill most of a round and no more, or one and a half
 // rounds and more.  Rounds of uneven groups run into each other, which over 64 K-steps and more makes up for an estimate that is a fifth
-// higher.  The tiles are counted for experts between half and one and a half times the average.  Of 320 layers 32 would be more
+// higher.  The tiles are counted for experts between half and one and a half times the average.  Of 320 layers 33 would be more
 // than 3 % faster with the other tiles (74 with 192 x 256 from one and a half rounds on whatever K is).  Whole layers (us,
 // tokens even, then by 1 / rank^1.1; 128 x 256 / 192 x 256):
 //   4096 x 14336, 8 experts:  194 rows 431 / 451, 456 / 469 (no);  256: 579 / 528, 587 / 535;  512: 908 / 875, 885 / 854;  1024: 1565 / 1515, 1529 / 1493
