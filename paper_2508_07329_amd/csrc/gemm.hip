@@ -70,7 +70,7 @@ enum { T128x256, T128x128, T128x128x3, T192x128, T192x256, T256x128, T256x256, N
 //   4096 x 16384:  333 rows 41.7 / 31.3,  600: 59 / 45,  777: 64 / 53,  2048: 121 / 113;   16384 x 4096:  777: 87 / 64,  1300: 121 / 83
 //   8192 x 8192:  333: 47 / 38,  600: 69 / 45,  1300: 106 / 77,  4096: 223 / 208;   5120 x 13824:  256: 35.8 / 30.0,  1024: 78 / 64
 //   4096 x 11008:  1024: 62 / 46;   2064 x 8208:  777: 24.2 / 21.7;   768 x 3072:  1024: 10.3 / 9.5
-// and without the last two shapes named (with all seven / without them): 879 rows of 544 x 12704 15.5 / 26.6, 418 of 864 x 10352 11.9 / 15.6
+// and with all seven / without 256 x 128 and 128 x 128 thrice to a CU:  879 rows of 544 x 12704 15.5 / 26.6, 418 of 864 x 10352 11.9 / 15.6
 constexpr TileShape TILES[N_TILES] = {
     {128, 256, 2, {7.146f, 11.345f}, {{0.3866f, 0.4416f}, {0.4107f, 0.8608f}}, 0.850f, 0.679f},
     {128, 128, 2, {5.549f, 7.319f}, {{0.2288f, 0.2614f}, {0.3044f, 0.5239f}}, 0.850f, 0.677f},
@@ -212,8 +212,8 @@ int cu_count() {
 //         between 256 and 384 (first two):  336 (1344 x 4416, 16), 29: 102 / 107, 104 / 106;  294 (3136 x 7616, 6), 60: 137 / 136, 127 / 130
 // One and a half to two units for each CU: one round of 128 x 128 tiles from 24 rows on, as long as few rows in all keep the
 // largest group of skewed routing within one row tile (192 tokens; at 224 a draw of the 56 rows above with 130 in one group: 301 / 332),
-// or within two where the round has room for another row tile (304 tokens).  More units than two for each CU: FEW, unless its own 128 x 256 tiles fill the chip and a second row tile
-// starts a round:
+// or within two where the round has room for another row tile (304 tokens).  More units than two for each CU: FEW, unless its own
+// 128 x 256 tiles fill the chip and a second row tile starts a round:
 //         768 (3072 x 8192, 16), 20: 235 / 239 / 233 / 247, 241 / 246 / 234 / 248;  36: 264 / 256 / 250 / 263, 274 / 280 / 263 / 276
 //         1024 (4096 x 7168, 16), 36: 289 / 282 / 281 / 291, 290 / 301 / 314 / 325;  56: 305 / 293 / 292 / 301, 312 / 316 / 325 / 336
 static int stream_mean_rows(const GemmArgs& a, int n_cu) {
@@ -233,8 +233,8 @@ static constexpr int FEW_MEAN_ROWS = 112;  // likewise for the form for few rows
 // Twice the work-groups also start, store and (experts without rows) end twice as often, which few K-steps in many tiles do not
 // carry: 128 x 12672, 32 experts, 4 rows 144 / 167, 512 x 9984, 32: 7 rows 156 / 176, 384 x 4032, 32: 14 rows 86 / 95, 1472 x 11648, 32:
 // 1 token 76 / 91, 1024 x 3840, 32: 12 rows 116 / 122, 768 x 1536, 32: 67 / 70;  and 768 x 1216, 16 (160 tiles of 128 x 256): 47 / 44,
-// 1472 x 11648, 8 (728): 109 / 110, 1792 x 6464, 12 (612), 26 rows: 123 / 118, 1408 x 4864, 16 (608): 111 / 107, 1152 x 11584, 6 (546), 11: 91 / 87, 1856 x 4096, 32 (1024), one
-// token 54 / 47; 2112 x 5696, 16 (720): 134 / 135.
+// 1472 x 11648, 8 (728): 109 / 110, 1792 x 6464, 12 (612), 26 rows: 123 / 118, 1408 x 4864, 16 (608): 111 / 107, 1152 x 11584, 6 (546),
+// 11: 91 / 87, 1856 x 4096, 32 (1024), one token 54 / 47, 2112 x 5696, 16 (720): 134 / 135.
 static bool narrow_gate_up(const GemmArgs& a, int mean, int n_cu) {
     return mean <= 32 && (a.K >= 28 * 64 || 4 * a.n_sel * cdiv(a.N, BN) <= (a.K >= 18 * 64 ? 12 : 5) * n_cu);
 }
